@@ -144,7 +144,7 @@ typedef enum eden_status {
 /* Creates a context on HIP device `hip_device` able to handle vectors up to d_max coordinates and
  * batches up to n_max senders per call.  Allocates everything any later call needs: per workspace slot (there are
  * min(n_max, 32)) 4 * D_max bytes for the transform's intermediate passes, D_max bytes for the one-byte indices of
- * b = 5, 6, 7 and 3/16 * D_max bytes for the coins of the EDEN_B_COIN budgets (none of the three if D_max <= 4096);
+ * b = 5, 6, 7 and 3/16 * D_max bytes for the coins of the EDEN_B_COIN budgets (neither of the two if D_max <= 4096);
  * 4 * (d_max + 64) bytes for the kept coordinates of an EDEN_B_SPARSE sender; 32 MiB for sender-group sums of the last
  * decode pass when D_max >= 2^19 and n_max > 1; plus a few KiB of partial sums per sender;
  * solves the Lloyd-Max tables of Sec. 3 in double precision on the host and uploads them.
@@ -203,8 +203,8 @@ int eden_decode_accumulate(eden_ctx *ctx, const void *const *msgs_dev, const uin
  * the same numbers, bit for bit, as zeroing an accumulator, eden_decode_accumulate over the n messages and
  * eden_finalize_mean with this n.  Arguments as in eden_decode_accumulate; mean_dev (device fp32[d], 16-byte
  * aligned) is written only, whatever it held.  For rounds whose n messages are decoded by one call.  When one launch of
- * the last pass sums all senders (no EDEN_B_SPARSE budget, padded dimension of the transform 2^19 .. 2^24 -- up to 2^27
- * without EDEN_B_HALF_PRE --, n at most 32) that pass stores the mean directly and the accumulator's three extra passes
+ * the last pass sums all senders (no EDEN_B_SPARSE budget, padded dimension of the transform at most 2^12 or 2^19 .. 2^24 --
+ * up to 2^27 without EDEN_B_HALF_PRE --, n at most 32) that pass stores the mean directly and the accumulator's three extra passes
  * over memory (zero, read, divide) do not happen; in every other case the call runs those three steps itself on
  * mean_dev. */
 int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t *client_ids,

@@ -22,7 +22,7 @@ struct eden_ctx {
     int log2D_max;
     uint32_t n_max;          // senders per call the workspace was sized for (chunks of kMaxBatch are used)
     uint32_t slots;          // workspace slots = min(n_max, kMaxBatch)
-    float *T;                // slots * D_max floats (nullptr if D_max <= 4096)
+    float *T;                // slots * D_max floats
     double *partials;        // 2 * slots * partial_stride doubles: |x|^2 partials, then sum u q partials
     uint32_t partial_stride;
     uint32_t compute_units;      // of the context's device
@@ -37,6 +37,7 @@ struct eden_ctx {
     DecScratch *dec_scratch; // slots
     DevTables *tables;
     uint32_t *dev_status;
+    uint32_t *arrived;           // counters of arrive_last (0 between launches)
     uint32_t *msg_flags;         // n_max words: the status bits of every message of the last eden_decode_accumulate call
     uint32_t last_decode_n = 0;  // how many of them that call wrote
     // optional kernel timing (eden_profile_*)
@@ -172,8 +173,8 @@ int eden_create(eden_ctx **out, uint64_t d_max, uint32_t n_max, int hip_device) 
     ctx->compute_units = (uint32_t)cus;
 
     bool ok = true;
+    ok = ok && hipMalloc(&ctx->T, (size_t)ctx->slots * D_max * sizeof(float)) == hipSuccess;
     if (ctx->log2D_max > kLoBits) {
-        ok = ok && hipMalloc(&ctx->T, (size_t)ctx->slots * D_max * sizeof(float)) == hipSuccess;
         ok = ok && hipMalloc(&ctx->codes, (size_t)ctx->slots * D_max) == hipSuccess;
     }
     ok = ok && hipMalloc(&ctx->stage, (size_t)(d_max + 64) * sizeof(float)) == hipSuccess;
@@ -194,6 +195,7 @@ int eden_create(eden_ctx **out, uint64_t d_max, uint32_t n_max, int hip_device) 
     ok = ok && hipMalloc(&ctx->dec_scratch, ctx->slots * sizeof(DecScratch)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->tables, sizeof(DevTables)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->dev_status, sizeof(uint32_t)) == hipSuccess;
+    ok = ok && hipMalloc(&ctx->arrived, sizeof(uint32_t)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->msg_flags, (size_t)n_max * sizeof(uint32_t)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->hist, 256 * sizeof(uint32_t)) == hipSuccess;
     if (ok) {
@@ -204,6 +206,7 @@ int eden_create(eden_ctx **out, uint64_t d_max, uint32_t n_max, int hip_device) 
         ok = ok && hipMemset(ctx->enc_scratch, 0, ctx->slots * sizeof(EncScratch)) == hipSuccess;
         ok = ok && hipMemset(ctx->dec_scratch, 0, ctx->slots * sizeof(DecScratch)) == hipSuccess;
         ok = ok && hipMemset(ctx->dev_status, 0, sizeof(uint32_t)) == hipSuccess;
+        ok = ok && hipMemset(ctx->arrived, 0, sizeof(uint32_t)) == hipSuccess;
         ok = ok && hipMemset(ctx->msg_flags, 0, (size_t)n_max * sizeof(uint32_t)) == hipSuccess;
         ok = ok && hipDeviceSynchronize() == hipSuccess;
     }
@@ -221,7 +224,7 @@ int eden_destroy(eden_ctx *ctx) {
     bool ok = guard.ok;
     for (hipEvent_t e : ctx->prof_start) ok = (hipEventDestroy(e) == hipSuccess) && ok;
     for (hipEvent_t e : ctx->prof_stop) ok = (hipEventDestroy(e) == hipSuccess) && ok;
-    void *ptrs[] = {ctx->T, ctx->dec_partial, ctx->stage, ctx->codes, ctx->hist, ctx->partials, ctx->enc_scratch, ctx->dec_scratch, ctx->tables, ctx->dev_status,
+    void *ptrs[] = {ctx->T, ctx->dec_partial, ctx->stage, ctx->codes, ctx->hist, ctx->partials, ctx->enc_scratch, ctx->dec_scratch, ctx->tables, ctx->dev_status, ctx->arrived,
                     ctx->coin.mask, ctx->coin.local, ctx->coin.group, ctx->coin.total, ctx->msg_flags};
     for (void *p : ptrs)
         if (p) ok = (hipFree(p) == hipSuccess) && ok;
@@ -560,7 +563,8 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
         }
         if (pl.lo_bits == 0) {
             Timed t(ctx, EDEN_K_DEC_SMALL, nb, st);
-            launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, ctx->dev_status, flags_out + first, st);
+            launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived,
+                             ctx->dev_status, flags_out + first, st);
         } else {
             // Strided passes first (every sender on its own), contiguous pass last (sums the senders in registers
             // and touches acc once).  With a single strided pass the workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).
@@ -632,10 +636,10 @@ int eden_decode_accumulate(eden_ctx *ctx, const void *const *msgs_dev, const uin
                                 static_cast<hipStream_t>(stream));
 }
 
-// The whole round of a receiver in one call.  When one launch of the 14-bit contiguous pass sums all the senders (no
-// sparsification before the rotation or the one by pairs, D >= 2^19, at most kMaxBatch senders) that pass writes the mean
-// itself: the accumulator is neither zeroed, nor read, nor passed over once more for the division.  Otherwise the three
-// steps run one after the other on mean_dev.
+// The whole round of a receiver in one call.  When one launch sums all the senders (no sparsification before the rotation or
+// the one by pairs, at most kMaxBatch senders, and D >= 2^19: the 14-bit contiguous pass, or D <= 4096: the single launch of
+// those sizes) that launch writes the mean itself: the accumulator is neither zeroed, nor read, nor passed over once more for
+// the division.  Otherwise the three steps run one after the other on mean_dev.
 int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t *client_ids, const uint32_t *b_q8,
                      uint32_t n, uint64_t d, uint64_t seed, const uint32_t *const *recv_bitmaps_dev, float *mean_dev,
                      void *stream) {
@@ -644,14 +648,15 @@ int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t 
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return EDEN_ERR_HIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (mode == 0 && n <= (uint32_t)kMaxBatch && make_plan(ceil_log2(d), false).lo_bits == 14) {
+    auto one_launch_sums = [](const Plan &pl) { return pl.lo_bits == 0 || pl.lo_bits == 14; };
+    if (mode == 0 && n <= (uint32_t)kMaxBatch && one_launch_sums(make_plan(ceil_log2(d), false))) {
         ctx->last_decode_n = n;
         return decode_range(ctx, msgs_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, recv_bitmaps_dev, mean_dev, ctx->msg_flags, st,
                             (float)n);
     }
     if (mode == 1 && n <= (uint32_t)kMaxBatch) {                 // pairs before the rotation: the same with one strided pass
         const Plan pl = make_plan(ceil_log2((d + 1) / 2), true);
-        if (pl.lo_bits == 14 && pl.nhi == 1) {
+        if (pl.lo_bits == 0 || (pl.lo_bits == 14 && pl.nhi == 1)) {
             std::vector<uint32_t> ones(n, 256u);
             ctx->last_decode_n = n;
             return decode_range(ctx, msgs_dev, client_ids, ones.data(), b_q8, n, d, 1, d, seed, recv_bitmaps_dev, mean_dev,

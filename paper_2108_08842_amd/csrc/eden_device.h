@@ -297,6 +297,27 @@ __device__ inline double block_sum(double v, double *red /* shared, THREADS/64 *
     return total;
 }
 
+// ---- values that one workgroup of a launch leaves for another of the same launch.  The eight XCDs have an L2 each, so such a
+// value is written through to memory and read past the caches (relaxed atomics of device scope: no cache is written back or
+// invalidated as a whole, which a release fence of device scope would do), and the counter is bumped when the writes have
+// been acknowledged.
+__device__ inline void store_through(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float load_through(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// True, in every thread, in the workgroup that arrives last of `total`; it finds what the others stored before they
+// arrived.  The last one puts the counter back to 0 for the next launch.  No workgroup waits for another.
+__device__ inline bool arrive_last(uint32_t *counter, uint32_t total, uint32_t *flag /* shared */) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this thread's stores have reached memory
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t last = before + 1u == total ? 1u : 0u;
+        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = last;
+    }
+    __syncthreads();
+    return *flag != 0u;
+}
+
 // Interval rank of one coordinate of the unnormalised transform against the scaled thresholds of I_b
 // (Sec. 2.2.1, Sec. 3), and its contribution |u| q to sum_i u_i Q_i (Sec. 2.3).  H = 2^(b-1) levels per sign.
 // A value exactly on a threshold stays in the interval closer to zero (strict compare); u = +0 is
@@ -543,6 +564,39 @@ __device__ inline uint32_t quantize_mixed(float u, bool up, const EncScratch *sc
     const uint32_t code_lo = neg ? (uint32_t)(HL - 1) - mag_lo : (uint32_t)HL + mag_lo;
     const uint32_t code_hi = neg ? (uint32_t)(HH - 1) - mag_hi : (uint32_t)HH + mag_hi;
     return up ? code_hi : code_lo;
+}
+
+// ---- encode: what the quantizers derive from |x|^2
+// After |x|^2 is known: the thresholds of I_b scaled to the unnormalised transform.
+// z = eta R(x) = u / |x| (Sec. 2.2.1 with d -> D), so z > t  <=>  u > t |x|.  Threads 0..7 fill one table entry each.
+__device__ inline void fill_enc_scratch(EncScratch *s, double n2, uint32_t b_q8, const DevTables *tab, uint32_t tid) {
+    if (tid > 7u) return;
+    int bits, k;
+    budget_of(b_q8, bits, k);
+    const double norm = sqrt(n2);
+    if (tid == 0u) s->n2 = n2;
+    if (grid_q15(b_q8)) {                                        // uniform grid: no table of thresholds, only the step
+        if (tid == 0u) s->grid_inv = (float)(32768.0 / ((double)grid_q15(b_q8) * norm));
+        return;
+    }
+    if (wide_bits(b_q8)) return;                                 // b = 5..8: the long tables are filled by fill_byte_tables
+    const int finer = budget_two_tables(b_q8) ? bits + 1 : bits;
+    s->thr[tid] = (float)(tab->t[bits][tid] * norm);
+    s->qpos[tid] = (float)tab->q[bits][tid];
+    s->thr2[tid] = (float)(tab->t[finer][tid] * norm);
+    s->qpos2[tid] = (float)tab->q[finer][tid];
+}
+// The tables of the one-byte budgets, one entry per thread (tid < 128): the centres of mass of the uniform grid's
+// intervals, or the positive centroids and scaled thresholds of the 32..256-level quantizers.
+__device__ inline void fill_byte_tables(EncScratch *s, uint32_t b_q8, double n2, const DevTables *tab, uint32_t tid) {
+    if (tid > (uint32_t)kGridMax) return;
+    if (const uint32_t q15 = grid_q15(b_q8)) {
+        s->grid_c[tid] = tid ? (float)grid_centroid((double)q15 / 32768.0, (int)tid) : 0.0f;
+    } else if (const uint32_t wb = wide_bits(b_q8)) {
+        const uint32_t H = 1u << (wb - 1u);
+        s->grid_c[tid] = tid < H ? (float)tab->q_big[wb - 5u][tid] : 0.0f;
+        s->wide_thr[tid] = tid < H ? (float)(tab->t_big[wb - 5u][tid] * sqrt(n2)) : INFINITY;   // padding for the bisection
+    }
 }
 
 // ---- operands of the matrix instructions (v_mfma_f32_32x32x16_f16 / _fp8_fp8).  Lane l = 32 h + m holds, of A (32 x 16), row m

@@ -12,7 +12,7 @@ namespace eden {
 // senders into acc).  Launchers of kernels that leave per-workgroup partial sums return how many partials each
 // sender got.
 
-// wave-tile passes and the small kernels (eden_kernels.hip)
+// wave-tile passes (eden_kernels.hip)
 // `d` with a `pre` flag next to it is the caller's dimension; pre != 0 (b = 1/2 with the sparsification before the
 // rotation) means the transformed vector has dimension ceil(d/2).  Every other `d` is the transformed dimension.
 uint32_t launch_enc_lo_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
@@ -47,11 +47,16 @@ void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_ele
 void launch_dec_lo_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
                         const DecScratch *scratch, int narrow, float *acc, hipStream_t st);
 void launch_finalize_mean(const float *acc, uint64_t d, uint32_t n, float *mean, hipStream_t st);
+// D <= 4096 (eden_kernels_small.hip): one launch per direction.
+// `msg_flags` (may be null): one status word per message of the launch, written by the kernel that checks the headers.
+// `pre` as in launch_dec_lo_last (2: into `slots`); `partial`: room for n * (output length of a sender) floats, used when the
+// senders do not fit one workgroup; `arrived`: a counter that is 0 between launches; mean_n > 0: acc is written with the sum
+// divided by mean_n instead of added to.
 void launch_enc_small(const EncBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
                       const DevTables *tab, uint32_t *dev_status, hipStream_t st);
-// `msg_flags` (may be null): one status word per message of the launch, written by the kernel that checks the headers
 void launch_dec_small(const DecBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
-                      const DevTables *tab, float *acc, uint32_t *dev_status, uint32_t *msg_flags, hipStream_t st);
+                      const DevTables *tab, float *acc, float mean_n, float *slots, float *partial, uint32_t *arrived,
+                      uint32_t *dev_status, uint32_t *msg_flags, hipStream_t st);
 // b = m/64: the kept coordinates of x packed into `stage` (m per block of 64), and added back from it into acc
 void launch_sparse_gather(const float *x, uint64_t d, uint32_t m, uint64_t seed, uint32_t client, float *stage, hipStream_t st);
 void launch_sparse_scatter(const float *stage, uint64_t d, uint32_t m, uint64_t seed, uint32_t client, float *acc, hipStream_t st);

@@ -13,44 +13,11 @@
 // that hold part of x) and the hi passes after it, the last one fused with quantization, <R(x),Q> and bit
 // packing (Sec. 2.2.1, 2.3).  Decode runs the hi passes first, the first one fused with unpacking and centroid
 // lookup (Sec. 2.2.2, 4.2), and the lo pass last: it applies the signs and sums the senders in registers before
-// touching the accumulator once.  D <= 4096 is handled by one workgroup per sender with the vector in LDS.
+// touching the accumulator once.  D <= 4096 is handled by eden_kernels_small.hip.
 #include "eden_device.h"
 #include "eden_kernels.h"
 
 namespace eden {
-
-// After |x|^2 is known: the thresholds of I_b scaled to the unnormalised transform.
-// z = eta R(x) = u / |x| (Sec. 2.2.1 with d -> D), so z > t  <=>  u > t |x|.
-__device__ inline void fill_enc_scratch(EncScratch *s, double n2, uint32_t b_q8, const DevTables *tab) {
-    int bits, k;
-    budget_of(b_q8, bits, k);
-    s->n2 = n2;
-    const double norm = sqrt(n2);
-    if (grid_q15(b_q8)) {                                        // uniform grid: no table of thresholds, only the step
-        s->grid_inv = (float)(32768.0 / ((double)grid_q15(b_q8) * norm));
-        return;
-    }
-    if (wide_bits(b_q8)) return;                                 // b = 5..8: the long tables are filled by fill_byte_tables
-    const int finer = budget_two_tables(b_q8) ? bits + 1 : bits;
-    for (int i = 0; i < 8; ++i) {
-        s->thr[i] = (float)(tab->t[bits][i] * norm);
-        s->qpos[i] = (float)tab->q[bits][i];
-        s->thr2[i] = (float)(tab->t[finer][i] * norm);
-        s->qpos2[i] = (float)tab->q[finer][i];
-    }
-}
-// The tables of the one-byte budgets, one entry per thread (tid < 128): the centres of mass of the uniform grid's
-// intervals, or the positive centroids and scaled thresholds of the 32..256-level quantizers.
-__device__ inline void fill_byte_tables(EncScratch *s, uint32_t b_q8, double n2, const DevTables *tab, uint32_t tid) {
-    if (tid > (uint32_t)kGridMax) return;
-    if (const uint32_t q15 = grid_q15(b_q8)) {
-        s->grid_c[tid] = tid ? (float)grid_centroid((double)q15 / 32768.0, (int)tid) : 0.0f;
-    } else if (const uint32_t wb = wide_bits(b_q8)) {
-        const uint32_t H = 1u << (wb - 1u);
-        s->grid_c[tid] = tid < H ? (float)tab->q_big[wb - 5u][tid] : 0.0f;
-        s->wide_thr[tid] = tid < H ? (float)(tab->t_big[wb - 5u][tid] * sqrt(n2)) : INFINITY;   // padding for the bisection
-    }
-}
 
 // ------------------------------------------------------------------------------------------------
 // hi passes
@@ -273,11 +240,9 @@ __global__ __launch_bounds__(256) void k_enc_norm(EncBatch B, const double *part
     for (uint32_t i = threadIdx.x; i < nparts; i += 256) s += pc[i];
     const double total = block_sum<256>(s, red);
     __shared__ double n2_all;
-    if (threadIdx.x == 0) {
-        fill_enc_scratch(&scratch[c], total, B.b_q8[c], tab);
-        n2_all = total;
-    }
+    if (threadIdx.x == 0) n2_all = total;
     __syncthreads();
+    fill_enc_scratch(&scratch[c], n2_all, B.b_q8[c], tab, threadIdx.x);
     fill_byte_tables(&scratch[c], B.b_q8[c], n2_all, tab, threadIdx.x);
 }
 
@@ -1262,239 +1227,6 @@ __global__ __launch_bounds__(256) void k_sq_error_finish(const double *partials,
 }
 
 // ------------------------------------------------------------------------------------------------
-// D <= 4096: one workgroup per sender, the padded vector lives in LDS.
-__device__ inline void fwht_lds(float *buf, uint32_t D) {
-    for (uint32_t h = 1; h < D; h <<= 1) {
-        __syncthreads();
-        for (uint32_t pidx = threadIdx.x; pidx < D / 2; pidx += blockDim.x) {
-            const uint32_t i = ((pidx & ~(h - 1)) << 1) | (pidx & (h - 1));
-            const float a = buf[i], b = buf[i + h];
-            buf[i] = a + b;
-            buf[i + h] = a - b;
-        }
-    }
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(256) void k_enc_small(EncBatch B, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
-                                                   const DevTables *tab, uint32_t *dev_status) {
-    __shared__ float buf[kLoTile];
-    __shared__ uint8_t code[kLoTile];
-    __shared__ double red[4];
-    __shared__ EncScratch s;
-    __shared__ __attribute__((aligned(8))) uint32_t coin_words[kLoTile / 32];   // coin budgets: the second part of the payload
-    __shared__ uint32_t wave_totals[4];
-    const uint32_t c = blockIdx.x;
-    const uint32_t D = 1u << log2D;
-    const float *x = B.x[c];
-    const uint64_t key = stream_key(seed, kStreamSign, B.client[c]);
-    const uint64_t prekey = stream_key(seed, kStreamSubsample, B.client[c]);
-    double n2p = 0.0;
-    for (uint32_t i = threadIdx.x; i < D; i += 256) {
-        float xi;
-        if (pre) {                                             // Sec. 4.1: x'[i] = 2 x[2i + o_i], sparsification before the rotation
-            const uint64_t src = 2ull * i + ((hash_word(prekey, i >> 6) >> (i & 63u)) & 1ull);
-            xi = (src < d) ? 2.0f * x[src] : 0.0f;
-        } else {
-            xi = (i < d) ? x[i] : 0.0f;
-        }
-        n2p += (double)xi * (double)xi;
-        const bool neg = (hash_word(key, i >> 6) >> (i & 63u)) & 1ull;
-        buf[i] = (neg ? -xi : xi) + 0.0f;
-    }
-    const double n2t = block_sum<256>(n2p, red);
-    const uint32_t b_q8 = B.b_q8[c];
-    if (threadIdx.x == 0) fill_enc_scratch(&s, n2t, b_q8, tab);
-    __syncthreads();
-    fill_byte_tables(&s, b_q8, s.n2, tab, threadIdx.x);
-    fwht_lds(buf, D);                                          // includes the barriers that publish `s`
-    int bits, k;
-    budget_of(b_q8, bits, k);
-    const int H = 1 << (bits - 1);
-    const double n2 = s.n2;
-    float ip = 0.0f;
-    const bool mix = budget_mixed(b_q8);                       // b = k + 1/2: one coordinate of every pair uses I_{k+1}
-    const uint32_t coin_frac = coin_q8(b_q8) & 255u;           // coin budgets: a coordinate with a coin uses I_{k+1}
-    const uint64_t mixkey = stream_key(seed, kStreamMix, B.client[c]);
-    const bool bytes = byte_budget(b_q8);                      // uniform grid (Sec. 4.3) or b = 5..8: one-byte indices
-    for (uint32_t i = threadIdx.x; i < D; i += 256) {
-        const float u = buf[i];
-        if (bytes) {                                           // grid_c and wide_thr are adjacent
-            code[i] = (uint8_t)(grid_q15(b_q8) ? quantize_byte<true>(u, 0u, s.grid_inv, s.grid_c, ip)
-                                               : quantize_byte<false>(u, wide_half_levels(b_q8), 0.0f, s.grid_c, ip));
-            continue;
-        }
-        const float a = fabsf(u);
-        const uint32_t g = i >> 1;
-        const bool up = coin_frac ? coin_of(mixkey, i, coin_frac)
-                                  : (mix && ((uint32_t)((hash_word(mixkey, g >> 6) >> (g & 63u)) & 1ull) == (i & 1u)));
-        const float *thr = up ? s.thr2 : s.thr, *qp = up ? s.qpos2 : s.qpos;
-        const int Hu = up ? 2 * H : H;
-        uint32_t mag = 0;
-        for (int t = 1; t < Hu; ++t) mag = (a > thr[t]) ? (uint32_t)t : mag;
-        ip = fmaf(a, qp[mag], ip);
-        const uint32_t neg = __float_as_uint(u) >> 31;
-        code[i] = (uint8_t)(neg ? (uint32_t)(Hu - 1) - mag : (uint32_t)Hu + mag);
-    }
-    const double ipt_t0 = block_sum<256>((double)ip, red);     // barriers inside also publish `code`
-    __shared__ double ip_shared;
-    if (threadIdx.x == 0) ip_shared = ipt_t0;
-    __syncthreads();
-    const double ipt = ip_shared;
-    // (a uniform grid so coarse that every coordinate falls into the interval around 0 leaves <R(x),Q> = 0)
-    const bool valid = (n2 > 0.0) && (n2 < INFINITY) && (ipt > 0.0);
-    uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
-    const uint32_t nsent = D / (uint32_t)k;                    // transmitted indices
-    const uint32_t nwords = 2u * ((nsent * (uint32_t)bits + 63u) / 64u);
-    const uint64_t subkey = stream_key(seed, kStreamSubsample, B.client[c]);
-    for (uint32_t w = threadIdx.x; w < nwords; w += 256) {       // payload bit 32 w + e = bit (pos % bits) of index pos / bits
-        uint32_t word = 0;
-        for (uint32_t e = 0; e < 32u; ++e) {
-            const uint32_t pos = 32u * w + e, j = pos / (uint32_t)bits, r = pos % (uint32_t)bits;
-            if (j >= nsent) break;
-            uint32_t i = j;
-            if (k == 2) i = 2u * j + (uint32_t)((hash_word(subkey, j >> 6) >> (j & 63u)) & 1ull);
-            word |= (((uint32_t)code[i] >> r) & 1u) << e;
-        }
-        payload[w] = valid ? word : 0u;
-    }
-    if (mix) {                                                 // second part: the top bit of every pair's finer index
-        const uint32_t npairs = D / 2u, nwords_b = 2u * ((npairs + 63u) / 64u);
-        for (uint32_t w = threadIdx.x; w < nwords_b; w += 256) {
-            uint32_t word = 0;
-            for (uint32_t e = 0; e < 32u; ++e) {
-                const uint32_t g = 32u * w + e;
-                if (g >= npairs) break;
-                const uint32_t i = 2u * g + (uint32_t)((hash_word(mixkey, g >> 6) >> (g & 63u)) & 1ull);
-                word |= (((uint32_t)code[i] >> bits) & 1u) << e;
-            }
-            payload[nwords + w] = valid ? word : 0u;
-        }
-    }
-    uint32_t extra_bits = 0;
-    if (coin_frac) {
-        // second part: the top bits of the coordinates with a coin, in coordinate order.  A thread looks after 16
-        // consecutive coordinates; a scan over the threads gives the place of its bits.
-        for (uint32_t w = threadIdx.x; w < (uint32_t)kLoTile / 32u; w += 256) coin_words[w] = 0u;
-        uint32_t m16 = 0, t16 = 0;
-        for (uint32_t e = 0; e < 16u; ++e) {
-            const uint32_t i = 16u * threadIdx.x + e;
-            if (i < D && coin_of(mixkey, i, coin_frac)) {
-                m16 |= 1u << e;
-                t16 |= (((uint32_t)code[i] >> bits) & 1u) << e;
-            }
-        }
-        const uint32_t before = block_exclusive_scan_256((uint32_t)__popc(m16), wave_totals, extra_bits);   // barriers inside
-        or_bits(coin_words, before, compress_bits(t16, m16), (uint32_t)__popc(m16));
-        __syncthreads();
-        const uint32_t nwords_b = 2u * ((extra_bits + 63u) / 64u);
-        for (uint32_t w = threadIdx.x; w < nwords_b; w += 256) payload[nwords + w] = valid ? coin_words[w] : 0u;
-    }
-    if (threadIdx.x == 0) {
-        MsgHeader h;
-        h.magic = kMagic; h.log2D = (uint32_t)log2D; h.d = hdr_d; h.b_q8 = B.hdr_b_q8[c]; h.client = B.client[c];
-        h.extra_bits = extra_bits; h.seed = seed; h.N2 = n2;
-        if (valid) {
-            h.IP = ipt * exp2(-0.5 * (double)log2D);
-            h.S = n2 / h.IP;
-            h.status = 0;
-        } else {
-            h.IP = 0.0; h.S = 0.0;
-            h.status = (n2 >= 0.0 && n2 < INFINITY) ? EDEN_DEV_ZERO_VECTOR : EDEN_DEV_NONFINITE;
-            atomicOr(dev_status, h.status);
-        }
-        *static_cast<MsgHeader *>(B.msg[c]) = h;
-    }
-}
-
-// One workgroup decodes the whole batch: per sender fill LDS with the dequantized rotated vector,
-// transform, apply the signs and add into per-thread sums; acc is touched once at the end.
-__global__ __launch_bounds__(256) void k_dec_small(DecBatch B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D,
-                                                   uint64_t seed, const DevTables *tab, float *acc, uint32_t *dev_status,
-                                                   uint32_t *msg_flags) {
-    __shared__ float buf[kLoTile];
-    __shared__ DecScratch s;
-    __shared__ uint32_t coin_m16[256], coin_pre[256], wave_totals[4];   // coin budgets: coins of 16 coordinates, coins before them
-    const uint32_t D = 1u << log2D;
-    float sum[kLoTile / 256];
-#pragma unroll
-    for (int r = 0; r < kLoTile / 256; ++r) sum[r] = 0.0f;
-    for (uint32_t c = 0; c < n; ++c) {
-        __syncthreads();
-        const uint32_t coin_frac = coin_q8(B.b_q8[c]) & 255u;
-        uint32_t extra_bits = 0;
-        if (coin_frac) {                                         // the receiver draws the same coins and counts them
-            const uint64_t ckey = stream_key(seed, kStreamMix, B.client[c]);
-            uint32_t m16 = 0;
-            for (uint32_t e = 0; e < 16u; ++e) {
-                const uint32_t i = 16u * threadIdx.x + e;
-                if (i < D && coin_of(ckey, i, coin_frac)) m16 |= 1u << e;
-            }
-            coin_m16[threadIdx.x] = m16;
-            coin_pre[threadIdx.x] = block_exclusive_scan_256((uint32_t)__popc(m16), wave_totals, extra_bits);
-        }
-        if (threadIdx.x < 64)
-            dec_prepare_wave(B.msg[c], B.bitmap[c], B.client[c], B.b_q8[c], B.hdr_b_q8[c], hdr_d, log2D, seed, tab, &s, dev_status,
-                             extra_bits, msg_flags ? msg_flags + c : nullptr);
-        __syncthreads();
-        const uint32_t b_q8 = B.b_q8[c];
-        int bits, k;
-        budget_of(b_q8, bits, k);
-        const uint32_t *payload = reinterpret_cast<const uint32_t *>(static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES);
-        const uint32_t *bm = B.bitmap[c];
-        const uint64_t subkey = stream_key(seed, kStreamSubsample, B.client[c]);
-        const uint32_t nwords = 2u * (((D / (uint32_t)k) * (uint32_t)bits + 63u) / 64u);
-        const bool mix = budget_mixed(b_q8);
-        const uint64_t mixkey = stream_key(seed, kStreamMix, B.client[c]);
-        for (uint32_t i = threadIdx.x; i < D; i += 256) {
-            const uint32_t pk = i >> 10;
-            bool here = bm ? ((bm[pk >> 5] >> (pk & 31u)) & 1u) : true;
-            uint32_t j = i;
-            if (k == 2) {
-                j = i >> 1;
-                const uint32_t off = (uint32_t)((hash_word(subkey, j >> 6) >> (j & 63u)) & 1ull);
-                here = here && ((i & 1u) == off);
-            }
-            const uint32_t bitpos = j * (uint32_t)bits, w0 = bitpos >> 5;
-            const uint32_t next = (w0 + 1u < nwords) ? payload[w0 + 1u] : 0u;       // a 3-bit index may straddle two words
-            const uint32_t idx = code_at(payload[w0], next, bitpos & 31u, bits);
-            float val = grid_q15(b_q8) ? dequantize_byte<true>(idx, 0u, s.grid_deq)
-                      : wide_bits(b_q8) ? dequantize_byte<false>(idx, wide_half_levels(b_q8), s.grid_deq) : s.deq[idx & 15u];
-            if (mix) {
-                const uint32_t g = i >> 1;
-                if ((uint32_t)((hash_word(mixkey, g >> 6) >> (g & 63u)) & 1ull) == (i & 1u))
-                    val = s.deq2[(((payload[nwords + (g >> 5)] >> (g & 31u)) & 1u) << bits) | idx];
-            }
-            if (coin_frac && ((coin_m16[i >> 4] >> (i & 15u)) & 1u)) {
-                const uint32_t rank = coin_pre[i >> 4] + (uint32_t)__popc(coin_m16[i >> 4] & ((1u << (i & 15u)) - 1u));
-                val = s.deq2[(((payload[nwords + (rank >> 5)] >> (rank & 31u)) & 1u) << bits) | idx];
-            }
-            buf[i] = here ? val : 0.0f;
-        }
-        fwht_lds(buf, D);
-        const uint64_t key = stream_key(seed, kStreamSign, B.client[c]);
-#pragma unroll
-        for (int r = 0; r < kLoTile / 256; ++r) {
-            const uint32_t i = threadIdx.x + 256u * r;
-            if (i < D) {
-                const bool neg = (hash_word(key, i >> 6) >> (i & 63u)) & 1ull;
-                const float val = neg ? -buf[i] : buf[i];
-                if (pre) {                                     // value i of this sender belongs at 2i + o_i (Sec. 4.1)
-                    const uint64_t pos = 2ull * i + ((hash_word(subkey, i >> 6) >> (i & 63u)) & 1ull);
-                    if (pos < d) acc[pos] += val;
-                } else {
-                    sum[r] += val;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kLoTile / 256; ++r) {
-        const uint32_t i = threadIdx.x + 256u * r;
-        if (!pre && i < d && i < D) acc[i] += sum[r];
-    }
-}
-
 // Writes up to kArgDoubles doubles that travel as kernel arguments (for a caller that may neither allocate nor stage a copy).
 struct ArgDoubles { double v[kArgDoubles]; };
 __global__ __launch_bounds__(kArgDoubles) void k_store_doubles(ArgDoubles a, uint32_t count, double *dst) {
@@ -1690,14 +1422,6 @@ void launch_sq_error(const float *a, const float *b, uint64_t d, double *partial
     if (blocks < 1u) blocks = 1u;
     hipLaunchKernelGGL(k_sq_error, dim3(blocks), dim3(256), 0, st, a, b, d, partials);
     hipLaunchKernelGGL(k_sq_error_finish, dim3(1), dim3(256), 0, st, partials, blocks, out);
-}
-void launch_enc_small(const EncBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
-                      const DevTables *tab, uint32_t *dev_status, hipStream_t st) {
-    hipLaunchKernelGGL(k_enc_small, dim3(n), dim3(256), 0, st, B, d, pre, hdr_d, log2D, seed, tab, dev_status);
-}
-void launch_dec_small(const DecBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
-                      const DevTables *tab, float *acc, uint32_t *dev_status, uint32_t *msg_flags, hipStream_t st) {
-    hipLaunchKernelGGL(k_dec_small, dim3(1), dim3(256), 0, st, B, n, d, pre, hdr_d, log2D, seed, tab, acc, dev_status, msg_flags);
 }
 void launch_store_doubles(const double *src_host, uint32_t count, double *dst, hipStream_t st) {
     ArgDoubles a;

@@ -96,6 +96,33 @@ def test_single_workgroup_sizes(ctx, d):
         _run_case(ctx, xs, [4, 5, 6], [384, 640, 896], w.seed + 2)
 
 
+@pytest.mark.parametrize("d,n", [(1, 17), (63, 16), (128, 33), (256, 17), (257, 8), (513, 5), (1024, 4), (2000, 3), (2049, 2), (4096, 7)])
+def test_single_launch_rounds_of_many_senders(ctx, d, n):
+    # D <= 4096: a workgroup decodes up to sixteen senders side by side and further workgroups leave their sums for the last one
+    # to arrive: sender counts on both sides of one workgroup, every number of waves per sender; with loss; the one-call
+    # receiver leaves the bits of the three calls; twice in a row (the counter is back at 0), and pairs before the rotation
+    from paper_2108_08842_amd import eden
+    kinds = [256, 512, 1024, eden.B_COIN(1.7), 128, 384, 768, eden.B_GRID(0.5224), 1536] if d > 1 else [256, 512, 2048]
+    # (a sender has four packets at d = 4096 and one below; at a rate of 0.1 one of the seven senders loses all of its four with
+    # probability 7e-4, which would rightly raise EDEN_DEV_NOTHING_ARRIVED: not with this seed)
+    for budgets, drop in (([kinds[c % len(kinds)] for c in range(n)], 0.1), ([eden.B_HALF_PRE] * n, 0.0)):
+        if eden.message_bytes(d, budgets[0]) == 0:
+            continue
+        w = synth.Workload("t", n, d, budgets, 600 + d % 1000, "lognormal_signed")
+        xs = [synth.client_vector(w, c) for c in range(n)]
+        ids = list(range(70, 70 + n))
+        _run_case(ctx, xs, ids, budgets, w.seed, drop_q32=int(drop * 2 ** 32) if d == 4096 else 0, also_oracle_msgs=False)
+        msgs = ctx.encode([torch.from_numpy(x).cuda() for x in xs], ids, budgets, w.seed)
+        acc = torch.zeros(d, device="cuda")
+        ctx.decode_accumulate(msgs, ids, budgets, d, w.seed, acc)
+        want = ctx.finalize_mean(acc, n)
+        for _ in range(2):
+            got = torch.full((d,), float("nan"), device="cuda")
+            ctx.decode_mean(msgs, ids, budgets, d, w.seed, got)
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+        assert ctx.last_decode_flags(n) == [0] * n
+
+
 @pytest.mark.parametrize("d", [4097, 8192, 20_000, (1 << 16) + 17, 300_000, 1 << 18])
 def test_multi_pass_sizes(ctx, d):
     w = synth.Workload("t", 8, d, [128, 256, 512, 1024, 768, 384, 640, 896], 200 + d % 1000, "lognormal_signed")
