@@ -349,6 +349,13 @@ static int sparsify_mode(const uint32_t *b_q8, uint32_t n) {
     return -1;
 }
 
+// m-of-64 senders that go through the workspace slots in batches
+static bool sparse_same_m(const eden_ctx *ctx, const uint32_t *b_q8, uint32_t n) {
+    bool same = ctx->T != nullptr;
+    for (uint32_t c = 0; c < n; ++c) same = same && sparse_m(b_q8[c]) != 0 && sparse_m(b_q8[c]) == sparse_m(b_q8[0]);
+    return same;
+}
+
 // Argument checks of eden_encode that do not depend on a context.
 static int check_encode_args(const float *const *x_dev, const uint32_t *client_ids, const uint32_t *b_q8, uint32_t n, uint64_t d,
                              void *const *msgs_dev, const size_t *msg_capacity) {
@@ -373,14 +380,11 @@ static int encode_on(eden_ctx *ctx, const float *const *x_dev, const uint32_t *c
     else { ones_big.assign(n, 256u); ones = ones_big.data(); }
     if (mode == 0) return encode_range(ctx, x_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, msgs_dev, st);
     if (mode == 1) return encode_range(ctx, x_dev, client_ids, ones, b_q8, n, d, 1, d, seed, msgs_dev, st);
-    // b = m/64.  Senders that share m and a multi-pass size: a launch gathers the kept coordinates of a batch into the
-    // workspace slots, and the 1-bit method then runs on the slots in place (a first-pass workgroup has read a tile
-    // before it writes it).
-    const uint32_t m0 = sparse_m(b_q8[0]);
-    const uint64_t dk0 = (uint64_t)m0 * ((d + 63) / 64);
-    bool same_m = ctx->T != nullptr && ceil_log2(dk0) > kLoBits;
-    for (uint32_t c = 0; c < n; ++c) same_m = same_m && sparse_m(b_q8[c]) == m0;
-    if (same_m) {
+    // b = m/64.  Senders that share m: a launch gathers the kept coordinates of a batch into the workspace slots, and the
+    // 1-bit method then runs on the slots in place (a first-pass workgroup has read a tile before it writes it).
+    if (sparse_same_m(ctx, b_q8, n)) {
+        const uint32_t m0 = sparse_m(b_q8[0]);
+        const uint64_t dk0 = (uint64_t)m0 * ((d + 63) / 64);
         const int log2Dk = ceil_log2(dk0);
         for (uint32_t first = 0; first < n; first += ctx->slots) {
             const uint32_t nb = (n - first < ctx->slots) ? n - first : ctx->slots;
@@ -392,7 +396,7 @@ static int encode_on(eden_ctx *ctx, const float *const *x_dev, const uint32_t *c
                 B.client[i] = client_ids[first + i];
                 slots_x[i] = ctx->T + ((size_t)i << log2Dk);
             }
-            launch_sparse_gather_batch(B, nb, d, m0, seed, ctx->T, log2Dk, st);
+            launch_sparse_gather(B, nb, d, m0, seed, ctx->T, log2Dk, st);
             if (!launch_ok()) return EDEN_ERR_HIP;
             const int rc = encode_range(ctx, slots_x, &client_ids[first], ones, &b_q8[first], nb, dk0, 0, d, seed,
                                         &msgs_dev[first], st);
@@ -403,7 +407,11 @@ static int encode_on(eden_ctx *ctx, const float *const *x_dev, const uint32_t *c
     // otherwise sender by sender: the kept coordinates packed into the staging vector, then the 1-bit method on it
     for (uint32_t c = 0; c < n; ++c) {
         const uint32_t m = sparse_m(b_q8[c]);
-        launch_sparse_gather(x_dev[c], d, m, seed, client_ids[c], ctx->stage, st);
+        EncBatch B;
+        std::memset(&B, 0, sizeof(B));
+        B.x[0] = x_dev[c];
+        B.client[0] = client_ids[c];
+        launch_sparse_gather(B, 1, d, m, seed, ctx->stage, 0, st);
         if (!launch_ok()) return EDEN_ERR_HIP;
         const float *xs = ctx->stage;
         const int rc = encode_range(ctx, &xs, &client_ids[c], ones, &b_q8[c], 1, (uint64_t)m * ((d + 63) / 64), 0, d, seed,
@@ -621,9 +629,10 @@ static int check_decode_args(eden_ctx *ctx, const void *const *msgs_dev, const u
     return mode < 0 ? EDEN_ERR_INVALID_ARG : mode;
 }
 
+// `mean_n` > 0 (only for m-of-64 senders that share m and fit one batch): acc is written with the sum divided by mean_n.
 static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs_dev, const uint32_t *client_ids,
                                 const uint32_t *b_q8, uint32_t n, uint64_t d, uint64_t seed,
-                                const uint32_t *const *recv_bitmaps_dev, float *acc_dev, hipStream_t st);
+                                const uint32_t *const *recv_bitmaps_dev, float *acc_dev, hipStream_t st, float mean_n = 0.0f);
 
 int eden_decode_accumulate(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t *client_ids,
                            const uint32_t *b_q8, uint32_t n, uint64_t d, uint64_t seed,
@@ -663,6 +672,8 @@ int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t 
                                 ctx->msg_flags, st, (float)n);
         }
     }
+    if (mode == 2 && n <= ctx->slots && sparse_same_m(ctx, b_q8, n))         // one launch adds the values of all senders
+        return decode_accumulate_on(ctx, mode, msgs_dev, client_ids, b_q8, n, d, seed, recv_bitmaps_dev, mean_dev, st, (float)n);
     launch_fill_zero(mean_dev, d, st);
     if (!launch_ok()) return EDEN_ERR_HIP;
     const int rc = decode_accumulate_on(ctx, mode, msgs_dev, client_ids, b_q8, n, d, seed, recv_bitmaps_dev, mean_dev, st);
@@ -676,19 +687,17 @@ int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t 
 
 static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs_dev, const uint32_t *client_ids,
                                 const uint32_t *b_q8, uint32_t n, uint64_t d, uint64_t seed,
-                                const uint32_t *const *recv_bitmaps_dev, float *acc_dev, hipStream_t st) {
+                                const uint32_t *const *recv_bitmaps_dev, float *acc_dev, hipStream_t st, float mean_n) {
     std::vector<uint32_t> ones(n, 256u);
     ctx->last_decode_n = n;
     if (mode == 0) return decode_range(ctx, msgs_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, recv_bitmaps_dev, acc_dev, ctx->msg_flags, st);
     if (mode == 1) return decode_range(ctx, msgs_dev, client_ids, ones.data(), b_q8, n, d, 1, d, seed, recv_bitmaps_dev, acc_dev, ctx->msg_flags, st);
-    // b = m/64 (the factor 64/m is folded into the dequantization).  Senders that share m and a multi-pass size: a batch
-    // is decoded without summing, every sender into its own workspace slot, and one launch adds the values to the
-    // coordinates of acc they were taken from.
-    const uint32_t m0 = sparse_m(b_q8[0]);
-    const uint64_t dk0 = (uint64_t)m0 * ((d + 63) / 64);
-    bool same_m = ctx->T != nullptr && ceil_log2(dk0) > kLoBits;
-    for (uint32_t c = 0; c < n; ++c) same_m = same_m && sparse_m(b_q8[c]) == m0;
-    if (same_m) {
+    // b = m/64 (the factor 64/m is folded into the dequantization).  Senders that share m: a batch is decoded without
+    // summing, every sender into its own workspace slot, and one launch adds the values to the coordinates of acc they were
+    // taken from.
+    if (sparse_same_m(ctx, b_q8, n)) {
+        const uint32_t m0 = sparse_m(b_q8[0]);
+        const uint64_t dk0 = (uint64_t)m0 * ((d + 63) / 64);
         const int log2Dk = ceil_log2(dk0);
         for (uint32_t first = 0; first < n; first += ctx->slots) {
             const uint32_t nb = (n - first < ctx->slots) ? n - first : ctx->slots;
@@ -698,7 +707,7 @@ static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs
             DecBatch B;
             std::memset(&B, 0, sizeof(B));
             for (uint32_t i = 0; i < nb; ++i) B.client[i] = client_ids[first + i];
-            launch_sparse_scatter_batch(B, nb, d, m0, seed, ctx->T, log2Dk, acc_dev, st);
+            launch_sparse_scatter(B, nb, d, m0, seed, ctx->T, log2Dk, acc_dev, mean_n, st);
             if (!launch_ok()) return EDEN_ERR_HIP;
         }
         return EDEN_OK;
@@ -714,7 +723,10 @@ static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs
         const int rc = decode_range(ctx, &msgs_dev[c], &client_ids[c], ones.data(), &b_q8[c], 1, dk, 0, d, seed,
                                     recv_bitmaps_dev ? &bm : nullptr, ctx->stage, ctx->msg_flags + c, st);
         if (rc != EDEN_OK) return rc;
-        launch_sparse_scatter(ctx->stage, d, m, seed, client_ids[c], acc_dev, st);
+        DecBatch B;
+        std::memset(&B, 0, sizeof(B));
+        B.client[0] = client_ids[c];
+        launch_sparse_scatter(B, 1, d, m, seed, ctx->stage, ceil_log2(dk), acc_dev, 0.0f, st);
         if (!launch_ok()) return EDEN_ERR_HIP;
     }
     return EDEN_OK;

@@ -57,13 +57,11 @@ void launch_enc_small(const EncBatch &B, uint32_t n, uint64_t d, int pre, uint64
 void launch_dec_small(const DecBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
                       const DevTables *tab, float *acc, float mean_n, float *slots, float *partial, uint32_t *arrived,
                       uint32_t *dev_status, uint32_t *msg_flags, hipStream_t st);
-// b = m/64: the kept coordinates of x packed into `stage` (m per block of 64), and added back from it into acc
-void launch_sparse_gather(const float *x, uint64_t d, uint32_t m, uint64_t seed, uint32_t client, float *stage, hipStream_t st);
-void launch_sparse_scatter(const float *stage, uint64_t d, uint32_t m, uint64_t seed, uint32_t client, float *acc, hipStream_t st);
-void launch_sparse_gather_batch(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, float *T, int log2Dk,
-                                hipStream_t st);
-void launch_sparse_scatter_batch(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, const float *T, int log2Dk,
-                                 float *acc, hipStream_t st);
+// b = m/64 (eden_kernels_sparse.hip): the kept coordinates of every x_c (m per block of 64) packed into out + (c << log2_stride),
+// and added back from there into acc, sender by sender; mean_n > 0: acc is written with the sum divided by mean_n instead
+void launch_sparse_gather(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, float *out, int log2_stride, hipStream_t st);
+void launch_sparse_scatter(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, const float *in, int log2_stride,
+                           float *acc, float mean_n, hipStream_t st);
 // b = 5, 6, 7: one-byte indices (B.codes[c], null for other senders) <-> the packed payload
 void launch_pack_bits(const EncBatch &B, uint32_t n, int log2D, hipStream_t st);
 void launch_unpack_bits(const DecBatch &B, uint32_t n, int log2D, uint8_t *codes_all, hipStream_t st);

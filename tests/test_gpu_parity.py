@@ -365,6 +365,26 @@ def test_sparse_budgets_m_of_64(ctx, d, m):
     assert eden.message_bytes(d, B) == o.message_bytes(d, B)
 
 
+@pytest.mark.parametrize("d,m,n", [(130, 63, 17), (4096, 1, 33), (4100, 32, 5), (65_537, 63, 40), (200_001, 6, 1), (900_000, 6, 17)])
+def test_sparse_rounds_of_many_senders(ctx, d, m, n):
+    # senders that share m: sender counts around the 16 waves of the scatter kernel and beyond one batch, kept vectors of at most
+    # 4096 coordinates and more, ragged ends; the one-call receiver leaves the bits of the three calls
+    from paper_2108_08842_amd import eden
+    budgets = [eden.B_SPARSE(m)] * n
+    w = synth.Workload("t", n, d, budgets, 1700 + d % 1000, "lognormal_signed")
+    xs = [synth.client_vector(w, c) for c in range(n)]
+    ids = list(range(30, 30 + n))
+    _run_case(ctx, xs, ids, budgets, w.seed, also_oracle_msgs=False)
+    msgs = ctx.encode([torch.from_numpy(x).cuda() for x in xs], ids, budgets, w.seed)
+    acc = torch.zeros(d, device="cuda")
+    ctx.decode_accumulate(msgs, ids, budgets, d, w.seed, acc)
+    want = ctx.finalize_mean(acc, n)
+    got = torch.full((d,), float("nan"), device="cuda")
+    ctx.decode_mean(msgs, ids, budgets, d, w.seed, got)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    assert ctx.last_decode_flags(n) == [0] * n
+
+
 def test_sparse_budget_that_keeps_only_padding(ctx):
     # d < 64 where every kept position of the block is a virtual zero: the documented outcome is a zero-vector message
     # (status bit, S = 0, all-zero payload) that contributes nothing, exactly as the oracle has it
