@@ -10,7 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libeden_hip.so")
 OBJ_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["eden_tables.cpp", "eden_kernels.hip", "eden_kernels_small.hip", "eden_kernels_sparse.hip", "eden_kernels_wg.hip", "eden_kernels_lo14.hip", "eden_api.hip"]
+SOURCES = ["eden_tables.cpp", "eden_kernels.hip", "eden_kernels_small.hip", "eden_kernels_sparse.hip", "eden_kernels_wg.hip", "eden_kernels_wg_dec.hip", "eden_kernels_lo14.hip", "eden_kernels_lo15.hip", "eden_api.hip"]
 
 
 def hipcc_path() -> str:

@@ -1,6 +1,6 @@
 // C ABI of the EDEN library (see include/eden.h for the contract of every call).
 // Host code only: argument checks, the pass plan, workspace, launches.  Every step of the path runs
-// in the kernels of eden_kernels.hip, eden_kernels_lo14.hip and eden_kernels_wg.hip.
+// in the kernels of eden_kernels*.hip.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -64,36 +64,30 @@ uint32_t coin_group_stride(int log2D_max) {
 // d rounded up to a multiple of 2^bits
 uint64_t round_up(uint64_t d, int bits) { return ((d + (1ull << bits) - 1) >> bits) << bits; }
 
-// Pass plan.  The contiguous pass covers the low 12 bits (wave tiles) or 14 bits (workgroup tiles); the
-// bits above it are covered by one or two strided passes: wave tiles handle up to 6 bits each,
-// workgroup tiles 7..10 bits.  D <= 2^24 needs two passes in all, D up to 2^27 three.  Encode runs the
-// passes in ascending bit order (contiguous first), decode in descending order (contiguous last).
-struct HiPass {
-    bool wg;    // workgroup-tile kernel (32-column tiles) or wave-tile kernel (64-column tiles)
-    int M, p;   // bits transformed, lowest bit
-    bool wide;  // wave-tile kernel with 8 columns per lane (top pass of the three-pass sizes; b = 1, 2, 4, 5..8, grid)
-};
+// Pass plan.  The contiguous pass covers the low 12 bits (wave tiles) or 14, 15, 16 bits (workgroup tiles); one strided pass
+// covers the bits above it: wave tiles handle up to 6 bits, workgroup tiles 7..11 bits.  Every D up to 2^27 needs two passes,
+// except D >= 2^25 when every sender of the launch has a one-byte budget: there a middle pass covers the bits 14 .. log2 D - 4
+// and wide wave tiles the top three.  Encode runs the contiguous pass first, decode runs it last.
 struct Plan {
     int lo_bits;        // 0: single-workgroup path (D <= 4096)
-    int nhi;
-    HiPass hi[2];       // ascending p
+    int M;              // bits of the strided pass, on top of the contiguous one (`wide`: of the middle pass)
+    bool wg;            // strided pass: workgroup-tile kernel (32-column tiles) or wave-tile kernel (64-column tiles)
+    bool wide;          // three passes
 };
-// `wide_ok`: every sender of the launch has b = 1, 2, 4 or a one-byte budget (what the wide top tile packs).
-Plan make_plan(int log2D, bool wide_ok) {
-    Plan pl{};
-    if (log2D <= kLoBits) return pl;
-    if (log2D <= 18) {
-        pl.lo_bits = 12; pl.nhi = 1; pl.hi[0] = {false, log2D - 12, 12, false};
-    } else if (log2D <= 24) {
-        const int M = log2D - 14;
-        pl.lo_bits = 14; pl.nhi = 1; pl.hi[0] = {M > 6, M, 14, false};
-    } else if (wide_ok) {
-        pl.lo_bits = 14; pl.nhi = 2; pl.hi[0] = {true, log2D - 17, 14, false}; pl.hi[1] = {false, 3, log2D - 3, true};
-    } else {
-        // the pass next to the payload gets as many rows per wave as the remaining bits allow (16..64)
-        pl.lo_bits = 14; pl.nhi = 2; pl.hi[0] = {true, 7, 14, false}; pl.hi[1] = {false, log2D - 21, 21, false};
-    }
-    return pl;
+Plan make_plan(int log2D, bool all_bytes) {
+    if (log2D <= kLoBits) return Plan{0, 0, false, false};
+    if (log2D >= 25 && all_bytes) return Plan{14, log2D - 17, false, true};
+    // from D = 2^25 on: the contiguous pass grows, first to the 2^15 coordinates a workgroup of 16 waves keeps on chip with
+    // its sums, at 2^27 to pairs of them; the strided pass has 11 bits at most (2^16 coordinates in registers)
+    const int lo = log2D <= 18 ? 12 : log2D <= 24 ? 14 : log2D <= 26 ? 15 : 16;
+    return Plan{lo, log2D - lo, log2D - lo > 6, false};
+}
+// whether the last decode launch of a batch sums all its senders and can write the mean itself
+bool one_launch_sums(const Plan &pl) { return pl.lo_bits != 12; }
+bool all_byte_budgets(const uint32_t *b_q8, uint32_t n) {
+    bool all = true;
+    for (uint32_t c = 0; c < n; ++c) all = all && byte_budget(b_q8[c]);
+    return all;
 }
 
 struct DeviceGuard {
@@ -242,10 +236,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                         void *const *msgs_dev, hipStream_t st) {
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;            // dimension of the vector that is transformed
     const int log2D = ceil_log2(d);
-    bool wide_ok = true;
-    for (uint32_t c = 0; c < n; ++c)
-        wide_ok = wide_ok && (b_kernel[c] == 256u || b_kernel[c] == 512u || b_kernel[c] == 1024u || byte_budget(b_kernel[c]));
-    const Plan pl = make_plan(log2D, wide_ok);
+    const Plan pl = make_plan(log2D, all_byte_budgets(b_kernel, n));
 
     for (uint32_t first = 0; first < n; first += kMaxBatch) {
         const uint32_t nb = (n - first < (uint32_t)kMaxBatch) ? n - first : (uint32_t)kMaxBatch;
@@ -286,7 +277,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             // (a word per 32 coordinates) and a small kernel strings them together: no atomics in the last pass.
             const uint32_t *pieces[kMaxBatch] = {};
             bool staged = false;
-            if (coins && ctx->codes && pl.hi[pl.nhi - 1].wg) {
+            if (coins && ctx->codes && pl.wg) {
                 for (uint32_t i = 0; i < nb; ++i) {
                     if (!coin_q8(B.b_q8[i])) continue;
                     B.codes[i] = ctx->codes + ((size_t)i << log2D);
@@ -294,38 +285,34 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                     staged = true;
                 }
             }
-            // The workspace goes through the blocked layout when a workgroup-tile pass reads it back right away (two-pass
-            // plans of D >= 2^21), unless the first pass works in place on the workspace (its input is a slot): its
-            // workgroups would then overwrite rows that others have not read yet.
-            bool blocked = pl.lo_bits == 14 && pl.nhi == 1 && pl.hi[0].wg;
+            // The workspace goes through the blocked layout when a workgroup-tile pass reads it (D >= 2^21), unless the first pass
+            // works in place on the workspace (its input is a slot, D <= 2^24): its workgroups would then overwrite rows that
+            // others have not read yet.
+            bool blocked = pl.wg;
             for (uint32_t i = 0; i < nb; ++i)
                 blocked = blocked && !(ctx->T && B.x[i] >= ctx->T && B.x[i] < ctx->T + ((size_t)ctx->slots << ctx->log2D_max));
             {
                 Timed t(ctx, EDEN_K_ENC_FIRST, nb, st);
-                nparts_n2 = pl.lo_bits == 14
-                                ? launch_enc_lo14_first(B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
-                                : launch_enc_lo_first(B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st);
+                nparts_n2 = pl.lo_bits >= 15   ? launch_enc_lo15_first(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
+                            : pl.lo_bits == 14 ? launch_enc_lo14_first(B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
+                                               : launch_enc_lo_first(B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st);
             }
             if (need_thresholds) {
                 Timed t(ctx, EDEN_K_ENC_NORM, nb, st);
                 launch_enc_norm(B, nb, part_n2, ctx->partial_stride, nparts_n2, ctx->enc_scratch, ctx->tables, st);
             }
-            uint64_t valid = round_up(d, pl.lo_bits);            // workspace elements written so far; the rest is zero
-            for (int i = 0; i < pl.nhi; ++i) {
-                const HiPass &h = pl.hi[i];
-                if (i < pl.nhi - 1) {
-                    Timed t(ctx, EDEN_K_MID, nb, st);
-                    launch_hix_mid(h.M, nb, ctx->T, log2D, valid, 1ull << log2D, st);
-                    valid = round_up(d, h.p + h.M);
-                } else {
-                    Timed t(ctx, EDEN_K_ENC_LAST, nb, st);
-                    nparts_ip = h.wg     ? launch_enc_hix_last(h.M, blocked, B, nb, d, log2D, seed, ctx->T, part_ip, ctx->partial_stride,
-                                                               ctx->enc_scratch, ctx->coin, st)
-                                : h.wide ? launch_enc_wide_last(B, nb, valid, log2D, ctx->T, part_ip, ctx->partial_stride,
-                                                                ctx->enc_scratch, st)
-                                         : launch_enc_hi_last(h.M, B, nb, valid, log2D, h.p, seed, ctx->T, part_ip,
-                                                              ctx->partial_stride, ctx->enc_scratch, ctx->coin, st);
-                }
+            if (pl.wide) {
+                Timed t(ctx, EDEN_K_MID, nb, st);
+                launch_hix_mid(pl.M, nb, ctx->T, log2D, round_up(d, 14), 1ull << log2D, st);
+            }
+            {
+                Timed t(ctx, EDEN_K_ENC_LAST, nb, st);
+                nparts_ip = pl.wide ? launch_enc_wide_last(B, nb, round_up(d, 14 + pl.M), log2D, ctx->T, part_ip, ctx->partial_stride,
+                                                           ctx->enc_scratch, st)
+                            : pl.wg ? launch_enc_hix_last(pl.M, pl.lo_bits, blocked, B, nb, d, log2D, seed, ctx->T, part_ip, ctx->partial_stride,
+                                                        ctx->enc_scratch, ctx->coin, st)
+                                  : launch_enc_hi_last(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, ctx->T, part_ip,
+                                                       ctx->partial_stride, ctx->enc_scratch, ctx->coin, st);
             }
             if (pack) launch_pack_bits(B, nb, log2D, st);
             if (staged) launch_coin_pack(B.b_q8, pieces, part_b, nb, log2D, ctx->coin, st);
@@ -349,9 +336,10 @@ static int sparsify_mode(const uint32_t *b_q8, uint32_t n) {
     return -1;
 }
 
-// m-of-64 senders that go through the workspace slots in batches
-static bool sparse_same_m(const eden_ctx *ctx, const uint32_t *b_q8, uint32_t n) {
-    bool same = ctx->T != nullptr;
+// m-of-64 senders that go through the workspace slots in batches (up to the sizes whose contiguous passes can work in place; the
+// launches of a single sender fill the chip beyond them)
+static bool sparse_same_m(const eden_ctx *ctx, const uint32_t *b_q8, uint32_t n, uint64_t d) {
+    bool same = ctx->T != nullptr && ceil_log2((uint64_t)sparse_m(b_q8[0]) * ((d + 63) / 64)) <= 24;
     for (uint32_t c = 0; c < n; ++c) same = same && sparse_m(b_q8[c]) != 0 && sparse_m(b_q8[c]) == sparse_m(b_q8[0]);
     return same;
 }
@@ -382,7 +370,7 @@ static int encode_on(eden_ctx *ctx, const float *const *x_dev, const uint32_t *c
     if (mode == 1) return encode_range(ctx, x_dev, client_ids, ones, b_q8, n, d, 1, d, seed, msgs_dev, st);
     // b = m/64.  Senders that share m: a launch gathers the kept coordinates of a batch into the workspace slots, and the
     // 1-bit method then runs on the slots in place (a first-pass workgroup has read a tile before it writes it).
-    if (sparse_same_m(ctx, b_q8, n)) {
+    if (sparse_same_m(ctx, b_q8, n, d)) {
         const uint32_t m0 = sparse_m(b_q8[0]);
         const uint64_t dk0 = (uint64_t)m0 * ((d + 63) / 64);
         const int log2Dk = ceil_log2(dk0);
@@ -544,10 +532,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
                         float mean_n = 0.0f) {
     const uint64_t d = pre == 1 ? (d_src + 1) / 2 : d_src;       // dimension of the decoded vectors
     const int log2D = ceil_log2(d);
-    bool wide_ok = true;
-    for (uint32_t c = 0; c < n; ++c)
-        wide_ok = wide_ok && (b_kernel[c] == 256u || b_kernel[c] == 512u || b_kernel[c] == 1024u || byte_budget(b_kernel[c]));
-    const Plan pl = make_plan(log2D, wide_ok);
+    const Plan pl = make_plan(log2D, all_byte_budgets(b_kernel, n));
 
     for (uint32_t first = 0; first < n; first += kMaxBatch) {
         const uint32_t nb = (n - first < (uint32_t)kMaxBatch) ? n - first : (uint32_t)kMaxBatch;
@@ -574,38 +559,37 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived,
                              ctx->dev_status, flags_out + first, st);
         } else {
-            // Strided passes first (every sender on its own), contiguous pass last (sums the senders in registers
-            // and touches acc once).  With a single strided pass the workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).
-            const int narrow = (pl.nhi == 1 && pre != 2) ? 1 : 0;
+            // Strided pass first (every sender on its own), contiguous pass last (sums the senders in registers
+            // and touches acc once).  The workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).
+            const int narrow = (pre != 2 && !pl.wide) ? 1 : 0;
             bool coins = false;                                  // the receiver draws and counts the same coins
             for (uint32_t i = 0; i < nb; ++i) coins = coins || coin_q8(B.b_q8[i]);
             if (coins) launch_coin_tables(B.client, B.b_q8, nullptr, nb, seed, log2D, ctx->coin, st);
             // header checks, arrival counts and dequantization tables: a launch of its own, unless the first pass does them
             const DecPrepareArgs prep{hdr_d, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, flags_out + first};
-            const HiPass &top = pl.hi[pl.nhi - 1];
-            const bool first_prepares = top.wg && !coins && dec_hix_first_prepares(top.M, B, nb, narrow);
+            const bool first_prepares = pl.wg && !coins && dec_hix_first_prepares(pl.M, pl.lo_bits, B, nb, narrow);
             if (!first_prepares) {
                 Timed t(ctx, EDEN_K_DEC_PREPARE, nb, st);
                 launch_dec_prepare(B, nb, hdr_d, log2D, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, ctx->coin.total,
                                    flags_out + first, st);
             }
-            for (int i = pl.nhi - 1; i >= 0; --i) {
-                const HiPass &h = pl.hi[i];
-                // what the passes after this one read: whole tiles of theirs that hold part of the first d coordinates
-                const uint64_t keep = round_up(d, h.p);
-                if (i == pl.nhi - 1) {
-                    Timed t(ctx, EDEN_K_DEC_FIRST, nb, st);
-                    if (h.wg) launch_dec_hix_first(h.M, B, nb, d, log2D, seed, ctx->dec_scratch, narrow, ctx->T, ctx->coin,
-                                                   first_prepares ? &prep : nullptr, st);
-                    else if (h.wide) launch_dec_wide_first(B, nb, keep, log2D, ctx->dec_scratch, ctx->T, st);
-                    else launch_dec_hi_first(h.M, B, nb, keep, log2D, h.p, seed, ctx->dec_scratch, narrow, ctx->T, ctx->coin, st);
-                } else {
-                    Timed t(ctx, EDEN_K_MID, nb, st);
-                    launch_hix_mid(h.M, nb, ctx->T, log2D, round_up(d, h.p + h.M), keep, st);
-                }
+            {
+                Timed t(ctx, EDEN_K_DEC_FIRST, nb, st);
+                if (pl.wide) launch_dec_wide_first(B, nb, round_up(d, 14 + pl.M), log2D, ctx->dec_scratch, ctx->T, st);
+                else if (pl.wg) launch_dec_hix_first(pl.M, pl.lo_bits, B, nb, d, log2D, seed, ctx->dec_scratch, narrow, ctx->T, ctx->coin,
+                                                first_prepares ? &prep : nullptr, st);
+                // what the last pass reads: whole tiles of it that hold part of the first d coordinates
+                else launch_dec_hi_first(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, ctx->dec_scratch, narrow, ctx->T,
+                                         ctx->coin, st);
+            }
+            if (pl.wide) {
+                Timed t(ctx, EDEN_K_MID, nb, st);
+                launch_hix_mid(pl.M, nb, ctx->T, log2D, round_up(d, 14 + pl.M), round_up(d, 14), st);
             }
             Timed t(ctx, EDEN_K_DEC_LAST, nb, st);
-            if (pl.lo_bits == 14)
+            if (pl.lo_bits >= 15)
+                launch_dec_lo15_last(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, acc_dev, mean_n, st);
+            else if (pl.lo_bits == 14)
                 launch_dec_lo14_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, narrow, acc_dev, 2 * ctx->compute_units,
                                      ctx->dec_partial, ctx->dec_partial_tiles, mean_n, st);
             else launch_dec_lo_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, narrow, acc_dev, st);
@@ -657,22 +641,20 @@ int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t 
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return EDEN_ERR_HIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    auto one_launch_sums = [](const Plan &pl) { return pl.lo_bits == 0 || pl.lo_bits == 14; };
-    if (mode == 0 && n <= (uint32_t)kMaxBatch && one_launch_sums(make_plan(ceil_log2(d), false))) {
+    if (mode == 0 && n <= (uint32_t)kMaxBatch && one_launch_sums(make_plan(ceil_log2(d), all_byte_budgets(b_q8, n)))) {
         ctx->last_decode_n = n;
         return decode_range(ctx, msgs_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, recv_bitmaps_dev, mean_dev, ctx->msg_flags, st,
                             (float)n);
     }
-    if (mode == 1 && n <= (uint32_t)kMaxBatch) {                 // pairs before the rotation: the same with one strided pass
-        const Plan pl = make_plan(ceil_log2((d + 1) / 2), true);
-        if (pl.lo_bits == 0 || (pl.lo_bits == 14 && pl.nhi == 1)) {
+    if (mode == 1 && n <= (uint32_t)kMaxBatch) {                 // pairs before the rotation
+        if (one_launch_sums(make_plan(ceil_log2((d + 1) / 2), false))) {
             std::vector<uint32_t> ones(n, 256u);
             ctx->last_decode_n = n;
             return decode_range(ctx, msgs_dev, client_ids, ones.data(), b_q8, n, d, 1, d, seed, recv_bitmaps_dev, mean_dev,
                                 ctx->msg_flags, st, (float)n);
         }
     }
-    if (mode == 2 && n <= ctx->slots && sparse_same_m(ctx, b_q8, n))         // one launch adds the values of all senders
+    if (mode == 2 && n <= ctx->slots && sparse_same_m(ctx, b_q8, n, d))         // one launch adds the values of all senders
         return decode_accumulate_on(ctx, mode, msgs_dev, client_ids, b_q8, n, d, seed, recv_bitmaps_dev, mean_dev, st, (float)n);
     launch_fill_zero(mean_dev, d, st);
     if (!launch_ok()) return EDEN_ERR_HIP;
@@ -695,7 +677,7 @@ static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs
     // b = m/64 (the factor 64/m is folded into the dequantization).  Senders that share m: a batch is decoded without
     // summing, every sender into its own workspace slot, and one launch adds the values to the coordinates of acc they were
     // taken from.
-    if (sparse_same_m(ctx, b_q8, n)) {
+    if (sparse_same_m(ctx, b_q8, n, d)) {
         const uint32_t m0 = sparse_m(b_q8[0]);
         const uint64_t dk0 = (uint64_t)m0 * ((d + 63) / 64);
         const int log2Dk = ceil_log2(dk0);
@@ -717,11 +699,13 @@ static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs
     for (uint32_t c = 0; c < n; ++c) {
         const uint32_t m = sparse_m(b_q8[c]);
         const uint64_t dk = (uint64_t)m * ((d + 63) / 64);
-        launch_fill_zero(ctx->stage, dk, st);
+        // (one sender: its "mean" is written, not added to a zeroed vector, where one launch does the whole sum)
+        const bool writes = one_launch_sums(make_plan(ceil_log2(dk), false));
+        if (!writes) launch_fill_zero(ctx->stage, dk, st);
         if (!launch_ok()) return EDEN_ERR_HIP;
         const uint32_t *bm = recv_bitmaps_dev ? recv_bitmaps_dev[c] : nullptr;
         const int rc = decode_range(ctx, &msgs_dev[c], &client_ids[c], ones.data(), &b_q8[c], 1, dk, 0, d, seed,
-                                    recv_bitmaps_dev ? &bm : nullptr, ctx->stage, ctx->msg_flags + c, st);
+                                    recv_bitmaps_dev ? &bm : nullptr, ctx->stage, ctx->msg_flags + c, st, writes ? 1.0f : 0.0f);
         if (rc != EDEN_OK) return rc;
         DecBatch B;
         std::memset(&B, 0, sizeof(B));

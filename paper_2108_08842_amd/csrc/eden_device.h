@@ -145,6 +145,7 @@ struct EncScratch {
     float thr2[8];          // mixed budgets: the same for I_{floor(b)+1}
     float qpos2[8];
     float grid_inv;         // uniform grid: 1 / (Delta |x|), so that round(u * grid_inv) is the index
+    float guess_c1, guess_c3, guess_cap, guess_up;      // b = 4: see quantize_guess
     unsigned pad;
     float grid_c[kGridMax + 1];     // uniform grid: centre of mass of the interval of index n >= 0; b = 5..8: positive centroids
     float wide_thr[128];            // b = 5..8: positive thresholds times |x|
@@ -203,6 +204,9 @@ __device__ inline float negate_where(float v, uint64_t mask) {
 __device__ inline float keep_where(float v, uint64_t mask) {
     return __builtin_amdgcn_inverse_ballot_w64(mask) ? v : 0.0f;
 }
+
+// a float that is the same in every lane, in a scalar register
+__device__ inline float uniform(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
 
 // The 64-bit value held by lane `src` (compile-time constant), as a wave-uniform scalar.
 __device__ inline uint64_t wave_read64(uint64_t v, int src) {
@@ -345,53 +349,52 @@ __device__ inline uint32_t quantize_one(float u, const EncScratch *sc, const flo
     return neg ? (uint32_t)(H - 1) - mag : (uint32_t)H + mag;
 }
 
-// The same search through a table, for kernels that spend their time on it (H = 8: fourteen instructions above).  |u| is
-// cut into kRankCells cells of equal width, the last threshold falling into the last but one; a cell holds at most one
-// threshold (the Lloyd-Max thresholds of up to 16 levels lie at least six cells apart), so the rank is the number of
-// thresholds in lower cells plus one compare.  The result is the one of magnitude_rank for every input: the cell number is a
-// monotone function of |u| (a rounded product, clamped and truncated), hence a value in a higher cell than a threshold is above
-// it and one in a lower cell is below it, and inside the threshold's own cell the compare decides as it does there.  |x| = 0:
-// `inv` is 0, every value is 0 and lands in cell 0, whose threshold is 0: rank 0.  A vector so small that 62 / threshold
-// overflows (|x| / sqrt(D) below 1e-37) would put several thresholds into one cell: fill_rank_table reports that (a cell's
-// `below` of kRankCollision) and the caller counts thresholds for that sender instead.
-constexpr int kRankCells = 64;
-constexpr uint32_t kRankCollision = 0x80000000u;
-struct RankCell {
-    float thr;              // the threshold inside the cell, +inf if there is none
-    float q_below, q_above; // centroids of the rank without and with that threshold passed
-    uint32_t below;         // thresholds in lower cells
+// The same search in one guess and one compare, for kernels that spend their time on it (16 levels: fourteen instructions above).
+// The number of a Lloyd-Max threshold is nearly a quadratic function of its value: with r(t) = t (1 + c3 |t|), t = u c1, through
+// thresholds H / 2 and H - 1, r differs from the number of every other threshold of I_4 by less than 0.07.  The threshold with the
+// number nearest to r is therefore the one above or the one below u, and comparing u with it alone gives the index.  The
+// result is the one of quantize_one for every input: the margin (0.43 of a number) is far beyond the rounding of r, t is capped
+// above the outermost threshold where r still rises, and the compare is exact: a value on a positive threshold stays below
+// it, one on a negative threshold (or on 0) stays above it, which "u > the float just below the threshold" says with
+// the same compare.  Where c1 would overflow (|x| below 2e-38) values and thresholds are multiplied by 2^60 first, exactly.
+// |x| = 0 or not finite: any index in range will do, the payload is cleared afterwards (the cap, a constant, keeps it in range).
+// Two four-byte reads of tables of 18 entries (lanes that hit one bank read one address: no conflicts); a table of 64 cells
+// with the threshold, both centroids and the count in 16 bytes cost three times their LDS time.
+template <int H>
+struct RankGuess {
+    float thr[2 * H + 2];   // [s], s = 1 .. 2 H - 1: the signed thresholds in order, as what u has to exceed
+    float q[2 * H + 2];     // [index + 1]: signed centroids
 };
-__device__ inline uint32_t rank_cell_of(float a, float inv) { return (uint32_t)fminf(a * inv, (float)(kRankCells - 1)); }
-__device__ inline float rank_cell_scale(const EncScratch *sc, int H) {
-    const float last = sc->thr[H - 1];
-    return last > 0.0f ? (float)(kRankCells - 2) / last : 0.0f;
-}
 template <int H>
-__device__ inline void fill_rank_table(RankCell *cells, const EncScratch *sc, uint32_t thread, float inv) {
-    if (thread >= (uint32_t)kRankCells) return;
-    RankCell e{__builtin_inff(), 0.0f, 0.0f, 0u};
-    uint32_t here = 0;
+__device__ inline void fill_rank_guess(RankGuess<H> &g, const EncScratch *sc, uint32_t thread) {
+    if (thread >= 2u * H + 2u) return;
+    const int j = (int)thread - H;                               // the float just below -thr (or 0) has the next larger magnitude
+    const float mag = (j > -H && j < H && j != 0) ? sc->thr[j < 0 ? -j : j] * sc->guess_up : 0.0f;
+    g.thr[thread] = j <= -H || j >= H ? __builtin_inff() : j > 0 ? mag : __uint_as_float(0x80000000u | (__float_as_uint(mag) + 1u));
+    const int index = (int)thread - 1;
+    g.q[thread] = index < 0 || index >= 2 * H ? 0.0f : index >= H ? sc->qpos[index - H] : -sc->qpos[H - 1 - index];
+}
+// at[i] = index + 1 of u[i], which is sc->guess_up times the value.  The table reads of N values are issued together: one value
+// after the other, as the compiler would schedule it, every value waits for the LDS twice.
+template <int H, int N>
+__device__ inline void quantize_guess(const float *u, const RankGuess<H> &g, const EncScratch *sc, uint32_t (&at)[N], float &ip) {
+    const float c1 = sc->guess_c1, c3 = sc->guess_c3, cap = sc->guess_cap;
+    float t[N];
 #pragma unroll
-    for (int t = 1; t < H; ++t) {
-        const uint32_t cell = rank_cell_of(sc->thr[t], inv);
-        e.below += cell < thread ? 1u : 0u;
-        if (cell == thread) { e.thr = sc->thr[t]; ++here; }
+    for (int i = 0; i < N; ++i) {
+        const float v = __builtin_amdgcn_fmed3f(u[i] * c1, -cap, cap);
+        at[i] = (uint32_t)fmaf(v, fmaf(fabsf(v), c3, 1.0f), (float)H + 0.5f);
+        t[i] = g.thr[at[i]];
     }
-    const bool collision = __ballot(here > 1u && sc->thr[H - 1] > 0.0f) != 0ull;      // (threads 0..63 are one wave)
-    e.q_below = sc->qpos[e.below];
-    e.q_above = sc->qpos[e.below + 1u < (uint32_t)H ? e.below + 1u : (uint32_t)H - 1u];
-    if (collision) e.below = kRankCollision;
-    cells[thread] = e;
-}
-template <int H>
-__device__ inline uint32_t quantize_one_table(float u, const RankCell *cells, float inv, float &ip) {
-    const float a = fabsf(u);
-    const RankCell e = cells[rank_cell_of(a, inv)];
-    const bool above = a > e.thr;
-    const uint32_t mag = e.below + (above ? 1u : 0u);
-    ip = fmaf(a, above ? e.q_above : e.q_below, ip);
-    const uint32_t neg = (uint32_t)((int)__float_as_uint(u) >> 31);      // all ones for a negative value
-    return (mag ^ neg) + (uint32_t)H;                                    // H + mag, or H - 1 - mag
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        at[i] += u[i] > t[i] ? 1u : 0u;
+        t[i] = g.q[at[i]];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) ip = fmaf(u[i], t[i], ip);       // (|u| |q|: u and its centroid have the same sign)
 }
 
 // ---- collecting ballots in lanes, and bit interleaving for the packed payload
@@ -585,6 +588,14 @@ __device__ inline void fill_enc_scratch(EncScratch *s, double n2, uint32_t b_q8,
     s->qpos[tid] = (float)tab->q[bits][tid];
     s->thr2[tid] = (float)(tab->t[finer][tid] * norm);
     s->qpos2[tid] = (float)tab->q[finer][tid];
+    if (bits == 4 && tid == 0u) {                                // r(x) = a x + b x |x|, x = u / (the last threshold): r = 4, 7 at thresholds 4, 7
+        const double last = tab->t[4][7], m = tab->t[4][4] / last, b = (7.0 - 4.0 / m) / (1.0 - m), a = 7.0 - b;
+        const double up = last * norm < 0x1p-124 ? 0x1p60 : 1.0;
+        s->guess_c1 = (float)(a / (last * norm * up));
+        s->guess_c3 = (float)(b / (a * a));
+        s->guess_cap = (float)(1.1 * a);
+        s->guess_up = (float)up;
+    }
 }
 // The tables of the one-byte budgets, one entry per thread (tid < 128): the centres of mass of the uniform grid's
 // intervals, or the positive centroids and scaled thresholds of the 32..256-level quantizers.
@@ -632,16 +643,49 @@ __device__ inline uint32_t narrow_pair_from_int16(uint32_t w) {
     return w;
 }
 
-// ---- blocked layout of the encoder's workspace between the 14-bit contiguous pass and a workgroup-tile strided pass that
+// ---- blocked layout of the encoder's workspace between the contiguous pass over P bits and a workgroup-tile strided pass that
 // covers all the bits above it.  Element (row r, column block cb of 32 coordinates, column) of a sender's slot sits, in
 // floats, at ((r / R) * 512 + cb) * (R * 32) + (r % R) * 32 + column with R = kBlockRows: the 128-byte segments of R
-// consecutive rows are interleaved.  Row-major would be r * 2^14 + cb * 32 + column.  (At 16 senders of 2^24: R = 4 took the
+// consecutive rows are interleaved.  Row-major would be r * 2^14 + cb * 32 + column.  (P = 14; rows of 2^P coordinates have 2^(P-5) column blocks.)  (At 16 senders of 2^24: R = 4 took the
 // strided pass from 170 to 156 us and left the contiguous pass where it was; R = 8 slowed both passes by 10 us.)
 constexpr uint32_t kBlockRows = 4;
 constexpr uint32_t kBlockRowBits = 2;
+template <int P>
 __host__ __device__ inline size_t blocked_offset(uint32_t row, uint32_t cb) {
-    return ((size_t)(row >> kBlockRowBits) << (14 + kBlockRowBits)) + ((size_t)cb << (5 + kBlockRowBits)) +
+    return ((size_t)(row >> kBlockRowBits) << (P + kBlockRowBits)) + ((size_t)cb << (5 + kBlockRowBits)) +
            ((size_t)(row & (kBlockRows - 1u)) << 5);
+}
+
+// Stores the 32 consecutive values every thread holds after the last stage of a contiguous pass over P bits as whole 128-byte lines: thread t's
+// run starts at coordinate 32 t of the (half) tile, so a wave owns 2048 consecutive coordinates; a wave-private
+// transpose through LDS (quads swizzled by the low three bits of the row: eight neighbouring lanes then hit 32
+// different banks in both directions; measured with SQ_LDS_BANK_CONFLICT) lets 8 neighbouring lanes store one line.
+// `L`: this wave's 2048 floats of LDS; `Tc`: the sender's workspace slot; `tile`: the tile = row of the strided
+// pass; `segment`: the wave's first run of 32 coordinates inside the row.
+// BLOCKED: the 128-byte segments of kBlockRows consecutive rows are interleaved (see blocked_offset): the strided pass
+// then finds kBlockRows of its 128-byte pieces next to each other.  Stores cost the same either way (6.9 TB/s in a pure
+// store loop); a pure read of the strided pattern went from 4.8 to 5.9 TB/s.
+template <int P, bool BLOCKED>
+__device__ inline void store_runs(const float (&v)[32], float *L, float *Tc, uint32_t tile, uint32_t segment) {
+    const uint32_t lane = threadIdx.x & 63u;
+    wave_lds_sync();
+    const uint32_t swz = lane & 7u;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        *reinterpret_cast<float4 *>(&L[lane * 32u + 4u * ((uint32_t)q ^ swz)]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    wave_lds_sync();
+    const uint32_t pos = lane & 7u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t row = 8u * (uint32_t)j + (lane >> 3);     // segment of 32 coordinates inside the wave's 2048
+        const float4 x = *reinterpret_cast<const float4 *>(&L[row * 32u + 4u * pos]);
+        const uint32_t quad = pos ^ (row & 7u);
+        // (write-back stores: with the streaming hint this pass ran 13% slower; the pass that reads the tiles back does
+        // better with the hint on its loads)
+        const size_t at = BLOCKED ? blocked_offset<P>(tile, segment + row) + 4u * quad
+                                  : ((size_t)tile << P) + 32u * (segment + row) + 4u * quad;
+        *reinterpret_cast<float4 *>(Tc + at) = x;
+    }
 }
 
 // ---- coin budgets: positions in the second part of the payload

@@ -26,8 +26,7 @@ void launch_coin_pack(const uint32_t *b_q8, const uint32_t *const *pieces, void 
                       const CoinTables &ct, hipStream_t st);
 void launch_coin_tables(const uint32_t *clients, const uint32_t *b_q8, void *const *part_b, uint32_t n, uint64_t seed, int log2D,
                         const CoinTables &ct, hipStream_t st);
-// wide strided tiles (8 rows x 512 columns per wave) for the top three index bits of D >= 2^25; b = 1, 2, 4, 5..8 and
-// the uniform grid
+// wide strided tiles (8 rows x 512 columns per wave) for the top three index bits of D >= 2^25, one-byte budgets only
 uint32_t launch_enc_wide_last(const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, const float *T, double *partials,
                               uint32_t partial_stride, const EncScratch *scratch, hipStream_t st);
 void launch_dec_wide_first(const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, const DecScratch *scratch, float *T,
@@ -75,11 +74,11 @@ void launch_sq_error(const float *a, const float *b, uint64_t d, double *partial
 void launch_hash_bits(uint64_t key, uint64_t nwords, uint64_t *out, hipStream_t st);
 void launch_loss_bitmap(uint64_t key, uint32_t npk, uint32_t drop_q32, uint32_t *bitmap, hipStream_t st);
 
-// workgroup-tile strided passes for D >= 2^21 (eden_kernels_wg.hip)
-uint32_t launch_enc_hix_last(int M, int blocked, const EncBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed, const float *T,
+// workgroup-tile strided passes for D >= 2^21: M bits on top of a contiguous pass over P bits (eden_kernels_wg.hip,
+// eden_kernels_wg_dec.hip)
+uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed, const float *T,
                              double *partials, uint32_t partial_stride, const EncScratch *scratch, const CoinTables &ct,
                              hipStream_t st);
-void launch_hix_mid(int M, uint32_t n, float *T, int log2D, uint64_t load_elems, uint64_t store_elems, hipStream_t st);
 // What dec_prepare_wave needs besides the batch; a first decode pass that is given it (`prep` not null) may do the work of
 // launch_dec_prepare itself, in one of its workgroups per sender, and then returns true: the caller leaves that launch out.
 struct DecPrepareArgs {
@@ -89,13 +88,14 @@ struct DecPrepareArgs {
     uint32_t *dev_status;
     uint32_t *msg_flags;                 // null or one word per sender of the batch
 };
-bool launch_dec_hix_first(int M, const DecBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
+void launch_hix_mid(int M, uint32_t n, float *T, int log2D, uint64_t load_elems, uint64_t store_elems, hipStream_t st);
+bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
                           const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, const DecPrepareArgs *prep,
                           hipStream_t st);
 // whether launch_dec_hix_first would do so for this batch
-bool dec_hix_first_prepares(int M, const DecBatch &B, uint32_t n, int narrow);
+bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int narrow);
 
-// 14-bit contiguous passes for D >= 2^19 (eden_kernels_lo14.hip)
+// 14-bit contiguous passes for D = 2^19 .. 2^24 (eden_kernels_lo14.hip)
 // `blocked`: write the workspace in the blocked layout (eden_device.h: blocked_offset) that launch_enc_hix_last reads
 // when told so; not for a first pass that works in place on the workspace
 uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int blocked, int log2D, uint64_t seed, float *T,
@@ -106,6 +106,13 @@ uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d, int pr
 void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
                           const DecScratch *scratch, int narrow, float *acc, uint32_t resident, float *partial,
                           uint32_t partial_tiles, float mean_n, hipStream_t st);
+
+// 15- and 16-bit contiguous passes for D = 2^25 .. 2^27 (eden_kernels_lo15.hip): the encoder's always writes the blocked layout,
+// the decoder's takes every b <= 1 sender's slot as fp16; pre == 2 (one output per sender) does not exist here
+uint32_t launch_enc_lo15_first(int P, const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
+                               double *partials, uint32_t partial_stride, hipStream_t st);
+void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, const float *T,
+                          const DecScratch *scratch, float *acc, float mean_n, hipStream_t st);
 
 }  // namespace eden
 #endif

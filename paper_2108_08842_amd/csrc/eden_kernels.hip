@@ -412,15 +412,14 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
 }
 
 // ------------------------------------------------------------------------------------------------
-// Wide strided tiles for the top three index bits of the three-pass sizes (D >= 2^25), budgets b = 1, 2, 4 and the
-// one-byte budgets (b = 5..8, uniform grid):
+// Wide strided tiles for the top three index bits of D >= 2^25 when every sender has a one-byte budget (b = 5..8, uniform grid):
+// these go through three passes.  (With two, the pass next to the payload moves the bytes in pieces of 32 and holds 2^16 values
+// while it searches 128 thresholds: one sender of 2^27 at b = 8 took 610 us instead of 600.)
 // a wave owns 8 rows of 512 consecutive coordinates at stride 2^p (p = log2 D - 3).  A lane holds, of every row,
 // the columns 4 l .. 4 l + 3 and 256 + 4 l .. 256 + 4 l + 3: each workspace access of a wave is then one dense
 // kilobyte (16 bytes per lane, no gaps; with 8 adjacent columns per lane the two halves of every 128-byte line
-// were written by different instructions and 1.7x the bytes reached memory), and a lane's four indices of a
-// half row are 4 b bits of payload: a half-word / byte / nibble per lane, 32..128 dense bytes per wave
-// (the one-column-per-lane wave tile moves a b = 4 payload in 32-byte pieces).
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// were written by different instructions and 1.7x the bytes reached memory), and a lane's four indices of a half row are
+// four bytes, 256 dense bytes per wave.
 constexpr int kWideRows = 8, kWideCols = 512;
 
 __device__ inline void wide_fwht(float (&v)[kWideRows][8]) {
@@ -434,10 +433,6 @@ __device__ inline void wide_fwht(float (&v)[kWideRows][8]) {
         for (int r = 0; r < kWideRows; ++r) v[r][e] = col[r];
     }
 }
-__device__ inline uint32_t wide_lane_xor1(uint32_t x) {         // value held by lane ^ 1
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);
-}
-
 // Encode, last pass (see k_enc_hi_last): index bits p .. p+2, quantization, sum_i u_i q_i, packing.
 __global__ __launch_bounds__(256) void k_enc_wide_last(EncBatch B, uint64_t valid_elems, int log2D, const float *T,
                                                        double *partials, uint32_t partial_stride,
@@ -464,15 +459,11 @@ __global__ __launch_bounds__(256) void k_enc_wide_last(EncBatch B, uint64_t vali
     char *payload = static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES;
     const uint32_t b_q8 = B.b_q8[c];
     const EncScratch *sc = &scratch[c];
-    __shared__ float qtabs[4][16];
-    __shared__ float gtabs[4][256];                              // one-byte budgets: centroids and thresholds
-    float *qtab = qtabs[wave_in_block()], *gtab = gtabs[wave_in_block()];
-    fill_qtab(qtab, sc, lane);
+    __shared__ float gtabs[4][256];                              // centroids and thresholds
+    float *gtab = gtabs[wave_in_block()];
     const float *byte_tab = sc->grid_c;                          // grid_c[128] and wide_thr[128] are one run of 256 floats
-    if (byte_budget(b_q8)) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) gtab[64 * q + lane] = byte_tab[64 * q + lane];
-    }
+    for (int q = 0; q < 4; ++q) gtab[64 * q + lane] = byte_tab[64 * q + lane];
     wave_lds_sync();
     float ip = 0.0f;
     // the choice of the budget sits outside the loops over the 16 groups (group = this lane's 4 coordinates of a row half)
@@ -482,27 +473,7 @@ __global__ __launch_bounds__(256) void k_enc_wide_last(EncBatch B, uint64_t vali
 #pragma unroll
             for (int h = 0; h < 2; ++h) pack((base + 256u * h + ((uint32_t)r << p)) / 4u + lane, r, h);
     };
-    if (b_q8 == 256u) {                                          // I_1: the index is the sign, |Q| = q_1
-        for_groups([&](uint32_t group, int r, int h) {
-            float sa = 0.0f;
-            uint32_t word = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sa += fabsf(v[r][4 * h + e]);
-                word |= ((~__float_as_uint(v[r][4 * h + e])) >> 31) << e;            // index 1 = non-negative
-            }
-            ip = fmaf(sa, kQ1, ip);
-            word |= wide_lane_xor1(word) << 4;                   // two lanes = one byte
-            if (!(lane & 1u)) reinterpret_cast<uint8_t *>(payload)[group >> 1] = (uint8_t)word;
-        });
-    } else if (b_q8 == 512u) {
-        for_groups([&](uint32_t group, int r, int h) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) word |= quantize_one<2>(v[r][4 * h + e], sc, qtab, ip) << (2 * e);
-            reinterpret_cast<uint8_t *>(payload)[group] = (uint8_t)word;
-        });
-    } else if (grid_q15(b_q8)) {                                  // uniform grid: one byte per coordinate
+    if (grid_q15(b_q8)) {                                        // uniform grid: one byte per coordinate
         const float inv = sc->grid_inv;
         for_groups([&](uint32_t group, int r, int h) {
             uint32_t word = 0;
@@ -510,7 +481,7 @@ __global__ __launch_bounds__(256) void k_enc_wide_last(EncBatch B, uint64_t vali
             for (int e = 0; e < 4; ++e) word |= quantize_byte<true>(v[r][4 * h + e], 0u, inv, gtab, ip) << (8 * e);
             reinterpret_cast<uint32_t *>(payload)[group] = word;
         });
-    } else if (wide_bits(b_q8)) {                                 // b = 5..8: one byte per coordinate
+    } else {                                                     // b = 5..8
         const uint32_t H = wide_half_levels(b_q8);
         uint32_t *dst = reinterpret_cast<uint32_t *>(B.codes[c] ? reinterpret_cast<char *>(B.codes[c]) : payload);
         for_groups([&](uint32_t group, int r, int h) {
@@ -518,13 +489,6 @@ __global__ __launch_bounds__(256) void k_enc_wide_last(EncBatch B, uint64_t vali
 #pragma unroll
             for (int e = 0; e < 4; ++e) word |= quantize_byte<false>(v[r][4 * h + e], H, 0.0f, gtab, ip) << (8 * e);
             dst[group] = word;
-        });
-    } else {
-        for_groups([&](uint32_t group, int r, int h) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) word |= quantize_one<8>(v[r][4 * h + e], sc, qtab, ip) << (4 * e);
-            reinterpret_cast<uint16_t *>(payload)[group] = (uint16_t)word;
         });
     }
     const double block_total = block_sum<256>((double)ip, red);
@@ -535,7 +499,6 @@ __global__ __launch_bounds__(256) void k_enc_wide_last(EncBatch B, uint64_t vali
 // p .. p+2.  A row segment of 512 coordinates lies inside one packet of 1024.
 __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t keep_elems, int log2D, const DecScratch *scratch,
                                                         float *T) {
-    __shared__ float table[4][16];
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id(), wv = wave_in_block();
     const int p = log2D - 3;
@@ -543,10 +506,9 @@ __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t kee
     const uint32_t base = tile * (uint32_t)kWideCols;
     __shared__ float gtabs[4][kGridMax + 1];
     const uint32_t b_q8 = B.b_q8[c];
-    if (lane < 16) table[wv][lane] = scratch[c].deq[lane];
-    if (byte_budget(b_q8)) { gtabs[wv][lane] = scratch[c].grid_deq[lane]; gtabs[wv][64 + lane] = scratch[c].grid_deq[64 + lane]; }
+    gtabs[wv][lane] = scratch[c].grid_deq[lane];
+    gtabs[wv][64 + lane] = scratch[c].grid_deq[64 + lane];
     wave_lds_sync();
-    const float *tb = table[wv];
     const char *payload = static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES;
     const char *bytes = B.codes[c] ? reinterpret_cast<const char *>(B.codes[c]) : payload;
     const uint32_t *bm = B.bitmap[c];
@@ -578,22 +540,13 @@ __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t kee
                 for (int e = 0; e < 4; ++e) v[r][4 * h + e] = ((here >> r) & 1u) ? value(word[r][h], e) : 0.0f;
     };
     const float *gt = gtabs[wv];
-    if (b_q8 == 256u) {
-        for_groups([&](uint32_t g) { return (uint32_t)reinterpret_cast<const uint8_t *>(payload)[g >> 1] >> (4u * (lane & 1u)); });
-        for_values([&](uint32_t w, int e) { return tb[(w >> e) & 1u]; });
-    } else if (b_q8 == 512u) {
-        for_groups([&](uint32_t g) { return (uint32_t)reinterpret_cast<const uint8_t *>(payload)[g]; });
-        for_values([&](uint32_t w, int e) { return tb[(w >> (2 * e)) & 3u]; });
-    } else if (grid_q15(b_q8)) {
+    if (grid_q15(b_q8)) {
         for_groups([&](uint32_t g) { return reinterpret_cast<const uint32_t *>(bytes)[g]; });
         for_values([&](uint32_t w, int e) { return dequantize_byte<true>((w >> (8 * e)) & 0xFFu, 0u, gt); });
-    } else if (wide_bits(b_q8)) {
+    } else {
         const uint32_t H = wide_half_levels(b_q8);
         for_groups([&](uint32_t g) { return reinterpret_cast<const uint32_t *>(bytes)[g]; });
         for_values([&](uint32_t w, int e) { return dequantize_byte<false>((w >> (8 * e)) & 0xFFu, H, gt); });
-    } else {
-        for_groups([&](uint32_t g) { return (uint32_t)reinterpret_cast<const uint16_t *>(payload)[g]; });
-        for_values([&](uint32_t w, int e) { return tb[(w >> (4 * e)) & 15u]; });
     }
     wide_fwht(v);
     const rsrc_t rt = make_rsrc(T + ((size_t)c << log2D), (uint32_t)(keep_elems * 4));

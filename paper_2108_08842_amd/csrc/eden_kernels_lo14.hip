@@ -54,37 +54,6 @@ __device__ inline void lo14_forward32(float (&v)[32], float *lds) {
     fwht_regs_low<32, 4>(v);                                     // bits 0..3 (bit 4 rides along)
 }
 
-// Stores the 32 consecutive values every thread holds after lo14_forward32 as whole 128-byte lines: thread t's
-// run starts at coordinate 32 t of the tile, so a wave owns 2048 consecutive coordinates; a wave-private
-// transpose through LDS (quads swizzled by the low three bits of the row: eight neighbouring lanes then hit 32
-// different banks in both directions; measured with SQ_LDS_BANK_CONFLICT) lets 8 neighbouring lanes store one line.
-// `L`: this wave's 2048 floats of LDS; `Tc`: the sender's workspace slot; `tile`: the tile = row of the strided pass.
-// BLOCKED: the 128-byte segments of kBlockRows consecutive rows are interleaved (see blocked_offset): the strided pass
-// then finds kBlockRows of its 128-byte pieces next to each other.  Stores cost the same either way (6.9 TB/s in a pure
-// store loop); a pure read of the strided pattern went from 4.8 to 5.9 TB/s.
-template <bool BLOCKED>
-__device__ inline void lo14_store_runs(const float (&v)[32], float *L, float *Tc, uint32_t tile, uint32_t wv) {
-    const uint32_t lane = threadIdx.x & 63u;
-    wave_lds_sync();
-    const uint32_t swz = lane & 7u;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        *reinterpret_cast<float4 *>(&L[lane * 32u + 4u * ((uint32_t)q ^ swz)]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    wave_lds_sync();
-    const uint32_t pos = lane & 7u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t row = 8u * (uint32_t)j + (lane >> 3);     // segment of 32 coordinates inside the wave's 2048
-        const float4 x = *reinterpret_cast<const float4 *>(&L[row * 32u + 4u * pos]);
-        const uint32_t quad = pos ^ (row & 7u);
-        // (write-back stores: with the streaming hint this pass ran 13% slower; the pass that reads the tiles back does
-        // better with the hint on its loads)
-        const size_t at = BLOCKED ? blocked_offset(tile, 64u * wv + row) + 4u * quad
-                                  : ((size_t)tile << kLo14Bits) + 2048u * wv + row * 32u + 4u * quad;
-        *reinterpret_cast<float4 *>(Tc + at) = x;
-    }
-}
-
 // Encode, first pass: x -> T.  Zero padding (Sec. 5: the transform needs a power of two), the sign diagonal of
 // the rotation from the shared seed (Sec. 2.1), |x|^2 for eta and S (Sec. 2.2.1, 2.3), index bits 0..13 of H.
 // Only the ceil(d / 2^14) tiles that hold part of x (rounded up to whole blocks of rows in the blocked layout) are
@@ -133,7 +102,7 @@ __global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t 
 #pragma unroll
     for (int a = 0; a < 32; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;   // + 0: no negative zeros
     lo14_forward32(u, lds);
-    lo14_store_runs<BLOCKED>(u, lds + wv * kXbWave, Tc, tile, wv);
+    store_runs<kLo14Bits, BLOCKED>(u, lds + wv * kXbWave, Tc, tile, 64u * wv);
     const double block_total = block_sum<512>(n2, red);
     if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
 }

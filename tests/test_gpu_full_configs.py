@@ -486,3 +486,31 @@ def test_two_to_the_26(budgets):
     assert err <= parity.MEAN_REL_L2
     assert ctx.last_device_status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("d", [(1 << 24) + 1, (1 << 25) + 40_000, (1 << 26) + 65_537])
+def test_two_passes_against_three_above_two_to_the_24(d):
+    # a launch of one-byte budgets alone goes through three passes, one that mixes in another budget through two: the same
+    # vector must get the same message and the same message the same decoded vector either way.  Sizes with a ragged last
+    # tile of 2^15 and of 2^16 coordinates and a ragged last group of tiles.  An index may differ by one level where the two
+    # roundings fall on different sides of a threshold: each way at most 1.6e-5 of 256-level indices (tests/parity.py).
+    from paper_2108_08842_amd import eden
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn(d, generator=gen, device="cuda")
+    zero = torch.zeros(d, device="cuda")
+    ctx = eden.Context(d_max=d, n_max=2, device=0)
+    seed = 1234567 + d
+    three = ctx.encode([x], [3], [2048], seed)[0]
+    two, nothing = ctx.encode([x, zero], [3, 4], [2048, 1024], seed)
+    a, b = three[64:].to(torch.int16), two[64:].to(torch.int16)
+    diff = (a - b).abs()
+    assert int(diff.max()) <= 1 and int((diff != 0).sum()) <= 2 * 1.6e-5 * a.numel()
+    s3, s2 = (m[32:56].cpu().numpy().view(np.float64) for m in (three, two))
+    np.testing.assert_allclose(s2, s3, rtol=1e-6)
+    alone, mixed = torch.empty(d, device="cuda"), torch.empty(d, device="cuda")
+    ctx.decode_mean([three], [3], [2048], d, seed, alone)
+    ctx.decode_mean([three, nothing], [3, 4], [2048, 1024], d, seed, mixed)
+    err = float((2.0 * mixed - alone).double().norm() / alone.double().norm())
+    assert err <= 1e-6, err                       # fp32 butterflies in another order: about sqrt(27) * 3e-8 each way
+    assert float((alone - x).double().norm() / x.double().norm()) < 0.02        # b = 8: sqrt of vNMSE 4e-5
+    ctx.close()

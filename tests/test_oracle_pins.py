@@ -959,3 +959,17 @@ def test_positive_thresholds_of_sixteen_levels_lie_several_search_cells_apart():
     assert np.min(np.diff(pos)) > 6.0 * cell
     cells = np.floor(pos[1:] / cell).astype(int)
     assert len(set(cells.tolist())) == 7 and cells[-1] == 62
+
+
+def test_numbers_of_the_sixteen_level_thresholds_are_nearly_quadratic_in_their_values():
+    # the library's b = 4 encoder guesses the number of the threshold nearest to z as z (c1 + c2 |z|) through thresholds 4 and 7
+    # and compares with that one alone (csrc/eden_device.h, RankGuess): right as long as the guess is off by less than 1/2 at
+    # every threshold (0.07 found), rises up to the cap at 1.1 times the last one and stays below 7.5 there
+    thr, _ = o.tables(4)
+    pos = thr[thr > 0]
+    p, number = pos / pos[-1], np.arange(1, 8)
+    b = (7.0 - 4.0 / p[3]) / (1.0 - p[3])
+    a = 7.0 - b
+    assert np.max(np.abs(p * (a + b * p) - number)) < 0.07
+    t_cap = 1.1 * a                               # the guess in t = a z: t (1 + b / a^2 t)
+    assert 7.0 < t_cap * (1 + b / a**2 * t_cap) < 7.45 and 1 + 2 * b / a**2 * t_cap > 0
