@@ -37,7 +37,7 @@ struct eden_ctx {
     DecScratch *dec_scratch; // slots
     DevTables *tables;
     uint32_t *dev_status;
-    uint32_t *arrived;           // counters of arrive_last (0 between launches)
+    uint32_t *arrived;           // counters of arrive_last (0 between launches): two per sender of an encode launch, one for decode
     uint32_t *msg_flags;         // n_max words: the status bits of every message of the last eden_decode_accumulate call
     uint32_t last_decode_n = 0;  // how many of them that call wrote
     // optional kernel timing (eden_profile_*)
@@ -48,6 +48,12 @@ struct eden_ctx {
 };
 
 namespace {
+
+constexpr uint32_t kArrivedCounters = 2 * kMaxBatch + 1;
+// An encode call is two launches (see EncTail) up to D = 2^18, whose passes are short wave-tile launches (32 senders of 2^17, b = 2:
+// 42.1 -> 35.6 us; one of 20,000: 21.4 -> 14.3), and up to this many coordinates of all senders together at D = 2^19 and 2^20 (2 senders
+// of 2^20: 22.5 -> 20.0 us; 4 senders: 23.5 -> 25.4, 8 senders: 30.9 -> 34.0; one sender of 2^21 .. 2^24: 3..5 us slower).
+constexpr uint64_t kTwoLaunchCoords = 1ull << 21;
 
 int ceil_log2(uint64_t d) {
     int l = 0;
@@ -189,7 +195,7 @@ int eden_create(eden_ctx **out, uint64_t d_max, uint32_t n_max, int hip_device) 
     ok = ok && hipMalloc(&ctx->dec_scratch, ctx->slots * sizeof(DecScratch)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->tables, sizeof(DevTables)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->dev_status, sizeof(uint32_t)) == hipSuccess;
-    ok = ok && hipMalloc(&ctx->arrived, sizeof(uint32_t)) == hipSuccess;
+    ok = ok && hipMalloc(&ctx->arrived, kArrivedCounters * sizeof(uint32_t)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->msg_flags, (size_t)n_max * sizeof(uint32_t)) == hipSuccess;
     ok = ok && hipMalloc(&ctx->hist, 256 * sizeof(uint32_t)) == hipSuccess;
     if (ok) {
@@ -200,7 +206,7 @@ int eden_create(eden_ctx **out, uint64_t d_max, uint32_t n_max, int hip_device) 
         ok = ok && hipMemset(ctx->enc_scratch, 0, ctx->slots * sizeof(EncScratch)) == hipSuccess;
         ok = ok && hipMemset(ctx->dec_scratch, 0, ctx->slots * sizeof(DecScratch)) == hipSuccess;
         ok = ok && hipMemset(ctx->dev_status, 0, sizeof(uint32_t)) == hipSuccess;
-        ok = ok && hipMemset(ctx->arrived, 0, sizeof(uint32_t)) == hipSuccess;
+        ok = ok && hipMemset(ctx->arrived, 0, kArrivedCounters * sizeof(uint32_t)) == hipSuccess;
         ok = ok && hipMemset(ctx->msg_flags, 0, (size_t)n_max * sizeof(uint32_t)) == hipSuccess;
         ok = ok && hipDeviceSynchronize() == hipSuccess;
     }
@@ -265,6 +271,9 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             double *part_n2 = ctx->partials, *part_ip = ctx->partials + (size_t)ctx->slots * ctx->partial_stride;
             bool need_thresholds = false;                        // b = 1 and 1/2 quantize by sign alone
             for (uint32_t i = 0; i < nb; ++i) need_thresholds = need_thresholds || B.b_q8[i] > 256u;
+            // two launches in all where the passes are short (see EncTail)
+            const bool two_launches = pl.lo_bits == 12 || (!pl.wg && pl.lo_bits == 14 && (uint64_t)nb << log2D <= kTwoLaunchCoords);
+            const EncTail tail{two_launches ? ctx->arrived : nullptr, ctx->enc_scratch, ctx->tables, hdr_d, ctx->dev_status, ctx->coin.total};
             bool coins = false;                                  // coin budgets: masks and prefix sums of the coins first
             void *part_b[kMaxBatch] = {};
             for (uint32_t i = 0; i < nb; ++i) {
@@ -294,10 +303,10 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             {
                 Timed t(ctx, EDEN_K_ENC_FIRST, nb, st);
                 nparts_n2 = pl.lo_bits >= 15   ? launch_enc_lo15_first(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
-                            : pl.lo_bits == 14 ? launch_enc_lo14_first(B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
-                                               : launch_enc_lo_first(B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st);
+                            : pl.lo_bits == 14 ? launch_enc_lo14_first(B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail, st)
+                                               : launch_enc_lo_first(B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail, st);
             }
-            if (need_thresholds) {
+            if (need_thresholds && !two_launches) {
                 Timed t(ctx, EDEN_K_ENC_NORM, nb, st);
                 launch_enc_norm(B, nb, part_n2, ctx->partial_stride, nparts_n2, ctx->enc_scratch, ctx->tables, st);
             }
@@ -312,13 +321,15 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                             : pl.wg ? launch_enc_hix_last(pl.M, pl.lo_bits, blocked, B, nb, d, log2D, seed, ctx->T, part_ip, ctx->partial_stride,
                                                         ctx->enc_scratch, ctx->coin, st)
                                   : launch_enc_hi_last(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, ctx->T, part_ip,
-                                                       ctx->partial_stride, ctx->enc_scratch, ctx->coin, st);
+                                                       ctx->partial_stride, ctx->enc_scratch, ctx->coin, tail, st);
             }
             if (pack) launch_pack_bits(B, nb, log2D, st);
             if (staged) launch_coin_pack(B.b_q8, pieces, part_b, nb, log2D, ctx->coin, st);
-            Timed t(ctx, EDEN_K_ENC_FINISH, nb, st);
-            launch_enc_finish(B, nb, hdr_d, log2D, seed, part_n2, nparts_n2, part_ip, nparts_ip, ctx->partial_stride,
-                              ctx->dev_status, ctx->coin.total, st);
+            if (!two_launches) {
+                Timed t(ctx, EDEN_K_ENC_FINISH, nb, st);
+                launch_enc_finish(B, nb, hdr_d, log2D, seed, part_n2, nparts_n2, part_ip, nparts_ip, ctx->partial_stride,
+                                  ctx->dev_status, ctx->coin.total, st);
+            }
         }
         if (!launch_ok()) return EDEN_ERR_HIP;
     }
@@ -437,7 +448,7 @@ constexpr size_t kOffTables = kOffEncScratch + static_align(EDEN_STATIC_MAX_N * 
 constexpr size_t kOffStatus = kOffTables + static_align(sizeof(DevTables));
 constexpr size_t kStaticCoinWords = kStaticDmax / 64;           // blocks of 64 coordinates per slot
 constexpr size_t kStaticCoinGroups = (kStaticCoinWords + kCoinGroup - 1) / kCoinGroup;
-constexpr size_t kOffCoinMask = kOffStatus + 256;
+constexpr size_t kOffCoinMask = kOffStatus + 512;                // status word, then the counters of arrive_last
 constexpr size_t kOffCoinLocal = kOffCoinMask + static_align(EDEN_STATIC_MAX_N * kStaticCoinWords * sizeof(uint64_t));
 constexpr size_t kOffCoinGroup = kOffCoinLocal + static_align(EDEN_STATIC_MAX_N * kStaticCoinWords * sizeof(uint32_t));
 constexpr size_t kOffCoinTotal = kOffCoinGroup + static_align(EDEN_STATIC_MAX_N * kStaticCoinGroups * sizeof(uint32_t));
@@ -478,6 +489,8 @@ int static_context(int dev, hipStream_t st, eden_ctx **out) {
         c.enc_scratch = reinterpret_cast<EncScratch *>(ptr + kOffEncScratch);
         c.tables = reinterpret_cast<DevTables *>(ptr + kOffTables);
         c.dev_status = reinterpret_cast<uint32_t *>(ptr + kOffStatus);
+        c.arrived = c.dev_status + 16;
+        static_assert((16 + kArrivedCounters) * sizeof(uint32_t) <= 512, "room for the counters");
         c.coin.mask = reinterpret_cast<uint64_t *>(ptr + kOffCoinMask);
         c.coin.local = reinterpret_cast<uint32_t *>(ptr + kOffCoinLocal);
         c.coin.group = reinterpret_cast<uint32_t *>(ptr + kOffCoinGroup);
@@ -487,7 +500,7 @@ int static_context(int dev, hipStream_t st, eden_ctx **out) {
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
         c.compute_units = (uint32_t)cus;
-        launch_fill_zero(reinterpret_cast<float *>(ptr + kOffEncScratch), (kOffStatus + 256 - kOffEncScratch) / sizeof(float), st);
+        launch_fill_zero(reinterpret_cast<float *>(ptr + kOffEncScratch), (kOffCoinMask - kOffEncScratch) / sizeof(float), st);
         std::vector<DevTables> host_tables(1);
         fill_host_tables(host_tables[0]);
         const double *src = reinterpret_cast<const double *>(&host_tables[0]);
@@ -556,7 +569,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
         }
         if (pl.lo_bits == 0) {
             Timed t(ctx, EDEN_K_DEC_SMALL, nb, st);
-            launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived,
+            launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived + 2 * kMaxBatch,
                              ctx->dev_status, flags_out + first, st);
         } else {
             // Strided pass first (every sender on its own), contiguous pass last (sums the senders in registers

@@ -610,6 +610,91 @@ __device__ inline void fill_byte_tables(EncScratch *s, uint32_t b_q8, double n2,
     }
 }
 
+// The sum of `count` partials in the order of 256 threads that take every 256th of them, whatever the workgroup's size: the same bits
+// in every kernel that needs it.  THROUGH: they were stored by workgroups of this launch.  `red`: 4 doubles in LDS; the
+// result in every thread.
+template <int THREADS, bool THROUGH>
+__device__ inline double ordered_sum(const double *part, uint32_t count, double *red) {
+    const uint32_t lane = lane_id();
+    for (uint32_t w = threadIdx.x >> 6; w < 4u; w += THREADS / 64) {
+        double s = 0.0;
+        for (uint32_t i = 64u * w + lane; i < count; i += 256u)
+            s += THROUGH ? __hip_atomic_load(part + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : part[i];
+        s = wave_sum(s);
+        if (lane == 0) red[w] = s;
+    }
+    __syncthreads();
+    const double total = ((0.0 + red[0]) + red[1]) + red[2] + red[3];
+    __syncthreads();
+    return total;
+}
+
+// ---- encode: the header of a message (one thread).  `total`: sum_i u_i q_i.  A zero or non-finite vector gets S = 0 and a status bit.
+// (<R(x),Q> = 0 can only happen on a uniform grid so coarse that every coordinate falls into the interval around 0.)
+__device__ inline bool enc_valid_norm(double n2) { return n2 > 0.0 && n2 < INFINITY; }
+__device__ inline void write_enc_header(const EncBatch &B, uint32_t c, uint64_t hdr_d, int log2D, uint64_t seed, double n2, double total,
+                                        uint32_t *dev_status, const uint32_t *coin_total) {
+    MsgHeader h;
+    h.magic = kMagic; h.log2D = (uint32_t)log2D; h.d = hdr_d; h.b_q8 = B.hdr_b_q8[c]; h.client = B.client[c];
+    h.extra_bits = coin_q8(B.b_q8[c]) ? coin_total[c] : 0u; h.seed = seed; h.N2 = n2;
+    if (enc_valid_norm(n2) && total > 0.0) {
+        h.IP = total * exp2(-0.5 * (double)log2D);               // <R(x),Q> = D^-1/2 sum u_i q_i
+        h.S = n2 / h.IP;                                         // Sec. 2.3
+        h.status = 0;
+    } else {
+        h.IP = 0.0; h.S = 0.0;
+        h.status = (n2 >= 0.0 && n2 < INFINITY) ? EDEN_DEV_ZERO_VECTOR : EDEN_DEV_NONFINITE;
+        atomicOr(dev_status, h.status);
+    }
+    *static_cast<MsgHeader *>(B.msg[c]) = h;
+}
+
+// ---- encode in two launches.  Where a pass is a few microseconds long, the launches between and after the passes (|x|^2 and the
+// thresholds; the scale and the header) cost as much as the passes: the workgroup of a sender that arrives last does that
+// work instead.  Every workgroup then waits once for its partial sum to reach memory, so longer passes keep the separate
+// launches (the rule and its figures: kTwoLaunchCoords in eden_api.hip).
+struct EncTail {
+    uint32_t *arrived;      // counters per sender: [c] of the first pass, [kMaxBatch + c] of the last; null: separate launches
+    EncScratch *scratch;
+    const DevTables *tab;
+    uint64_t hdr_d;
+    uint32_t *dev_status;
+    const uint32_t *coin_total;
+};
+// first pass: |x|^2 of the sender and what the quantizers derive from it
+template <int THREADS>
+__device__ inline void enc_first_tail(const EncTail &f, const EncBatch &B, uint32_t c, double block_total, double *part, double *red4,
+                                      uint32_t *flag) {
+    if (threadIdx.x == 0) __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!arrive_last(f.arrived + c, gridDim.x, flag)) return;
+    const double n2 = ordered_sum<THREADS, true>(part, gridDim.x, red4);
+    fill_enc_scratch(&f.scratch[c], n2, B.b_q8[c], f.tab, threadIdx.x);
+    for (uint32_t i = threadIdx.x; i <= (uint32_t)kGridMax; i += THREADS) fill_byte_tables(&f.scratch[c], B.b_q8[c], n2, f.tab, i);
+}
+// last pass: the header
+template <int THREADS>
+__device__ inline void enc_last_tail(const EncTail &f, const EncBatch &B, uint32_t c, int log2D, uint64_t seed, double block_total,
+                                     double *part, double *red4, uint32_t *flag) {
+    if (threadIdx.x == 0) __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!arrive_last(f.arrived + kMaxBatch + c, gridDim.x, flag)) return;
+    const double total = ordered_sum<THREADS, true>(part, gridDim.x, red4);
+    if (threadIdx.x == 0) write_enc_header(B, c, f.hdr_d, log2D, seed, f.scratch[c].n2, total, f.dev_status, f.coin_total);
+}
+// The payload of a vector without a usable norm is all zero: what a row of a wave tile owes of it, the 64 coordinates from `first`
+// on.  (The second part of a coin budget is cleared by a kernel of its own.)
+__device__ inline void zero_payload_row(const EncBatch &B, uint32_t c, int log2D, uint64_t first) {
+    const uint32_t b_q8 = B.b_q8[c];
+    int bits, k;
+    budget_of(b_q8, bits, k);
+    char *payload = static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES;
+    const bool codes = wide_bits(b_q8) != 0u && B.codes[c] != nullptr;           // b = 5, 6, 7: one-byte indices, packed later
+    uint32_t *dst = codes ? reinterpret_cast<uint32_t *>(B.codes[c] + first)
+                          : reinterpret_cast<uint32_t *>(payload + first * (uint32_t)bits / 8u / (uint32_t)k);
+    const uint32_t words = codes ? 16u : 2u * (uint32_t)bits / (uint32_t)k;
+    for (uint32_t i = 0; i < words; ++i) dst[i] = 0;
+    if (budget_mixed(b_q8)) reinterpret_cast<uint32_t *>(payload + payload_a_bytes(1ull << log2D, bits, 1))[first >> 6] = 0u;
+}
+
 // ---- operands of the matrix instructions (v_mfma_f32_32x32x16_f16 / _fp8_fp8).  Lane l = 32 h + m holds, of A (32 x 16), row m
 // and k = 8 h .. 8 h + 7; of B (16 x 32), column m and the same k; of the 32 x 32 result, column m and rows
 // 8 (r / 4) + 4 h + r % 4 in registers r = 0 .. 15 (checked on the device with random integer matrices).

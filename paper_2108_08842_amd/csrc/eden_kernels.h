@@ -15,11 +15,12 @@ namespace eden {
 // wave-tile passes (eden_kernels.hip)
 // `d` with a `pre` flag next to it is the caller's dimension; pre != 0 (b = 1/2 with the sparsification before the
 // rotation) means the transformed vector has dimension ceil(d/2).  Every other `d` is the transformed dimension.
+// `tail`: see EncTail (eden_device.h)
 uint32_t launch_enc_lo_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
-                             double *partials, uint32_t partial_stride, hipStream_t st);
+                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
 uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, int p, uint64_t seed,
                             const float *T, double *partials, uint32_t partial_stride, const EncScratch *scratch,
-                            const CoinTables &ct, hipStream_t st);
+                            const CoinTables &ct, const EncTail &tail, hipStream_t st);
 // coin budgets (multi-pass sizes): the coins of the senders that have such a budget, with their prefix sums; `part_b`
 // (encode) points at the second part of every such sender's payload, which is cleared; null on the receiver's side
 void launch_coin_pack(const uint32_t *b_q8, const uint32_t *const *pieces, void *const *part_b, uint32_t n, int log2D,
@@ -99,7 +100,7 @@ bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int nar
 // `blocked`: write the workspace in the blocked layout (eden_device.h: blocked_offset) that launch_enc_hix_last reads
 // when told so; not for a first pass that works in place on the workspace
 uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int blocked, int log2D, uint64_t seed, float *T,
-                               double *partials, uint32_t partial_stride, hipStream_t st);
+                               double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
 // `resident`: workgroups of the kernel the device holds at once (2 per CU); `partial`: room for `partial_tiles`
 // tiles of 2^14 floats, used when tiles are split over several workgroups by sender.
 // `mean_n` > 0 (pre == 0 only): acc is not read; acc[i] = (0 + the sum over the senders) / mean_n

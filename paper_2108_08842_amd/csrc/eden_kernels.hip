@@ -127,9 +127,10 @@ __device__ inline void hi_quantize_pack(const float (&v)[R], const EncScratch *s
 template <int M, uint32_t ONLY = 0>
 __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_elems, int log2D, int p, uint64_t seed,
                                                      const float *T, double *partials, uint32_t partial_stride,
-                                                     const EncScratch *scratch, CoinTables ct) {
+                                                     const EncScratch *scratch, CoinTables ct, EncTail tail) {
     constexpr int R = 1 << M;
     __shared__ double red[4];
+    __shared__ uint32_t last_flag;
     __shared__ float qtabs[4][16];
     __shared__ float gtabs[4][256];                              // one-byte budgets: centroids and thresholds
     const uint32_t c = blockIdx.y;
@@ -149,7 +150,9 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
         uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
         const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
         const uint64_t my_row = base + ((uint64_t)(lane & (R - 1)) << p);       // lane r < R finishes row r
-        if (b_q8 <= 256u) {
+        if (tail.arrived && !enc_valid_norm(scratch[c].n2)) {
+            if (lane < R) zero_payload_row(B, c, log2D, my_row);
+        } else if (b_q8 <= 256u) {
             // I_1 = {(-inf,0],[0,inf)}: the index is the sign; <R(x),Q> = q_1 sum |u| / sqrt(D)
             float sa = 0.0f;
 #pragma unroll
@@ -225,7 +228,8 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
         }
     }
     const double block_total = block_sum<256>((double)ip, red);
-    if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    if (tail.arrived) enc_last_tail<256>(tail, B, c, log2D, seed, block_total, partials + (size_t)c * partial_stride, red, &last_flag);
+    else if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
 }
 
 // One workgroup per sender: sums the per-workgroup partials of |x|^2 in index order (deterministic)
@@ -235,15 +239,9 @@ __global__ __launch_bounds__(256) void k_enc_norm(EncBatch B, const double *part
                                                   uint32_t nparts, EncScratch *scratch, const DevTables *tab) {
     __shared__ double red[4];
     const uint32_t c = blockIdx.x;
-    const double *pc = partials + (size_t)c * partial_stride;
-    double s = 0.0;
-    for (uint32_t i = threadIdx.x; i < nparts; i += 256) s += pc[i];
-    const double total = block_sum<256>(s, red);
-    __shared__ double n2_all;
-    if (threadIdx.x == 0) n2_all = total;
-    __syncthreads();
-    fill_enc_scratch(&scratch[c], n2_all, B.b_q8[c], tab, threadIdx.x);
-    fill_byte_tables(&scratch[c], B.b_q8[c], n2_all, tab, threadIdx.x);
+    const double n2 = ordered_sum<256, false>(partials + (size_t)c * partial_stride, nparts, red);
+    fill_enc_scratch(&scratch[c], n2, B.b_q8[c], tab, threadIdx.x);
+    fill_byte_tables(&scratch[c], B.b_q8[c], n2, tab, threadIdx.x);
 }
 
 // Decode, first pass in wave tiles (Sec. 2.2.2, 4.2): unpack, centroid lookup times S/(p sqrt D) (or the unit
@@ -572,9 +570,10 @@ __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t kee
 // `pre` (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is
 // x'[g] = 2 x[2g + o_g], g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
 __global__ __launch_bounds__(128) void k_enc_lo_first(EncBatch B, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
-                                                      double *partials, uint32_t partial_stride) {
+                                                      double *partials, uint32_t partial_stride, EncTail tail) {
     __shared__ float lds[2][64 * kLdsRow];
-    __shared__ double red[2];
+    __shared__ double red[4];
+    __shared__ uint32_t last_flag;
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id();
     const uint32_t wv = wave_in_block();
@@ -625,7 +624,8 @@ __global__ __launch_bounds__(128) void k_enc_lo_first(EncBatch B, uint64_t d_src
         for (int j = 0; j < 64; ++j) __builtin_nontemporal_store(L[j * kLdsRow + lane], Tc + 64 * j);
     }
     const double block_total = block_sum<128>(n2, red);
-    if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    if (tail.arrived) enc_first_tail<128>(tail, B, c, block_total, partials + (size_t)c * partial_stride, red, &last_flag);
+    else if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
 }
 
 // One workgroup per sender: sums the partials of sum_i u_i q_i in index order, forms
@@ -637,26 +637,11 @@ __global__ __launch_bounds__(256) void k_enc_finish(EncBatch B, uint64_t hdr_d, 
                                                     uint32_t partial_stride, uint32_t payload_words_b1,
                                                     uint32_t *dev_status, const uint32_t *coin_total) {
     __shared__ double red[4];
-    __shared__ double n2_shared;
     const uint32_t c = blockIdx.x;
-    const double *pn = partials_n2 + (size_t)c * partial_stride;
-    const double *pi = partials_ip + (size_t)c * partial_stride;
-    double s = 0.0;
-    for (uint32_t i = threadIdx.x; i < nparts_n2; i += 256) s += pn[i];
-    const double n2_t0 = block_sum<256>(s, red);                  // |x|^2, same summation order as k_enc_norm
-    s = 0.0;
-    for (uint32_t i = threadIdx.x; i < nparts_ip; i += 256) s += pi[i];
-    const double total = block_sum<256>(s, red);
-    if (threadIdx.x == 0) n2_shared = n2_t0;
-    __syncthreads();
-    const double n2 = n2_shared;
-    __shared__ double ip_shared;
-    if (threadIdx.x == 0) ip_shared = total;
-    __syncthreads();
-    // <R(x),Q> = 0 can only happen on a uniform grid so coarse that every coordinate falls into the interval around 0
-    const bool valid = (n2 > 0.0) && (n2 < INFINITY) && (ip_shared > 0.0);
+    const double n2 = ordered_sum<256, false>(partials_n2 + (size_t)c * partial_stride, nparts_n2, red);
+    const double total = ordered_sum<256, false>(partials_ip + (size_t)c * partial_stride, nparts_ip, red);
     const uint32_t b_q8 = B.b_q8[c];
-    if (!valid) {
+    if (!(enc_valid_norm(n2) && total > 0.0)) {
         uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
         int bits, k;
         budget_of(b_q8, bits, k);
@@ -664,21 +649,7 @@ __global__ __launch_bounds__(256) void k_enc_finish(EncBatch B, uint64_t hdr_d, 
         const uint64_t nw = (payload_a_bytes(D, bits, k) + (coin_q8(b_q8) ? coin_b_bytes(coin_total[c]) : payload_b_bytes(D, b_q8))) / 4;
         for (uint64_t i = threadIdx.x; i < nw; i += 256) payload[i] = 0u;
     }
-    if (threadIdx.x == 0) {
-        MsgHeader h;
-        h.magic = kMagic; h.log2D = (uint32_t)log2D; h.d = hdr_d; h.b_q8 = B.hdr_b_q8[c]; h.client = B.client[c];
-        h.extra_bits = coin_q8(b_q8) ? coin_total[c] : 0u; h.seed = seed; h.N2 = n2;
-        if (valid) {
-            h.IP = total * exp2(-0.5 * (double)log2D);       // <R(x),Q> = D^-1/2 sum u_i q_i
-            h.S = n2 / h.IP;                                  // Sec. 2.3
-            h.status = 0;
-        } else {
-            h.IP = 0.0; h.S = 0.0;
-            h.status = (n2 >= 0.0 && n2 < INFINITY) ? EDEN_DEV_ZERO_VECTOR : EDEN_DEV_NONFINITE;
-            atomicOr(dev_status, h.status);
-        }
-        *static_cast<MsgHeader *>(B.msg[c]) = h;
-    }
+    if (threadIdx.x == 0) write_enc_header(B, c, hdr_d, log2D, seed, n2, total, dev_status, coin_total);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1063,7 +1034,7 @@ __global__ void k_loss_bitmap(uint64_t key, uint32_t npk, uint32_t drop_q32, uin
 
 uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, int p, uint64_t seed,
                             const float *T, double *partials, uint32_t partial_stride, const EncScratch *scratch,
-                            const CoinTables &ct, hipStream_t st) {
+                            const CoinTables &ct, const EncTail &tail, hipStream_t st) {
     const uint32_t ntiles = 1u << (log2D - 6 - M);
     dim3 grid((ntiles + 3) / 4, n);
     bool all1 = M >= 5, all2 = M >= 5, all4 = M >= 5;            // one budget for all (two-pass sizes): its own instance
@@ -1074,7 +1045,7 @@ uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid
     }
 #define EDEN_ENC_HI_LAST(MM, ONLY)                                                                                            \
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_hi_last<MM, ONLY>), grid, dim3(256), 0, st, B, valid_elems, log2D, p, seed, T, partials, \
-                       partial_stride, scratch, ct)
+                       partial_stride, scratch, ct, tail)
     if (all1) { if (M == 5) EDEN_ENC_HI_LAST(5, 256u); else EDEN_ENC_HI_LAST(6, 256u); }
     else if (all2) { if (M == 5) EDEN_ENC_HI_LAST(5, 512u); else EDEN_ENC_HI_LAST(6, 512u); }
     else if (all4) { if (M == 5) EDEN_ENC_HI_LAST(5, 1024u); else EDEN_ENC_HI_LAST(6, 1024u); }
@@ -1147,11 +1118,11 @@ void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_ele
 #undef EDEN_DEC_HI_FIRST
 }
 uint32_t launch_enc_lo_first(const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
-                             double *partials, uint32_t partial_stride, hipStream_t st) {
+                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st) {
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
     const uint32_t tiles = (uint32_t)((d + (1u << kLoBits) - 1) >> kLoBits);
     dim3 grid((tiles + 1) / 2, n);
-    hipLaunchKernelGGL(k_enc_lo_first, grid, dim3(128), 0, st, B, d_src, pre, log2D, seed, T, partials, partial_stride);
+    hipLaunchKernelGGL(k_enc_lo_first, grid, dim3(128), 0, st, B, d_src, pre, log2D, seed, T, partials, partial_stride, tail);
     return grid.x;
 }
 void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed, const DevTables *tab,

@@ -63,9 +63,10 @@ __device__ inline void lo14_forward32(float (&v)[32], float *lds) {
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
 template <bool PRE, bool BLOCKED>
 __global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
-                                                        double *partials, uint32_t partial_stride) {
+                                                        double *partials, uint32_t partial_stride, EncTail tail) {
     __shared__ __attribute__((aligned(16))) float lds[kLo14LdsWords];
     __shared__ double red[8];
+    __shared__ uint32_t last_flag;
     const uint32_t c = blockIdx.y, t = threadIdx.x, lane = t & 63u;
     const uint32_t wv = wave_in_block();
     const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));           // reads past d_src give the zero padding
@@ -104,7 +105,8 @@ __global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t 
     lo14_forward32(u, lds);
     store_runs<kLo14Bits, BLOCKED>(u, lds + wv * kXbWave, Tc, tile, 64u * wv);
     const double block_total = block_sum<512>(n2, red);
-    if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    if (tail.arrived) enc_first_tail<512>(tail, B, c, block_total, partials + (size_t)c * partial_stride, red, &last_flag);
+    else if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
 }
 
 // Decode, last pass: index bits 0..13 of H for every sender, that sender's sign diagonal (R^-1 = s o D^-1/2 H,
@@ -572,7 +574,7 @@ __global__ __launch_bounds__(256) void k_dec_lo14_combine(float *acc, uint64_t d
 }
 
 uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int blocked, int log2D, uint64_t seed, float *T,
-                               double *partials, uint32_t partial_stride, hipStream_t st) {
+                               double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st) {
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
     uint32_t tiles = (uint32_t)((d + (1u << kLo14Bits) - 1) >> kLo14Bits);
     // blocked layout: whole blocks of rows are written (a tile beyond d reads zeros and stores zeros), so that the strided
@@ -580,7 +582,7 @@ uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d_src, in
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
 #define EDEN_ENC_LO14(PRE, BLK) \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo14_first<PRE, BLK>), grid, dim3(512), 0, st, B, d_src, log2D, seed, T, partials, partial_stride)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo14_first<PRE, BLK>), grid, dim3(512), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
     if (pre) { if (blocked) EDEN_ENC_LO14(true, true); else EDEN_ENC_LO14(true, false); }
     else { if (blocked) EDEN_ENC_LO14(false, true); else EDEN_ENC_LO14(false, false); }
 #undef EDEN_ENC_LO14

@@ -262,6 +262,35 @@ def test_decode_is_additive_and_repeatable(ctx):
     assert torch.equal(acc_all, acc_all2)
 
 
+@pytest.mark.parametrize("d,n", [(5000, 12), (100_000, 12), (300_000, 2), (900_000, 2)])
+def test_zero_and_nonfinite_vectors_of_every_budget_in_two_launches(ctx, d, n):
+    # sizes at which the last workgroup of a sender writes thresholds and header: a vector without a usable norm gets an all-zero
+    # payload (every byte of it: the buffers hold a pattern before), S = 0 and its status bit; its neighbours the message they
+    # get alone; twice, since the counters of the first call have to be back at 0
+    from paper_2108_08842_amd import eden
+    kinds = [256, 128, 512, 768, 1024, 384, 640, 896, 1536, 2048, eden.B_GRID(0.5224), eden.B_COIN(2.4)]
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    good = torch.randn(d, generator=gen, device="cuda")
+    bad = [torch.zeros(d, device="cuda"), good.clone()]
+    bad[1][d // 3] = float("inf")
+    for first in range(0, len(kinds), n):
+        budgets = kinds[first:first + n]
+        want = [ctx.encode([good], [c], [b], 17)[0] for c, b in enumerate(budgets)]
+        for which, status in ((0, eden.DEV_ZERO_VECTOR), (1, eden.DEV_NONFINITE), (None, 0)):
+            xs = [bad[which] if which is not None and c % 2 == 0 else good for c in range(len(budgets))]
+            msgs = [torch.full((eden.message_bytes(d, b),), 0xA5, dtype=torch.uint8, device="cuda") for b in budgets]
+            ctx.encode(xs, list(range(len(budgets))), budgets, 17, msgs)
+            assert ctx.last_device_status() == status
+            for c, m in enumerate(msgs):
+                length = eden.message_length(m[:64].cpu().numpy().tobytes())
+                if xs[c] is good:
+                    assert torch.equal(m[:length], want[c][:length]), budgets[c]
+                else:
+                    assert not m[64:length].any().item(), budgets[c]
+                    assert int(m[28 - 4:28].cpu().numpy().view(np.uint32)[0]) == status
+                    assert float(m[32:40].cpu().numpy().view(np.float64)[0]) == 0.0
+
+
 def test_degenerate_vectors_and_status(ctx):
     from paper_2108_08842_amd import eden
     for d in (100, 10_000):
