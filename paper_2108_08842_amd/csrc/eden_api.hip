@@ -88,8 +88,6 @@ Plan make_plan(int log2D, bool all_bytes) {
     const int lo = log2D <= 18 ? 12 : log2D <= 24 ? 14 : log2D <= 26 ? 15 : 16;
     return Plan{lo, log2D - lo, log2D - lo > 6, false};
 }
-// whether the last decode launch of a batch sums all its senders and can write the mean itself
-bool one_launch_sums(const Plan &pl) { return pl.lo_bits != 12; }
 bool all_byte_budgets(const uint32_t *b_q8, uint32_t n) {
     bool all = true;
     for (uint32_t c = 0; c < n; ++c) all = all && byte_budget(b_q8[c]);
@@ -538,7 +536,7 @@ int eden_encode_static(const float *const *x_dev, const uint32_t *client_ids, co
 // for the arguments; `d_src` is the length of acc, `bitmaps` may be null).  pre == 2 (multi-pass sizes only, n at
 // most one launch): nothing is added to acc; every sender's decoded vector is left in its workspace slot.
 // `flags_out`: where the status word of message 0 of this range goes (device, one word per message).
-// `mean_n` > 0 (only where fused_mean_applies says so): acc is written with the sum divided by mean_n instead of added to.
+// `mean_n` > 0 (n at most one launch): acc is written with the sum divided by mean_n instead of added to.
 static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t *client_ids, const uint32_t *b_kernel,
                         const uint32_t *b_hdr, uint32_t n, uint64_t d_src, int pre, uint64_t hdr_d, uint64_t seed,
                         const uint32_t *const *bitmaps, float *acc_dev, uint32_t *flags_out, hipStream_t st,
@@ -574,7 +572,8 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
         } else {
             // Strided pass first (every sender on its own), contiguous pass last (sums the senders in registers
             // and touches acc once).  The workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).
-            const int narrow = (pre != 2 && !pl.wide) ? 1 : 0;
+            // (at D <= 2^18 the last pass works in place, one sender at a time: the same integers as fp32)
+            const int narrow = (pre == 2 || pl.wide) ? 0 : pl.lo_bits == 12 ? 2 : 1;
             bool coins = false;                                  // the receiver draws and counts the same coins
             for (uint32_t i = 0; i < nb; ++i) coins = coins || coin_q8(B.b_q8[i]);
             if (coins) launch_coin_tables(B.client, B.b_q8, nullptr, nb, seed, log2D, ctx->coin, st);
@@ -605,7 +604,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             else if (pl.lo_bits == 14)
                 launch_dec_lo14_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, narrow, acc_dev, 2 * ctx->compute_units,
                                      ctx->dec_partial, ctx->dec_partial_tiles, mean_n, st);
-            else launch_dec_lo_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, narrow, acc_dev, st);
+            else launch_dec_lo_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, acc_dev, mean_n, st);
         }
         if (!launch_ok()) return EDEN_ERR_HIP;
     }
@@ -626,7 +625,7 @@ static int check_decode_args(eden_ctx *ctx, const void *const *msgs_dev, const u
     return mode < 0 ? EDEN_ERR_INVALID_ARG : mode;
 }
 
-// `mean_n` > 0 (only for m-of-64 senders that share m and fit one batch): acc is written with the sum divided by mean_n.
+// `mean_n` > 0 (senders that fit one batch): acc is written with the sum divided by mean_n.
 static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs_dev, const uint32_t *client_ids,
                                 const uint32_t *b_q8, uint32_t n, uint64_t d, uint64_t seed,
                                 const uint32_t *const *recv_bitmaps_dev, float *acc_dev, hipStream_t st, float mean_n = 0.0f);
@@ -642,9 +641,8 @@ int eden_decode_accumulate(eden_ctx *ctx, const void *const *msgs_dev, const uin
                                 static_cast<hipStream_t>(stream));
 }
 
-// The whole round of a receiver in one call.  When one launch sums all the senders (no sparsification before the rotation or
-// the one by pairs, at most kMaxBatch senders, and D >= 2^19: the 14-bit contiguous pass, or D <= 4096: the single launch of
-// those sizes) that launch writes the mean itself: the accumulator is neither zeroed, nor read, nor passed over once more for
+// The whole round of a receiver in one call.  When one launch sums all the senders (at most kMaxBatch of them; m-of-64 senders
+// that share m) that launch writes the mean itself: the accumulator is neither zeroed, nor read, nor passed over once more for
 // the division.  Otherwise the three steps run one after the other on mean_dev.
 int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t *client_ids, const uint32_t *b_q8,
                      uint32_t n, uint64_t d, uint64_t seed, const uint32_t *const *recv_bitmaps_dev, float *mean_dev,
@@ -654,20 +652,8 @@ int eden_decode_mean(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t 
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return EDEN_ERR_HIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (mode == 0 && n <= (uint32_t)kMaxBatch && one_launch_sums(make_plan(ceil_log2(d), all_byte_budgets(b_q8, n)))) {
-        ctx->last_decode_n = n;
-        return decode_range(ctx, msgs_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, recv_bitmaps_dev, mean_dev, ctx->msg_flags, st,
-                            (float)n);
-    }
-    if (mode == 1 && n <= (uint32_t)kMaxBatch) {                 // pairs before the rotation
-        if (one_launch_sums(make_plan(ceil_log2((d + 1) / 2), false))) {
-            std::vector<uint32_t> ones(n, 256u);
-            ctx->last_decode_n = n;
-            return decode_range(ctx, msgs_dev, client_ids, ones.data(), b_q8, n, d, 1, d, seed, recv_bitmaps_dev, mean_dev,
-                                ctx->msg_flags, st, (float)n);
-        }
-    }
-    if (mode == 2 && n <= ctx->slots && sparse_same_m(ctx, b_q8, n, d))         // one launch adds the values of all senders
+    // one batch: the launch that sums its senders writes the mean
+    if ((mode == 2 ? n <= ctx->slots && sparse_same_m(ctx, b_q8, n, d) : n <= (uint32_t)kMaxBatch))
         return decode_accumulate_on(ctx, mode, msgs_dev, client_ids, b_q8, n, d, seed, recv_bitmaps_dev, mean_dev, st, (float)n);
     launch_fill_zero(mean_dev, d, st);
     if (!launch_ok()) return EDEN_ERR_HIP;
@@ -685,8 +671,8 @@ static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs
                                 const uint32_t *const *recv_bitmaps_dev, float *acc_dev, hipStream_t st, float mean_n) {
     std::vector<uint32_t> ones(n, 256u);
     ctx->last_decode_n = n;
-    if (mode == 0) return decode_range(ctx, msgs_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, recv_bitmaps_dev, acc_dev, ctx->msg_flags, st);
-    if (mode == 1) return decode_range(ctx, msgs_dev, client_ids, ones.data(), b_q8, n, d, 1, d, seed, recv_bitmaps_dev, acc_dev, ctx->msg_flags, st);
+    if (mode == 0) return decode_range(ctx, msgs_dev, client_ids, b_q8, b_q8, n, d, 0, d, seed, recv_bitmaps_dev, acc_dev, ctx->msg_flags, st, mean_n);
+    if (mode == 1) return decode_range(ctx, msgs_dev, client_ids, ones.data(), b_q8, n, d, 1, d, seed, recv_bitmaps_dev, acc_dev, ctx->msg_flags, st, mean_n);
     // b = m/64 (the factor 64/m is folded into the dequantization).  Senders that share m: a batch is decoded without
     // summing, every sender into its own workspace slot, and one launch adds the values to the coordinates of acc they were
     // taken from.
@@ -712,13 +698,9 @@ static int decode_accumulate_on(eden_ctx *ctx, int mode, const void *const *msgs
     for (uint32_t c = 0; c < n; ++c) {
         const uint32_t m = sparse_m(b_q8[c]);
         const uint64_t dk = (uint64_t)m * ((d + 63) / 64);
-        // (one sender: its "mean" is written, not added to a zeroed vector, where one launch does the whole sum)
-        const bool writes = one_launch_sums(make_plan(ceil_log2(dk), false));
-        if (!writes) launch_fill_zero(ctx->stage, dk, st);
-        if (!launch_ok()) return EDEN_ERR_HIP;
         const uint32_t *bm = recv_bitmaps_dev ? recv_bitmaps_dev[c] : nullptr;
         const int rc = decode_range(ctx, &msgs_dev[c], &client_ids[c], ones.data(), &b_q8[c], 1, dk, 0, d, seed,
-                                    recv_bitmaps_dev ? &bm : nullptr, ctx->stage, ctx->msg_flags + c, st, writes ? 1.0f : 0.0f);
+                                    recv_bitmaps_dev ? &bm : nullptr, ctx->stage, ctx->msg_flags + c, st, 1.0f);     // (the mean of one: written, not added)
         if (rc != EDEN_OK) return rc;
         DecBatch B;
         std::memset(&B, 0, sizeof(B));

@@ -40,12 +40,14 @@ void launch_enc_finish(const EncBatch &B, uint32_t n, uint64_t hdr_d, int log2D,
 void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed, const DevTables *tab,
                         DecScratch *scratch, uint32_t *dev_status, const uint32_t *coin_total, uint32_t *msg_flags,
                         hipStream_t st);
+// `narrow`: the slots of b <= 1 senders hold 0 = values, 1 = the integers before the scale as fp16, 2 = as fp32
 void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, int p, uint64_t seed,
                          const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, hipStream_t st);
 // pre: 0 = sum the senders into acc; 1 = the same with the pairs scatter of EDEN_B_HALF_PRE; 2 = no sum, every sender's
-// decoded vector goes back into its own workspace slot (fp32, `narrow` must be 0)
+// decoded vector goes back into its own workspace slot.  The workspace is fp32; for pre 0 and 1 the slots of b <= 1 senders hold
+// integers (`narrow` = 2 of launch_dec_hi_first).  mean_n > 0: acc is written with the sum divided by mean_n.
 void launch_dec_lo_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
-                        const DecScratch *scratch, int narrow, float *acc, hipStream_t st);
+                        const DecScratch *scratch, float *acc, float mean_n, hipStream_t st);
 void launch_finalize_mean(const float *acc, uint64_t d, uint32_t n, float *mean, hipStream_t st);
 // D <= 4096 (eden_kernels_small.hip): one launch per direction.
 // `msg_flags` (may be null): one status word per message of the launch, written by the kernel that checks the headers.

@@ -267,8 +267,8 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
     uint64_t base;
     hi_tile_origin<M>(tile, p, base);
     const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
-    const bool i16 = narrow && b_q8 <= 256u;
-    if (lane < 16) table[wv][lane] = (i16 && lane == 1) ? 1.0f : scratch[c].deq[lane];
+    const bool unit = narrow != 0 && b_q8 <= 256u, i16 = narrow == 1 && b_q8 <= 256u;      // narrow == 2: the integers as fp32
+    if (lane < 16) table[wv][lane] = (unit && lane == 1) ? 1.0f : scratch[c].deq[lane];
     else if (lane < 32) table[wv][lane] = scratch[c].deq2[lane - 16];
     if (byte_budget(b_q8)) { gtabs[wv][lane] = scratch[c].grid_deq[lane]; gtabs[wv][64 + lane] = scratch[c].grid_deq[64 + lane]; }
     wave_lds_sync();
@@ -778,97 +778,94 @@ __global__ __launch_bounds__(256) void k_coin_pack(CoinPackBatch B, int log2D, C
     B.part_b[c][word] = bits;
 }
 
-// Decode, last pass in wave tiles: index bits 0..11 of H for every sender, that sender's sign diagonal
-// (R^-1 = s o D^-1/2 H, Sec. 2.2.2; D^-1/2 is inside the dequantization scale), sum over senders in registers,
-// one contiguous read-modify-write of acc.  A lane ends with 64 consecutive coordinates = one sign word.
-// `pre` (b = 1/2 with the sparsification first, Sec. 4.1): the decoded vector has dimension ceil(d_src/2) and value g
-// of sender c belongs at coordinate 2g + o_g of acc (o_g from c's SUB-SAMPLING stream); since the places differ from
-// sender to sender, every sender's values are added to acc directly.
-// pre == 2: nothing is summed; every sender's decoded vector is written back into its own workspace slot (fp32, in
-// place: a wave has read its tile before it writes it), for a caller that puts the values elsewhere afterwards.
-__global__ __launch_bounds__(128) void k_dec_lo_last(DecBatch B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed,
-                                                     float *T, const DecScratch *scratch, int narrow, float *acc) {
+// Decode, last pass in wave tiles: index bits 0..11 of H of one sender's vector and its sign diagonal (R^-1 = s o D^-1/2 H,
+// Sec. 2.2.2; D^-1/2 is inside the dequantization scale), in place in the sender's workspace slot (a wave has read its tile
+// before it writes it).  A lane ends with 64 consecutive coordinates = one sign word.
+// One wave per (tile, sender): at these sizes (D <= 2^18) there are at most 64 tiles, and a wave that summed all senders of its
+// tile one after the other left the chip idle (32 senders of 60,000, b = 1: 80 of the round's 139 us).  The sum follows in
+// k_dec_lo_combine.
+__global__ __launch_bounds__(128) void k_dec_lo_last(DecBatch B, uint64_t d, int log2D, uint64_t seed, float *T) {
     __shared__ float lds[2][64 * kLdsRow];
-    const uint32_t lane = lane_id(), wv = wave_in_block();
+    const uint32_t lane = lane_id(), wv = wave_in_block(), c = blockIdx.y;
     const uint32_t tile = blockIdx.x * 2u + wv;
     const uint64_t tile_base = (uint64_t)tile << kLoBits;
-    const uint64_t d = pre == 1 ? (d_src + 1) / 2 : d_src;       // dimension of the decoded vector
     if (tile_base >= d) return;                                  // whole tile in the padding (no block-wide barrier below)
     const uint64_t first = tile_base + 64u * lane;               // this lane's 64 coordinates after the transpose
-    float *L = lds[wv];
-    float sum[64];
+    float *L = lds[wv], *slot = T + ((size_t)c << log2D);
+    float v[64];
 #pragma unroll
-    for (int k = 0; k < 64; ++k) sum[k] = 0.0f;
-    for (uint32_t c = 0; c < n; ++c) {
-        const bool i16 = narrow && B.b_q8[c] <= 256u;
-        float v[64];
-        if (i16) {
-            const short *t16 = reinterpret_cast<const short *>(T + ((size_t)c << log2D)) + tile_base + lane;
+    for (int j = 0; j < 64; ++j) v[j] = slot[tile_base + lane + 64 * j];
+    fwht_regs<64>(v);                                            // index bits 6..11
 #pragma unroll
-            for (int j = 0; j < 64; ++j) v[j] = narrow_value(__builtin_nontemporal_load(t16 + 64 * j));
-        } else {
-            const float *t32 = T + ((size_t)c << log2D) + tile_base + lane;
+    for (int j = 0; j < 64; ++j) L[j * kLdsRow + lane] = v[j];
+    wave_lds_sync();
 #pragma unroll
-            for (int j = 0; j < 64; ++j) v[j] = __builtin_nontemporal_load(t32 + 64 * j);
-        }
-        fwht_regs<64>(v);                                        // index bits 6..11
-#pragma unroll
-        for (int j = 0; j < 64; ++j) L[j * kLdsRow + lane] = v[j];
-        wave_lds_sync();
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const float4 t = *reinterpret_cast<const float4 *>(&L[lane * kLdsRow + 4 * q]);
-            v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-        }
-        wave_lds_sync();                                         // the next sender overwrites the rows
-        fwht_regs<64>(v);                                        // index bits 0..5
-        const uint32_t scale = __float_as_uint(i16 ? scratch[c].deq[1] : 1.0f) & 0x7FFFFFFFu;   // > 0; x*1+s is exact
-        const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), first >> 6);
-        const uint32_t wlo = (uint32_t)word, whi = (uint32_t)(word >> 32);
-        if (pre == 2) {
-            float *dst = T + ((size_t)c << log2D) + first;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                float o4[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int k = 4 * q + e;
-                    const uint32_t sbit = ((k < 32 ? wlo : whi) << (31 - (k & 31))) & 0x80000000u;
-                    o4[e] = v[k] * __uint_as_float(scale | sbit);
-                }
-                *reinterpret_cast<float4 *>(dst + 4 * q) = make_float4(o4[0], o4[1], o4[2], o4[3]);
-            }
-            continue;
-        }
-        if (pre) {
-            const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), first >> 6);
-#pragma unroll
-            for (int k = 0; k < 64; ++k) {
-                const uint32_t sbit = ((k < 32 ? wlo : whi) << (31 - (k & 31))) & 0x80000000u;
-                const uint64_t pos = 2 * (first + k) + ((offs >> k) & 1ull);
-                if (first + k < d && pos < d_src) acc[pos] = fmaf(v[k], __uint_as_float(scale | sbit), acc[pos]);
-            }
-            continue;
-        }
-#pragma unroll
-        for (int k = 0; k < 32; ++k)
-            sum[k] = fmaf(v[k], __uint_as_float(scale | ((wlo << (31 - k)) & 0x80000000u)), sum[k]);   // bit 1 -> s_i = -1
-#pragma unroll
-        for (int k = 0; k < 32; ++k)
-            sum[32 + k] = fmaf(v[32 + k], __uint_as_float(scale | ((whi << (31 - k)) & 0x80000000u)), sum[32 + k]);
+    for (int q = 0; q < 16; ++q) {
+        const float4 t = *reinterpret_cast<const float4 *>(&L[lane * kLdsRow + 4 * q]);
+        v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
     }
-    if (pre) return;
-    if (first + 64 <= d) {
+    fwht_regs<64>(v);                                            // index bits 0..5
+    const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), first >> 6);
+    const uint32_t wlo = (uint32_t)word, whi = (uint32_t)(word >> 32);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            float4 a = *reinterpret_cast<const float4 *>(acc + first + 4 * q);
-            a.x += sum[4 * q]; a.y += sum[4 * q + 1]; a.z += sum[4 * q + 2]; a.w += sum[4 * q + 3];
-            *reinterpret_cast<float4 *>(acc + first + 4 * q) = a;
+    for (int k = 0; k < 64; ++k)                                 // bit 1 -> s_i = -1
+        v[k] = __uint_as_float(__float_as_uint(v[k]) ^ (((k < 32 ? wlo : whi) << (31 - (k & 31))) & 0x80000000u));
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        *reinterpret_cast<float4 *>(&L[lane * kLdsRow + 4 * q]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    wave_lds_sync();
+#pragma unroll
+    for (int j = 0; j < 64; ++j) slot[tile_base + lane + 64 * j] = L[j * kLdsRow + lane];
+}
+
+// The sum over the senders of what k_dec_lo_last left in their slots, one after the other; the magnitude S/(p sqrt D) q_1 of a
+// b <= 1 sender (whose slot holds exact integers) is applied here.  Four values per thread.  mean_n > 0: acc is written with the
+// sum divided by mean_n instead of added to.
+// PRE (b = 1/2 with the sparsification first, Sec. 4.1): value g of sender c belongs at coordinate 2g + o_g of acc (o_g from c's
+// SUB-SAMPLING stream), g < ceil(d/2).
+template <bool PRE>
+__global__ __launch_bounds__(64) void k_dec_lo_combine(DecBatch B, uint32_t n, uint64_t d, int log2D, uint64_t seed, const float *T,
+                                                       const DecScratch *scratch, float *acc, float mean_n) {
+    constexpr int NS = PRE ? 8 : 4;                              // outputs per thread
+    const uint64_t g = 4u * ((uint64_t)blockIdx.x * 64u + threadIdx.x), out = (PRE ? 2u : 1u) * g;
+    if (out >= d) return;
+    float sum[NS];
+#pragma unroll
+    for (int e = 0; e < NS; ++e) sum[e] = 0.0f;
+    const bool overwrite = mean_n > 0.0f;
+    float old[NS];
+#pragma unroll
+    for (int e = 0; e < NS; ++e) old[e] = (!overwrite && out + e < d) ? acc[out + e] : 0.0f;
+#pragma unroll 8
+    for (uint32_t c = 0; c < n; ++c) {
+        const float4 v = *reinterpret_cast<const float4 *>(T + ((size_t)c << log2D) + g);
+        const float scale = B.b_q8[c] <= 256u ? fabsf(scratch[c].deq[1]) : 1.0f;
+        const float x[4] = {v.x, v.y, v.z, v.w};
+        if constexpr (PRE) {
+            const uint32_t offs = (uint32_t)(hash_word(stream_key(seed, kStreamSubsample, B.client[c]), g >> 6) >> (g & 63u));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool odd = (offs >> e) & 1u;
+                sum[2 * e] = odd ? sum[2 * e] : fmaf(x[e], scale, sum[2 * e]);
+                sum[2 * e + 1] = odd ? fmaf(x[e], scale, sum[2 * e + 1]) : sum[2 * e + 1];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = fmaf(x[e], scale, sum[e]);
         }
+    }
+    const float div = overwrite ? mean_n : 1.0f;
+#pragma unroll
+    for (int e = 0; e < NS; ++e) sum[e] = (old[e] + sum[e]) / div;
+    if (out + NS <= d) {                                         // (acc is 16-byte aligned)
+#pragma unroll
+        for (int q = 0; q < NS / 4; ++q)
+            *reinterpret_cast<float4 *>(acc + out + 4 * q) = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
     } else {
 #pragma unroll
-        for (int k = 0; k < 64; ++k)
-            if (first + k < d) acc[first + k] += sum[k];
+        for (int e = 0; e < NS; ++e)
+            if (out + e < d) acc[out + e] = sum[e];
     }
 }
 
@@ -1131,10 +1128,15 @@ void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D
     hipLaunchKernelGGL(k_dec_prepare, dim3(n), dim3(64), 0, st, B, hdr_d, log2D, seed, tab, scratch, dev_status, coin_total,
                        msg_flags);
 }
-void launch_dec_lo_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
-                        const DecScratch *scratch, int narrow, float *acc, hipStream_t st) {
-    dim3 grid(1u << (log2D - kLoBits - 1));
-    hipLaunchKernelGGL(k_dec_lo_last, grid, dim3(128), 0, st, B, n, d, pre, log2D, seed, T, scratch, narrow, acc);
+void launch_dec_lo_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
+                        const DecScratch *scratch, float *acc, float mean_n, hipStream_t st) {
+    const uint64_t d = pre == 1 ? (d_src + 1) / 2 : d_src;       // dimension of the decoded vectors
+    const uint32_t tiles = (uint32_t)((d + (1u << kLoBits) - 1) >> kLoBits);
+    hipLaunchKernelGGL(k_dec_lo_last, dim3((tiles + 1) / 2, n), dim3(128), 0, st, B, d, log2D, seed, T);
+    if (pre == 2) return;
+    const dim3 grid((uint32_t)((d + 255) / 256));                // four values per thread
+    if (pre == 1) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo_combine<true>), grid, dim3(64), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo_combine<false>), grid, dim3(64), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
 }
 void launch_finalize_mean(const float *acc, uint64_t d, uint32_t n, float *mean, hipStream_t st) {
     const int vec = ((reinterpret_cast<uintptr_t>(acc) | reinterpret_cast<uintptr_t>(mean)) & 15u) == 0;
