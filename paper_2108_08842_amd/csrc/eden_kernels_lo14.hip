@@ -617,6 +617,9 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
         K = resident / tiles;
         if (K > n) K = n;
         while (K > 1 && (uint64_t)(K - 1) * rest > partial_tiles) --K;    // what the partial buffer holds
+        // no more groups than it takes for the longest one (10 senders of 2^20: 5 groups of 2 instead of 8, 31.3 -> 25.3 us with the combine)
+        const uint32_t most = (n + K - 1) / K;
+        K = (n + most - 1) / most;
     }
     if (K == 1) { full = tiles; rest = 0; }
     dim3 grid(full + rest * K);
