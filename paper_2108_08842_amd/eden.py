@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from array import array
 from typing import Optional, Sequence
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -35,6 +36,7 @@ EXPORTS = [
     "eden_kernel_name", "eden_sq_error", "eden_index_entropy", "eden_encode_static",
     "eden_last_decode_flags", "eden_message_length", "eden_decode_mean",
 ]
+_SEED_MASK = 2 ** 64 - 1
 B_HALF_PRE = 0x10080     # b = 1/2 with the sparsification before the rotation (EDEN_B_HALF_PRE)
 
 
@@ -87,13 +89,14 @@ def lib():
     L.eden_destroy.restype = ci
     L.eden_message_bytes.argtypes = [u64, u32]
     L.eden_message_bytes.restype = sz
-    L.eden_encode.argtypes = [vp, P(vp), P(u32), P(u32), u32, u64, u64, P(vp), P(sz), vp]
+    # (the arrays of a batch travel as addresses: see _u64s)
+    L.eden_encode.argtypes = [vp, vp, vp, vp, u32, u64, u64, vp, vp, vp]
     L.eden_encode.restype = ci
-    L.eden_encode_static.argtypes = [P(vp), P(u32), P(u32), u32, u64, u64, P(vp), P(sz), vp]
+    L.eden_encode_static.argtypes = [vp, vp, vp, u32, u64, u64, vp, vp, vp]
     L.eden_encode_static.restype = ci
-    L.eden_decode_accumulate.argtypes = [vp, P(vp), P(u32), P(u32), u32, u64, u64, P(vp), vp, vp]
+    L.eden_decode_accumulate.argtypes = [vp, vp, vp, vp, u32, u64, u64, vp, vp, vp]
     L.eden_decode_accumulate.restype = ci
-    L.eden_decode_mean.argtypes = [vp, P(vp), P(u32), P(u32), u32, u64, u64, P(vp), vp, vp]
+    L.eden_decode_mean.argtypes = [vp, vp, vp, vp, u32, u64, u64, vp, vp, vp]
     L.eden_decode_mean.restype = ci
     L.eden_finalize_mean.argtypes = [vp, vp, u64, u32, vp, vp]
     L.eden_finalize_mean.restype = ci
@@ -153,32 +156,50 @@ def get_tables(bits: int):
 
 
 def _stream_ptr(stream=None):
+    """Address of a stream, by default the current one of the current device (without a Stream object around it)."""
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
-def _u32_array(values: Sequence[int]):
-    return (ctypes.c_uint32 * len(values))(*[int(v) for v in values])
+# Arrays of a batch as (object that owns the memory, address): the C side takes them by address and copies what it needs before
+# the call returns.  The array module builds them several times faster than ctypes does, which matters for calls whose kernels
+# take a few microseconds.
+def _u64s(values):
+    try:
+        a = array("Q", values)
+    except (TypeError, OverflowError):                           # anything int() takes; None is a null pointer
+        a = array("Q", [int(v or 0) & _SEED_MASK for v in values])
+    return a, a.buffer_info()[0]
 
 
-def _ptr_array(ptrs: Sequence[Optional[int]]):
-    return (ctypes.c_void_p * len(ptrs))(*[ctypes.c_void_p(p) if p else None for p in ptrs])
+def _u32s(values):
+    try:
+        a = array("I", values)
+    except (TypeError, OverflowError):
+        a = array("I", [int(v) & 0xFFFFFFFF for v in values])
+    return a, a.buffer_info()[0]
+
+
+def _ptrs_or_null(ptrs):
+    return (None, None) if ptrs is None else _u64s([p or 0 for p in ptrs])      # null: no bitmap for that sender
+
+
+def _device_ptrs(tensors):
+    return [t.data_ptr() for t in tensors]
 
 
 def encode_static_raw(x_ptrs, client_ids, b_q8, d, seed, msg_ptrs, msg_caps, stream=None) -> int:
     """eden_encode_static on the current device: the library's status code, nothing raised."""
-    n = len(x_ptrs)
-    caps = (ctypes.c_size_t * n)(*[int(c) for c in msg_caps])
-    return lib().eden_encode_static(_ptr_array(x_ptrs), _u32_array(client_ids), _u32_array(b_q8), n, d,
-                                    ctypes.c_uint64(seed & (2 ** 64 - 1)), _ptr_array(msg_ptrs), caps, _stream_ptr(stream))
+    x, ids, b, m, caps = _u64s(x_ptrs), _u32s(client_ids), _u32s(b_q8), _u64s(msg_ptrs), _u64s(msg_caps)
+    return lib().eden_encode_static(x[1], ids[1], b[1], len(x_ptrs), d, seed & _SEED_MASK, m[1], caps[1], _stream_ptr(stream))
 
 
 def encode_static(xs, client_ids, b_q8, seed: int, msgs, stream=None):
     """The sender side without a context and without any allocation: `msgs` are caller-allocated uint8 tensors."""
     d = xs[0].numel()
-    rc = encode_static_raw([x.data_ptr() for x in xs], client_ids, b_q8, d, seed, [m.data_ptr() for m in msgs],
-                           [m.numel() for m in msgs], stream)
+    rc = encode_static_raw(_device_ptrs(xs), client_ids, b_q8, d, seed, _device_ptrs(msgs), [m.numel() for m in msgs], stream)
     if rc != OK:
         raise EdenError(rc, "eden_encode_static")
     return msgs
@@ -208,25 +229,18 @@ class Context:
 
     # ---- raw calls: return the library's status code, raise nothing
     def encode_raw(self, x_ptrs, client_ids, b_q8, d, seed, msg_ptrs, msg_caps, stream=None) -> int:
-        n = len(x_ptrs)
-        caps = (ctypes.c_size_t * n)(*[int(c) for c in msg_caps])
-        return lib().eden_encode(self._h, _ptr_array(x_ptrs), _u32_array(client_ids), _u32_array(b_q8), n, d,
-                                 ctypes.c_uint64(seed & (2 ** 64 - 1)), _ptr_array(msg_ptrs), caps,
-                                 _stream_ptr(stream))
+        x, ids, b, m, caps = _u64s(x_ptrs), _u32s(client_ids), _u32s(b_q8), _u64s(msg_ptrs), _u64s(msg_caps)
+        return lib().eden_encode(self._h, x[1], ids[1], b[1], len(x_ptrs), d, seed & _SEED_MASK, m[1], caps[1], _stream_ptr(stream))
 
     def decode_accumulate_raw(self, msg_ptrs, client_ids, b_q8, d, seed, bitmap_ptrs, acc_ptr, stream=None) -> int:
-        n = len(msg_ptrs)
-        bm = _ptr_array(bitmap_ptrs) if bitmap_ptrs is not None else None
-        return lib().eden_decode_accumulate(self._h, _ptr_array(msg_ptrs), _u32_array(client_ids), _u32_array(b_q8),
-                                            n, d, ctypes.c_uint64(seed & (2 ** 64 - 1)), bm,
-                                            ctypes.c_void_p(acc_ptr), _stream_ptr(stream))
+        m, ids, b, bm = _u64s(msg_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs_or_null(bitmap_ptrs)
+        return lib().eden_decode_accumulate(self._h, m[1], ids[1], b[1], len(msg_ptrs), d, seed & _SEED_MASK, bm[1], acc_ptr,
+                                            _stream_ptr(stream))
 
     def decode_mean_raw(self, msg_ptrs, client_ids, b_q8, d, seed, bitmap_ptrs, mean_ptr, stream=None) -> int:
-        n = len(msg_ptrs)
-        bm = _ptr_array(bitmap_ptrs) if bitmap_ptrs is not None else None
-        return lib().eden_decode_mean(self._h, _ptr_array(msg_ptrs), _u32_array(client_ids), _u32_array(b_q8),
-                                      n, d, ctypes.c_uint64(seed & (2 ** 64 - 1)), bm,
-                                      ctypes.c_void_p(mean_ptr), _stream_ptr(stream))
+        m, ids, b, bm = _u64s(msg_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs_or_null(bitmap_ptrs)
+        return lib().eden_decode_mean(self._h, m[1], ids[1], b[1], len(msg_ptrs), d, seed & _SEED_MASK, bm[1], mean_ptr,
+                                      _stream_ptr(stream))
 
     def finalize_mean_raw(self, acc_ptr, d, n, mean_ptr, stream=None) -> int:
         return lib().eden_finalize_mean(self._h, ctypes.c_void_p(acc_ptr), d, n, ctypes.c_void_p(mean_ptr),
@@ -239,12 +253,12 @@ class Context:
 
     def encode(self, xs, client_ids, b_q8, seed: int, msgs=None, stream=None):
         d = xs[0].numel()
+        import torch
         for x in xs:
-            assert x.is_cuda and x.dtype.is_floating_point and x.element_size() == 4 and x.is_contiguous() and x.numel() == d
+            assert x.is_cuda and x.dtype is torch.float32 and x.is_contiguous() and x.numel() == d
         if msgs is None:
             msgs = self.alloc_messages(d, b_q8)
-        rc = self.encode_raw([x.data_ptr() for x in xs], client_ids, b_q8, d, seed,
-                             [m.data_ptr() for m in msgs], [m.numel() for m in msgs], stream)
+        rc = self.encode_raw(_device_ptrs(xs), client_ids, b_q8, d, seed, _device_ptrs(msgs), [m.numel() for m in msgs], stream)
         if rc != OK:
             raise EdenError(rc, "eden_encode")
         return msgs
@@ -252,7 +266,7 @@ class Context:
     def decode_accumulate(self, msgs, client_ids, b_q8, d: int, seed: int, acc, bitmaps=None, stream=None):
         assert acc.is_cuda and acc.element_size() == 4 and acc.numel() == d and acc.is_contiguous()
         bm = None if bitmaps is None else [None if b is None else b.data_ptr() for b in bitmaps]
-        rc = self.decode_accumulate_raw([m.data_ptr() for m in msgs], client_ids, b_q8, d, seed, bm,
+        rc = self.decode_accumulate_raw(_device_ptrs(msgs), client_ids, b_q8, d, seed, bm,
                                         acc.data_ptr(), stream)
         if rc != OK:
             raise EdenError(rc, "eden_decode_accumulate")
@@ -262,7 +276,7 @@ class Context:
         """The receiver's whole round: mean = (1/n) sum of the n decoded vectors, written (not added) to `mean`."""
         assert mean.is_cuda and mean.element_size() == 4 and mean.numel() == d and mean.is_contiguous()
         bm = None if bitmaps is None else [None if b is None else b.data_ptr() for b in bitmaps]
-        rc = self.decode_mean_raw([m.data_ptr() for m in msgs], client_ids, b_q8, d, seed, bm, mean.data_ptr(), stream)
+        rc = self.decode_mean_raw(_device_ptrs(msgs), client_ids, b_q8, d, seed, bm, mean.data_ptr(), stream)
         if rc != OK:
             raise EdenError(rc, "eden_decode_mean")
         return mean
