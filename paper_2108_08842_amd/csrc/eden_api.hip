@@ -579,7 +579,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             if (coins) launch_coin_tables(B.client, B.b_q8, nullptr, nb, seed, log2D, ctx->coin, st);
             // header checks, arrival counts and dequantization tables: a launch of its own, unless the first pass does them
             const DecPrepareArgs prep{hdr_d, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, flags_out + first};
-            const bool first_prepares = pl.wg && !coins && dec_hix_first_prepares(pl.M, pl.lo_bits, B, nb, narrow);
+            const bool first_prepares = pl.wg ? !coins && dec_hix_first_prepares(pl.M, pl.lo_bits, B, nb, narrow) : !pl.wide;
             if (!first_prepares) {
                 Timed t(ctx, EDEN_K_DEC_PREPARE, nb, st);
                 launch_dec_prepare(B, nb, hdr_d, log2D, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, ctx->coin.total,
@@ -591,7 +591,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
                 else if (pl.wg) launch_dec_hix_first(pl.M, pl.lo_bits, B, nb, d, log2D, seed, ctx->dec_scratch, narrow, ctx->T, ctx->coin,
                                                 first_prepares ? &prep : nullptr, st);
                 // what the last pass reads: whole tiles of it that hold part of the first d coordinates
-                else launch_dec_hi_first(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, ctx->dec_scratch, narrow, ctx->T,
+                else launch_dec_hi_first(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, prep, narrow, ctx->T,
                                          ctx->coin, st);
             }
             if (pl.wide) {

@@ -888,10 +888,18 @@ __device__ inline void dec_prepare_wave(const void *msg, const uint32_t *bitmap,
     if (lane == 0) {
         out->flags = flags;
         if (msg_flag) *msg_flag = flags;                         // per message, for eden_last_decode_flags
-        if (flags & (EDEN_DEV_HEADER_MISMATCH | EDEN_DEV_NOTHING_ARRIVED)) atomicOr(dev_status, flags);
+        if (dev_status && (flags & (EDEN_DEV_HEADER_MISMATCH | EDEN_DEV_NOTHING_ARRIVED))) atomicOr(dev_status, flags);
     }
 }
 
+// What dec_prepare_wave needs besides the batch, for a first decode pass that does the work of launch_dec_prepare itself.
+struct DecPrepareArgs {
+    uint64_t hdr_d, seed;
+    const DevTables *tab;
+    DecScratch *scratch;
+    uint32_t *dev_status;
+    uint32_t *msg_flags;                 // null or one word per sender of the batch
+};
 
 }  // namespace eden
 #endif

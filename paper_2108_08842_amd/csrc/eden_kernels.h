@@ -40,9 +40,9 @@ void launch_enc_finish(const EncBatch &B, uint32_t n, uint64_t hdr_d, int log2D,
 void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed, const DevTables *tab,
                         DecScratch *scratch, uint32_t *dev_status, const uint32_t *coin_total, uint32_t *msg_flags,
                         hipStream_t st);
-// `narrow`: the slots of b <= 1 senders hold 0 = values, 1 = the integers before the scale as fp16, 2 = as fp32
+// Does the work of launch_dec_prepare itself.  `narrow`: the slots of b <= 1 senders hold 0 = values, 1 = the integers before the scale as fp16, 2 = as fp32
 void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, int p, uint64_t seed,
-                         const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, hipStream_t st);
+                         const DecPrepareArgs &prep, int narrow, float *T, const CoinTables &ct, hipStream_t st);
 // pre: 0 = sum the senders into acc; 1 = the same with the pairs scatter of EDEN_B_HALF_PRE; 2 = no sum, every sender's
 // decoded vector goes back into its own workspace slot.  The workspace is fp32; for pre 0 and 1 the slots of b <= 1 senders hold
 // integers (`narrow` = 2 of launch_dec_hi_first).  mean_n > 0: acc is written with the sum divided by mean_n.
@@ -82,15 +82,6 @@ void launch_loss_bitmap(uint64_t key, uint32_t npk, uint32_t drop_q32, uint32_t 
 uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed, const float *T,
                              double *partials, uint32_t partial_stride, const EncScratch *scratch, const CoinTables &ct,
                              hipStream_t st);
-// What dec_prepare_wave needs besides the batch; a first decode pass that is given it (`prep` not null) may do the work of
-// launch_dec_prepare itself, in one of its workgroups per sender, and then returns true: the caller leaves that launch out.
-struct DecPrepareArgs {
-    uint64_t hdr_d, seed;
-    const DevTables *tab;
-    DecScratch *scratch;
-    uint32_t *dev_status;
-    uint32_t *msg_flags;                 // null or one word per sender of the batch
-};
 void launch_hix_mid(int M, uint32_t n, float *T, int log2D, uint64_t load_elems, uint64_t store_elems, hipStream_t st);
 bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
                           const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, const DecPrepareArgs *prep,

@@ -255,22 +255,35 @@ __global__ __launch_bounds__(256) void k_enc_norm(EncBatch B, const double *part
 // that one branch (the shared one spills 304 bytes at its 96 registers).
 template <int M, uint32_t ONLY = 0>
 __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t keep_elems, int log2D, int p, uint64_t seed,
-                                                      const DecScratch *scratch, int narrow, float *T, CoinTables ct) {
+                                                      DecPrepareArgs prep, int narrow, float *T, CoinTables ct) {
     constexpr int R = 1 << M;
+    __shared__ DecScratch ds;
     __shared__ float table[4][32];
     __shared__ float gtabs[4][kGridMax + 1];                     // uniform grid: dequantized centres of mass
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id(), wv = wave_in_block();
     const uint32_t tile = blockIdx.x * 4u + wv;
-    const uint32_t ntiles = 1u << (log2D - 6 - M);
+    const uint32_t ntiles = 1u << (log2D - 6 - M);               // a multiple of 4
+    const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
+    // Header checks, arrival counts and the dequantization table: every workgroup of a sender does them for itself (a launch of
+    // its own took 4 us in front of passes of 5 to 15), the first one for the later passes and the status words too.  The unit
+    // pattern of a b <= 1 sender needs none of it here.
+    const bool first_wg = blockIdx.x == 0;
+    if (wv == 0 && (first_wg || narrow == 0 || b_q8 > 256u))
+        dec_prepare_wave(B.msg[c], B.bitmap[c], B.client[c], b_q8, B.hdr_b_q8[c], prep.hdr_d, log2D, prep.seed, prep.tab, &ds,
+                         first_wg ? prep.dev_status : nullptr, coin_q8(b_q8) ? ct.total[c] : 0u,
+                         first_wg && prep.msg_flags ? prep.msg_flags + c : nullptr);
+    __syncthreads();
+    if (first_wg)
+        for (uint32_t i = threadIdx.x; i < sizeof(DecScratch) / 4; i += 256u)
+            reinterpret_cast<uint32_t *>(&prep.scratch[c])[i] = reinterpret_cast<const uint32_t *>(&ds)[i];
     if (tile >= ntiles) return;
     uint64_t base;
     hi_tile_origin<M>(tile, p, base);
-    const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
     const bool unit = narrow != 0 && b_q8 <= 256u, i16 = narrow == 1 && b_q8 <= 256u;      // narrow == 2: the integers as fp32
-    if (lane < 16) table[wv][lane] = (unit && lane == 1) ? 1.0f : scratch[c].deq[lane];
-    else if (lane < 32) table[wv][lane] = scratch[c].deq2[lane - 16];
-    if (byte_budget(b_q8)) { gtabs[wv][lane] = scratch[c].grid_deq[lane]; gtabs[wv][64 + lane] = scratch[c].grid_deq[64 + lane]; }
+    if (lane < 16) table[wv][lane] = (unit && lane == 1) ? 1.0f : ds.deq[lane];
+    else if (lane < 32) table[wv][lane] = ds.deq2[lane - 16];
+    if (byte_budget(b_q8)) { gtabs[wv][lane] = ds.grid_deq[lane]; gtabs[wv][64 + lane] = ds.grid_deq[64 + lane]; }
     wave_lds_sync();
     const float *tb = table[wv], *tb2 = table[wv] + 16;
     const uint32_t *payload = reinterpret_cast<const uint32_t *>(static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES);
@@ -1096,7 +1109,7 @@ void launch_coin_pack(const uint32_t *b_q8, const uint32_t *const *pieces, void 
     hipLaunchKernelGGL(k_coin_pack, dim3((blocks + 255u) / 256u, n), dim3(256), 0, st, B, log2D, ct);
 }
 void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, int p, uint64_t seed,
-                         const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, hipStream_t st) {
+                         const DecPrepareArgs &prep, int narrow, float *T, const CoinTables &ct, hipStream_t st) {
     const uint32_t ntiles = 1u << (log2D - 6 - M);
     dim3 grid((ntiles + 3) / 4, n);
     bool all1 = M >= 5, all2 = M >= 5, all4 = M >= 5;            // one budget for all (two-pass sizes): its own instance
@@ -1106,7 +1119,7 @@ void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_ele
         all4 = all4 && B.b_q8[c] == 1024u && !B.codes[c];
     }
 #define EDEN_DEC_HI_FIRST(MM, ONLY)                                                                                           \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_hi_first<MM, ONLY>), grid, dim3(256), 0, st, B, keep_elems, log2D, p, seed, scratch, \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_hi_first<MM, ONLY>), grid, dim3(256), 0, st, B, keep_elems, log2D, p, seed, prep, \
                        narrow, T, ct)
     if (all1) { if (M == 5) EDEN_DEC_HI_FIRST(5, 256u); else EDEN_DEC_HI_FIRST(6, 256u); }
     else if (all2) { if (M == 5) EDEN_DEC_HI_FIRST(5, 512u); else EDEN_DEC_HI_FIRST(6, 512u); }
