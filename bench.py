@@ -41,25 +41,24 @@ def model_bytes(n, d, D, budgets):
 
 def kernel_bytes(kind, senders, d, D, mean_bits, narrow, fused_mean=False):
     """Algorithmic bytes one launch of a kernel kind must move (what its role reads + what it writes).
-    The contiguous pass works on whole tiles of 2^12 (D <= 2^18) or 2^14 coordinates and only touches the tiles
-    that hold part of the first d coordinates; the strided passes read / write the rest as implicit zeros.
-    `narrow`: the decode workspace of this workload is fp16 (every sender has b <= 1 and 2^13 <= D <= 2^24).
+    The contiguous pass works on whole tiles of 2^12 (D <= 2^18), 2^14, 2^15 (D >= 2^25) or 2^16 (2^27) coordinates and only
+    touches the tiles that hold part of the first d coordinates; the strided pass reads / writes the rest as implicit zeros.
+    `narrow`: the decode workspace of this workload is fp16 (every sender has b <= 1 and D >= 2^19).
     `fused_mean`: the last decode pass stores the mean (4 d) instead of a read-modify-write of the accumulator."""
     log2D = D.bit_length() - 1
-    lo = 12 if log2D <= 18 else 14
+    lo = 12 if log2D <= 18 else 14 if log2D <= 24 else 15 if log2D <= 26 else 16
 
     def ru(bits):                                     # d rounded up to whole tiles of 2^bits, at most D
         return min(D, -(-d >> bits) << bits)
 
     payload = D * mean_bits / 8.0
     ws = 2 if narrow else 4                           # decode workspace bytes per element
-    top = ru(lo) if log2D <= 24 else ru(24)           # what the pass next to the payload reads (encode) / writes (decode)
     per_sender = {
         "enc_first": 4 * d + 4 * ru(lo),              # x in, workspace out
-        "mid": 4 * ru(14) + 4 * ru(24),               # workspace in and out (three-pass sizes)
-        "enc_last": 4 * top + payload,                # workspace in, packed indices out
-        "dec_first": payload + ws * top,              # packed indices in, workspace out
-        "dec_last": ws * ru(lo),                      # workspace in (per sender) ...
+        "enc_last": 4 * ru(lo) + payload,             # workspace in, packed indices out
+        "dec_first": payload + ws * ru(lo),           # packed indices in, workspace out
+        # workspace in (per sender; D <= 2^18: in and out, and in once more for the sum) ...
+        "dec_last": ws * ru(lo) * (3 if lo == 12 else 1),
     }
     if kind == "dec_last":
         return senders * per_sender[kind] + (4 if fused_mean else 8) * d     # ... plus the accumulator (or the mean)
@@ -165,7 +164,7 @@ def main():
     D = 1 << (d - 1).bit_length()
     log2D = D.bit_length() - 1
     mean_bits = sum(w.b_q8) / len(w.b_q8) / 256.0
-    narrow = all(b <= 256 for b in w.b_q8) and 13 <= log2D <= 24
+    narrow = all(b <= 256 for b in w.b_q8) and log2D >= 19
 
     xs_host = [synth.client_vector(w, c) for c in range(n)]
     xs = [torch.from_numpy(x).cuda() for x in xs_host]

@@ -58,7 +58,7 @@ def build(verbose: bool = True, incremental: bool = False) -> str:
     `incremental`: skip sources whose object file is newer than the source and every header."""
     os.makedirs(OBJ_DIR, exist_ok=True)
     common = [hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-              # packed fp32 instructions are kept off on this hardware pool
+              # packed fp32 instructions stay off: some of their forms have given wrong results
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
               "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(PKG, "csrc")]
     objs = [os.path.join(OBJ_DIR, s + ".o") for s in SOURCES]
