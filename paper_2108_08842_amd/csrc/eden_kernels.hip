@@ -252,9 +252,13 @@ __global__ __launch_bounds__(256) void k_enc_norm(EncBatch B, const double *part
 // (Five waves per SIMD are requested: the budgets with two loads per value would otherwise set the register count
 // for all of them; measured 0.057 against 0.073 ms on 32 senders at D = 2^20.)
 // ONLY != 0: every sender of the launch has this budget (1, 2 or 4 bits, indices in the payload); the instance then holds
-// that one branch (the shared one spills 304 bytes at its 96 registers).
+// that one branch (the shared one spills at its 96 registers).  kSimple: every sender has 1/2, 1, 2 or 4 bits, in any mix; without
+// the branches of the others four waves per SIMD do (32 senders of 2^20, those budgets mixed: 53.9 -> 45.6 us; the encoder's
+// last pass gained nothing from such an instance).
+constexpr uint32_t kSimple = 1u;
+__host__ __device__ inline bool simple_budget(uint32_t b_q8) { return b_q8 == 128u || b_q8 == 256u || b_q8 == 512u || b_q8 == 1024u; }
 template <int M, uint32_t ONLY = 0>
-__global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t keep_elems, int log2D, int p, uint64_t seed,
+__global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(DecBatch B, uint64_t keep_elems, int log2D, int p, uint64_t seed,
                                                       DecPrepareArgs prep, int narrow, float *T, CoinTables ct) {
     constexpr int R = 1 << M;
     __shared__ DecScratch ds;
@@ -264,7 +268,8 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
     const uint32_t lane = lane_id(), wv = wave_in_block();
     const uint32_t tile = blockIdx.x * 4u + wv;
     const uint32_t ntiles = 1u << (log2D - 6 - M);               // a multiple of 4
-    const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
+    constexpr bool SIMPLE = ONLY == kSimple;
+    const uint32_t b_q8 = ONLY > kSimple ? ONLY : B.b_q8[c];
     // Header checks, arrival counts and the dequantization table: every workgroup of a sender does them for itself (a launch of
     // its own took 4 us in front of passes of 5 to 15), the first one for the later passes and the status words too.  The unit
     // pattern of a b <= 1 sender needs none of it here.
@@ -283,7 +288,7 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
     const bool unit = narrow != 0 && b_q8 <= 256u, i16 = narrow == 1 && b_q8 <= 256u;      // narrow == 2: the integers as fp32
     if (lane < 16) table[wv][lane] = (unit && lane == 1) ? 1.0f : ds.deq[lane];
     else if (lane < 32) table[wv][lane] = ds.deq2[lane - 16];
-    if (byte_budget(b_q8)) { gtabs[wv][lane] = ds.grid_deq[lane]; gtabs[wv][64 + lane] = ds.grid_deq[64 + lane]; }
+    if (!SIMPLE && byte_budget(b_q8)) { gtabs[wv][lane] = ds.grid_deq[lane]; gtabs[wv][64 + lane] = ds.grid_deq[64 + lane]; }
     wave_lds_sync();
     const float *tb = table[wv], *tb2 = table[wv] + 16;
     const uint32_t *payload = reinterpret_cast<const uint32_t *>(static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES);
@@ -311,7 +316,7 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
             const uint32_t neg = (~(w >> (lane >> 1)) & 1u) << 31;          // index 0 = negative
             v[r] = kept ? __uint_as_float(mag | neg) : 0.0f;
         }
-    } else if (byte_budget(b_q8)) {
+    } else if (!SIMPLE && byte_budget(b_q8)) {
         // one byte per coordinate: the index on the uniform grid (Sec. 4.3) or of a 32..256-level quantizer
         const uint8_t *bytes = B.codes[c] ? B.codes[c] : reinterpret_cast<const uint8_t *>(payload);
         const rsrc_t rp = make_rsrc(bytes + base, (1u << log2D) - (uint32_t)base);
@@ -325,7 +330,7 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
 #pragma unroll
             for (int r = 0; r < R; ++r) v[r] = dequantize_byte<false>(__float_as_uint(v[r]), H, gtabs[wv]);
         }
-    } else if (budget_mixed(b_q8)) {
+    } else if (!SIMPLE && budget_mixed(b_q8)) {
         // b = bits + 1/2 (Sec. 4.1): every coordinate has `bits` bits in the first part; the coordinate of each pair
         // that the MIX stream selects was quantized with the finer table and has its top bit in the second part
         const uint64_t key = stream_key(seed, kStreamMix, B.client[c]);
@@ -347,7 +352,7 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
             const uint32_t top = (wb >> (lane >> 1)) & 1u;
             v[r] = up ? tb2[(top << bits) | low] : tb[low];
         }
-    } else if (coin_q8(b_q8)) {
+    } else if (!SIMPLE && coin_q8(b_q8)) {
         // coin budgets (Sec. 4.1): every coordinate has `bits` bits in the first part; a coordinate with a coin was
         // quantized with the finer table and has its top bit in the second part, at the position of its rank among the coins
         const uint32_t w = (uint32_t)(my_row >> 6);
@@ -376,7 +381,7 @@ __global__ __launch_bounds__(256, 5) void k_dec_hi_first(DecBatch B, uint64_t ke
             const uint32_t top = (uint32_t)(wave_read64(window_mine, r) >> lanes_below(m)) & 1u;
             v[r] = __builtin_amdgcn_inverse_ballot_w64(m) ? tb2[(top << bits) | low] : tb[low];
         }
-    } else if (bits == 3) {
+    } else if (!SIMPLE && bits == 3) {
         // 64 columns x 3 bits = 6 words per row; an index may straddle two words
         const uint32_t lbits = lane * 3u;
         const rsrc_t rp = make_rsrc(payload + (base >> 6) * 6u, payload_bytes - (uint32_t)(base >> 6) * 24u);
@@ -1113,10 +1118,12 @@ void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_ele
     const uint32_t ntiles = 1u << (log2D - 6 - M);
     dim3 grid((ntiles + 3) / 4, n);
     bool all1 = M >= 5, all2 = M >= 5, all4 = M >= 5;            // one budget for all (two-pass sizes): its own instance
+    bool simple = M >= 5;
     for (uint32_t c = 0; c < n; ++c) {
         all1 = all1 && B.b_q8[c] == 256u;
         all2 = all2 && B.b_q8[c] == 512u && !B.codes[c];
         all4 = all4 && B.b_q8[c] == 1024u && !B.codes[c];
+        simple = simple && simple_budget(B.b_q8[c]);
     }
 #define EDEN_DEC_HI_FIRST(MM, ONLY)                                                                                           \
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_hi_first<MM, ONLY>), grid, dim3(256), 0, st, B, keep_elems, log2D, p, seed, prep, \
@@ -1124,6 +1131,7 @@ void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_ele
     if (all1) { if (M == 5) EDEN_DEC_HI_FIRST(5, 256u); else EDEN_DEC_HI_FIRST(6, 256u); }
     else if (all2) { if (M == 5) EDEN_DEC_HI_FIRST(5, 512u); else EDEN_DEC_HI_FIRST(6, 512u); }
     else if (all4) { if (M == 5) EDEN_DEC_HI_FIRST(5, 1024u); else EDEN_DEC_HI_FIRST(6, 1024u); }
+    else if (simple) { if (M == 5) EDEN_DEC_HI_FIRST(5, kSimple); else EDEN_DEC_HI_FIRST(6, kSimple); }
     else EDEN_HI_SWITCH(M, EDEN_DEC_HI_FIRST(MM, 0u));
 #undef EDEN_DEC_HI_FIRST
 }
