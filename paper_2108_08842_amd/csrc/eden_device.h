@@ -665,7 +665,11 @@ struct EncTail {
 template <int THREADS>
 __device__ inline void enc_first_tail(const EncTail &f, const EncBatch &B, uint32_t c, double block_total, double *part, double *red4,
                                       uint32_t *flag) {
-    if (threadIdx.x == 0) __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (each pass also clears the other pass's counter, so that calls which overlapped against the rules leave nothing behind)
+        if (blockIdx.x == 0) f.arrived[kMaxBatch + c] = 0u;
+    }
     if (!arrive_last(f.arrived + c, gridDim.x, flag)) return;
     const double n2 = ordered_sum<THREADS, true>(part, gridDim.x, red4);
     fill_enc_scratch(&f.scratch[c], n2, B.b_q8[c], f.tab, threadIdx.x);
@@ -675,7 +679,10 @@ __device__ inline void enc_first_tail(const EncTail &f, const EncBatch &B, uint3
 template <int THREADS>
 __device__ inline void enc_last_tail(const EncTail &f, const EncBatch &B, uint32_t c, int log2D, uint64_t seed, double block_total,
                                      double *part, double *red4, uint32_t *flag) {
-    if (threadIdx.x == 0) __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (blockIdx.x == 0) f.arrived[c] = 0u;
+    }
     if (!arrive_last(f.arrived + kMaxBatch + c, gridDim.x, flag)) return;
     const double total = ordered_sum<THREADS, true>(part, gridDim.x, red4);
     if (threadIdx.x == 0) write_enc_header(B, c, f.hdr_d, log2D, seed, f.scratch[c].n2, total, f.dev_status, f.coin_total);
