@@ -143,7 +143,7 @@ typedef enum eden_status {
 
 /* Creates a context on HIP device `hip_device` able to handle vectors up to d_max coordinates and
  * batches up to n_max senders per call.  Allocates everything any later call needs: per workspace slot (there are
- * min(n_max, 32)) 4 * D_max bytes for the transform's intermediate passes, D_max bytes for the one-byte indices of
+ * min(n_max, 32)) 4 * max(D_max, 64) bytes for the transform's intermediate passes, D_max bytes for the one-byte indices of
  * b = 5, 6, 7 and 3/16 * D_max bytes for the coins of the EDEN_B_COIN budgets (neither of the two if D_max <= 4096);
  * 4 * (d_max + 64) bytes for the kept coordinates of an EDEN_B_SPARSE sender; 32 MiB for sender-group sums of the last
  * decode pass when D_max >= 2^19 and n_max > 1; plus a few KiB of partial sums per sender;

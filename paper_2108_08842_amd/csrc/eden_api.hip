@@ -22,7 +22,8 @@ struct eden_ctx {
     int log2D_max;
     uint32_t n_max;          // senders per call the workspace was sized for (chunks of kMaxBatch are used)
     uint32_t slots;          // workspace slots = min(n_max, kMaxBatch)
-    float *T;                // slots * D_max floats
+    float *T;                // slots * slot_floats floats
+    uint64_t slot_floats;    // D_max, but at least 64: for d < 64 the kept coordinates of an m-of-64 sender are more than d
     double *partials;        // 2 * slots * partial_stride doubles: |x|^2 partials, then sum u q partials
     uint32_t partial_stride;
     uint32_t compute_units;      // of the context's device
@@ -165,13 +166,14 @@ int eden_create(eden_ctx **out, uint64_t d_max, uint32_t n_max, int hip_device) 
     ctx->n_max = n_max;
     ctx->slots = n_max < (uint32_t)kMaxBatch ? n_max : (uint32_t)kMaxBatch;
     const uint64_t D_max = 1ull << ctx->log2D_max;
+    ctx->slot_floats = D_max < 64 ? 64 : D_max;
     ctx->partial_stride = (uint32_t)(D_max / 256 + 16);
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hip_device) != hipSuccess || cus <= 0) cus = 256;
     ctx->compute_units = (uint32_t)cus;
 
     bool ok = true;
-    ok = ok && hipMalloc(&ctx->T, (size_t)ctx->slots * D_max * sizeof(float)) == hipSuccess;
+    ok = ok && hipMalloc(&ctx->T, (size_t)ctx->slots * ctx->slot_floats * sizeof(float)) == hipSuccess;
     if (ctx->log2D_max > kLoBits) {
         ok = ok && hipMalloc(&ctx->codes, (size_t)ctx->slots * D_max) == hipSuccess;
     }
@@ -345,10 +347,11 @@ static int sparsify_mode(const uint32_t *b_q8, uint32_t n) {
     return -1;
 }
 
-// m-of-64 senders that go through the workspace slots in batches (up to the sizes whose contiguous passes can work in place; the
-// launches of a single sender fill the chip beyond them)
+// m-of-64 senders that go through the workspace slots in batches: their padded kept vectors fit a slot each, and their contiguous
+// passes can work in place (the launches of a single sender fill the chip beyond those sizes)
 static bool sparse_same_m(const eden_ctx *ctx, const uint32_t *b_q8, uint32_t n, uint64_t d) {
-    bool same = ctx->T != nullptr && ceil_log2((uint64_t)sparse_m(b_q8[0]) * ((d + 63) / 64)) <= 24;
+    const int log2Dk = ceil_log2((uint64_t)sparse_m(b_q8[0]) * ((d + 63) / 64));
+    bool same = log2Dk <= 24 && (1ull << log2Dk) <= ctx->slot_floats;
     for (uint32_t c = 0; c < n; ++c) same = same && sparse_m(b_q8[c]) != 0 && sparse_m(b_q8[c]) == sparse_m(b_q8[0]);
     return same;
 }
@@ -480,6 +483,7 @@ int static_context(int dev, hipStream_t st, eden_ctx **out) {
         c.n_max = EDEN_STATIC_MAX_N;
         c.slots = EDEN_STATIC_MAX_N;
         c.T = reinterpret_cast<float *>(ptr + kOffT);
+        c.slot_floats = kStaticDmax;
         c.codes = ptr + kOffCodes;
         c.stage = reinterpret_cast<float *>(ptr + kOffStage);
         c.partials = reinterpret_cast<double *>(ptr + kOffPartials);

@@ -414,6 +414,40 @@ def test_sparse_rounds_of_many_senders(ctx, d, m, n):
     assert ctx.last_decode_flags(n) == [0] * n
 
 
+@pytest.mark.parametrize("d_max,n", [(1, 32), (5, 17), (17, 40), (32, 32), (33, 17), (64, 9)])
+def test_sparse_rounds_in_contexts_of_a_few_coordinates(d_max, n):
+    # d < 64 and m > d: the kept vectors (m values of the one block, padded to as many as 64) are longer than the vectors, and the
+    # workspace slots of a context for so small a d_max have to hold them; afterwards the context's tables are what they were
+    from paper_2108_08842_amd import eden
+    small = eden.Context(d_max=d_max, n_max=n, device=0)
+    for d in sorted({1, d_max}):
+        for m in (63, 33, 2):
+            budgets = [eden.B_SPARSE(m)] * n
+            w = synth.Workload("t", n, d, budgets, 2300 + 64 * d + m, "normal")
+            xs = [synth.client_vector(w, c) for c in range(n)]
+            ids = list(range(500, 500 + n))
+            print(f"small context d_max={d_max} n={n} d={d} m={m}", flush=True)
+            msgs = small.encode([torch.from_numpy(x).cuda() for x in xs], ids, budgets, w.seed)
+            stats = parity.EncodeParity()
+            omsgs = [parity.to_oracle_message(t) for t in msgs]
+            for c in range(n):                       # (a sender whose kept positions are all padding: a zero vector on both sides)
+                parity.check_encode(xs[c], w.seed, ids[c], budgets[c], omsgs[c], stats)
+            parity.finish_encode(stats)
+            acc = torch.zeros(d, device="cuda")
+            small.decode_accumulate(msgs, ids, budgets, d, w.seed, acc)
+            want = small.finalize_mean(acc, n)
+            got = torch.full((d,), float("nan"), device="cuda")
+            small.decode_mean(msgs, ids, budgets, d, w.seed, got)
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+            assert parity.rel_l2(got.cpu().numpy(), o.decode_mean(omsgs, d)) <= parity.MEAN_REL_L2
+        small.last_device_status()
+        b = [(256, 768, 2048)[c % 3] for c in range(n)]
+        w = synth.Workload("t", n, d, b, 2400 + d, "normal")
+        _run_case(small, [synth.client_vector(w, c) for c in range(n)], list(range(n)), b, w.seed)
+    torch.cuda.synchronize()
+    small.close()
+
+
 def test_sparse_budget_that_keeps_only_padding(ctx):
     # d < 64 where every kept position of the block is a virtual zero: the documented outcome is a zero-vector message
     # (status bit, S = 0, all-zero payload) that contributes nothing, exactly as the oracle has it
