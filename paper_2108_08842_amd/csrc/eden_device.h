@@ -675,17 +675,45 @@ __device__ inline void enc_first_tail(const EncTail &f, const EncBatch &B, uint3
     fill_enc_scratch(&f.scratch[c], n2, B.b_q8[c], f.tab, threadIdx.x);
     for (uint32_t i = threadIdx.x; i <= (uint32_t)kGridMax; i += THREADS) fill_byte_tables(&f.scratch[c], B.b_q8[c], n2, f.tab, i);
 }
-// last pass: the header
+// What a message whose sums are unusable owes beside its header: a payload of zeros, `codes` the one-byte indices that it is packed
+// from later.
+template <int THREADS>
+__device__ inline void zero_payload(const EncBatch &B, uint32_t c, int log2D, const uint32_t *coin_total, bool codes) {
+    const uint32_t b_q8 = B.b_q8[c];
+    int bits, k;
+    budget_of(b_q8, bits, k);
+    const uint64_t D = 1ull << log2D;
+    uint32_t *dst = codes ? reinterpret_cast<uint32_t *>(B.codes[c])
+                          : reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
+    const uint64_t words = (codes ? D : payload_a_bytes(D, bits, k) + (coin_q8(b_q8) ? coin_b_bytes(coin_total[c]) : payload_b_bytes(D, b_q8))) / 4;
+    for (uint64_t i = threadIdx.x; i < words; i += THREADS) dst[i] = 0u;
+}
+// Whether sum_i u_i q_i may turn out unusable (not positive, or NaN) although |x|^2 is usable.  Every value of the transform and
+// of its stages is at most sqrt(D) |x|, so with D |x|^2 <= 2^254 nothing overflows in fp32 and no inf - inf arises; with |x| >= 2^-100
+// no product of a value in an interval that does not touch 0 underflows.  (A grid so coarse that every index is 0 has a zero payload anyway.)
+__device__ inline bool enc_sum_in_doubt(double n2, int log2D) {
+    return enc_valid_norm(n2) && !(n2 >= 0x1p-200 && n2 * (double)(1ull << log2D) <= 0x1p254);
+}
+// last pass: the header; and the zero payload of a sender whose sum is unusable.  Other workgroups have stored pieces of that
+// payload, some of them from other XCDs: where the sum is in doubt every workgroup therefore writes its L2 back before it arrives
+// (no other sender pays for that), and the last one clears after it has seen them all.
 template <int THREADS>
 __device__ inline void enc_last_tail(const EncTail &f, const EncBatch &B, uint32_t c, int log2D, uint64_t seed, double block_total,
                                      double *part, double *red4, uint32_t *flag) {
+    const double n2 = f.scratch[c].n2;
+    const bool doubt = enc_sum_in_doubt(n2, log2D);
     if (threadIdx.x == 0) {
         __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (blockIdx.x == 0) f.arrived[c] = 0u;
     }
+    if (doubt) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (!arrive_last(f.arrived + kMaxBatch + c, gridDim.x, flag)) return;
     const double total = ordered_sum<THREADS, true>(part, gridDim.x, red4);
-    if (threadIdx.x == 0) write_enc_header(B, c, f.hdr_d, log2D, seed, f.scratch[c].n2, total, f.dev_status, f.coin_total);
+    if (doubt && !(total > 0.0)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        zero_payload<THREADS>(B, c, log2D, f.coin_total, wide_bits(B.b_q8[c]) != 0u && B.codes[c] != nullptr);
+    }
+    if (threadIdx.x == 0) write_enc_header(B, c, f.hdr_d, log2D, seed, n2, total, f.dev_status, f.coin_total);
 }
 // The payload of a vector without a usable norm is all zero: what a row of a wave tile owes of it, the 64 coordinates from `first`
 // on.  (The second part of a coin budget is cleared by a kernel of its own.)

@@ -652,21 +652,12 @@ __global__ __launch_bounds__(128) void k_enc_lo_first(EncBatch B, uint64_t d_src
 __global__ __launch_bounds__(256) void k_enc_finish(EncBatch B, uint64_t hdr_d, int log2D, uint64_t seed,
                                                     const double *partials_n2, uint32_t nparts_n2,
                                                     const double *partials_ip, uint32_t nparts_ip,
-                                                    uint32_t partial_stride, uint32_t payload_words_b1,
-                                                    uint32_t *dev_status, const uint32_t *coin_total) {
+                                                    uint32_t partial_stride, uint32_t *dev_status, const uint32_t *coin_total) {
     __shared__ double red[4];
     const uint32_t c = blockIdx.x;
     const double n2 = ordered_sum<256, false>(partials_n2 + (size_t)c * partial_stride, nparts_n2, red);
     const double total = ordered_sum<256, false>(partials_ip + (size_t)c * partial_stride, nparts_ip, red);
-    const uint32_t b_q8 = B.b_q8[c];
-    if (!(enc_valid_norm(n2) && total > 0.0)) {
-        uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
-        int bits, k;
-        budget_of(b_q8, bits, k);
-        const uint64_t D = 32ull * payload_words_b1;
-        const uint64_t nw = (payload_a_bytes(D, bits, k) + (coin_q8(b_q8) ? coin_b_bytes(coin_total[c]) : payload_b_bytes(D, b_q8))) / 4;
-        for (uint64_t i = threadIdx.x; i < nw; i += 256) payload[i] = 0u;
-    }
+    if (!(enc_valid_norm(n2) && total > 0.0)) zero_payload<256>(B, c, log2D, coin_total, false);
     if (threadIdx.x == 0) write_enc_header(B, c, hdr_d, log2D, seed, n2, total, dev_status, coin_total);
 }
 
@@ -1086,9 +1077,8 @@ void launch_enc_norm(const EncBatch &B, uint32_t n, const double *partials, uint
 void launch_enc_finish(const EncBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed,
                        const double *partials_n2, uint32_t nparts_n2, const double *partials_ip, uint32_t nparts_ip,
                        uint32_t partial_stride, uint32_t *dev_status, const uint32_t *coin_total, hipStream_t st) {
-    const uint32_t words_b1 = 1u << (log2D - 5);
     hipLaunchKernelGGL(k_enc_finish, dim3(n), dim3(256), 0, st, B, hdr_d, log2D, seed, partials_n2, nparts_n2, partials_ip,
-                       nparts_ip, partial_stride, words_b1, dev_status, coin_total);
+                       nparts_ip, partial_stride, dev_status, coin_total);
 }
 void launch_coin_tables(const uint32_t *clients, const uint32_t *b_q8, void *const *part_b, uint32_t n, uint64_t seed, int log2D,
                         const CoinTables &ct, hipStream_t st) {

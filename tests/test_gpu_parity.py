@@ -291,6 +291,45 @@ def test_zero_and_nonfinite_vectors_of_every_budget_in_two_launches(ctx, d, n):
                     assert float(m[32:40].cpu().numpy().view(np.float64)[0]) == 0.0
 
 
+@pytest.mark.parametrize("d,n", [(3000, 12), (5000, 12), (100_000, 12), (300_000, 2), (900_000, 2), (300_000, 12), (2_500_000, 3)])
+def test_finite_vectors_whose_transform_overflows_or_vanishes(ctx, d, n):
+    # |x|^2 (in double) is fine but <R(x),Q> (from fp32 values) is NaN or 0: such a message says EDEN_DEV_ZERO_VECTOR and has S = 0
+    # and an all-zero payload at every size and in every way the encoder is launched, whatever the buffer held; its neighbours get
+    # the message they get among usable vectors, and the receiver adds nothing for it
+    from paper_2108_08842_amd import eden
+    kinds = [256, 128, 512, 768, 1024, 384, 640, 896, 1536, 2048, eden.B_GRID(0.5224), eden.B_COIN(2.4)]
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    good = torch.randn(d, generator=gen, device="cuda")
+    huge = (torch.randint(0, 2, (d,), generator=gen, device="cuda") * 2 - 1) * 3e38      # two stages: inf, then inf - inf
+    tiny = torch.zeros(d, device="cuda")
+    tiny[d // 2] = 1.4e-45                        # the smallest float: u q of an inner interval (q < 1/2) rounds to 0
+    for first in range(0, len(kinds), n):
+        budgets = kinds[first:first + n]
+        ids = list(range(len(budgets)))
+        want = ctx.encode([good] * len(ids), ids, budgets, 18)
+        for bad in (huge, tiny):
+            xs = [bad if c % 2 == 0 else good for c in ids]
+            msgs = [torch.full((eden.message_bytes(d, b),), 0xA5, dtype=torch.uint8, device="cuda") for b in budgets]
+            print(f"d={d} budgets={budgets} {'huge' if bad is huge else 'tiny'}", flush=True)
+            ctx.encode(xs, ids, budgets, 18, msgs)
+            ctx.last_device_status()
+            for c, m in enumerate(msgs):
+                raw = m.cpu().numpy()
+                length = eden.message_length(raw[:64].tobytes())
+                if xs[c] is good:
+                    assert torch.equal(m[:length], want[c][:length]), budgets[c]
+                    continue
+                status, S = int(raw[24:28].view(np.uint32)[0]), float(raw[32:40].view(np.float64)[0])
+                if bad is huge or budgets[c] == 512:
+                    assert status == eden.DEV_ZERO_VECTOR, (budgets[c], status)
+                if status:
+                    assert S == 0.0 and not raw[64:length].any(), budgets[c]
+            if bad is huge:
+                acc = torch.zeros(d, device="cuda")
+                ctx.decode_accumulate(msgs[::2], ids[::2], budgets[::2], d, 18, acc)
+                assert not acc.any().item() and ctx.last_decode_flags(len(ids[::2])) == [eden.DEV_ZERO_VECTOR] * len(ids[::2])
+
+
 def test_degenerate_vectors_and_status(ctx):
     from paper_2108_08842_amd import eden
     for d in (100, 10_000):
