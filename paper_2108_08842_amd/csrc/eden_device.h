@@ -356,8 +356,10 @@ __device__ inline uint32_t quantize_one(float u, const EncScratch *sc, const flo
 // result is the one of quantize_one for every input: the margin (0.43 of a number) is far beyond the rounding of r, t is capped
 // above the outermost threshold where r still rises, and the compare is exact: a value on a positive threshold stays below
 // it, one on a negative threshold (or on 0) stays above it, which "u > the float just below the threshold" says with
-// the same compare.  Where c1 would overflow (|x| below 2e-38) values and thresholds are multiplied by 2^60 first, exactly.
-// |x| = 0 or not finite: any index in range will do, the payload is cleared afterwards (the cap, a constant, keeps it in range).
+// the same compare.  Where c1 would overflow (|x| below 2e-38) values and thresholds are multiplied by 2^60 first, exactly.  Where
+// |x| is so large that outer thresholds are +inf (beyond 1.4e38), no value exceeds one of those: the cap then is the t at which r
+// is 0.4 above the last finite threshold's number, so that this one decides about everything beyond.
+// |x| = 0 or not finite, u = NaN: any index in range will do, the payload is cleared afterwards (the cap keeps it in range).
 // Two four-byte reads of tables of 18 entries (lanes that hit one bank read one address: no conflicts); a table of 64 cells
 // with the threshold, both centroids and the count in 16 bytes cost three times their LDS time.
 template <int H>
@@ -368,7 +370,8 @@ struct RankGuess {
 template <int H>
 __device__ inline void fill_rank_guess(RankGuess<H> &g, const EncScratch *sc, uint32_t thread) {
     if (thread >= 2u * H + 2u) return;
-    const int j = (int)thread - H;                               // the float just below -thr (or 0) has the next larger magnitude
+    // the float just below -thr (or 0) has the next larger magnitude (next to an infinite one is a NaN, which the cap keeps out of use)
+    const int j = (int)thread - H;
     const float mag = (j > -H && j < H && j != 0) ? sc->thr[j < 0 ? -j : j] * sc->guess_up : 0.0f;
     g.thr[thread] = j <= -H || j >= H ? __builtin_inff() : j > 0 ? mag : __uint_as_float(0x80000000u | (__float_as_uint(mag) + 1u));
     const int index = (int)thread - 1;
@@ -590,10 +593,12 @@ __device__ inline void fill_enc_scratch(EncScratch *s, double n2, uint32_t b_q8,
     s->qpos2[tid] = (float)tab->q[finer][tid];
     if (bits == 4 && tid == 0u) {                                // r(x) = a x + b x |x|, x = u / (the last threshold): r = 4, 7 at thresholds 4, 7
         const double last = tab->t[4][7], m = tab->t[4][4] / last, b = (7.0 - 4.0 / m) / (1.0 - m), a = 7.0 - b;
-        const double up = last * norm < 0x1p-124 ? 0x1p60 : 1.0;
+        const double up = last * norm < 0x1p-124 ? 0x1p60 : 1.0, c3 = b / (a * a);
+        int top = 7;                                             // the last threshold that is a finite float
+        while (top > 0 && !((float)(tab->t[4][top] * norm) < INFINITY)) --top;
         s->guess_c1 = (float)(a / (last * norm * up));
-        s->guess_c3 = (float)(b / (a * a));
-        s->guess_cap = (float)(1.1 * a);
+        s->guess_c3 = (float)c3;
+        s->guess_cap = (float)(top == 7 ? 1.1 * a : (sqrt(1.0 + 4.0 * c3 * (top + 0.4)) - 1.0) / (2.0 * c3));
         s->guess_up = (float)up;
     }
 }

@@ -188,9 +188,9 @@ def test_rounds_of_one_integer_budget(ctx, d, b_q8):
 
 @pytest.mark.parametrize("scale", [1.0, 2e-38])
 def test_four_bit_instance_writes_what_the_shared_kernel_writes(ctx, scale):
-    # a launch whose senders all have b = 4 (interval search by table, transposing pack) and a launch that mixes budgets (threshold
-    # counting, ballots) write the same message for the same sender, bit for bit; also for a vector so small that the table's
-    # cell width underflows and the instance has to count thresholds itself
+    # a launch whose senders all have b = 4 (interval search by a guess and one compare, transposing pack) and a launch that mixes
+    # budgets (threshold counting, ballots) write the same message for the same sender, bit for bit; also for a vector so small that
+    # the factor of the guess would overflow and the instance scales values and thresholds first
     d = (1 << 21) - 3
     w = synth.Workload("t", 2, d, [1024, 1024], 99, "lognormal_signed")
     xs = [synth.client_vector(w, c) for c in range(2)]
@@ -202,6 +202,25 @@ def test_four_bit_instance_writes_what_the_shared_kernel_writes(ctx, scale):
     torch.cuda.synchronize()
     assert ctx.last_device_status() == 0
     assert torch.equal(alone[0], mixed[0])
+
+
+@pytest.mark.parametrize("peak,spikes", [(3.2e38, 5), (3.35e38, 5), (3.3e38, 3), (3.3e38, 2), (3.3e38, 1)])
+def test_four_bit_instance_where_outer_thresholds_are_infinite(ctx, peak, spikes):
+    # |x| beyond 1.4e38: the outer thresholds of I_4 times |x| exceed the largest float, while the values u (sums of a few spikes and
+    # some noise, at most 3.4e38) do not: the outermost one infinite (|x| = 1.43e38 and 1.50e38), then one to all seven more of them;
+    # the indices are those of the kernel that counts thresholds
+    d = (1 << 21) - 3
+    rng = np.random.default_rng(spikes)
+    x = rng.standard_normal(d)
+    x *= 0.04e38 / np.abs(x).sum()                               # the noise moves no value by more than 4e36
+    x[rng.choice(d, spikes, replace=False)] = peak / spikes * rng.choice([-1.0, 1.0], spikes)
+    x_dev = [torch.from_numpy(x.astype(np.float32)).cuda(), torch.randn(d, device="cuda")]
+    alone = ctx.encode(x_dev, [5, 6], [1024, 1024], 98)
+    mixed = ctx.encode(x_dev, [5, 6], [1024, 512], 98)
+    assert ctx.last_device_status() == 0
+    assert torch.equal(alone[0][64:], mixed[0][64:])
+    codes = torch.cat([alone[0][64:] & 15, alone[0][64:] >> 4])
+    assert codes.unique().numel() >= 2 and bool(((codes >= 0) & (codes < 16)).all())
 
 
 @pytest.mark.parametrize("d", [5000, 70_000, 300_000])
