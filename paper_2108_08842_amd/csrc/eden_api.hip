@@ -38,7 +38,8 @@ struct eden_ctx {
     DecScratch *dec_scratch; // slots
     DevTables *tables;
     uint32_t *dev_status;
-    uint32_t *arrived;           // counters of arrive_last (0 between launches): two per sender of an encode launch, one for decode
+    uint32_t *arrived;           // counters of arrive_last (0 between launches): two per sender of an encode launch, kDecCounters for decode
+    uint32_t dec_turn = 0;       // which of those the next small decode launch uses
     uint32_t *msg_flags;         // n_max words: the status bits of every message of the last eden_decode_accumulate call
     uint32_t last_decode_n = 0;  // how many of them that call wrote
     // optional kernel timing (eden_profile_*)
@@ -50,7 +51,7 @@ struct eden_ctx {
 
 namespace {
 
-constexpr uint32_t kArrivedCounters = 2 * kMaxBatch + 1;
+constexpr uint32_t kArrivedCounters = 2 * kMaxBatch + kDecCounters;
 // An encode call is two launches (see EncTail) up to D = 2^18, whose passes are short wave-tile launches (32 senders of 2^17, b = 2:
 // 42.1 -> 35.6 us; one of 20,000: 21.4 -> 14.3), and up to this many coordinates of all senders together at D = 2^19 and 2^20 (2 senders
 // of 2^20: 22.5 -> 20.0 us; 4 senders: 23.5 -> 25.4, 8 senders: 30.9 -> 34.0; one sender of 2^21 .. 2^24: 3..5 us slower).
@@ -572,7 +573,8 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
         if (pl.lo_bits == 0) {
             Timed t(ctx, EDEN_K_DEC_SMALL, nb, st);
             launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived + 2 * kMaxBatch,
-                             ctx->dev_status, flags_out + first, st);
+                             ctx->dec_turn, ctx->dev_status, flags_out + first, st);
+            ctx->dec_turn = (ctx->dec_turn + 1u) % kDecCounters;
         } else {
             // Strided pass first (every sender on its own), contiguous pass last (sums the senders in registers
             // and touches acc once).  The workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).

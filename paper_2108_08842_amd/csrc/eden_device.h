@@ -13,6 +13,7 @@
 namespace eden {
 
 constexpr int kMaxBatch = 32;            // senders handled by one launch; larger batches are chunked
+constexpr uint32_t kDecCounters = 8;     // arrival counters of the small decode launches, used in turn (see k_dec_small)
 constexpr int kLoBits = 12;              // index bits transformed by the contiguous (wave-tile) pass
 constexpr int kLoTile = 1 << kLoBits;    // 4096 coordinates = 64 lanes x 64 registers
 constexpr int kLdsRow = 68;              // padded row length (floats) of the 64x64 LDS transpose

@@ -52,12 +52,12 @@ void launch_finalize_mean(const float *acc, uint64_t d, uint32_t n, float *mean,
 // D <= 4096 (eden_kernels_small.hip): one launch per direction.
 // `msg_flags` (may be null): one status word per message of the launch, written by the kernel that checks the headers.
 // `pre` as in launch_dec_lo_last (2: into `slots`); `partial`: room for n * (output length of a sender) floats, used when the
-// senders do not fit one workgroup; `arrived`: a counter that is 0 between launches; mean_n > 0: acc is written with the sum
-// divided by mean_n instead of added to.
+// senders do not fit one workgroup; `arrived`: kDecCounters counters that are 0 between launches, `turn`: the one of this
+// launch (the next one of the context for every launch); mean_n > 0: acc is written with the sum divided by mean_n instead of added to.
 void launch_enc_small(const EncBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
                       const DevTables *tab, uint32_t *dev_status, hipStream_t st);
 void launch_dec_small(const DecBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
-                      const DevTables *tab, float *acc, float mean_n, float *slots, float *partial, uint32_t *arrived,
+                      const DevTables *tab, float *acc, float mean_n, float *slots, float *partial, uint32_t *arrived, uint32_t turn,
                       uint32_t *dev_status, uint32_t *msg_flags, hipStream_t st);
 // b = m/64 (eden_kernels_sparse.hip): the kept coordinates of every x_c (m per block of 64) packed into out + (c << log2_stride),
 // and added back from there into acc, sender by sender; mean_n > 0: acc is written with the sum divided by mean_n instead

@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64 * W) void k_enc_small(EncBatch B, uint64_t d, in
 template <int W>
 __global__ __launch_bounds__(1024) void k_dec_small(DecBatch B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D,
                                                     uint64_t seed, const DevTables *tab, int any_coin, float *acc, float mean_n,
-                                                    float *slots, float *partial, uint32_t *arrived, uint32_t *dev_status,
+                                                    float *slots, float *partial, uint32_t *arrived, uint32_t turn, uint32_t *dev_status,
                                                     uint32_t *msg_flags) {
     constexpr uint32_t TEAMS = 16u / W, T = 64u * W;
     __shared__ float buf[8192];                                  // 256 floats per wave; the senders' results (pre == 1: twice as many)
@@ -434,7 +434,12 @@ __global__ __launch_bounds__(1024) void k_dec_small(DecBatch B, uint32_t n, uint
         if (!one_block) store_through(partial + (size_t)blockIdx.x * stride + i, sum);
         else if (i < d) acc[i] = ((mean_n > 0.0f ? 0.0f : acc[i]) + sum) / div;
     }
-    if (one_block || !arrive_last(arrived, gridDim.x, &last_flag)) return;
+    if (one_block) return;
+    // Calls that overlapped against the rules may leave a counter non-zero, and with it this launch would add too early or never.
+    // The launches of a context take the counters in turn and clear all but their own, so the calls after such an overlap
+    // find theirs at 0.  (A captured launch keeps its counter: any other decode of the context clears it.)
+    if (blockIdx.x == 0 && threadIdx.x < kDecCounters && threadIdx.x != turn) arrived[threadIdx.x] = 0u;
+    if (!arrive_last(arrived + turn, gridDim.x, &last_flag)) return;
     for (uint32_t i = threadIdx.x; i < stride && i < d; i += blockDim.x) {
         float sum = 0.0f;
         for (uint32_t g = 0; g < gridDim.x; g += 8) {            // eight loads in flight: one after the other took 1 us each
@@ -464,7 +469,7 @@ void launch_enc_small(const EncBatch &B, uint32_t n, uint64_t d, int pre, uint64
                                          tab, dev_status))
 }
 void launch_dec_small(const DecBatch &B, uint32_t n, uint64_t d, int pre, uint64_t hdr_d, int log2D, uint64_t seed,
-                      const DevTables *tab, float *acc, float mean_n, float *slots, float *partial, uint32_t *arrived,
+                      const DevTables *tab, float *acc, float mean_n, float *slots, float *partial, uint32_t *arrived, uint32_t turn,
                       uint32_t *dev_status, uint32_t *msg_flags, hipStream_t st) {
     int any_coin = 0;
     for (uint32_t c = 0; c < n; ++c) any_coin |= coin_q8(B.b_q8[c]) != 0u;
@@ -472,7 +477,7 @@ void launch_dec_small(const DecBatch &B, uint32_t n, uint64_t d, int pre, uint64
     const uint32_t teams = n < 16u / waves ? n : 16u / waves;    // senders per workgroup of at most 1024 threads
     dim3 grid((n + teams - 1) / teams), block(64u * waves * teams);
     EDEN_SMALL_SWITCH(hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_small<W>), grid, block, 0, st, B, n, d, pre, hdr_d, log2D, seed, tab,
-                                         any_coin, acc, mean_n, slots, partial, arrived, dev_status, msg_flags))
+                                         any_coin, acc, mean_n, slots, partial, arrived, turn, dev_status, msg_flags))
 }
 
 }  // namespace eden

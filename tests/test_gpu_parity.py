@@ -675,6 +675,43 @@ def test_step_can_be_captured_in_a_graph(ctx, kind):
     assert ctx.last_device_status() == 0
 
 
+@pytest.mark.parametrize("d,n", [(700, 20), (4096, 7), (20_000, 3)])
+def test_captured_rounds_of_the_sizes_that_count_arrivals(ctx, d, n):
+    # several workgroups per decode launch (d <= 4096) and the two-launch encoder: a captured round keeps the arrival counters it was
+    # captured with; replays between eager rounds with other numbers of workgroups, more of them than there are counters
+    kinds = [256, 512, 1024, 384, 1536]
+    budgets = [kinds[c % len(kinds)] for c in range(n)]
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    xs = [torch.randn(d, generator=gen, device="cuda") for _ in range(n)]
+    ids = list(range(n))
+    msgs = ctx.alloc_messages(d, budgets)
+    mean = torch.empty(d, device="cuda")
+
+    def step():
+        ctx.encode(xs, ids, budgets, 31, msgs=msgs)
+        ctx.decode_mean(msgs, ids, budgets, d, 31, mean)
+
+    step()
+    eager, first = mean.clone(), msgs[0].clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    half = torch.empty(d, device="cuda")
+    for turn in range(12):
+        k = 1 + (5 * turn) % n
+        ctx.decode_mean(msgs[:k], ids[:k], budgets[:k], d, 31, half)
+        mean.fill_(3.0)
+        msgs[0].zero_()
+        graph.replay()
+        assert torch.equal(mean, eager) and torch.equal(msgs[0], first)
+    assert ctx.last_device_status() == 0
+
+
 @pytest.mark.parametrize("d,budgets,drop", [
     (3000, [256, 512, 1024], 0),                               # one workgroup per sender: the three steps inside the call
     (200_000, [128, 256, 768], 0.2),                           # 12-bit contiguous pass: the same
