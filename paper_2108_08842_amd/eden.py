@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes
 import os
 from array import array
+from operator import index
 from typing import Optional, Sequence
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -89,7 +90,7 @@ def lib():
     L.eden_destroy.restype = ci
     L.eden_message_bytes.argtypes = [u64, u32]
     L.eden_message_bytes.restype = sz
-    # (the arrays of a batch travel as addresses: see _u64s)
+    # (the arrays of a batch travel as addresses: see _elements)
     L.eden_encode.argtypes = [vp, vp, vp, vp, u32, u64, u64, vp, vp, vp]
     L.eden_encode.restype = ci
     L.eden_encode_static.argtypes = [vp, vp, vp, u32, u64, u64, vp, vp, vp]
@@ -166,15 +167,26 @@ def _stream_ptr(stream=None):
 # Arrays of a batch as (object that owns the memory, address): the C side takes them by address and copies what it needs before
 # the call returns.  The array module builds them several times faster than ctypes does, which matters for calls whose kernels
 # take a few microseconds.
+def _elements(values):
+    """A sequence as a list of its elements (the array module would take bytes as raw memory, and an iterator that fails half
+    way could not be read again: without a length it is refused)."""
+    len(values)
+    return list(values)
+
+
 def _u64s(values):
+    if type(values) is not list:
+        values = _elements(values)
     try:
         a = array("Q", values)
-    except (TypeError, OverflowError):                           # anything int() takes; None is a null pointer
-        a = array("Q", [int(v or 0) & _SEED_MASK for v in values])
+    except (TypeError, OverflowError):                           # anything int() takes
+        a = array("Q", [int(v) & _SEED_MASK for v in values])
     return a, a.buffer_info()[0]
 
 
 def _u32s(values):
+    if type(values) is not list:
+        values = _elements(values)
     try:
         a = array("I", values)
     except (TypeError, OverflowError):
@@ -182,8 +194,18 @@ def _u32s(values):
     return a, a.buffer_info()[0]
 
 
+def _ptrs(values):
+    if type(values) is not list:
+        values = _elements(values)
+    try:
+        a = array("Q", values)
+    except (TypeError, OverflowError):                           # None is a null pointer; no conversions
+        a = array("Q", [0 if v is None else index(v) & _SEED_MASK for v in values])
+    return a, a.buffer_info()[0]
+
+
 def _ptrs_or_null(ptrs):
-    return (None, None) if ptrs is None else _u64s([p or 0 for p in ptrs])      # null: no bitmap for that sender
+    return (None, None) if ptrs is None else _ptrs(ptrs)        # null: no bitmap at all, or none for that sender
 
 
 def _device_ptrs(tensors):
@@ -192,7 +214,7 @@ def _device_ptrs(tensors):
 
 def encode_static_raw(x_ptrs, client_ids, b_q8, d, seed, msg_ptrs, msg_caps, stream=None) -> int:
     """eden_encode_static on the current device: the library's status code, nothing raised."""
-    x, ids, b, m, caps = _u64s(x_ptrs), _u32s(client_ids), _u32s(b_q8), _u64s(msg_ptrs), _u64s(msg_caps)
+    x, ids, b, m, caps = _ptrs(x_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs(msg_ptrs), _u64s(msg_caps)
     return lib().eden_encode_static(x[1], ids[1], b[1], len(x_ptrs), d, seed & _SEED_MASK, m[1], caps[1], _stream_ptr(stream))
 
 
@@ -229,16 +251,16 @@ class Context:
 
     # ---- raw calls: return the library's status code, raise nothing
     def encode_raw(self, x_ptrs, client_ids, b_q8, d, seed, msg_ptrs, msg_caps, stream=None) -> int:
-        x, ids, b, m, caps = _u64s(x_ptrs), _u32s(client_ids), _u32s(b_q8), _u64s(msg_ptrs), _u64s(msg_caps)
+        x, ids, b, m, caps = _ptrs(x_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs(msg_ptrs), _u64s(msg_caps)
         return lib().eden_encode(self._h, x[1], ids[1], b[1], len(x_ptrs), d, seed & _SEED_MASK, m[1], caps[1], _stream_ptr(stream))
 
     def decode_accumulate_raw(self, msg_ptrs, client_ids, b_q8, d, seed, bitmap_ptrs, acc_ptr, stream=None) -> int:
-        m, ids, b, bm = _u64s(msg_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs_or_null(bitmap_ptrs)
+        m, ids, b, bm = _ptrs(msg_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs_or_null(bitmap_ptrs)
         return lib().eden_decode_accumulate(self._h, m[1], ids[1], b[1], len(msg_ptrs), d, seed & _SEED_MASK, bm[1], acc_ptr,
                                             _stream_ptr(stream))
 
     def decode_mean_raw(self, msg_ptrs, client_ids, b_q8, d, seed, bitmap_ptrs, mean_ptr, stream=None) -> int:
-        m, ids, b, bm = _u64s(msg_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs_or_null(bitmap_ptrs)
+        m, ids, b, bm = _ptrs(msg_ptrs), _u32s(client_ids), _u32s(b_q8), _ptrs_or_null(bitmap_ptrs)
         return lib().eden_decode_mean(self._h, m[1], ids[1], b[1], len(msg_ptrs), d, seed & _SEED_MASK, bm[1], mean_ptr,
                                       _stream_ptr(stream))
 

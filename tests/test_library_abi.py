@@ -105,3 +105,29 @@ def test_header_is_plain_c_and_library_links_from_c(eden, tmp_path):
     subprocess.run(cmd, check=True, capture_output=True, text=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True)
     assert "abi ok" in out.stdout
+
+
+def test_arrays_of_a_batch_hold_the_elements_of_any_sequence(eden):
+    # ids, budgets, sizes and pointers as the C side reads them, from lists, tuples, ranges, numpy arrays and bytes (whose elements
+    # count, not their memory); negative and oversized integers wrap; what has no length or is no integer is refused
+    import ctypes
+
+    def read(made, kind):
+        owner, address = made
+        return list((kind * len(owner)).from_address(address)) if len(owner) else []
+
+    u32, u64 = ctypes.c_uint32, ctypes.c_uint64
+    for values in ([3, 1, 2, 7], (3, 1, 2, 7), np.array([3, 1, 2, 7], dtype=np.int64), bytes([3, 1, 2, 7]), bytearray([3, 1, 2, 7]),
+                   np.array([3, 1, 2, 7], dtype=np.uint8), [np.int32(3), 1, True + 1, 7.0]):
+        assert read(eden._u32s(values), u32) == [3, 1, 2, 7] and read(eden._u64s(values), u64) == [3, 1, 2, 7]
+    assert read(eden._u32s(range(5)), u32) == [0, 1, 2, 3, 4]
+    assert read(eden._u32s([-1, 2 ** 32 + 5]), u32) == [2 ** 32 - 1, 5]
+    assert read(eden._u64s([2 ** 64 - 1, 2 ** 64 + 5]), u64) == [2 ** 64 - 1, 5]
+    assert read(eden._ptrs([4096, None, 0]), u64) == [4096, 0, 0] and read(eden._ptrs((None,)), u64) == [0]
+    assert eden._ptrs_or_null(None) == (None, None) and read(eden._ptrs_or_null([None, 64]), u64) == [0, 64]
+    for refused in (lambda: eden._u32s(iter([1, 2])), lambda: eden._u64s(v for v in (1, -1)), lambda: eden._ptrs(iter([64])),
+                    lambda: eden._ptrs([1.5]), lambda: eden._ptrs(["64"]), lambda: eden._u64s([None]), lambda: eden._u32s([None])):
+        with pytest.raises(TypeError):
+            refused()
+    with pytest.raises(ValueError):
+        eden._u32s("abcd")
