@@ -157,11 +157,13 @@ def get_tables(bits: int):
 
 
 def _stream_ptr(stream=None):
-    """Address of a stream, by default the current one of the current device (without a Stream object around it)."""
+    """Address of a stream, by default the current one of the current device (without a Stream object around it where torch
+    offers that)."""
     import torch
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 # Arrays of a batch as (object that owns the memory, address): the C side takes them by address and copies what it needs before

@@ -131,3 +131,16 @@ def test_arrays_of_a_batch_hold_the_elements_of_any_sequence(eden):
             refused()
     with pytest.raises(ValueError):
         eden._u32s("abcd")
+
+
+def test_stream_address_without_the_short_cut(eden, monkeypatch):
+    # torch's raw stream is a private name: without it the public Stream object gives the same address
+    torch = pytest.importorskip("torch")
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert eden._stream_ptr() == 0x1234
+    assert eden._stream_ptr(Stream()) == 0x1234
