@@ -79,8 +79,8 @@ __device__ inline uint32_t hix_row2(uint32_t g, int ph, int s) {
 // Exchange of half `PHASE`: stage-1 registers -> LDS -> registers that hold all low row bits of
 // RHL high-row values; then the butterflies over those low row bits.  Split in two so that a caller can
 // start loading the next tile into the registers the write has just freed.
-template <int M, int PHASE>
-__device__ inline void hix_exchange_write(const float (&v)[64], float *lds) {
+template <int M, int PHASE, int N>
+__device__ inline void hix_exchange_write(const float (&v)[N], float *lds) {
     using X = HiX<M>;
     const uint32_t col = threadIdx.x & 31u, g = threadIdx.x >> 5;
     // an LDS instruction reaches 64 KiB beyond its address register: M = 11 gets one register per 64 KiB (left to itself the

@@ -201,6 +201,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
     constexpr int p = P;
     constexpr int NW = X::RP / 32;
     constexpr bool UNIT = MODE == 0;
+    constexpr bool SHARED = ONLY == 0u && (MODE == 1 || MODE == 2);
     const uint32_t c = blockIdx.y;
     const uint32_t tile0 = xcd_local_tile<16 / TPW>() * TPW;
     const uint32_t col = threadIdx.x & 31u, g = threadIdx.x >> 5;
@@ -248,14 +249,32 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
         const uint32_t next_off = tile_off(tile0 + k + 1);
         fwht_regs<64>(v);
         float out[X::RP];
+        // The instances that serve several budgets hold one copy of the code behind the exchange for both halves: with two, 75 and 100 KB,
+        // more than the instruction cache, they were slower in halves than in one piece (M = 7..9) and spilled 32 to 48 registers, now 0
+        // and 6 to 17.  (One sender of 7,000,001, b = 8: 48.8 -> 40.0 us, in one piece 41.9; 8 of 4,000,037 with b = 1, 3, 1.5, 8:
+        // 121 -> 98, 106; one of 10^8 at 2.7 bits: 617 -> 547, in three passes 555.)  The trip count is hidden from the compiler, which
+        // would otherwise unroll by threading jumps.
+        int halves = X::PH;
+        float cur[SHARED ? X::RP : 1];
+        if constexpr (SHARED) {
+            asm volatile("" : "+s"(halves));
 #pragma unroll
-        for (int ph = 0; ph < X::PH; ++ph) {
-            if (ph == 0) hix_exchange_write<M, 0>(v, lds);
+            for (int r = 0; r < X::RP; ++r) cur[r] = v[r];
+        }
+#pragma unroll(SHARED ? 1 : X::PH)
+        for (int ph = 0; ph < halves; ++ph) {
+            if constexpr (SHARED) {
+                hix_exchange_write<M, 0>(cur, lds);
+#pragma unroll
+                for (int r = 0; r < X::RP; ++r) cur[r] = v[X::RP + r];
+            } else if (ph == 0) hix_exchange_write<M, 0>(v, lds);
             else hix_exchange_write<M, X::PH - 1>(v, lds);
-            if (k + 1 < TPW) {
+            if constexpr (TPW > 1) {
+                if (k + 1 < TPW) {
 #pragma unroll
-                for (int r = ph * X::RP; r < (ph + 1) * X::RP; ++r)
-                    v[r] = buf_load(rt, off1, next_off + row_off(r));
+                    for (int r = ph * X::RP; r < (ph + 1) * X::RP; ++r)
+                        v[r] = buf_load(rt, off1, next_off + row_off(r));
+                }
             }
             hix_exchange_read<M, !UNIT>(lds, out);               // every sender b <= 1: the last stage is fused into the signs
             if (UNIT) hix_sign_words_pairs<M>(out, ip, held[k][ph]);
@@ -266,7 +285,15 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
                 }
                 hix_quantize_pack<M, P, 4, 0, true>(out, ph, sc, qtab, payload, reinterpret_cast<uint16_t *>(payload), mixkey, base, ip, ct,
                                                  c, log2D, payload, &guess);
-            } else if (b_q8 <= 256u) hix_sign_words<M>(out, ip, held[k][ph]);
+            } else if (SHARED && b_q8 <= 256u) {
+                uint32_t words[NW];
+                hix_sign_words<M>(out, ip, words);
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {                   // (ph is a variable here: no index into registers)
+                    held[k][0][w] = ph == 0 ? words[w] : held[k][0][w];
+                    held[k][X::PH - 1][w] = words[w];
+                }
+            }
             else if (byte_budget(b_q8)) {
                 // uniform grid (Sec. 4.3) or b = 5..8: one byte per coordinate; a row segment of the tile is 32 bytes
                 uint8_t *bytes = (B.codes[c] ? B.codes[c] : reinterpret_cast<uint8_t *>(payload)) + base + col;
@@ -421,9 +448,9 @@ uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint3
     // every other launch: one tile per workgroup (with the blocked workspace two tiles per workgroup are slower at every size:
     // 16 senders at D = 2^23, 0.151 -> 0.142 ms at b = 2, 0.34 -> 0.18 ms at b = 1.5, 0.255 -> 0.144 ms for the b = 4 instance)
     dim3 grid(tiles, n);
-    // One budget for all senders: b = 3 and the budgets k + 1/2 have instances that hold only their branch (the shared ones
-    // spill 76 and 188 bytes at M = 10; 16 senders at D = 2^24: 0.40 -> 0.24 ms at b = 1.5, 0.277 -> 0.253 ms at b = 3; at
-    // b = 2 such an instance gained nothing).
+    // One budget for all senders: b = 3 and the budgets k + 1/2 have instances that hold only their branch (16 senders at D = 2^24,
+    // against shared instances that still spilled: 0.40 -> 0.24 ms at b = 1.5, 0.277 -> 0.253 ms at b = 3; at b = 2 such an instance
+    // gained nothing).
     uint32_t same = B.b_q8[0];
     for (uint32_t c = 1; c < n; ++c) if (B.b_q8[c] != same) same = 0;
 #define EDEN_ENC_HIX_ONLY(MODE, ONLY)                                                                                         \
