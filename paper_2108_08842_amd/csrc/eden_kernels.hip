@@ -546,6 +546,8 @@ __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t kee
         for (int r = 0; r < kWideRows; ++r)
 #pragma unroll
             for (int h = 0; h < 2; ++h) word[r][h] = fetch((base + ((uint32_t)r << p) + 256u * h) / 4u + lane);
+#pragma unroll
+        for (int r = 0; r < kWideRows; ++r) asm volatile("" : "+v"(word[r][0]), "+v"(word[r][1]));      // else each is loaded where it is used
     };
     auto for_values = [&](auto &&value) {
 #pragma unroll
