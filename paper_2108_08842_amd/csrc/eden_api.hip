@@ -595,7 +595,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
                 Timed t(ctx, EDEN_K_DEC_FIRST, nb, st);
                 if (pl.wide) launch_dec_wide_first(B, nb, round_up(d, 14 + pl.M), log2D, ctx->dec_scratch, ctx->T, st);
                 else if (pl.wg) launch_dec_hix_first(pl.M, pl.lo_bits, B, nb, d, log2D, seed, ctx->dec_scratch, narrow, ctx->T, ctx->coin,
-                                                first_prepares ? &prep : nullptr, st);
+                                                first_prepares ? &prep : nullptr, ctx->compute_units, st);
                 // what the last pass reads: whole tiles of it that hold part of the first d coordinates
                 else launch_dec_hi_first(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, prep, narrow, ctx->T,
                                          ctx->coin, st);

@@ -22,11 +22,11 @@
 
 namespace eden {
 
-template <int M>
+template <int M, int PIECES = 2>
 struct HiX {
     static constexpr int RL = 1 << (M - 6);       // row groups: the low M-6 row bits live across thread groups
     static constexpr int THREADS = 32 * RL;
-    static constexpr int PH = 2;                    // halves of the exchange
+    static constexpr int PH = PIECES;               // pieces (halves) of the exchange
     static constexpr int RP = 64 / PH;            // registers exchanged per half
     static constexpr int RHL = RP / RL;           // high-row values a thread holds after the exchange
     static constexpr int LDS_FLOATS = RP * RL * 32;
@@ -68,9 +68,9 @@ __device__ inline uint64_t hix_base(uint32_t tile, int p) {
 template <int M>
 __device__ inline uint32_t hix_row1(uint32_t g, uint32_t r) { return g + (uint32_t)HiX<M>::RL * r; }
 // row held after the exchange of half ph in register s by a thread of group g
-template <int M>
+template <int M, int PIECES = 2>
 __device__ inline uint32_t hix_row2(uint32_t g, int ph, int s) {
-    using X = HiX<M>;
+    using X = HiX<M, PIECES>;
     const uint32_t e = (uint32_t)s / X::RL, rl = (uint32_t)s % X::RL;
     const uint32_t rh = (uint32_t)ph * X::RP + g * X::RHL + e;
     return rl + (uint32_t)X::RL * rh;

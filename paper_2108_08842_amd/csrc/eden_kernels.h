@@ -85,7 +85,7 @@ uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint3
 void launch_hix_mid(int M, uint32_t n, float *T, int log2D, uint64_t load_elems, uint64_t store_elems, hipStream_t st);
 bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
                           const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, const DecPrepareArgs *prep,
-                          hipStream_t st);
+                          uint32_t compute_units, hipStream_t st);
 // whether launch_dec_hix_first would do so for this batch
 bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int narrow);
 

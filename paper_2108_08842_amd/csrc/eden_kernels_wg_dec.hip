@@ -253,9 +253,9 @@ __device__ inline void fwht_pk(s16x2 (&v)[N]) {
 
 // (Four waves per SIMD are requested so that two of the 512-thread workgroups of M = 10 share a CU: measured
 // 0.103 ms against 0.133 ms per launch on 16 senders at D = 2^24, at the price of five spilled registers.)
-template <int M, int P>
+template <int M, int P, int PIECES>
 __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first_pk(DecBatch B, uint64_t d, int log2D, uint64_t seed, float *T) {
-    using X = HiX<M>;
+    using X = HiX<M, PIECES>;
     constexpr int p = P;
     __shared__ uint32_t lds[X::LDS_FLOATS];
     const uint32_t c = blockIdx.y;
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first_pk(DecBatc
 #pragma unroll
         for (int s2 = 0; s2 < X::RP; ++s2)
             __builtin_amdgcn_raw_buffer_store_b32(narrow_pair_from_int16(__builtin_bit_cast(uint32_t, out[s2])), rt, (int)off2,
-                                                  (int)((hix_row2<M>(0, ph, s2) << p) * 2u), kStream);
+                                                  (int)((hix_row2<M, PIECES>(0, ph, s2) << p) * 2u), kStream);
     }
 }
 
@@ -631,7 +631,7 @@ bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int nar
 }
 bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
                           const DecScratch *scratch, int narrow, float *T, const CoinTables &ct, const DecPrepareArgs *prep,
-                          hipStream_t st) {
+                          uint32_t compute_units, hipStream_t st) {
     bool all_unit = narrow != 0;                                 // every sender b <= 1: packed int16 kernel
     for (uint32_t c = 0; c < n; ++c) all_unit = all_unit && B.b_q8[c] <= 256u;
     bool loss = false;
@@ -660,7 +660,13 @@ bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t 
     }
     if (all_unit) {
         dim3 grid(hix_tiles(M, log2D) / 2, n);                   // 64-column tiles
-        EDEN_HIX_SWITCH(M, P, hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_hix_first_pk<MM, PP>), grid, dim3(HiX<MM>::THREADS), 0, st, B, d, log2D, seed, T));
+        // The exchange in one piece while the workgroups of the launch are all resident with its larger LDS (160 KiB a CU); in halves
+        // beyond (M = 7, b = 1/2, first pass and all: 8 senders 38.1 us in one piece, 40.5 in halves; 32 senders 77.1 and 71.8).
+        const bool one_piece = M <= 9 && (uint64_t)grid.x * n * ((256u << (M - 6)) * 32u) <= (uint64_t)compute_units * (160u << 10);
+#define EDEN_DEC_PK(PIECES) \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_hix_first_pk<MM, PP, PIECES>), grid, dim3(HiX<MM>::THREADS), 0, st, B, d, log2D, seed, T)
+        if (one_piece) EDEN_HIX_SWITCH(M, P, EDEN_DEC_PK((MM <= 9 ? 1 : 2))) else EDEN_HIX_SWITCH(M, P, EDEN_DEC_PK(2))
+#undef EDEN_DEC_PK
         return false;
     }
     dim3 grid(hix_tiles(M, log2D), n);
