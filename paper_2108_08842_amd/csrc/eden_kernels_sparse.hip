@@ -151,9 +151,12 @@ __global__ __launch_bounds__(128) void k_sparse_gather(EncBatch B, uint32_t d, u
 
 // acc[i] += the values of all senders whose selection holds coordinate i, one sender after the other (the factor 64/m is already
 // in the values); mean_n > 0: acc is written with the sum divided by mean_n instead of added to.
-// A workgroup takes 64 blocks = 4096 coordinates: its waves select for one sender at a time, and then its threads add, four
+// A workgroup takes 64 blocks = 4096 coordinates: its waves select for one sender at a time, and then its threads add, NQ times four
 // coordinates at a time.  Two workgroups of eight waves share a CU, one selecting while the other adds: 121 us at the size
 // above; sixteen waves, alone on a CU, 147 us; four waves 126 us; 64 or 80 registers instead of 109 spill: 210 and 162 us.
+// One or two senders leave most of eight waves idle while the others select, and have no other sender's loads to overlap with:
+// fewer waves where the launch fills the chip all the same, and NQ = 4 (see launch_sparse_scatter).
+template <int NQ>
 __global__ __launch_bounds__(512) void k_sparse_scatter(DecBatch B, uint32_t n, uint32_t d, uint32_t m, uint64_t seed, const float *in,
                                                          int log2_stride, float *acc, float mean_n) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
@@ -163,41 +166,96 @@ __global__ __launch_bounds__(512) void k_sparse_scatter(DecBatch B, uint32_t n, 
         sparse_table(stream_key(seed, kStreamSparse, B.client[c]), first, m, lane, tables + c * 2u * kSparseWave);
     __syncthreads();
     const float div = mean_n > 0.0f ? mean_n : 1.0f;
-    for (uint32_t q = threadIdx.x; q < 1024u; q += blockDim.x) {
-        const uint32_t i = first * 64u + 4u * q;
-        if (i >= d) break;
-        const uint32_t shift = 4u * (q & 7u), below = (1u << shift) - 1u;
-        float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
+    const bool overwrite = mean_n > 0.0f;
+    for (uint32_t q0 = threadIdx.x; q0 < 1024u; q0 += NQ * blockDim.x) {
+        if (first * 64u + 4u * q0 >= d) break;
+        float sum[NQ][4], old[NQ][4];
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const uint32_t i = first * 64u + 4u * (q0 + (uint32_t)j * blockDim.x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[j][e] = old[j][e] = 0.0f;
+            if (!overwrite) load4_padded(acc, i, d, true, old[j]);               // (acc is 16-byte aligned)
+        }
+#pragma unroll 4 / NQ
         for (uint32_t c = 0; c < n; ++c) {
-            const KeptHalf h = tables[c * 2u * kSparseWave + (q >> 3)];
             // (a read beyond the slot can only be one whose value is not used: 0 by the buffer bounds)
             const rsrc_t r = make_rsrc(in + ((size_t)c << log2_stride), 4u << log2_stride);
-            uint32_t at = (first * m + h.slot + (uint32_t)__popc(h.mask & below)) * 4u;
-            const uint32_t kept = h.mask >> shift;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {                        // no branch per value: the loads of several senders are in flight
-                const float value = buf_load_keep(r, at, 0u);
-                sum[e] += ((kept >> e) & 1u) ? value : 0.0f;
-                at += ((kept >> e) & 1u) << 2;
+            for (int j = 0; j < NQ; ++j) {
+                const uint32_t q = q0 + (uint32_t)j * blockDim.x, shift = 4u * (q & 7u), below = (1u << shift) - 1u;
+                const KeptHalf h = tables[c * 2u * kSparseWave + (q >> 3)];
+                uint32_t at = (first * m + h.slot + (uint32_t)__popc(h.mask & below)) * 4u;
+                if (NQ > 1 && first * 64u + 4u * q >= d) at = 0xFFFFFFE0u;       // blocks beyond the last one: out of bounds, 0
+                const uint32_t kept = h.mask >> shift;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {                    // no branch per value: the loads of several senders are in flight
+                    const float value = buf_load_keep(r, at, 0u);
+                    sum[j][e] += ((kept >> e) & 1u) ? value : 0.0f;
+                    at += ((kept >> e) & 1u) << 2;
+                }
             }
         }
-        const bool overwrite = mean_n > 0.0f;
-        if (i + 3u < d) {                                        // (acc is 16-byte aligned)
-            float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (!overwrite) a = *reinterpret_cast<const float4 *>(acc + i);
-            a.x = (a.x + sum[0]) / div; a.y = (a.y + sum[1]) / div; a.z = (a.z + sum[2]) / div; a.w = (a.w + sum[3]) / div;
-            *reinterpret_cast<float4 *>(acc + i) = a;
-        } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (i + e < d) acc[i + e] = ((overwrite ? 0.0f : acc[i + e]) + sum[e]) / div;
+        for (int j = 0; j < NQ; ++j) {
+            const uint32_t i = first * 64u + 4u * (q0 + (uint32_t)j * blockDim.x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[j][e] = (old[j][e] + sum[j][e]) / div;
+            if (i + 3u < d) {
+                *reinterpret_cast<float4 *>(acc + i) = make_float4(sum[j][0], sum[j][1], sum[j][2], sum[j][3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < d) acc[i + e] = sum[j][e];
+            }
         }
+    }
+}
+
+// The same by a workgroup of eight waves per 64 blocks, for launches that would leave most of the chip idle: one wave selects while the
+// others wait with their 512 coordinates in registers, then all of them compact and store.  (Up to 1024 groups of 64 blocks; whole
+// encode, against two waves on their own: one sender of 2^20, m = 32, 23.7 -> 21.1 us; 8 of 300,007 29.4 -> 27.2; one of 4,000,037
+// 32.1 -> 29.3; beyond, 2048 groups of 8 senders of 2^20 28.7 -> 30.4 and one sender of 7,000,001 34.3 -> 34.8.)
+__global__ __launch_bounds__(512) void k_sparse_gather_team(EncBatch B, uint32_t d, uint32_t m, uint64_t seed, float *out, int log2_stride) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    const uint32_t lane = lane_id(), wv = wave_in_block(), c = blockIdx.y;
+    const uint32_t blocks = (d + 63u) >> 6, first = blockIdx.x * kSparseWave;
+    KeptHalf *table = reinterpret_cast<KeptHalf *>(lds);
+    float *run = reinterpret_cast<float *>(lds + 4u * kSparseWave);
+    const float *x = B.x[c];
+    const bool vec = (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    float v[2][4];
+#pragma unroll
+    for (uint32_t it = 0; it < 2u; ++it) load4_padded(x, first * 64u + (2u * wv + it) * 256u + 4u * lane, d, vec, v[it]);
+    if (wv == 0) sparse_table(stream_key(seed, kStreamSparse, B.client[c]), first, m, lane, table);
+    __syncthreads();
+    const uint32_t shift = 4u * (lane & 7u), below = (1u << shift) - 1u;
+#pragma unroll
+    for (uint32_t it = 0; it < 2u; ++it) {                       // 256 coordinates = 8 halves per turn
+        const KeptHalf h = table[(2u * wv + it) * 8u + (lane >> 3)];
+        uint32_t at = h.slot + (uint32_t)__popc(h.mask & below);
+        const uint32_t kept = h.mask >> shift;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((kept >> e) & 1u) run[at++] = v[it][e];
+    }
+    __syncthreads();
+    float *dst = out + ((size_t)c << log2_stride) + (size_t)first * m;
+    if (first + kSparseWave <= blocks) {
+        for (uint32_t i = threadIdx.x; i < 16u * m; i += 512u) reinterpret_cast<float4 *>(dst)[i] = reinterpret_cast<const float4 *>(run)[i];
+    } else {
+        for (uint32_t i = threadIdx.x; i < (blocks - first) * m; i += 512u) dst[i] = run[i];
     }
 }
 
 void launch_sparse_gather(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, float *out, int log2_stride, hipStream_t st) {
     const uint32_t blocks = (uint32_t)((d + 63) / 64);
+    const uint32_t groups = (blocks + kSparseWave - 1) / kSparseWave;
+    if ((uint64_t)groups * n <= 1024) {
+        hipLaunchKernelGGL(k_sparse_gather_team, dim3(groups, n), dim3(512), 2u * kSparseWave * (uint32_t)sizeof(KeptHalf) + kSparseWave * m * 4u, st,
+                           B, (uint32_t)d, m, seed, out, log2_stride);
+        return;
+    }
     const uint32_t bytes = 2u * (2u * kSparseWave * (uint32_t)sizeof(KeptHalf) + kSparseWave * m * 4u);        // at most 34 KiB
     hipLaunchKernelGGL(k_sparse_gather, dim3((blocks + 2u * kSparseWave - 1) / (2u * kSparseWave), n), dim3(128), bytes, st, B, (uint32_t)d, m,
                        seed, out, log2_stride);
@@ -205,9 +263,17 @@ void launch_sparse_gather(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m,
 void launch_sparse_scatter(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, const float *in, int log2_stride,
                            float *acc, float mean_n, hipStream_t st) {
     const uint32_t blocks = (uint32_t)((d + 63) / 64);
-    const uint32_t waves = n < 8u ? n : 8u;                    // one wave per sender selects
-    hipLaunchKernelGGL(k_sparse_scatter, dim3((blocks + kSparseWave - 1) / kSparseWave), dim3(64u * waves),
-                       n * 2u * kSparseWave * (uint32_t)sizeof(KeptHalf), st, B, n, (uint32_t)d, m, seed, in, log2_stride, acc, mean_n);
+    const uint32_t groups = (blocks + kSparseWave - 1) / kSparseWave;
+    // one or two senders: as many waves per workgroup, from 8 down to 1, as leave the launch at 4096 waves, 16 for each CU (whole decode,
+    // m = 32: one sender of 250,000 24.6 us with one wave, 15.1 with eight; of 4,000,037 45.0, 36.5 with eight, 33.1 with four and NQ = 4;
+    // of 11,173,962 66.0, 68.4 with eight, 58.8 with one and NQ = 4)
+    uint32_t waves = 8u;
+    while (n <= 2u && waves > 1u && groups * waves > 4096u) waves >>= 1;
+    const uint32_t lds = n * 2u * kSparseWave * (uint32_t)sizeof(KeptHalf);
+    if (n <= 2u && waves <= 4u)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sparse_scatter<4>), dim3(groups), dim3(64u * waves), lds, st, B, n, (uint32_t)d, m, seed, in, log2_stride, acc, mean_n);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sparse_scatter<1>), dim3(groups), dim3(64u * waves), lds, st, B, n, (uint32_t)d, m, seed, in, log2_stride, acc, mean_n);
 }
 
 }  // namespace eden

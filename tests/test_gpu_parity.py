@@ -472,6 +472,27 @@ def test_sparse_rounds_of_many_senders(ctx, d, m, n):
     assert ctx.last_decode_flags(n) == [0] * n
 
 
+@pytest.mark.parametrize("d,m,n", [(2_097_153, 63, 2), (4_200_001, 1, 1), (8_400_010, 6, 2), (8_400_010, 33, 1), (4_194_304, 9, 1)])
+def test_sparse_rounds_of_one_or_two_senders(d, m, n):
+    # the scatter launch takes four, two and one wave per workgroup from 2^21, 2^22 and 2^23 coordinates on (four quads per thread,
+    # blocks and quads beyond the last coordinate among them); the gather launch one wave or a team of eight per 64 blocks
+    from paper_2108_08842_amd import eden
+    own = eden.Context(d_max=d, n_max=n, device=0)
+    budgets = [eden.B_SPARSE(m)] * n
+    w = synth.Workload("t", n, d, budgets, 2500 + d % 1000, "normal")
+    xs = [synth.client_vector(w, c) for c in range(n)]
+    ids = [90 + c for c in range(n)]
+    _run_case(own, xs, ids, budgets, w.seed, also_oracle_msgs=False)
+    msgs = own.encode([torch.from_numpy(x).cuda() for x in xs], ids, budgets, w.seed)
+    acc = torch.zeros(d, device="cuda")
+    own.decode_accumulate(msgs, ids, budgets, d, w.seed, acc)
+    got = torch.full((d,), float("nan"), device="cuda")
+    own.decode_mean(msgs, ids, budgets, d, w.seed, got)
+    assert torch.equal(got.view(torch.int32), own.finalize_mean(acc, n).view(torch.int32))
+    torch.cuda.synchronize()
+    own.close()
+
+
 @pytest.mark.parametrize("d_max,n", [(1, 32), (5, 17), (17, 40), (32, 32), (33, 17), (64, 9)])
 def test_sparse_rounds_in_contexts_of_a_few_coordinates(d_max, n):
     # d < 64 and m > d: the kept vectors (m values of the one block, padded to as many as 64) are longer than the vectors, and the
