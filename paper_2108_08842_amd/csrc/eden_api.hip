@@ -52,10 +52,17 @@ struct eden_ctx {
 namespace {
 
 constexpr uint32_t kArrivedCounters = 2 * kMaxBatch + kDecCounters;
-// An encode call is two launches (see EncTail) up to D = 2^18, whose passes are short wave-tile launches (32 senders of 2^17, b = 2:
-// 42.1 -> 35.6 us; one of 20,000: 21.4 -> 14.3), and up to this many coordinates of all senders together at D = 2^19 and 2^20 (2 senders
-// of 2^20: 22.5 -> 20.0 us; 4 senders: 23.5 -> 25.4, 8 senders: 30.9 -> 34.0; one sender of 2^21 .. 2^24: 3..5 us slower).
+// Whether an encode call is two launches (see EncTail) instead of four, or of three when every sender has b <= 1 and no thresholds are
+// needed.  Two take less time where the passes are so short that the launches count, and more where most workgroups wait for their
+// partial sums to arrive (device time, us, b = 2, four launches -> two: one sender of 20,000 16.0 -> 14.4, 32 of 2^17 26.8 -> 25.5, 8 of
+// 2^18 21.7 -> 21.1, 16 of 2^18 25.4 -> 27.6, 32 of 2^18 28.9 -> 32.6, 2 of 2^20 22.5 -> 20.3, 8 of 2^20 30.9 -> 34.0; one sender
+// of 2^21 .. 2^24 3..5 more.  b = 1, three -> two: 32 of 20,000 24.1 -> 21.9, 16 of 2^16 18.5 -> 17.5, one of 2^16 12.4 -> 13.8 (the
+// same when the host launches it: 14.0, 14.1), 8 of 2^17 15.2 -> 16.5, 32 of 2^18 24.2 -> 29.9, one of 2^20 15.1 -> 16.0).
 constexpr uint64_t kTwoLaunchCoords = 1ull << 21;
+bool encode_in_two_launches(int log2D, uint32_t n, bool need_thresholds) {
+    if (!need_thresholds) return log2D <= 16;
+    return log2D <= 17 || (log2D <= 20 && (uint64_t)n << log2D <= kTwoLaunchCoords);
+}
 
 int ceil_log2(uint64_t d) {
     int l = 0;
@@ -272,8 +279,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             double *part_n2 = ctx->partials, *part_ip = ctx->partials + (size_t)ctx->slots * ctx->partial_stride;
             bool need_thresholds = false;                        // b = 1 and 1/2 quantize by sign alone
             for (uint32_t i = 0; i < nb; ++i) need_thresholds = need_thresholds || B.b_q8[i] > 256u;
-            // two launches in all where the passes are short (see EncTail)
-            const bool two_launches = pl.lo_bits == 12 || (!pl.wg && pl.lo_bits == 14 && (uint64_t)nb << log2D <= kTwoLaunchCoords);
+            const bool two_launches = encode_in_two_launches(log2D, nb, need_thresholds);
             const EncTail tail{two_launches ? ctx->arrived : nullptr, ctx->enc_scratch, ctx->tables, hdr_d, ctx->dev_status, ctx->coin.total};
             bool coins = false;                                  // coin budgets: masks and prefix sums of the coins first
             void *part_b[kMaxBatch] = {};
