@@ -617,9 +617,13 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
         K = resident / tiles;
         if (K > n) K = n;
         while (K > 1 && (uint64_t)(K - 1) * rest > partial_tiles) --K;    // what the partial buffer holds
-        // no more groups than it takes for the longest one (10 senders of 2^20: 5 groups of 2 instead of 8, 31.3 -> 25.3 us with the combine)
-        const uint32_t most = (n + K - 1) / K;
-        K = (n + most - 1) / most;
+        // No more groups than it takes for the longest one, where that spares a third of them or where the workgroups would take up
+        // nearly every slot of the chip (a CU with one workgroup runs it faster).  Whole decode, us, all groups / fewer: 10 senders of
+        // 2^20, b = 2 (512 -> 320 workgroups) 42.2 / 38.4; 20 of 2^20 (512 -> 448) 58.1 / 54.2; 9 of 2,000,000 (492 -> 369) 60.5 / 58.1; 14 of
+        // 600,000 (481 -> 259) 40.0 / 36.1; but 12 of 1,500,000 (460 -> 368) 54.6 / 58.5, 8 of 1,500,000 at b = 1 34.6 / 35.9 and 31 of
+        // 600,000 (481 -> 407) 51.2 / 53.5, which keep them all.
+        const uint32_t most = (n + K - 1) / K, fewer = (n + most - 1) / most;
+        if (3 * fewer <= 2 * K || 20 * K * tiles >= 19 * resident) K = fewer;
     }
     if (K == 1) { full = tiles; rest = 0; }
     dim3 grid(full + rest * K);
