@@ -306,7 +306,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             // others have not read yet.
             bool blocked = pl.wg;
             for (uint32_t i = 0; i < nb; ++i)
-                blocked = blocked && !(ctx->T && B.x[i] >= ctx->T && B.x[i] < ctx->T + ((size_t)ctx->slots << ctx->log2D_max));
+                blocked = blocked && !(B.x[i] >= ctx->T && B.x[i] < ctx->T + (size_t)ctx->slots * ctx->slot_floats);
             {
                 Timed t(ctx, EDEN_K_ENC_FIRST, nb, st);
                 nparts_n2 = pl.lo_bits >= 15   ? launch_enc_lo15_first(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
@@ -544,8 +544,8 @@ int eden_encode_static(const float *const *x_dev, const uint32_t *client_ids, co
 }
 
 // Decodes n messages whose transformed vectors all have the same dimension and adds them to acc (see encode_range
-// for the arguments; `d_src` is the length of acc, `bitmaps` may be null).  pre == 2 (multi-pass sizes only, n at
-// most one launch): nothing is added to acc; every sender's decoded vector is left in its workspace slot.
+// for the arguments; `d_src` is the length of acc, `bitmaps` may be null).  pre == 2 (up to D = 2^24, n at most one
+// launch): nothing is added to acc; every sender's decoded vector is left in its workspace slot.
 // `flags_out`: where the status word of message 0 of this range goes (device, one word per message).
 // `mean_n` > 0 (n at most one launch): acc is written with the sum divided by mean_n instead of added to.
 static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32_t *client_ids, const uint32_t *b_kernel,

@@ -658,7 +658,7 @@ __device__ inline void write_enc_header(const EncBatch &B, uint32_t c, uint64_t 
 // ---- encode in two launches.  Where a pass is a few microseconds long, the launches between and after the passes (|x|^2 and the
 // thresholds; the scale and the header) cost as much as the passes: the workgroup of a sender that arrives last does that
 // work instead.  Every workgroup then waits once for its partial sum to reach memory, so longer passes keep the separate
-// launches (the rule and its figures: kTwoLaunchCoords in eden_api.hip).
+// launches (the rule and its figures: encode_in_two_launches in eden_api.hip).
 struct EncTail {
     uint32_t *arrived;      // counters per sender: [c] of the first pass, [kMaxBatch + c] of the last; null: separate launches
     EncScratch *scratch;

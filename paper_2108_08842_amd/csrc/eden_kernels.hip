@@ -1,4 +1,4 @@
-// HIP kernels of the EDEN hot path for gfx950 (MI355X), wave-tile passes and the small sizes.  Wave64 throughout.
+// HIP kernels of the EDEN hot path for gfx950 (MI355X): wave-tile passes, scalars and headers, helpers.  Wave64 throughout.
 //
 // The rotation R x = D^-1/2 H (s o x) (Sec. 2.2.1; Sec. 5: randomized Hadamard transform) is computed
 // unnormalised, u = H (s o x), with the D^-1/2 folded into scalars.  The index bits of the padded

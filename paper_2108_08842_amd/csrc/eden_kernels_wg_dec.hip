@@ -210,22 +210,18 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
 #pragma unroll
         for (int s = 0; s < X::RP; ++s)
             __builtin_amdgcn_raw_buffer_store_b16(narrow_bits(out[s]), rt, (int)(off2 >> 1), (int)((hix_row2<M>(0, 0, s) << (p + 2)) >> 1), kStream);
-        if constexpr (X::PH == 2) {
-            hix_exchange<M, 1>(v, lds, out);
+        hix_exchange<M, 1>(v, lds, out);
 #pragma unroll
-            for (int s = 0; s < X::RP; ++s)
-                __builtin_amdgcn_raw_buffer_store_b16(narrow_bits(out[s]), rt, (int)(off2 >> 1), (int)((hix_row2<M>(0, 1, s) << (p + 2)) >> 1), kStream);
-        }
+        for (int s = 0; s < X::RP; ++s)
+            __builtin_amdgcn_raw_buffer_store_b16(narrow_bits(out[s]), rt, (int)(off2 >> 1), (int)((hix_row2<M>(0, 1, s) << (p + 2)) >> 1), kStream);
     } else {
         const rsrc_t rt = make_rsrc(slot + base_off, (rows_used << (p + 2)) - base_off);
         hix_exchange<M, 0>(v, lds, out);
 #pragma unroll
         for (int s = 0; s < X::RP; ++s) buf_store(rt, off2, hix_row2<M>(0, 0, s) << (p + 2), out[s]);
-        if constexpr (X::PH == 2) {
-            hix_exchange<M, 1>(v, lds, out);
+        hix_exchange<M, 1>(v, lds, out);
 #pragma unroll
-            for (int s = 0; s < X::RP; ++s) buf_store(rt, off2, hix_row2<M>(0, 1, s) << (p + 2), out[s]);
-        }
+        for (int s = 0; s < X::RP; ++s) buf_store(rt, off2, hix_row2<M>(0, 1, s) << (p + 2), out[s]);
     }
 }
 
