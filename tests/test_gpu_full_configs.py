@@ -305,13 +305,13 @@ def _sampled_rows_check(x64, seed, client, idx_gpu_at, samples, thresholds):
     return near
 
 
-def test_three_pass_size():
-    """D = 2^25: lo14, workgroup-tile strided pass on bits 14..20, wave-tile strided pass on bits 21..24."""
+def test_two_to_the_25():
+    """D = 2^25: 15 contiguous bits and the 10-bit workgroup tile above them (an integer and a coin budget, shared instances)."""
     from paper_2108_08842_amd import eden
     d = (1 << 24) + 12345
     coin = eden.B_COIN(1.5)
-    w = synth.Workload("three_pass", 3, d, [256, 768, coin], 25, "normal_outliers")
-    print(f"three passes: n=3 d={d} D=2^25 budgets={w.b_q8} seed={w.seed}", flush=True)
+    w = synth.Workload("two_to_the_25", 3, d, [256, 768, coin], 25, "normal_outliers")
+    print(f"2^25: n=3 d={d} D=2^25 budgets={w.b_q8} seed={w.seed}", flush=True)
     xs = [synth.client_vector(w, c) for c in range(3)]
     ctx = eden.Context(d_max=d, n_max=3, device=0)
     msgs = ctx.encode([torch.from_numpy(x).cuda() for x in xs], [5, 9, 12], w.b_q8, w.seed)
@@ -340,13 +340,13 @@ def test_three_pass_size():
     ctx.close()
 
 
-def test_three_pass_size_wide_tiles():
-    """D = 2^25 with b = 1, 2, 4 only: lo14, workgroup-tile strided pass on bits 14..21, and the wide wave tile
-    (8 rows x 512 columns, 8 columns per lane) on bits 22..24 next to the payload."""
+def test_two_to_the_25_with_one_byte_budgets_among_others():
+    """D = 2^25 with b = 1, 2, 4, the uniform grid and b = 6 in one launch: the same two passes (only launches of one-byte budgets
+    alone take three), fp16 and fp32 slots side by side."""
     from paper_2108_08842_amd import eden
     d = (1 << 24) + 54321
-    w = synth.Workload("three_pass_wide", 5, d, [256, 512, 1024, eden.B_GRID(0.5224), 1536], 26, "lognormal_signed")
-    print(f"three passes, wide tiles: n=5 d={d} D=2^25 budgets={w.b_q8} seed={w.seed}", flush=True)
+    w = synth.Workload("two_to_the_25_bytes", 5, d, [256, 512, 1024, eden.B_GRID(0.5224), 1536], 26, "lognormal_signed")
+    print(f"2^25, one-byte budgets among others: n=5 d={d} D=2^25 budgets={w.b_q8} seed={w.seed}", flush=True)
     xs = [synth.client_vector(w, c) for c in range(5)]
     ctx = eden.Context(d_max=d, n_max=5, device=0)
     ids = [2, 7, 11, 13, 17]
@@ -389,7 +389,7 @@ def _sampled_decode_check(om, acc_at, d, samples):
 
 @pytest.mark.timeout(1200)
 def test_config5_full_size():
-    """n=8, d=2^27, b=4: three passes through memory (lo14, the 10-bit workgroup tile, the wide wave tile).  One whole
+    """n=8, d=2^27, b=4: two passes through memory (16 contiguous bits in pairs of workgroups, the 11-bit workgroup tile).  One whole
     sender goes through the oracle coordinate by coordinate in both directions; two more are checked on sampled
     coordinates computed from single rows of H; the batch through properties that hold at any size."""
     from paper_2108_08842_amd import eden
@@ -453,10 +453,10 @@ def test_config5_full_size():
 
 
 @pytest.mark.timeout(1200)
-@pytest.mark.parametrize("budgets", [[512], [768, 384]], ids=["wide_plan_b2", "wave_plan_b3_b1p5"])
+@pytest.mark.parametrize("budgets", [[512], [768, 384]], ids=["b2", "b3_b1p5"])
 def test_two_to_the_26(budgets):
-    """D = 2^26, whole senders through the oracle in both pass plans: lo14 + the 9-bit workgroup tile + the wide wave
-    tile (every sender b in {1, 2, 4}), and lo14 + the 7-bit workgroup tile + a 5-bit wave tile on bits 21..25."""
+    """D = 2^26, whole senders through the oracle: 15 contiguous bits + the 11-bit workgroup tile, in the instance that serves every
+    integer budget and in the one that serves k + 1/2 and coins too."""
     from paper_2108_08842_amd import eden
     d = (1 << 26) - 70_001                                       # a ragged last tile in every pass
     n = len(budgets)
