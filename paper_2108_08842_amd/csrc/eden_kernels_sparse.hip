@@ -264,11 +264,12 @@ void launch_sparse_scatter(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m
                            float *acc, float mean_n, hipStream_t st) {
     const uint32_t blocks = (uint32_t)((d + 63) / 64);
     const uint32_t groups = (blocks + kSparseWave - 1) / kSparseWave;
-    // one or two senders: as many waves per workgroup, from 8 down to 1, as leave the launch at 4096 waves, 16 for each CU (whole decode,
-    // m = 32: one sender of 250,000 24.6 us with one wave, 15.1 with eight; of 4,000,037 45.0, 36.5 with eight, 33.1 with four and NQ = 4;
-    // of 11,173,962 66.0, 68.4 with eight, 58.8 with one and NQ = 4)
+    // fewer than eight senders: as many waves per workgroup, from 8 down to one per sender, as leave the launch at 4096 waves, 16 for
+    // each CU (whole decode, m = 32: one sender of 250,000 24.6 us with one wave, 15.1 with eight; of 4,000,037 45.0, 36.5 with eight,
+    // 33.1 with four and NQ = 4; of 11,173,962 66.0, 68.4 with eight, 58.8 with one and NQ = 4; four of 2^24 153.8 with four waves,
+    // 159.1 with eight)
     uint32_t waves = 8u;
-    while (n <= 2u && waves > 1u && groups * waves > 4096u) waves >>= 1;
+    while (waves > n && groups * waves > 4096u) waves >>= 1;
     const uint32_t lds = n * 2u * kSparseWave * (uint32_t)sizeof(KeptHalf);
     if (n <= 2u && waves <= 4u)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sparse_scatter<4>), dim3(groups), dim3(64u * waves), lds, st, B, n, (uint32_t)d, m, seed, in, log2_stride, acc, mean_n);
