@@ -162,8 +162,10 @@ def _stream_ptr(stream=None):
     import torch
     if stream is not None:
         return stream.cuda_stream
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 # Arrays of a batch as (object that owns the memory, address): the C side takes them by address and copies what it needs before

@@ -140,6 +140,7 @@ def test_stream_address_without_the_short_cut(eden, monkeypatch):
     class Stream:
         cuda_stream = 0x1234
 
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
     assert eden._stream_ptr() == 0x1234
