@@ -15,8 +15,8 @@
 // XCD (workgroups i and i + 8), so the second read of a line is meant to find it in that XCD's L2.
 // (measured: the encoder's pass fetches every line from memory once).
 // It replaces a 14-bit contiguous pass and a second strided pass (one more trip through memory per direction).  8 senders of 2^27,
-// b = 4: this pass 1.98 ms (encode) and 1.20 ms (decode), the strided ones 1.31 and 1.30 ms; a round 8.03 -> 5.90 ms; at 2^25
-// 1.94 -> 1.21 ms, with b = 1 1.91 -> 0.99 ms.  With one workgroup per CU what is left is the time in which its waves all wait
+// b = 4: this pass 1.96 ms (encode) and 1.10 ms (decode), the strided ones 1.37 and 1.39 ms; a round 8.03 -> 5.85 ms; at 2^25
+// 1.94 -> 1.16 ms, with b = 1 1.91 -> 0.91 ms.  With one workgroup per CU what is left is the time in which its waves all wait
 // for memory or all compute (vector instructions 48%, 31% of the time).
 #include "eden_device.h"
 #include "eden_kernels.h"
