@@ -310,6 +310,27 @@ def test_zero_and_nonfinite_vectors_of_every_budget_in_two_launches(ctx, d, n):
                     assert float(m[32:40].cpu().numpy().view(np.float64)[0]) == 0.0
 
 
+@pytest.mark.parametrize("d,n", [(65_536, 16), (131_072, 16), (250_000, 16), (1_000_000, 4)])
+def test_messages_do_not_depend_on_the_number_of_launches(ctx, d, n):
+    # an encode call is two, three or four launches by the coordinates of all its senders and by whether one of them needs thresholds:
+    # a sender alone, among others and among others that all have b <= 1 writes the same message, bit for bit
+    from paper_2108_08842_amd import eden
+    kinds = [256, 512, 1536, 128, 1024, eden.B_COIN(1.6), 384, eden.B_GRID(0.5224), 2048, 768]
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    xs = [torch.randn(d, generator=gen, device="cuda") for _ in range(n)]
+    ids = list(range(n))
+
+    def same(a, b):
+        length = eden.message_length(a[:64].cpu().numpy().tobytes())
+        return torch.equal(a[:length], b[:length])
+
+    for budgets in ([kinds[c % len(kinds)] for c in ids], [(256, 128)[c % 2] for c in ids]):
+        msgs = ctx.encode(xs, ids, budgets, 41)
+        for c in ids[:len(kinds)]:
+            assert same(msgs[c], ctx.encode([xs[c]], [c], [budgets[c]], 41)[0]), (c, budgets[c])
+    assert ctx.last_device_status() == 0
+
+
 @pytest.mark.parametrize("d,n", [(3000, 12), (5000, 12), (100_000, 12), (300_000, 2), (900_000, 2), (300_000, 12), (2_500_000, 3)])
 def test_finite_vectors_whose_transform_overflows_or_vanishes(ctx, d, n):
     # |x|^2 (in double) is fine but <R(x),Q> (from fp32 values) is NaN or 0: such a message says EDEN_DEV_ZERO_VECTOR and has S = 0
