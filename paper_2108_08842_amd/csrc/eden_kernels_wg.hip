@@ -249,11 +249,12 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
         const uint32_t next_off = tile_off(tile0 + k + 1);
         fwht_regs<64>(v);
         float out[X::RP];
-        // The instances that serve several budgets hold one copy of the code behind the exchange for both halves: with two, 75 and 100 KB,
-        // more than the instruction cache, they were slower in halves than in one piece (M = 7..9) and spilled 32 to 48 registers, now 0
-        // and 6 to 17.  (One sender of 7,000,001, b = 8: 48.8 -> 40.0 us, in one piece 41.9; 8 of 4,000,037 with b = 1, 3, 1.5, 8:
-        // 121 -> 98, 106; one of 10^8 at 2.7 bits: 617 -> 547, in three passes 555.)  The trip count is hidden from the compiler, which
-        // would otherwise unroll by threading jumps.
+        // The instances that serve several budgets hold one copy of the code behind the exchange for both halves, fed from `cur`.  With
+        // two copies (75 KB in MODE 1, more than the instruction cache) or with the halves told apart by conditions (MODE 2, 100 KB in
+        // one copy) they spilled 32 to 48 registers, now 0 and 6 to 17, and were slower in halves than in one piece at M = 7..9.  (One
+        // sender of 7,000,001, b = 8: 48.8 -> 40.0 us, in one piece 41.9; 8 of 4,000,037 with b = 1, 3, 1.5, 8: 121 -> 98, 106; one of
+        // 10^8 at 2.7 bits: 617 -> 547, in three passes 555.)  The trip count is hidden from the compiler, which would otherwise unroll
+        // by threading jumps.
         int halves = X::PH;
         float cur[SHARED ? X::RP : 1];
         if constexpr (SHARED) {
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
 #pragma unroll
             for (int r = 0; r < X::RP; ++r) cur[r] = v[r];
         }
-#pragma unroll(SHARED ? 1 : X::PH)
+#pragma unroll SHARED ? 1 : X::PH
         for (int ph = 0; ph < halves; ++ph) {
             if constexpr (SHARED) {
                 hix_exchange_write<M, 0>(cur, lds);

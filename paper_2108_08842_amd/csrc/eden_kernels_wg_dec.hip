@@ -250,7 +250,7 @@ __device__ inline void fwht_pk(s16x2 (&v)[N]) {
 // (Four waves per SIMD are requested so that two of the 512-thread workgroups of M = 10 share a CU: measured
 // 0.103 ms against 0.133 ms per launch on 16 senders at D = 2^24, at the price of five spilled registers.)
 template <int M, int P, int PIECES>
-__global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first_pk(DecBatch B, uint64_t d, int log2D, uint64_t seed, float *T) {
+__global__ __launch_bounds__(HiX<M>::THREADS, PIECES == 2 ? 4 : M == 9 ? 2 : 3) void k_dec_hix_first_pk(DecBatch B, uint64_t d, int log2D, uint64_t seed, float *T) {
     using X = HiX<M, PIECES>;
     constexpr int p = P;
     __shared__ uint32_t lds[X::LDS_FLOATS];
