@@ -154,8 +154,8 @@ __global__ __launch_bounds__(128) void k_sparse_gather(EncBatch B, uint32_t d, u
 // A workgroup takes 64 blocks = 4096 coordinates: its waves select for one sender at a time, and then its threads add, NQ times four
 // coordinates at a time.  Two workgroups of eight waves share a CU, one selecting while the other adds: 121 us at the size
 // above; sixteen waves, alone on a CU, 147 us; four waves 126 us; 64 or 80 registers instead of 109 spill: 210 and 162 us.
-// One or two senders leave most of eight waves idle while the others select, and have no other sender's loads to overlap with:
-// fewer waves where the launch fills the chip all the same, and NQ = 4 (see launch_sparse_scatter).
+// Few senders leave most of eight waves idle while the others select, and one or two have no other sender's loads to overlap with:
+// four waves where the launch fills the chip all the same, and NQ = 4 (see launch_sparse_scatter).
 template <int NQ>
 __global__ __launch_bounds__(512) void k_sparse_scatter(DecBatch B, uint32_t n, uint32_t d, uint32_t m, uint64_t seed, const float *in,
                                                          int log2_stride, float *acc, float mean_n) {
@@ -264,14 +264,13 @@ void launch_sparse_scatter(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m
                            float *acc, float mean_n, hipStream_t st) {
     const uint32_t blocks = (uint32_t)((d + 63) / 64);
     const uint32_t groups = (blocks + kSparseWave - 1) / kSparseWave;
-    // fewer than eight senders: as many waves per workgroup, from 8 down to one per sender, as leave the launch at 4096 waves, 16 for
-    // each CU (whole decode, m = 32: one sender of 250,000 24.6 us with one wave, 15.1 with eight; of 4,000,037 45.0, 36.5 with eight,
-    // 33.1 with four and NQ = 4; of 11,173,962 66.0, 68.4 with eight, 58.8 with one and NQ = 4; four of 2^24 153.8 with four waves,
-    // 159.1 with eight)
-    uint32_t waves = 8u;
-    while (waves > n && groups * waves > 4096u) waves >>= 1;
+    // Fewer than eight senders: four waves per workgroup once eight would make more than 4096, 16 for each CU; with one or two senders
+    // NQ = 4 then.  (Whole decode, m = 32: one sender of 250,000 24.6 us with one wave and NQ = 1, 15.1 with eight; with 1, 2, 4 waves and
+    // NQ = 4 and with 8: one of 4,000,037 37.6, 35.4, 32.9, 36.6; of 11,173,962 58.7, 56.7, 57.4, 66.0; two of 11,173,962 84.2, 80.4,
+    // 78.6, 88.1; four of 2^24, NQ = 1, 154.9 with four, 160.7 with eight; six 229 and 240.)
+    const uint32_t waves = n < 8u && groups * 8u > 4096u ? 4u : 8u;
     const uint32_t lds = n * 2u * kSparseWave * (uint32_t)sizeof(KeptHalf);
-    if (n <= 2u && waves <= 4u)
+    if (n <= 2u && waves == 4u)
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sparse_scatter<4>), dim3(groups), dim3(64u * waves), lds, st, B, n, (uint32_t)d, m, seed, in, log2_stride, acc, mean_n);
     else
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sparse_scatter<1>), dim3(groups), dim3(64u * waves), lds, st, B, n, (uint32_t)d, m, seed, in, log2_stride, acc, mean_n);

@@ -493,10 +493,10 @@ def test_sparse_rounds_of_many_senders(ctx, d, m, n):
     assert ctx.last_decode_flags(n) == [0] * n
 
 
-@pytest.mark.parametrize("d,m,n", [(2_097_153, 63, 2), (4_200_001, 1, 1), (8_400_010, 6, 2), (8_400_010, 33, 1), (4_194_304, 9, 1)])
+@pytest.mark.parametrize("d,m,n", [(2_097_152, 5, 1), (2_097_153, 63, 2), (4_200_001, 1, 1), (8_400_010, 6, 2), (8_400_010, 33, 1), (4_194_304, 9, 1)])
 def test_sparse_rounds_of_one_or_two_senders(d, m, n):
-    # the scatter launch takes four, two and one wave per workgroup from 2^21, 2^22 and 2^23 coordinates on (four quads per thread,
-    # blocks and quads beyond the last coordinate among them); the gather launch one wave or a team of eight per 64 blocks
+    # the scatter launch takes four waves per workgroup from 2^21 coordinates on (four quads per thread, blocks and quads beyond the
+    # last coordinate among them) and eight below; the gather launch one wave or a team of eight per 64 blocks
     from paper_2108_08842_amd import eden
     own = eden.Context(d_max=d, n_max=n, device=0)
     budgets = [eden.B_SPARSE(m)] * n
