@@ -38,7 +38,7 @@ struct eden_ctx {
     DecScratch *dec_scratch; // slots
     DevTables *tables;
     uint32_t *dev_status;
-    uint32_t *arrived;           // counters of arrive_last (0 between launches): two per sender of an encode launch, kDecCounters for decode
+    uint32_t *arrived;           // arrival counters (0 between launches): one per sender of an encode launch, kDecCounters for decode
     uint32_t dec_turn = 0;       // which of those the next small decode launch uses
     uint32_t *msg_flags;         // n_max words: the status bits of every message of the last eden_decode_accumulate call
     uint32_t last_decode_n = 0;  // how many of them that call wrote
@@ -51,18 +51,7 @@ struct eden_ctx {
 
 namespace {
 
-constexpr uint32_t kArrivedCounters = 2 * kMaxBatch + kDecCounters;
-// Whether an encode call is two launches (see EncTail) instead of four, or of three when every sender has b <= 1 and no thresholds are
-// needed.  Two take less time where the passes are so short that the launches count, and more where most workgroups wait for their
-// partial sums to arrive (device time, us, b = 2, four launches -> two: one sender of 20,000 16.0 -> 14.4, 32 of 2^17 26.8 -> 25.5, 8 of
-// 2^18 21.7 -> 21.1, 16 of 2^18 25.4 -> 27.6, 32 of 2^18 28.9 -> 32.6, 2 of 2^20 22.5 -> 20.3, 8 of 2^20 30.9 -> 34.0; one sender
-// of 2^21 .. 2^24 3..5 more.  b = 1, three -> two: 32 of 20,000 24.1 -> 21.9, 16 of 2^16 18.5 -> 17.5, one of 2^16 12.4 -> 13.8 (the
-// same when the host launches it: 14.0, 14.1), 8 of 2^17 15.2 -> 16.5, 32 of 2^18 24.2 -> 29.9, one of 2^20 15.1 -> 16.0).
-constexpr uint64_t kTwoLaunchCoords = 1ull << 21;
-bool encode_in_two_launches(int log2D, uint32_t n, bool need_thresholds) {
-    if (!need_thresholds) return log2D <= 16;
-    return log2D <= 17 || (log2D <= 20 && (uint64_t)n << log2D <= kTwoLaunchCoords);
-}
+constexpr uint32_t kArrivedCounters = kMaxBatch * kEncCounterStride + kDecCounters;       // words: one per sender of an encode launch, then those of decode
 
 int ceil_log2(uint64_t d) {
     int l = 0;
@@ -279,8 +268,6 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             double *part_n2 = ctx->partials, *part_ip = ctx->partials + (size_t)ctx->slots * ctx->partial_stride;
             bool need_thresholds = false;                        // b = 1 and 1/2 quantize by sign alone
             for (uint32_t i = 0; i < nb; ++i) need_thresholds = need_thresholds || B.b_q8[i] > 256u;
-            const bool two_launches = encode_in_two_launches(log2D, nb, need_thresholds);
-            const EncTail tail{two_launches ? ctx->arrived : nullptr, ctx->enc_scratch, ctx->tables, hdr_d, ctx->dev_status, ctx->coin.total};
             bool coins = false;                                  // coin budgets: masks and prefix sums of the coins first
             void *part_b[kMaxBatch] = {};
             for (uint32_t i = 0; i < nb; ++i) {
@@ -301,6 +288,10 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                     staged = true;
                 }
             }
+            // wave-tile plans (D <= 2^20): the last pass takes care of thresholds and headers itself, see EncTail
+            const bool two_launches = !pl.wg && !pl.wide;
+            EncTail tail{two_launches ? ctx->arrived : nullptr, part_n2, ctx->partial_stride, 0u, ctx->enc_scratch, ctx->tables, hdr_d,
+                         ctx->dev_status, ctx->coin.total};
             // The workspace goes through the blocked layout when a workgroup-tile pass reads it (D >= 2^21), unless the first pass
             // works in place on the workspace (its input is a slot, D <= 2^24): its workgroups would then overwrite rows that
             // others have not read yet.
@@ -313,6 +304,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                             : pl.lo_bits == 14 ? launch_enc_lo14_first(B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail, st)
                                                : launch_enc_lo_first(B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail, st);
             }
+            tail.n2_count = nparts_n2;
             if (need_thresholds && !two_launches) {
                 Timed t(ctx, EDEN_K_ENC_NORM, nb, st);
                 launch_enc_norm(B, nb, part_n2, ctx->partial_stride, nparts_n2, ctx->enc_scratch, ctx->tables, st);
@@ -328,7 +320,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                             : pl.wg ? launch_enc_hix_last(pl.M, pl.lo_bits, blocked, B, nb, d, log2D, seed, ctx->T, part_ip, ctx->partial_stride,
                                                         ctx->enc_scratch, ctx->coin, st)
                                   : launch_enc_hi_last(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, ctx->T, part_ip,
-                                                       ctx->partial_stride, ctx->enc_scratch, ctx->coin, tail, st);
+                                                       ctx->partial_stride, ctx->coin, tail, st);
             }
             if (pack) launch_pack_bits(B, nb, log2D, st);
             if (staged) launch_coin_pack(B.b_q8, pieces, part_b, nb, log2D, ctx->coin, st);
@@ -456,7 +448,7 @@ constexpr size_t kOffTables = kOffEncScratch + static_align(EDEN_STATIC_MAX_N * 
 constexpr size_t kOffStatus = kOffTables + static_align(sizeof(DevTables));
 constexpr size_t kStaticCoinWords = kStaticDmax / 64;           // blocks of 64 coordinates per slot
 constexpr size_t kStaticCoinGroups = (kStaticCoinWords + kCoinGroup - 1) / kCoinGroup;
-constexpr size_t kOffCoinMask = kOffStatus + 512;                // status word, then the counters of arrive_last
+constexpr size_t kOffCoinMask = kOffStatus + static_align((16 + kArrivedCounters) * sizeof(uint32_t));    // status word, then the arrival counters
 constexpr size_t kOffCoinLocal = kOffCoinMask + static_align(EDEN_STATIC_MAX_N * kStaticCoinWords * sizeof(uint64_t));
 constexpr size_t kOffCoinGroup = kOffCoinLocal + static_align(EDEN_STATIC_MAX_N * kStaticCoinWords * sizeof(uint32_t));
 constexpr size_t kOffCoinTotal = kOffCoinGroup + static_align(EDEN_STATIC_MAX_N * kStaticCoinGroups * sizeof(uint32_t));
@@ -499,7 +491,6 @@ int static_context(int dev, hipStream_t st, eden_ctx **out) {
         c.tables = reinterpret_cast<DevTables *>(ptr + kOffTables);
         c.dev_status = reinterpret_cast<uint32_t *>(ptr + kOffStatus);
         c.arrived = c.dev_status + 16;
-        static_assert((16 + kArrivedCounters) * sizeof(uint32_t) <= 512, "room for the counters");
         c.coin.mask = reinterpret_cast<uint64_t *>(ptr + kOffCoinMask);
         c.coin.local = reinterpret_cast<uint32_t *>(ptr + kOffCoinLocal);
         c.coin.group = reinterpret_cast<uint32_t *>(ptr + kOffCoinGroup);
@@ -578,7 +569,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
         }
         if (pl.lo_bits == 0) {
             Timed t(ctx, EDEN_K_DEC_SMALL, nb, st);
-            launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived + 2 * kMaxBatch,
+            launch_dec_small(B, nb, d_src, pre, hdr_d, log2D, seed, ctx->tables, acc_dev, mean_n, ctx->T, ctx->T, ctx->arrived + kMaxBatch * kEncCounterStride,
                              ctx->dec_turn, ctx->dev_status, flags_out + first, st);
             ctx->dec_turn = (ctx->dec_turn + 1u) % kDecCounters;
         } else {

@@ -13,6 +13,7 @@
 namespace eden {
 
 constexpr int kMaxBatch = 32;            // senders handled by one launch; larger batches are chunked
+constexpr uint32_t kEncCounterStride = 32;  // words between the arrival counters of two senders: a memory line each (see enc_last_tail)
 constexpr uint32_t kDecCounters = 8;     // arrival counters of the small decode launches, used in turn (see k_dec_small)
 constexpr int kLoBits = 12;              // index bits transformed by the contiguous (wave-tile) pass
 constexpr int kLoTile = 1 << kLoBits;    // 4096 coordinates = 64 lanes x 64 registers
@@ -142,9 +143,9 @@ struct DevTables {
 struct EncScratch {
     double n2;              // |x|^2 (Sec. 2.2.1: equals |R(x)|^2)
     float thr[8];           // positive thresholds of I_b times |x|: compared against |H(s o x)|
-    float qpos[8];          // positive centroids
     float thr2[8];          // mixed budgets: the same for I_{floor(b)+1}
-    float qpos2[8];
+    float qpos[8];          // positive centroids
+    float qpos2[8];         // (the kernels look centroids up in qpos .. qpos2 as one run of 16 floats)
     float grid_inv;         // uniform grid: 1 / (Delta |x|), so that round(u * grid_inv) is the index
     float guess_c1, guess_c3, guess_cap, guess_up;      // b = 4: see quantize_guess
     unsigned pad;
@@ -152,8 +153,9 @@ struct EncScratch {
     float wide_thr[128];            // b = 5..8: positive thresholds times |x|
 };
 
-static_assert(offsetof(EncScratch, wide_thr) == offsetof(EncScratch, grid_c) + 128 * sizeof(float),
-              "the kernels copy centroids and thresholds as one run of 256 floats");
+static_assert(offsetof(EncScratch, wide_thr) == offsetof(EncScratch, grid_c) + 128 * sizeof(float) &&
+                  offsetof(EncScratch, qpos2) == offsetof(EncScratch, qpos) + 8 * sizeof(float),
+              "the kernels use centroids and thresholds of the one-byte budgets as one run of 256 floats, qpos and qpos2 as one of 16");
 
 // per-message scalars of one decode
 struct DecScratch {
@@ -327,12 +329,26 @@ __device__ inline bool arrive_last(uint32_t *counter, uint32_t total, uint32_t *
 // (Sec. 2.2.1, Sec. 3), and its contribution |u| q to sum_i u_i Q_i (Sec. 2.3).  H = 2^(b-1) levels per sign.
 // A value exactly on a threshold stays in the interval closer to zero (strict compare); u = +0 is
 // non-negative.  thr[0] is unused (it is the threshold 0, decided by the sign).
-// The thresholds are wave-uniform scalars (sc->thr); the centroid is looked up in `qtab`, a copy of sc->qpos
-// (entries 0..7) and sc->qpos2 (8..15) in LDS: counting the thresholds below |u| and one LDS read cost 2 H + 3
+// The thresholds are wave-uniform scalars (Thresholds); the centroid is looked up in `qtab`, the workgroup's copy of qpos
+// (entries 0..7) and qpos2 (8..15) in LDS: counting the thresholds below |u| and one LDS read cost 2 H + 3
 // instructions where a select chain that carries the centroid along costs 3 H (measured 20% on a b = 4 pass).
-__device__ inline void fill_qtab(float *qtab, const EncScratch *sc, uint32_t lane) {
-    if (lane < 8) qtab[lane] = sc->qpos[lane];
-    else if (lane < 16) qtab[lane] = sc->qpos2[lane - 8];
+struct Thresholds {
+    float thr[8], thr2[8];
+};
+__device__ inline Thresholds thresholds_of(const EncScratch *s) {
+    Thresholds t;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { t.thr[i] = s->thr[i]; t.thr2[i] = s->thr2[i]; }
+    return t;
+}
+__device__ inline Thresholds uniform_thresholds(const EncScratch &s /* shared */) {
+    Thresholds t;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        t.thr[i] = uniform(s.thr[i]);
+        t.thr2[i] = uniform(s.thr2[i]);
+    }
+    return t;
 }
 template <int H>
 __device__ inline uint32_t magnitude_rank(float a, const float (&thr)[8]) {
@@ -342,9 +358,9 @@ __device__ inline uint32_t magnitude_rank(float a, const float (&thr)[8]) {
     return mag;
 }
 template <int H>
-__device__ inline uint32_t quantize_one(float u, const EncScratch *sc, const float *qtab, float &ip) {
+__device__ inline uint32_t quantize_one(float u, const Thresholds &th, const float *qtab, float &ip) {
     const float a = fabsf(u);
-    const uint32_t mag = magnitude_rank<H>(a, sc->thr);
+    const uint32_t mag = magnitude_rank<H>(a, th.thr);
     ip = fmaf(a, qtab[mag], ip);
     const uint32_t neg = __float_as_uint(u) >> 31;
     return neg ? (uint32_t)(H - 1) - mag : (uint32_t)H + mag;
@@ -562,10 +578,10 @@ __device__ inline uint32_t wide_half_levels(uint32_t b_q8) { return wide_bits(b_
 // b = K + 1/2 (Sec. 4.1): the index of one coordinate, K+1 bits wide where `up` (quantized with I_{K+1}), else K
 // bits (I_K), and its contribution |u| q to sum_i u_i Q_i.
 template <int K>
-__device__ inline uint32_t quantize_mixed(float u, bool up, const EncScratch *sc, const float *qtab, float &ip) {
+__device__ inline uint32_t quantize_mixed(float u, bool up, const Thresholds &th, const float *qtab, float &ip) {
     constexpr int HL = 1 << (K - 1), HH = 1 << K;
     const float a = fabsf(u);
-    const uint32_t mag_lo = magnitude_rank<HL>(a, sc->thr), mag_hi = magnitude_rank<HH>(a, sc->thr2);
+    const uint32_t mag_lo = magnitude_rank<HL>(a, th.thr), mag_hi = magnitude_rank<HH>(a, th.thr2);
     ip = fmaf(a, qtab[up ? 8u + mag_hi : mag_lo], ip);
     const bool neg = (__float_as_uint(u) >> 31) != 0u;
     const uint32_t code_lo = neg ? (uint32_t)(HL - 1) - mag_lo : (uint32_t)HL + mag_lo;
@@ -603,29 +619,31 @@ __device__ inline void fill_enc_scratch(EncScratch *s, double n2, uint32_t b_q8,
         s->guess_up = (float)up;
     }
 }
+__device__ inline void fill_grid_table(EncScratch *s, uint32_t q15, uint32_t tid) {
+    s->grid_c[tid] = tid ? (float)grid_centroid((double)q15 / 32768.0, (int)tid) : 0.0f;
+}
+// b = wb = 5..8
+__device__ inline void fill_wide_tables(EncScratch *s, uint32_t wb, double n2, const DevTables *tab, uint32_t tid) {
+    const uint32_t H = 1u << (wb - 1u);
+    s->grid_c[tid] = tid < H ? (float)tab->q_big[wb - 5u][tid] : 0.0f;
+    s->wide_thr[tid] = tid < H ? (float)(tab->t_big[wb - 5u][tid] * sqrt(n2)) : INFINITY;       // padding for the bisection
+}
 // The tables of the one-byte budgets, one entry per thread (tid < 128): the centres of mass of the uniform grid's
 // intervals, or the positive centroids and scaled thresholds of the 32..256-level quantizers.
 __device__ inline void fill_byte_tables(EncScratch *s, uint32_t b_q8, double n2, const DevTables *tab, uint32_t tid) {
     if (tid > (uint32_t)kGridMax) return;
-    if (const uint32_t q15 = grid_q15(b_q8)) {
-        s->grid_c[tid] = tid ? (float)grid_centroid((double)q15 / 32768.0, (int)tid) : 0.0f;
-    } else if (const uint32_t wb = wide_bits(b_q8)) {
-        const uint32_t H = 1u << (wb - 1u);
-        s->grid_c[tid] = tid < H ? (float)tab->q_big[wb - 5u][tid] : 0.0f;
-        s->wide_thr[tid] = tid < H ? (float)(tab->t_big[wb - 5u][tid] * sqrt(n2)) : INFINITY;   // padding for the bisection
-    }
+    if (const uint32_t q15 = grid_q15(b_q8)) fill_grid_table(s, q15, tid);
+    else if (const uint32_t wb = wide_bits(b_q8)) fill_wide_tables(s, wb, n2, tab, tid);
 }
 
 // The sum of `count` partials in the order of 256 threads that take every 256th of them, whatever the workgroup's size: the same bits
-// in every kernel that needs it.  THROUGH: they were stored by workgroups of this launch.  `red`: 4 doubles in LDS; the
-// result in every thread.
-template <int THREADS, bool THROUGH>
+// in every kernel that needs it.  `red`: 4 doubles in LDS; the result in every thread.
+template <int THREADS>
 __device__ inline double ordered_sum(const double *part, uint32_t count, double *red) {
     const uint32_t lane = lane_id();
     for (uint32_t w = threadIdx.x >> 6; w < 4u; w += THREADS / 64) {
         double s = 0.0;
-        for (uint32_t i = 64u * w + lane; i < count; i += 256u)
-            s += THROUGH ? __hip_atomic_load(part + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : part[i];
+        for (uint32_t i = 64u * w + lane; i < count; i += 256u) s += part[i];
         s = wave_sum(s);
         if (lane == 0) red[w] = s;
     }
@@ -634,6 +652,31 @@ __device__ inline double ordered_sum(const double *part, uint32_t count, double 
     __syncthreads();
     return total;
 }
+// The same by one wave alone, from partials that workgroups of this launch have stored.
+__device__ inline double ordered_sum_through(const double *part, uint32_t count) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (uint32_t i = lane_id(); i < count; i += 256u)
+#pragma unroll
+        for (uint32_t w = 0; w < 4u; ++w)
+            if (i + 64u * w < count) s[w] += __hip_atomic_load(part + i + 64u * w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s[w] = wave_sum(s[w]);
+    return ((0.0 + s[0]) + s[1]) + s[2] + s[3];
+}
+// The same in two steps, for a workgroup of 256 threads that issues the loads in front of those of its tile and adds while these are on
+// their way (loads come back in order).
+struct EarlyPartials {
+    double x;
+    __device__ inline void load(const double *part, uint32_t count /* <= 256 */) { x = threadIdx.x < count ? part[threadIdx.x] : 0.0; }
+    // in every thread; `red`: 4 doubles in LDS
+    __device__ inline double sum(double *red) const {
+        const double s = wave_sum(x);
+        if (lane_id() == 0) red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        return ((0.0 + red[0]) + red[1]) + red[2] + red[3];
+    }
+};
 
 // ---- encode: the header of a message (one thread).  `total`: sum_i u_i q_i.  A zero or non-finite vector gets S = 0 and a status bit.
 // (<R(x),Q> = 0 can only happen on a uniform grid so coarse that every coordinate falls into the interval around 0.)
@@ -655,31 +698,51 @@ __device__ inline void write_enc_header(const EncBatch &B, uint32_t c, uint64_t 
     *static_cast<MsgHeader *>(B.msg[c]) = h;
 }
 
-// ---- encode in two launches.  Where a pass is a few microseconds long, the launches between and after the passes (|x|^2 and the
-// thresholds; the scale and the header) cost as much as the passes: the workgroup of a sender that arrives last does that
-// work instead.  Every workgroup then waits once for its partial sum to reach memory, so longer passes keep the separate
-// launches (the rule and its figures: encode_in_two_launches in eden_api.hip).
+// ---- encode in two launches (D <= 2^20: the plans whose strided pass runs in wave tiles).  The thresholds need |x|^2, the sum over all
+// workgroups of the first pass, and the header needs the sum over all workgroups of the last one; launches of their own for these sums
+// cost 4 to 6 us each.  Instead
+// - every workgroup of the last pass adds the partial sums of |x|^2 up again: the loads go out in front of those of its tile, and the
+//   sum and the thresholds are ready about when the tile is there (the centres of mass of a uniform grid, which do not depend on
+//   |x|, are left in `scratch` by the first pass);
+// - the workgroup of a sender that finishes last writes the header.  Only the first wave of a workgroup waits for its partial sum
+//   to reach memory, and every sender's counter has a memory line of its own (512 arrivals on neighbouring words took 36 us, on a
+//   line per sender 10).
+// Encode, us, launches of their own -> this: 10 senders of 2^20, b = 2 38.9 -> 34.3; 32 of 2^17, b = 2 25.2 -> 20.9; 24 of 300,007, b = 2
+// 35.4 -> 30.8; 32 of 250,000, b = 1 23.8 -> 22.5; one of 20,000, b = 2 (where the workgroup that arrived last filled the thresholds,
+// too) 14.1 -> 13.4.  The workgroup-tile passes (D >= 2^21) keep the separate launches: with 512 workgroups per sender the arrivals
+// alone take longer, and adding up 684 partial sums per workgroup costs 16 senders of 2^24 at b = 4 9 us.
 struct EncTail {
-    uint32_t *arrived;      // counters per sender: [c] of the first pass, [kMaxBatch + c] of the last; null: separate launches
+    uint32_t *arrived;      // kEncCounterStride words apart, a counter per sender, 0 between calls; null: launches of their own
+    const double *part_n2;  // the partial sums of |x|^2, n2_stride apart per sender, n2_count <= 256 of them
+    uint32_t n2_stride, n2_count;
     EncScratch *scratch;
     const DevTables *tab;
     uint64_t hdr_d;
     uint32_t *dev_status;
     const uint32_t *coin_total;
 };
-// first pass: |x|^2 of the sender and what the quantizers derive from it
+// first pass, one workgroup per sender: the counter of the last pass is cleared (it is 0 already unless calls overlapped against
+// the rules), and a uniform grid gets its table.
 template <int THREADS>
-__device__ inline void enc_first_tail(const EncTail &f, const EncBatch &B, uint32_t c, double block_total, double *part, double *red4,
-                                      uint32_t *flag) {
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // (each pass also clears the other pass's counter, so that calls which overlapped against the rules leave nothing behind)
-        if (blockIdx.x == 0) f.arrived[kMaxBatch + c] = 0u;
+__device__ inline void enc_first_side(const EncTail &f, uint32_t c, uint32_t b_q8) {
+    if (!f.arrived || blockIdx.x != 0) return;
+    if (threadIdx.x == 0) f.arrived[c * kEncCounterStride] = 0u;
+    if (grid_q15(b_q8))
+        for (uint32_t i = threadIdx.x; i <= (uint32_t)kGridMax; i += THREADS) fill_grid_table(&f.scratch[c], grid_q15(b_q8), i);
+}
+// last pass, 256 threads: |x|^2 of the sender and what the quantizers derive from it, in LDS.  Barriers inside.
+__device__ inline void enc_scratch_to_lds(const EncTail &f, uint32_t c, uint32_t b_q8, const EarlyPartials &early, EncScratch &s, double *red4) {
+    const double n2 = early.sum(red4);
+    if (b_q8 <= 256u) {
+        if (threadIdx.x == 0) s.n2 = n2;
+    } else {
+        fill_enc_scratch(&s, n2, b_q8, f.tab, threadIdx.x);
+        if (threadIdx.x <= (uint32_t)kGridMax) {
+            if (wide_bits(b_q8)) fill_wide_tables(&s, wide_bits(b_q8), n2, f.tab, threadIdx.x);
+            else if (grid_q15(b_q8)) s.grid_c[threadIdx.x] = f.scratch[c].grid_c[threadIdx.x];
+        }
     }
-    if (!arrive_last(f.arrived + c, gridDim.x, flag)) return;
-    const double n2 = ordered_sum<THREADS, true>(part, gridDim.x, red4);
-    fill_enc_scratch(&f.scratch[c], n2, B.b_q8[c], f.tab, threadIdx.x);
-    for (uint32_t i = threadIdx.x; i <= (uint32_t)kGridMax; i += THREADS) fill_byte_tables(&f.scratch[c], B.b_q8[c], n2, f.tab, i);
+    __syncthreads();
 }
 // What a message whose sums are unusable owes beside its header: a payload of zeros, `codes` the one-byte indices that it is packed
 // from later.
@@ -704,20 +767,29 @@ __device__ inline bool enc_sum_in_doubt(double n2, int log2D) {
 // payload, some of them from other XCDs: where the sum is in doubt every workgroup therefore writes its L2 back before it arrives
 // (no other sender pays for that), and the last one clears after it has seen them all.
 template <int THREADS>
-__device__ inline void enc_last_tail(const EncTail &f, const EncBatch &B, uint32_t c, int log2D, uint64_t seed, double block_total,
-                                     double *part, double *red4, uint32_t *flag) {
-    const double n2 = f.scratch[c].n2;
-    const bool doubt = enc_sum_in_doubt(n2, log2D);
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (blockIdx.x == 0) f.arrived[c] = 0u;
-    }
-    if (doubt) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    if (!arrive_last(f.arrived + kMaxBatch + c, gridDim.x, flag)) return;
-    const double total = ordered_sum<THREADS, true>(part, gridDim.x, red4);
-    if (doubt && !(total > 0.0)) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        zero_payload<THREADS>(B, c, log2D, f.coin_total, wide_bits(B.b_q8[c]) != 0u && B.codes[c] != nullptr);
+__device__ inline void enc_last_tail(const EncTail &f, const EncBatch &B, uint32_t c, int log2D, uint64_t seed, double n2,
+                                     double block_total, double *part, uint32_t *flag) {
+    double total;
+    if (!enc_sum_in_doubt(n2, log2D)) {
+        if (threadIdx.x >= 64u) return;                          // (no barrier from here on)
+        uint32_t before = 0;
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the store has reached memory
+            before = __hip_atomic_fetch_add(f.arrived + c * kEncCounterStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (__builtin_amdgcn_readfirstlane(before) + 1u != gridDim.x) return;
+        if (threadIdx.x == 0) __hip_atomic_store(f.arrived + c * kEncCounterStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        total = ordered_sum_through(part, gridDim.x);
+    } else {
+        if (threadIdx.x == 0) __hip_atomic_store(part + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (!arrive_last(f.arrived + c * kEncCounterStride, gridDim.x, flag)) return;
+        total = ordered_sum_through(part, gridDim.x);            // (every wave the same)
+        if (!(total > 0.0)) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            zero_payload<THREADS>(B, c, log2D, f.coin_total, wide_bits(B.b_q8[c]) != 0u && B.codes[c] != nullptr);
+        }
     }
     if (threadIdx.x == 0) write_enc_header(B, c, f.hdr_d, log2D, seed, n2, total, f.dev_status, f.coin_total);
 }

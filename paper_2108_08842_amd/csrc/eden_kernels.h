@@ -19,8 +19,8 @@ namespace eden {
 uint32_t launch_enc_lo_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
                              double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
 uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, int p, uint64_t seed,
-                            const float *T, double *partials, uint32_t partial_stride, const EncScratch *scratch,
-                            const CoinTables &ct, const EncTail &tail, hipStream_t st);
+                            const float *T, double *partials, uint32_t partial_stride, const CoinTables &ct, const EncTail &tail,
+                            hipStream_t st);
 // coin budgets (multi-pass sizes): the coins of the senders that have such a budget, with their prefix sums; `part_b`
 // (encode) points at the second part of every such sender's payload, which is cleared; null on the receiver's side
 void launch_coin_pack(const uint32_t *b_q8, const uint32_t *const *pieces, void *const *part_b, uint32_t n, int log2D,

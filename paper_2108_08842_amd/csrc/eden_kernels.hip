@@ -71,7 +71,7 @@ __device__ inline void store_row_planes(const uint32_t (&plane)[4][2], uint32_t 
 // with I_{K+1}; their top bits go to the second part in coordinate order, the row's first one at bit `my_off`.
 // `my_row`: first coordinate of the row that this lane (< R) finishes.
 template <int R, int K, int MIX>
-__device__ inline void hi_quantize_pack(const float (&v)[R], const EncScratch *sc, const float *qtab, uint64_t mixkey,
+__device__ inline void hi_quantize_pack(const float (&v)[R], const Thresholds &th, const float *qtab, uint64_t mixkey,
                                         uint64_t my_row, uint32_t *part_a, uint32_t *part_b, float &ip,
                                         uint64_t my_mask = 0, uint32_t my_off = 0) {
     constexpr int H = 1 << (K - 1);
@@ -92,12 +92,12 @@ __device__ inline void hi_quantize_pack(const float (&v)[R], const EncScratch *s
             } else {
                 up = __builtin_amdgcn_inverse_ballot_w64(wave_read64(my_mask, r));
             }
-            code = quantize_mixed<K>(v[r], up, sc, qtab, ip);
+            code = quantize_mixed<K>(v[r], up, th, qtab, ip);
             const uint64_t m = __ballot((code >> K) & 1u);
             top[0] = put_lane<r>(lo32(m), top[0]);
             top[1] = put_lane<r>(hi32(m), top[1]);
         } else {
-            code = quantize_one<H>(v[r], sc, qtab, ip);
+            code = quantize_one<H>(v[r], th, qtab, ip);
         }
 #pragma unroll
         for (int b = 0; b < K; ++b) {
@@ -127,18 +127,19 @@ __device__ inline void hi_quantize_pack(const float (&v)[R], const EncScratch *s
 template <int M, uint32_t ONLY = 0>
 __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_elems, int log2D, int p, uint64_t seed,
                                                      const float *T, double *partials, uint32_t partial_stride,
-                                                     const EncScratch *scratch, CoinTables ct, EncTail tail) {
+                                                     CoinTables ct, EncTail tail) {
     constexpr int R = 1 << M;
     __shared__ double red[4];
     __shared__ uint32_t last_flag;
-    __shared__ float qtabs[4][16];
-    __shared__ float gtabs[4][256];                              // one-byte budgets: centroids and thresholds
+    __shared__ EncScratch es;
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id();
-    const uint32_t tile = blockIdx.x * 4u + wave_in_block();
-    const uint32_t ntiles = 1u << (log2D - 6 - M);
+    const uint32_t tile = blockIdx.x * 4u + wave_in_block();     // (2^(p-6) tiles: a multiple of 4)
+    const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
     float ip = 0.0f;
-    if (tile < ntiles) {
+    EarlyPartials early;
+    early.load(tail.part_n2 + (size_t)c * tail.n2_stride, tail.n2_count);
+    {
         uint64_t base;
         hi_tile_origin<M>(tile, p, base);
         const rsrc_t rt = make_rsrc(T + ((size_t)c << log2D), (uint32_t)(valid_elems * 4));
@@ -146,11 +147,13 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
         float v[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = buf_load(rt, lane_off, base_off + ((uint32_t)r << (p + 2)));
-        fwht_regs<R>(v);
+        enc_scratch_to_lds(tail, c, b_q8, early, es, red);
+        // (the butterflies stand behind the norm's branch: in front of it the compiler moves half of them into it, and holds 138 registers)
+        const bool valid = enc_valid_norm(es.n2);
+        if (valid) fwht_regs<R>(v);
         uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
-        const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
         const uint64_t my_row = base + ((uint64_t)(lane & (R - 1)) << p);       // lane r < R finishes row r
-        if (tail.arrived && !enc_valid_norm(scratch[c].n2)) {
+        if (!valid) {
             if (lane < R) zero_payload_row(B, c, log2D, my_row);
         } else if (b_q8 <= 256u) {
             // I_1 = {(-inf,0],[0,inf)}: the index is the sign; <R(x),Q> = q_1 sum |u| / sqrt(D)
@@ -179,20 +182,14 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
                 }
             }
         } else {
-            const EncScratch *sc = &scratch[c];
-            float *qtab = qtabs[wave_in_block()];
-            fill_qtab(qtab, sc, lane);
-            wave_lds_sync();
+            const Thresholds sc = uniform_thresholds(es);
+            const float *qtab = es.qpos;
             const uint64_t mixkey = stream_key(seed, kStreamMix, B.client[c]);
             uint32_t *part_b = payload + payload_a_bytes(1ull << log2D, (int)(b_q8 >> 8), 1) / 4;
             if (byte_budget(b_q8)) {
                 // uniform grid (Sec. 4.3) or b = 5..8: one byte per coordinate; a row of the tile is 64 consecutive bytes
-                float *ctab = gtabs[wave_in_block()];
-                const float *byte_tab = sc->grid_c;              // grid_c[128] and wide_thr[128] are one run of 256 floats
-#pragma unroll
-                for (int q = 0; q < 4; ++q) ctab[64 * q + lane] = byte_tab[64 * q + lane];       // centroids, then thresholds
-                wave_lds_sync();
-                const float inv = sc->grid_inv;
+                const float *ctab = es.grid_c;                   // centroids, then thresholds: one run of 256 floats
+                const float inv = es.grid_inv;
                 uint8_t *bytes = B.codes[c] ? B.codes[c] : reinterpret_cast<uint8_t *>(payload);
                 const uint32_t H = wide_half_levels(b_q8);
                 if (grid_q15(b_q8)) {                            // the indices replace the values in their registers
@@ -228,8 +225,7 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
         }
     }
     const double block_total = block_sum<256>((double)ip, red);
-    if (tail.arrived) enc_last_tail<256>(tail, B, c, log2D, seed, block_total, partials + (size_t)c * partial_stride, red, &last_flag);
-    else if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    enc_last_tail<256>(tail, B, c, log2D, seed, es.n2, block_total, partials + (size_t)c * partial_stride, &last_flag);
 }
 
 // One workgroup per sender: sums the per-workgroup partials of |x|^2 in index order (deterministic)
@@ -239,7 +235,7 @@ __global__ __launch_bounds__(256) void k_enc_norm(EncBatch B, const double *part
                                                   uint32_t nparts, EncScratch *scratch, const DevTables *tab) {
     __shared__ double red[4];
     const uint32_t c = blockIdx.x;
-    const double n2 = ordered_sum<256, false>(partials + (size_t)c * partial_stride, nparts, red);
+    const double n2 = ordered_sum<256>(partials + (size_t)c * partial_stride, nparts, red);
     fill_enc_scratch(&scratch[c], n2, B.b_q8[c], tab, threadIdx.x);
     fill_byte_tables(&scratch[c], B.b_q8[c], n2, tab, threadIdx.x);
 }
@@ -592,8 +588,7 @@ __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t kee
 __global__ __launch_bounds__(128) void k_enc_lo_first(EncBatch B, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
                                                       double *partials, uint32_t partial_stride, EncTail tail) {
     __shared__ float lds[2][64 * kLdsRow];
-    __shared__ double red[4];
-    __shared__ uint32_t last_flag;
+    __shared__ double red[2];
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id();
     const uint32_t wv = wave_in_block();
@@ -644,8 +639,8 @@ __global__ __launch_bounds__(128) void k_enc_lo_first(EncBatch B, uint64_t d_src
         for (int j = 0; j < 64; ++j) __builtin_nontemporal_store(L[j * kLdsRow + lane], Tc + 64 * j);
     }
     const double block_total = block_sum<128>(n2, red);
-    if (tail.arrived) enc_first_tail<128>(tail, B, c, block_total, partials + (size_t)c * partial_stride, red, &last_flag);
-    else if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    enc_first_side<128>(tail, c, B.b_q8[c]);
 }
 
 // One workgroup per sender: sums the partials of sum_i u_i q_i in index order, forms
@@ -657,8 +652,8 @@ __global__ __launch_bounds__(256) void k_enc_finish(EncBatch B, uint64_t hdr_d, 
                                                     uint32_t partial_stride, uint32_t *dev_status, const uint32_t *coin_total) {
     __shared__ double red[4];
     const uint32_t c = blockIdx.x;
-    const double n2 = ordered_sum<256, false>(partials_n2 + (size_t)c * partial_stride, nparts_n2, red);
-    const double total = ordered_sum<256, false>(partials_ip + (size_t)c * partial_stride, nparts_ip, red);
+    const double n2 = ordered_sum<256>(partials_n2 + (size_t)c * partial_stride, nparts_n2, red);
+    const double total = ordered_sum<256>(partials_ip + (size_t)c * partial_stride, nparts_ip, red);
     if (!(enc_valid_norm(n2) && total > 0.0)) zero_payload<256>(B, c, log2D, coin_total, false);
     if (threadIdx.x == 0) write_enc_header(B, c, hdr_d, log2D, seed, n2, total, dev_status, coin_total);
 }
@@ -1041,7 +1036,7 @@ __global__ void k_loss_bitmap(uint64_t key, uint32_t npk, uint32_t drop_q32, uin
     }
 
 uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, int p, uint64_t seed,
-                            const float *T, double *partials, uint32_t partial_stride, const EncScratch *scratch,
+                            const float *T, double *partials, uint32_t partial_stride,
                             const CoinTables &ct, const EncTail &tail, hipStream_t st) {
     const uint32_t ntiles = 1u << (log2D - 6 - M);
     dim3 grid((ntiles + 3) / 4, n);
@@ -1053,7 +1048,7 @@ uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid
     }
 #define EDEN_ENC_HI_LAST(MM, ONLY)                                                                                            \
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_hi_last<MM, ONLY>), grid, dim3(256), 0, st, B, valid_elems, log2D, p, seed, T, partials, \
-                       partial_stride, scratch, ct, tail)
+                       partial_stride, ct, tail)
     if (all1) { if (M == 5) EDEN_ENC_HI_LAST(5, 256u); else EDEN_ENC_HI_LAST(6, 256u); }
     else if (all2) { if (M == 5) EDEN_ENC_HI_LAST(5, 512u); else EDEN_ENC_HI_LAST(6, 512u); }
     else if (all4) { if (M == 5) EDEN_ENC_HI_LAST(5, 1024u); else EDEN_ENC_HI_LAST(6, 1024u); }

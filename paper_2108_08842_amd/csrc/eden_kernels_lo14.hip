@@ -66,7 +66,6 @@ __global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t 
                                                         double *partials, uint32_t partial_stride, EncTail tail) {
     __shared__ __attribute__((aligned(16))) float lds[kLo14LdsWords];
     __shared__ double red[8];
-    __shared__ uint32_t last_flag;
     const uint32_t c = blockIdx.y, t = threadIdx.x, lane = t & 63u;
     const uint32_t wv = wave_in_block();
     const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));           // reads past d_src give the zero padding
@@ -105,8 +104,8 @@ __global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t 
     lo14_forward32(u, lds);
     store_runs<kLo14Bits, BLOCKED>(u, lds + wv * kXbWave, Tc, tile, 64u * wv);
     const double block_total = block_sum<512>(n2, red);
-    if (tail.arrived) enc_first_tail<512>(tail, B, c, block_total, partials + (size_t)c * partial_stride, red, &last_flag);
-    else if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    enc_first_side<512>(tail, c, B.b_q8[c]);
 }
 
 // Decode, last pass: index bits 0..13 of H for every sender, that sender's sign diagonal (R^-1 = s o D^-1/2 H,

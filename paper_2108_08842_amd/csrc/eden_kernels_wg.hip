@@ -56,6 +56,7 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
         });
         return;
     }
+    const Thresholds th = thresholds_of(sc);
     uint32_t plane[BITS][NW], top[NW], offs16[NW], coin_off[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -81,12 +82,12 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
             const uint32_t ob = __builtin_amdgcn_readlane(offs16[s / 32], 32 + s % 32);
             const uint32_t offs = (lane < 32u) ? oa : ob;
             const bool up = MIX == 1 ? ((offs >> (col >> 1)) & 1u) == (col & 1u) : ((offs >> col) & 1u) != 0u;
-            code = quantize_mixed<BITS>(out[s], up, sc, qtab, ip);
+            code = quantize_mixed<BITS>(out[s], up, th, qtab, ip);
             const uint64_t m = __ballot((code >> BITS) & 1u);
             top[s / 32] = put_lane<s % 32>(lo32(m), top[s / 32]);
             top[s / 32] = put_lane<32 + s % 32>(hi32(m), top[s / 32]);
         } else {
-            code = quantize_one<H>(out[s], sc, qtab, ip);
+            code = quantize_one<H>(out[s], th, qtab, ip);
         }
 #pragma unroll
         for (int b = 0; b < BITS; ++b) {
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
     const uint64_t mixkey = stream_key(seed, kStreamMix, B.client[c]);
     if constexpr (MODE == 3) fill_rank_guess<8>(guess, sc, threadIdx.x);     // published, like qtab, by the first barrier of the exchange
     if (!UNIT) {
-        fill_qtab(qtab, sc, threadIdx.x);
+        if (threadIdx.x < 16u) qtab[threadIdx.x] = sc->qpos[threadIdx.x];       // qpos and qpos2 are one run
         if (byte_budget(b_q8)) {                                 // centroids, then thresholds: one run of 256 floats
             const float *byte_tab = sc->grid_c;
             for (uint32_t i = threadIdx.x; i < 256u; i += X::THREADS) gtab[i] = byte_tab[i];

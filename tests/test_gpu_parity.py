@@ -331,6 +331,26 @@ def test_messages_do_not_depend_on_the_number_of_launches(ctx, d, n):
     assert ctx.last_device_status() == 0
 
 
+@pytest.mark.parametrize("d", [4097, 8192, (1 << 17) + 1, 1 << 18, (1 << 18) + 1, 1 << 20])
+def test_full_launches_of_the_two_launch_encoder(ctx, d):
+    # 32 senders, smallest and largest size of every plan in wave tiles: each workgroup of the last pass adds the norm's partial sums up
+    # for itself, and the one that finishes last writes the header.  Every message is the one its sender writes alone, whatever its
+    # neighbours are (zero, not finite), twice in a row
+    from paper_2108_08842_amd import eden
+    kinds = [512, 1024, 256, 1536, 128, eden.B_GRID(0.5224), 384, 2048]
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    good = torch.randn(d, generator=gen, device="cuda")
+    bad = good.clone()
+    bad[d - 1] = float("nan")
+    budgets = [kinds[c % len(kinds)] for c in range(32)]
+    xs = [bad if c % 7 == 3 else torch.zeros_like(good) if c % 7 == 5 else good for c in range(32)]
+    for _ in range(2):
+        msgs = ctx.encode(xs, list(range(32)), budgets, 43)
+        for c in range(32):
+            assert torch.equal(msgs[c], ctx.encode([xs[c]], [c], [budgets[c]], 43)[0]), (c, budgets[c])
+    assert ctx.last_device_status() == eden.DEV_ZERO_VECTOR | eden.DEV_NONFINITE
+
+
 @pytest.mark.parametrize("d,n", [(3000, 12), (5000, 12), (100_000, 12), (300_000, 2), (900_000, 2), (300_000, 12), (2_500_000, 3)])
 def test_finite_vectors_whose_transform_overflows_or_vanishes(ctx, d, n):
     # |x|^2 (in double) is fine but <R(x),Q> (from fp32 values) is NaN or 0: such a message says EDEN_DEV_ZERO_VECTOR and has S = 0
