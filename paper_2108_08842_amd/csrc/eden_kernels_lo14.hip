@@ -1,7 +1,8 @@
-// The 14-bit contiguous pass with 32 registers per thread (gfx950).
+// The 14-bit contiguous passes (gfx950).
 //
-// A workgroup of 8 waves owns 2^14 consecutive coordinates.  Every thread keeps 32 values, so the 14 index
-// bits are covered by three groups of in-register butterfly stages:
+// Decode: a workgroup of 16 waves owns 2^14 consecutive coordinates, 16 values per thread (eden_lo.h), or runs ten of the 14 bits on the
+// matrix cores where the values are small integers.  Encode: 8 waves, 32 values per thread, so that the 14 index bits are covered
+// by three groups of in-register butterfly stages:
 //
 //   group 1   bits 9..13   v[a] = coordinate 512 a + 64 wave + lane  (coalesced loads, 256 B per wave load)
 //   exchange  through LDS between all waves (registers <-> bits 4..8)
@@ -10,13 +11,10 @@
 //   group 3   bits 0..3
 //
 // Afterwards thread t holds the 32 consecutive coordinates 32 t + e, e = 0..31: one half of a 64-bit sign word
-// of the rotation, and one 128-byte line of the workspace or the accumulator.
-//
-// 32 registers (instead of 64) halve the LDS a wave needs for its exchanges, which doubles the number of
-// resident waves per CU (16).  The encode pass built on this is bound by memory, the decode pass (which repeats
-// the transform for every sender of a tile) by vector-ALU issue.
+// of the rotation, and one 128-byte line of the workspace.  The encode pass is bound by memory.
 #include "eden_device.h"
 #include "eden_kernels.h"
+#include "eden_lo.h"
 
 namespace eden {
 
@@ -119,142 +117,100 @@ __global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t 
 // group k > 0 stores its sum in partial[k-1][tile - full_tiles][2^14]; k_dec_lo14_combine then adds those to
 // acc in the order k = 1, 2, ... (fixed, so the result does not depend on scheduling).
 //
-// PRE (b = 1/2 with the sparsification first, Sec. 4.1): the decoded vectors have dimension ceil(d_src/2) and value g
-// of sender c belongs at coordinate 2g + o_g of acc (o_g from c's SUB-SAMPLING stream).  A thread then keeps the 64
-// accumulator coordinates of its 32 pairs in registers and adds every value to the member of the pair it belongs
-// to; the launcher does not split tiles in this mode.
 // `separate`: K = n, one sender per workgroup, nothing is summed: every sender's decoded tile is written back into its own
 // workspace slot (`partial` is then the workspace; fp32, in place: the workgroup has read the tile before it writes
 // it), for a caller that puts the values elsewhere afterwards.
-// WIDE_ONLY: no sender of the launch has an fp16 slot (every b > 1): the instance without that branch in the sender loop
-// (116 registers instead of 125; 16 senders at D = 2^24: 0.170 -> 0.160 ms).
-template <bool PRE, bool WIDE_ONLY = false>
-__global__ __launch_bounds__(512) void k_dec_lo14_last(DecBatch B, uint32_t n, uint64_t d_src, int log2D, uint64_t seed,
+// WIDE_ONLY: no sender of the launch has an fp16 slot (every b > 1): the instance without that branch in the sender loop.
+// AHEAD: the values of sender c + 1 are on their way while those of sender c are transformed, for the launches that do not split
+// tiles (whole decode at b = 4, us, with / without: 4 senders of 11,173,962 92 / 95, 16 298 / 305; with split tiles the other workgroup
+// of the CU fills that time: 10 of 2^20, b = 2 36.9 / 34.9).
+//
+// 16 values per thread, 64 registers, two workgroups of 16 waves per CU.  With 32 values in 8 waves (116 registers, half as many
+// waves), whole decode: 8 senders of 300,007, b = 2 26.9 -> 23.5 us; one of 11,173,962, b = 4 65 -> 43, 16 of them 314 -> 299; 32 of 2^20 with
+// 1/2, 1, 2 and 4 bits 83 -> 77.
+template <bool WIDE_ONLY, bool AHEAD>
+__global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
                                                        const float *T, const DecScratch *scratch, int narrow_arg, float *acc,
                                                        uint32_t full_tiles, uint32_t K, uint32_t split_tiles,
                                                        float *partial, int separate, float mean_n) {
-    __shared__ __attribute__((aligned(16))) float lds[kLo14LdsWords];
+    __shared__ __attribute__((aligned(16))) float lds[Lo16<14>::LDS_FLOATS];
     const int narrow = WIDE_ONLY ? 0 : narrow_arg;
-    constexpr int NS = PRE ? 64 : 32;                            // accumulator coordinates per thread
-    const uint64_t d = d_src;                                    // bound of acc
-    const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block();
     uint32_t tile = blockIdx.x, c_begin = 0, c_end = n;
-    float *part_run = nullptr;                                   // this thread's 32 values in the partial buffer
+    float *part_tile = nullptr;                                  // this tile in the partial buffer
     if (blockIdx.x >= full_tiles) {
         const uint32_t idx = blockIdx.x - full_tiles, k = idx % K;
         tile = full_tiles + idx / K;
         c_begin = (uint32_t)(((uint64_t)n * k) / K);
         c_end = (uint32_t)(((uint64_t)n * (k + 1)) / K);
-        if (separate) part_run = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits) + 32u * t;
-        else if (k > 0) part_run = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits) + 32u * t;
+        if (separate) part_tile = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits);
+        else if (k > 0) part_tile = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits);
     }
-    const uint64_t tile_base = (uint64_t)tile << kLo14Bits;
-    const uint64_t first = tile_base + 32u * t;
-    const size_t in_off = tile_base + wv * 64u + lane;
-    float sum[NS];
+    const uint32_t tile_base = tile << kLo14Bits;
+    float sum[16];
 #pragma unroll
-    for (int e = 0; e < NS; ++e) sum[e] = 0.0f;
+    for (int e = 0; e < 16; ++e) sum[e] = 0.0f;
 
-    auto load = [&](uint32_t c, float (&dst_regs)[32]) {
+    auto load = [&](uint32_t c, float (&dst)[16]) {
         if (narrow && B.b_q8[c] <= 256u) {
-            const short *t16 = reinterpret_cast<const short *>(T + ((size_t)c << log2D)) + in_off;
+            const rsrc_t r16 = make_rsrc(T + ((size_t)c << log2D), 2u << log2D);
 #pragma unroll
-            for (int a = 0; a < 32; ++a) dst_regs[a] = __int_as_float((int)__builtin_nontemporal_load(t16 + 512 * a));
+            for (int a = 0; a < 16; ++a)
+                dst[a] = __uint_as_float((uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r16, (int)(t * 2u), (int)((tile_base + 1024u * a) * 2u), kStream));
         } else {
-            const float *t32 = T + ((size_t)c << log2D) + in_off;
+            const rsrc_t r32 = make_rsrc(T + ((size_t)c << log2D), 4u << log2D);
 #pragma unroll
-            for (int a = 0; a < 32; ++a) dst_regs[a] = __builtin_nontemporal_load(t32 + 512 * a);
+            for (int a = 0; a < 16; ++a) dst[a] = buf_load(r32, t * 4u, (tile_base + 1024u * a) * 4u);
         }
     };
-    // One sender: `cur` holds its 32 loaded values (PRE: they are loaded here, with 64 accumulators there is no room to
-    // load ahead); the loads of sender c + 1 go into the same registers once the values have been converted.  (Two
-    // alternating register sets would save the compiler's copy of the loaded set, but need more than 128 registers.)
-    auto one_sender = [&](uint32_t c, float (&cur)[32]) {
+    float next[16];
+    if (AHEAD && c_begin < c_end) load(c_begin, next);
+    for (uint32_t c = c_begin; c < c_end; ++c) {
         const bool i16 = narrow && B.b_q8[c] <= 256u;
-        float u[32];
-        if constexpr (PRE) load(c, cur);
+        if (!AHEAD) load(c, next);
+        float u[16];
 #pragma unroll
-        for (int a = 0; a < 32; ++a) {
-            u[a] = i16 ? narrow_value((short)__float_as_int(cur[a])) : cur[a];
-        }
+        for (int a = 0; a < 16; ++a) u[a] = i16 ? narrow_value((short)__float_as_int(next[a])) : next[a];
         __builtin_amdgcn_sched_barrier(0);                       // the conversions stay above the next sender's loads
-        if (!PRE && c + 1 < c_end) load(c + 1, cur);
-        lo14_forward32(u, lds);
+        if (AHEAD && c + 1 < c_end) load(c + 1, next);
+        if (c > c_begin) __syncthreads();                        // LDS is free again
+        lo_forward16<kLo14Bits>(u, lds);
         const uint32_t scale = __float_as_uint(i16 ? scratch[c].deq[1] : 1.0f) & 0x7FFFFFFFu;   // > 0; x*1+s is exact
-        // the wave's 2048 coordinates use 32 sign words: lane l < 32 hashes word l, every thread fetches its own
-        const uint64_t key = stream_key(seed, kStreamSign, B.client[c]);
-        const uint64_t mine = hash_word(key, ((tile_base + 512u * (wv * 4u)) >> 6) + (lane & 31u));
-        const uint32_t src = ((lane >> 4) * 8u) + ((lane & 15u) >> 1);      // word of this thread's run, wave-relative
-        const uint32_t wlo = (uint32_t)__shfl((int)(uint32_t)mine, (int)src, 64);
-        const uint32_t whi = (uint32_t)__shfl((int)(uint32_t)(mine >> 32), (int)src, 64);
-        const uint32_t bits = (t & 1u) ? whi : wlo;              // 32 sign bits of this thread's run
-        if constexpr (PRE) {
-            const uint64_t okey = stream_key(seed, kStreamSubsample, B.client[c]);
-            const uint64_t omine = hash_word(okey, ((tile_base + 512u * (wv * 4u)) >> 6) + (lane & 31u));
-            const uint32_t olo = (uint32_t)__shfl((int)(uint32_t)omine, (int)src, 64);
-            const uint32_t ohi = (uint32_t)__shfl((int)(uint32_t)(omine >> 32), (int)src, 64);
-            const uint32_t offs = (t & 1u) ? ohi : olo;          // which member of each of this thread's 32 pairs
+        const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t >> 2));
+        const uint32_t bits = (uint32_t)(word >> (16u * (t & 3u)));      // 16 sign bits of this thread's run
 #pragma unroll
-            for (int e = 0; e < 32; ++e) {
-                const uint32_t sgn = (bits << (31 - e)) & 0x80000000u;
-                const float val = u[e] * __uint_as_float(scale | sgn);
-                const bool odd = (offs >> e) & 1u;
-                sum[2 * e] += odd ? 0.0f : val;
-                sum[2 * e + 1] += odd ? val : 0.0f;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 32; ++e) {
-                // hash bit 1 -> s_i = -1: the factor is the scale with bit e of the sign word moved to the sign position
-                // (one shift, one bit-field insert)
-                const uint32_t shifted = bits << (31 - e);
-                const uint32_t factor = (scale & 0x7FFFFFFFu) | (shifted & 0x80000000u);
-                sum[e] = fmaf(u[e], __uint_as_float(factor), sum[e]);
-            }
+        for (int e = 0; e < 16; ++e) {
+            // hash bit 1 -> s_i = -1: the factor is the scale with bit e of the sign word moved to the sign position
+            // (one shift, one bit-field insert)
+            const uint32_t factor = (scale & 0x7FFFFFFFu) | ((bits << (31 - e)) & 0x80000000u);
+            sum[e] = fmaf(u[e], __uint_as_float(factor), sum[e]);
         }
-        __syncthreads();                                         // LDS is reused by the next sender
-    };
-    float loaded[32];
-    if (!PRE && c_begin < c_end) load(c_begin, loaded);
-    for (uint32_t c = c_begin; c < c_end; ++c) one_sender(c, loaded);
-    if constexpr (PRE) {                                         // this thread's 32 pairs = 64 consecutive coordinates of acc
-        const uint64_t out = 2 * first;
-        if (out + 64 <= d) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                float4 a = *reinterpret_cast<const float4 *>(acc + out + 4 * q);
-                a.x += sum[4 * q]; a.y += sum[4 * q + 1]; a.z += sum[4 * q + 2]; a.w += sum[4 * q + 3];
-                *reinterpret_cast<float4 *>(acc + out + 4 * q) = a;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 64; ++e)
-                if (out + e < d) acc[out + e] += sum[e];
-        }
-        return;
     }
-    if (part_run) {
+    float4 x[4];
+    wave_quads(sum, lds + wv * Lo16<14>::ROW, x);
+    const uint32_t at = 1024u * wv + 4u * lane;                  // quad j: coordinates at + 256 j .. + 3 of the tile
+    if (part_tile) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-            *reinterpret_cast<float4 *>(part_run + 4 * q) = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<float4 *>(part_tile + at + 256 * j) = x[j];
         return;
     }
     // mean_n > 0: acc is written, not added to; the division happens here when no other workgroup adds to this tile
     const bool overwrite = mean_n > 0.0f;
     const float div = (overwrite && blockIdx.x < full_tiles) ? mean_n : 1.0f;
-    if (tile_base + (1u << kLo14Bits) <= d) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+    for (int j = 0; j < 4; ++j) {
+        const uint64_t i = tile_base + at + 256 * j;
+        if (i + 4 <= d) {
             float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (!overwrite) a = *reinterpret_cast<const float4 *>(acc + first + 4 * q);
-            a.x = (a.x + sum[4 * q]) / div; a.y = (a.y + sum[4 * q + 1]) / div;
-            a.z = (a.z + sum[4 * q + 2]) / div; a.w = (a.w + sum[4 * q + 3]) / div;
-            *reinterpret_cast<float4 *>(acc + first + 4 * q) = a;
-        }
-    } else {                                                     // the one tile that straddles d
+            if (!overwrite) a = *reinterpret_cast<const float4 *>(acc + i);
+            a.x = (a.x + x[j].x) / div; a.y = (a.y + x[j].y) / div; a.z = (a.z + x[j].z) / div; a.w = (a.w + x[j].w) / div;
+            *reinterpret_cast<float4 *>(acc + i) = a;
+        } else {                                                 // the quad that straddles d, and those beyond
+            const float v[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
 #pragma unroll
-        for (int e = 0; e < 32; ++e)
-            if (first + e < d) acc[first + e] = ((overwrite ? 0.0f : acc[first + e]) + sum[e]) / div;
+            for (int e = 0; e < 4; ++e)
+                if (i + e < d) acc[i + e] = ((overwrite ? 0.0f : acc[i + e]) + v[e]) / div;
+        }
     }
 }
 
@@ -592,17 +548,12 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
                           uint32_t partial_tiles, float mean_n, hipStream_t st) {
     const uint64_t d = pre == 1 ? (d_src + 1) / 2 : d_src;       // dimension of the decoded vectors
     const uint32_t tiles = (uint32_t)((d + (1u << kLo14Bits) - 1) >> kLo14Bits);     // tiles that reach below d
-    if (pre == 1) {
-        if (narrow)                                              // fp16 workspace of small integers: on the matrix cores
-            hipLaunchKernelGGL(k_dec_lo14_last_pairs, dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc,
-                               mean_n);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<true>), dim3(tiles), dim3(512), 0, st, B, n, d_src, log2D, seed, T,
-                               scratch, narrow, acc, tiles, 1u, 0u, partial, 0, 0.0f);
+    if (pre == 1) {                                              // (fp16 workspace of small integers: on the matrix cores)
+        hipLaunchKernelGGL(k_dec_lo14_last_pairs, dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
         return;
     }
     if (pre == 2) {                                              // every sender on its own, back into its workspace slot
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<false>), dim3(tiles * n), dim3(512), 0, st, B, n, d_src, log2D, seed,
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<true, false>), dim3(tiles * n), dim3(1024), 0, st, B, n, d_src, log2D, seed,
                            T, scratch, 0, acc, 0u, n, tiles, T, 1, 0.0f);
         return;
     }
@@ -632,12 +583,13 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
     else {
         bool none16 = true;                                      // no sender with an fp16 slot
         for (uint32_t c = 0; c < n; ++c) none16 = none16 && !(narrow && B.b_q8[c] <= 256u);
-        if (none16)
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<false, true>), grid, dim3(512), 0, st, B, n, d_src, log2D, seed, T,
-                               scratch, narrow, acc, full, K, rest, partial, 0, mean_n);
-        else
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<false>), grid, dim3(512), 0, st, B, n, d_src, log2D, seed, T, scratch,
-                               narrow, acc, full, K, rest, partial, 0, mean_n);
+#define EDEN_DEC_LO14_LAST(WIDE_ONLY, AHEAD)                                                                                          \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<WIDE_ONLY, AHEAD>), grid, dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, \
+                       narrow, acc, full, K, rest, partial, 0, mean_n)
+        if (!none16) EDEN_DEC_LO14_LAST(false, false);
+        else if (K > 1) EDEN_DEC_LO14_LAST(true, false);
+        else EDEN_DEC_LO14_LAST(true, true);
+#undef EDEN_DEC_LO14_LAST
     }
     if (K > 1) {
         dim3 cgrid((uint32_t)((((uint64_t)rest << kLo14Bits) / 4 + 255) / 256));
