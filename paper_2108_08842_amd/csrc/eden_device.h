@@ -15,9 +15,7 @@ namespace eden {
 constexpr int kMaxBatch = 32;            // senders handled by one launch; larger batches are chunked
 constexpr uint32_t kEncCounterStride = 32;  // words between the arrival counters of two senders: a memory line each (see enc_last_tail)
 constexpr uint32_t kDecCounters = 8;     // arrival counters of the small decode launches, used in turn (see k_dec_small)
-constexpr int kLoBits = 12;              // index bits transformed by the contiguous (wave-tile) pass
-constexpr int kLoTile = 1 << kLoBits;    // 4096 coordinates = 64 lanes x 64 registers
-constexpr int kLdsRow = 68;              // padded row length (floats) of the 64x64 LDS transpose
+constexpr int kLoBits = 12;              // index bits transformed by the contiguous pass up to D = 2^18
 
 // ---- shared randomness (Sec. 2.1): counter hash = splitmix64 stream started at a per-(seed,stream,client) key
 constexpr uint64_t kPhi = 0x9E3779B97F4A7C15ull;
@@ -277,15 +275,48 @@ __device__ inline void fwht_regs(float (&v)[N]) {
     }
 }
 
+// The value of another lane, by data-parallel primitives instead of the cross-lane path through the LDS (a sum over the wave took 0.3 us
+// that way): lane ^ 1, lane ^ 2 inside a quad; then, since every lane of a quad (8, 16 lanes) already holds the same sum, the mirrored
+// lane of 8 and of 16 stand for lane ^ 4 and lane ^ 8.
+template <int CTRL>
+__device__ inline uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false); }
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)dpp_u32<CTRL>((uint32_t)b) | ((uint64_t)dpp_u32<CTRL>((uint32_t)(b >> 32)) << 32));
+}
+enum : int { kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141, kDppMirror16 = 0x140 };
+// the values of both lanes of a pair (lane, lane ^ 16) or (lane, lane ^ 32), the lower one's first
+template <int X>
+__device__ inline void lane_pair(uint32_t v, uint32_t &lower, uint32_t &upper) {
+    static_assert(X == 16 || X == 32, "rows of 16 lanes");
+    const auto r = X == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    lower = r[0]; upper = r[1];
+}
+template <int X>
+__device__ inline double pair_sum(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    uint32_t lo0, lo1, hi0, hi1;
+    lane_pair<X>((uint32_t)b, lo0, lo1);
+    lane_pair<X>((uint32_t)(b >> 32), hi0, hi1);
+    return __builtin_bit_cast(double, (uint64_t)lo0 | ((uint64_t)hi0 << 32)) + __builtin_bit_cast(double, (uint64_t)lo1 | ((uint64_t)hi1 << 32));
+}
 __device__ inline double wave_sum(double v) {          // fixed order: deterministic
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp_f64<kDppXor1>(v);
+    v += dpp_f64<kDppXor2>(v);
+    v += dpp_f64<kDppMirror8>(v);
+    v += dpp_f64<kDppMirror16>(v);
+    return pair_sum<32>(pair_sum<16>(v));
 }
 __device__ inline uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp_u32<kDppXor1>(v);
+    v += dpp_u32<kDppXor2>(v);
+    v += dpp_u32<kDppMirror8>(v);
+    v += dpp_u32<kDppMirror16>(v);
+    uint32_t a, b;
+    lane_pair<16>(v, a, b);
+    lane_pair<32>(a + b, a, b);
+    return a + b;
 }
 
 // block-level deterministic sum of one double per thread; result valid in thread 0

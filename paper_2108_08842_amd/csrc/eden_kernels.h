@@ -16,8 +16,6 @@ namespace eden {
 // `d` with a `pre` flag next to it is the caller's dimension; pre != 0 (b = 1/2 with the sparsification before the
 // rotation) means the transformed vector has dimension ceil(d/2).  Every other `d` is the transformed dimension.
 // `tail`: see EncTail (eden_device.h)
-uint32_t launch_enc_lo_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
-                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
 uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, int p, uint64_t seed,
                             const float *T, double *partials, uint32_t partial_stride, const CoinTables &ct, const EncTail &tail,
                             hipStream_t st);
@@ -89,11 +87,11 @@ bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t 
 // whether launch_dec_hix_first would do so for this batch
 bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int narrow);
 
-// 14-bit contiguous passes for D = 2^19 .. 2^24 (eden_kernels_lo14.hip)
-// `blocked`: write the workspace in the blocked layout (eden_device.h: blocked_offset) that launch_enc_hix_last reads
+// 12- and 14-bit contiguous passes for D <= 2^24 (eden_kernels_lo14.hip)
+// `blocked` (P = 14): write the workspace in the blocked layout (eden_device.h: blocked_offset) that launch_enc_hix_last reads
 // when told so; not for a first pass that works in place on the workspace
-uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d, int pre, int blocked, int log2D, uint64_t seed, float *T,
-                               double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
+uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d, int pre, int blocked, int log2D, uint64_t seed, float *T,
+                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
 // `resident`: workgroups of the kernel the device holds at once (2 per CU); `partial`: room for `partial_tiles`
 // tiles of 2^14 floats, used when tiles are split over several workgroups by sender.
 // `mean_n` > 0 (pre == 0 only): acc is not read; acc[i] = (0 + the sum over the senders) / mean_n

@@ -4,8 +4,8 @@
 // unnormalised, u = H (s o x), with the D^-1/2 folded into scalars.  The index bits of the padded
 // dimension D = 2^L are split into groups; one kernel ("pass") transforms one group:
 //
-//   lo pass   bits 0..11   one wave owns 4096 consecutive coordinates: 64 registers per lane, six
-//                          butterfly stages in registers, a 64x64 transpose through LDS, six more.
+//   lo pass   bits 0..11   a workgroup of four waves owns 4096 consecutive coordinates, 16 values per thread (eden_lo.h); the
+//                          encoder's is in eden_kernels_lo14.hip.
 //   hi pass   bits p..p+M-1 (M <= 6): one wave owns 2^M rows of 64 consecutive coordinates at stride 2^p;
 //                          every lane keeps one column in registers; no LDS at all.
 //
@@ -16,6 +16,7 @@
 // touching the accumulator once.  D <= 4096 is handled by eden_kernels_small.hip.
 #include "eden_device.h"
 #include "eden_kernels.h"
+#include "eden_lo.h"
 
 namespace eden {
 
@@ -577,72 +578,6 @@ __global__ __launch_bounds__(256) void k_dec_wide_first(DecBatch B, uint64_t kee
 }
 
 // ------------------------------------------------------------------------------------------------
-// Encode, first pass in wave tiles: x -> T.  Zero padding (Sec. 5: the transform needs a power of two), the
-// sign diagonal of the rotation from the shared seed (Sec. 2.1), |x|^2 for eta and S (Sec. 2.2.1, 2.3), index
-// bits 0..11 of H.  Only the ceil(d / 4096) tiles that hold part of x are transformed and written; the strided
-// pass that follows reads the others as zero through its buffer bounds.  Loads and stores are both in the
-// layout "register j = coordinates 64 j + lane" (256 contiguous bytes per wave access), so the tile goes
-// through the wave-private 64x64 LDS transpose twice.
-// `pre` (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is
-// x'[g] = 2 x[2g + o_g], g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
-__global__ __launch_bounds__(128) void k_enc_lo_first(EncBatch B, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
-                                                      double *partials, uint32_t partial_stride, EncTail tail) {
-    __shared__ float lds[2][64 * kLdsRow];
-    __shared__ double red[2];
-    const uint32_t c = blockIdx.y;
-    const uint32_t lane = lane_id();
-    const uint32_t wv = wave_in_block();
-    const uint32_t tile = blockIdx.x * 2u + wv;
-    const uint64_t tile_base = (uint64_t)tile << kLoBits;
-    const uint64_t d = pre ? (d_src + 1) / 2 : d_src;            // dimension of the vector that is transformed
-    double n2 = 0.0;
-    if (tile_base < d) {                                         // wave-uniform; no block-wide barrier inside
-        const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));      // reads past d_src give the zero padding
-        float v[64];
-        if (pre) {
-            // register j = 64 consecutive pairs = one word of offsets: lane l hashes the word of register l
-            const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), (tile_base >> 6) + lane);
-#pragma unroll
-            for (int j = 0; j < 64; ++j) {
-                const uint32_t odd = __builtin_amdgcn_inverse_ballot_w64(wave_read64(offs, j)) ? 4u : 0u;
-                v[j] = 2.0f * buf_load(rx, lane * 8u + odd, (uint32_t)tile_base * 8u + 512u * j);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 64; ++j) v[j] = buf_load(rx, lane * 4u, (uint32_t)tile_base * 4u + 256u * j);
-        }
-#pragma unroll
-        for (int j = 0; j < 64; ++j) n2 += (double)v[j] * (double)v[j];
-        // register j = 64 consecutive coordinates = one sign word: lane l hashes the word of register l,
-        // register j reads it back as a lane mask
-        const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + lane);
-#pragma unroll
-        for (int j = 0; j < 64; ++j) v[j] = negate_where(v[j], wave_read64(mine, j)) + 0.0f;   // + 0: no negative zeros
-        fwht_regs<64>(v);                                        // index bits 6..11
-        float *L = lds[wv];
-#pragma unroll
-        for (int j = 0; j < 64; ++j) L[j * kLdsRow + lane] = v[j];
-        wave_lds_sync();
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const float4 t = *reinterpret_cast<const float4 *>(&L[lane * kLdsRow + 4 * q]);
-            v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-        }
-        fwht_regs<64>(v);                                        // index bits 0..5; lane holds 64 consecutive values
-        wave_lds_sync();
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-            *reinterpret_cast<float4 *>(&L[lane * kLdsRow + 4 * q]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        wave_lds_sync();
-        float *Tc = T + ((size_t)c << log2D) + tile_base + lane;
-#pragma unroll
-        for (int j = 0; j < 64; ++j) __builtin_nontemporal_store(L[j * kLdsRow + lane], Tc + 64 * j);
-    }
-    const double block_total = block_sum<128>(n2, red);
-    if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
-    enc_first_side<128>(tail, c, B.b_q8[c]);
-}
-
 // One workgroup per sender: sums the partials of sum_i u_i q_i in index order, forms
 // <R(x),Q> = D^-1/2 sum and the scale S = |x|^2 / <R(x),Q> (Sec. 2.3), writes the header.
 // A zero or non-finite vector gets S = 0, a status bit and an all-zero payload.
@@ -784,45 +719,57 @@ __global__ __launch_bounds__(256) void k_coin_pack(CoinPackBatch B, int log2D, C
     B.part_b[c][word] = bits;
 }
 
-// Decode, last pass in wave tiles: index bits 0..11 of H of one sender's vector and its sign diagonal (R^-1 = s o D^-1/2 H,
-// Sec. 2.2.2; D^-1/2 is inside the dequantization scale), in place in the sender's workspace slot (a wave has read its tile
-// before it writes it).  A lane ends with 64 consecutive coordinates = one sign word.
-// One wave per (tile, sender): at these sizes (D <= 2^18) there are at most 64 tiles, and a wave that summed all senders of its
+// Decode, last pass at D <= 2^18: index bits 0..11 of H of one sender's vector and its sign diagonal (R^-1 = s o D^-1/2 H,
+// Sec. 2.2.2; D^-1/2 is inside the dequantization scale), in place in the sender's workspace slot (a workgroup has read its tile
+// before it writes it).
+// One workgroup per (tile, sender): at these sizes (D <= 2^18) there are at most 64 tiles, and a wave that summed all senders of its
 // tile one after the other left the chip idle (32 senders of 60,000, b = 1: 80 of the round's 139 us).  The sum follows in
-// k_dec_lo_combine.
-__global__ __launch_bounds__(128) void k_dec_lo_last(DecBatch B, uint64_t d, int log2D, uint64_t seed, float *T) {
-    __shared__ float lds[2][64 * kLdsRow];
-    const uint32_t lane = lane_id(), wv = wave_in_block(), c = blockIdx.y;
-    const uint32_t tile = blockIdx.x * 2u + wv;
-    const uint64_t tile_base = (uint64_t)tile << kLoBits;
-    if (tile_base >= d) return;                                  // whole tile in the padding (no block-wide barrier below)
-    const uint64_t first = tile_base + 64u * lane;               // this lane's 64 coordinates after the transpose
-    float *L = lds[wv], *slot = T + ((size_t)c << log2D);
-    float v[64];
+// k_dec_lo_combine.  16 values per thread (eden_lo.h): a wave per tile with 64 of them was the longer chain.
+// ONE: the launch has one sender, whose values go to acc at once (mean_n > 0: written, divided by mean_n; else added).
+template <bool ONE>
+__global__ __launch_bounds__(256, 8) void k_dec_lo_last(DecBatch B, uint64_t d, int log2D, uint64_t seed, float *T, const DecScratch *scratch,
+                                                     float *acc, float mean_n) {
+    __shared__ __attribute__((aligned(16))) float lds[Lo16<kLoBits>::LDS_FLOATS];
+    const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block(), c = blockIdx.y;
+    const uint32_t tile_base = blockIdx.x << kLoBits;
+    float *slot = T + ((size_t)c << log2D);
+    const rsrc_t rt = make_rsrc(slot, 4u << log2D);
+    float v[16];
 #pragma unroll
-    for (int j = 0; j < 64; ++j) v[j] = slot[tile_base + lane + 64 * j];
-    fwht_regs<64>(v);                                            // index bits 6..11
+    for (int a = 0; a < 16; ++a) v[a] = buf_load_keep(rt, 4u * t, 4u * (tile_base + 256u * a));
+    lo_forward16<kLoBits>(v, lds);
+    const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t >> 2));
+    const uint32_t bits = (uint32_t)(word >> (16u * (t & 3u)));          // 16 sign bits of this thread's run
 #pragma unroll
-    for (int j = 0; j < 64; ++j) L[j * kLdsRow + lane] = v[j];
-    wave_lds_sync();
+    for (int e = 0; e < 16; ++e)                                 // bit 1 -> s_i = -1
+        v[e] = __uint_as_float(__float_as_uint(v[e]) ^ ((bits << (31 - e)) & 0x80000000u));
+    float4 x[4];
+    wave_quads(v, lds + wv * (Lo16<kLoBits>::LDS_FLOATS / 4), x);
+    const float scale = ONE && B.b_q8[0] <= 256u ? fabsf(scratch[0].deq[1]) : 1.0f;
+    const bool overwrite = mean_n > 0.0f;
+    const float div = overwrite ? mean_n : 1.0f;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const float4 t = *reinterpret_cast<const float4 *>(&L[lane * kLdsRow + 4 * q]);
-        v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t i = tile_base + 1024u * wv + 256u * (uint32_t)j + 4u * lane;
+        if constexpr (!ONE) {
+            *reinterpret_cast<float4 *>(slot + i) = x[j];
+        } else {                                                 // the arithmetic of k_dec_lo_combine
+            const float y[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+            float z[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float old = !overwrite && i + e < d ? acc[i + e] : 0.0f;
+                z[e] = (old + fmaf(y[e], scale, 0.0f)) / div;
+            }
+            if (i + 4 <= d) {                                    // (acc is 16-byte aligned)
+                *reinterpret_cast<float4 *>(acc + i) = make_float4(z[0], z[1], z[2], z[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < d) acc[i + e] = z[e];
+            }
+        }
     }
-    fwht_regs<64>(v);                                            // index bits 0..5
-    const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), first >> 6);
-    const uint32_t wlo = (uint32_t)word, whi = (uint32_t)(word >> 32);
-#pragma unroll
-    for (int k = 0; k < 64; ++k)                                 // bit 1 -> s_i = -1
-        v[k] = __uint_as_float(__float_as_uint(v[k]) ^ (((k < 32 ? wlo : whi) << (31 - (k & 31))) & 0x80000000u));
-    wave_lds_sync();
-#pragma unroll
-    for (int q = 0; q < 16; ++q)
-        *reinterpret_cast<float4 *>(&L[lane * kLdsRow + 4 * q]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    wave_lds_sync();
-#pragma unroll
-    for (int j = 0; j < 64; ++j) slot[tile_base + lane + 64 * j] = L[j * kLdsRow + lane];
 }
 
 // The sum over the senders of what k_dec_lo_last left in their slots, one after the other; the magnitude S/(p sqrt D) q_1 of a
@@ -1122,14 +1069,6 @@ void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_ele
     else EDEN_HI_SWITCH(M, EDEN_DEC_HI_FIRST(MM, 0u));
 #undef EDEN_DEC_HI_FIRST
 }
-uint32_t launch_enc_lo_first(const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
-                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st) {
-    const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
-    const uint32_t tiles = (uint32_t)((d + (1u << kLoBits) - 1) >> kLoBits);
-    dim3 grid((tiles + 1) / 2, n);
-    hipLaunchKernelGGL(k_enc_lo_first, grid, dim3(128), 0, st, B, d_src, pre, log2D, seed, T, partials, partial_stride, tail);
-    return grid.x;
-}
 void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed, const DevTables *tab,
                         DecScratch *scratch, uint32_t *dev_status, const uint32_t *coin_total, uint32_t *msg_flags,
                         hipStream_t st) {
@@ -1140,7 +1079,11 @@ void launch_dec_lo_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre, 
                         const DecScratch *scratch, float *acc, float mean_n, hipStream_t st) {
     const uint64_t d = pre == 1 ? (d_src + 1) / 2 : d_src;       // dimension of the decoded vectors
     const uint32_t tiles = (uint32_t)((d + (1u << kLoBits) - 1) >> kLoBits);
-    hipLaunchKernelGGL(k_dec_lo_last, dim3((tiles + 1) / 2, n), dim3(128), 0, st, B, d, log2D, seed, T);
+    if (n == 1 && pre == 0) {
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo_last<true>), dim3(tiles, 1), dim3(256), 0, st, B, d, log2D, seed, T, scratch, acc, mean_n);
+        return;
+    }
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo_last<false>), dim3(tiles, n), dim3(256), 0, st, B, d, log2D, seed, T, scratch, acc, mean_n);
     if (pre == 2) return;
     const dim3 grid((uint32_t)((d + 255) / 256));                // four values per thread
     if (pre == 1) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo_combine<true>), grid, dim3(64), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);

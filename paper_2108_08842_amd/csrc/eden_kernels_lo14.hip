@@ -1,17 +1,9 @@
-// The 14-bit contiguous passes (gfx950).
+// The contiguous passes for D <= 2^24 (gfx950): the encoder's over 12 or 14 bits, the decoder's over 14.
 //
-// Decode: a workgroup of 16 waves owns 2^14 consecutive coordinates, 16 values per thread (eden_lo.h), or runs ten of the 14 bits on the
-// matrix cores where the values are small integers.  Encode: 8 waves, 32 values per thread, so that the 14 index bits are covered
-// by three groups of in-register butterfly stages:
-//
-//   group 1   bits 9..13   v[a] = coordinate 512 a + 64 wave + lane  (coalesced loads, 256 B per wave load)
-//   exchange  through LDS between all waves (registers <-> bits 4..8)
-//   group 2   bits 4..8
-//   exchange  through LDS inside groups of 16 lanes (registers <-> bits 0..3, bit 4 stays a register bit)
-//   group 3   bits 0..3
-//
-// Afterwards thread t holds the 32 consecutive coordinates 32 t + e, e = 0..31: one half of a 64-bit sign word
-// of the rotation, and one 128-byte line of the workspace.  The encode pass is bound by memory.
+// A workgroup owns 2^12 or 2^14 consecutive coordinates, 16 values per thread (eden_lo.h); where all values of a decode launch are small
+// integers, ten of the 14 bits run on the matrix cores.  The encode pass is bound by memory where a launch fills the chip (16 senders of
+// 11,173,962: 1.43 GB at 6.1 TB/s, 32 values per thread the same) and by the length of a wave's chain where it does not: encode of one
+// sender of 20,000, b = 2 12.9 -> 10.5 us, 8 of 131,072 15.2 -> 13.0 with four waves per 4096 coordinates instead of one.
 #include "eden_device.h"
 #include "eden_kernels.h"
 #include "eden_lo.h"
@@ -19,91 +11,65 @@
 namespace eden {
 
 constexpr int kLo14Bits = 14;
-constexpr int kXaSlab = 8 * 64 + 16;            // words per value of a: 8 waves x 64 lanes, +16 so that the two
-                                                // slabs read by a half-wave fall into different banks
-constexpr int kXbRow = 36;                      // 32 values + 4: rows of consecutive lanes start 4 banks apart
-constexpr int kXbWave = 64 * kXbRow + 48;       // one wave's region of the second exchange
-constexpr int kLo14LdsWords = 8 * kXbWave;      // 75264 bytes; the first exchange needs 32 * kXaSlab words
-static_assert(kLo14LdsWords >= 32 * kXaSlab, "LDS sizing");
-
-// in:  v[a] = coordinate 512 a + 64 wave + lane of the tile
-// out: v[e] = coordinate 512 (t >> 4) + 32 (t & 15) + e, fully transformed over the 14 bits
-__device__ inline void lo14_forward32(float (&v)[32], float *lds) {
-    const uint32_t t = threadIdx.x, lane = t & 63u, wv = t >> 6;
-    fwht_regs<32>(v);                                            // bits 9..13
-#pragma unroll
-    for (int a = 0; a < 32; ++a) lds[a * kXaSlab + wv * 64 + lane] = v[a];
-    __syncthreads();
-    const uint32_t c0123 = t & 15u, a2 = t >> 4;
-#pragma unroll
-    for (int r = 0; r < 32; ++r) v[r] = lds[a2 * kXaSlab + (r >> 2) * 64 + (r & 3) * 16 + c0123];
-    fwht_regs<32>(v);                                            // bits 4..8 (register bit 0 = index bit 4)
-    __syncthreads();                                             // all reads done before the regions are reused
-    float *L = lds + wv * kXbWave;
-    const uint32_t g = lane >> 4;
-#pragma unroll
-    for (int r = 0; r < 32; ++r) L[(g * 16 + (r >> 1)) * kXbRow + g * 16 + (r & 1) * 16 + c0123] = v[r];
-    wave_lds_sync();
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const float4 x = *reinterpret_cast<const float4 *>(&L[lane * kXbRow + g * 16 + 4 * q]);
-        v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
-    }
-    fwht_regs_low<32, 4>(v);                                     // bits 0..3 (bit 4 rides along)
-}
 
 // Encode, first pass: x -> T.  Zero padding (Sec. 5: the transform needs a power of two), the sign diagonal of
-// the rotation from the shared seed (Sec. 2.1), |x|^2 for eta and S (Sec. 2.2.1, 2.3), index bits 0..13 of H.
-// Only the ceil(d / 2^14) tiles that hold part of x (rounded up to whole blocks of rows in the blocked layout) are
-// transformed and written: a tile of padding stays zero under these 14 bits, and the strided pass that follows reads it
+// the rotation from the shared seed (Sec. 2.1), |x|^2 for eta and S (Sec. 2.2.1, 2.3), index bits 0 .. P-1 of H, P = 12 or 14.
+// Only the ceil(d / 2^P) tiles that hold part of x (rounded up to whole blocks of rows in the blocked layout) are
+// transformed and written: a tile of padding stays zero under these bits, and the strided pass that follows reads it
 // as zero through its buffer bounds.
 // PRE (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is x'[g] = 2 x[2g + o_g],
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
-template <bool PRE, bool BLOCKED>
-__global__ __launch_bounds__(512, 4) void k_enc_lo14_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
-                                                        double *partials, uint32_t partial_stride, EncTail tail) {
-    __shared__ __attribute__((aligned(16))) float lds[kLo14LdsWords];
-    __shared__ double red[8];
+template <int P, bool PRE, bool BLOCKED>
+__global__ __launch_bounds__(Lo16<P>::T, 8) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
+                                                             double *partials, uint32_t partial_stride, EncTail tail) {
+    constexpr uint32_t THREADS = Lo16<P>::T, WAVES = THREADS / 64;
+    __shared__ __attribute__((aligned(16))) float lds[Lo16<P>::LDS_FLOATS];
+    __shared__ double red[WAVES];
     const uint32_t c = blockIdx.y, t = threadIdx.x, lane = t & 63u;
     const uint32_t wv = wave_in_block();
     const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));           // reads past d_src give the zero padding
     float *Tc = T + ((size_t)c << log2D);
-    const uint64_t key = stream_key(seed, kStreamSign, B.client[c]);
-    const uint32_t lane_off = (wv * 64u + lane) * 4u;
-    const uint32_t tile = blockIdx.x;                            // one tile per workgroup: two workgroups share a CU, and
-                                                                 // their phases interleave better than two tiles in one
-                                                                 // workgroup with the second one's loads issued early
-    // element 512 a + 64 wave + lane of the tile; with PRE it comes from x[2 i + o_i], and register a of this wave is
-    // 64 consecutive pairs = one word of offsets (lane l < 32 hashes the word of register l)
-    float u[32];
+    const uint32_t tile = blockIdx.x;                            // one tile per workgroup: the phases of two workgroups on a CU
+                                                                 // interleave better than two tiles in one workgroup with the
+                                                                 // second one's loads issued early
+    // element THREADS a + t of the tile: register a of this wave is 64 consecutive coordinates = one sign word; lane l hashes
+    // the word of register l % 16.  With PRE it comes from x[2 i + o_i], and the register is 64 pairs = one word of offsets
+    const uint64_t word = ((uint64_t)tile << (P - 6)) + WAVES * (lane & 15u) + wv;
+    float u[16];
     if constexpr (PRE) {
-        const uint64_t prekey = stream_key(seed, kStreamSubsample, B.client[c]);
-        const uint64_t offs = hash_word(prekey, ((uint64_t)tile << (kLo14Bits - 6)) + 8u * (lane & 31u) + wv);
+        const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), word);
 #pragma unroll
-        for (int a = 0; a < 32; ++a) {
+        for (int a = 0; a < 16; ++a) {
             const uint32_t odd = __builtin_amdgcn_inverse_ballot_w64(wave_read64(offs, a)) ? 4u : 0u;
-            u[a] = 2.0f * buf_load(rx, 2u * lane_off + odd, (tile << (kLo14Bits + 3)) + 4096u * a);
+            u[a] = 2.0f * buf_load(rx, 8u * t + odd, (tile << (P + 3)) + 8u * THREADS * a);
         }
     } else {
 #pragma unroll
-        for (int a = 0; a < 32; ++a) u[a] = buf_load(rx, lane_off, (tile << (kLo14Bits + 2)) + 2048u * a);
+        for (int a = 0; a < 16; ++a) u[a] = buf_load(rx, 4u * t, (tile << (P + 2)) + 4u * THREADS * a);
     }
+    const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), word);
     double n2 = 0.0;
 #pragma unroll
-    for (int a = 0; a < 32; ++a) {
+    for (int a = 0; a < 16; ++a) {
         n2 += (double)u[a] * (double)u[a];
         if ((a & 7) == 7) __builtin_amdgcn_sched_barrier(0);     // keeps the widened values of one group live at a time
     }
-    // register a of this wave = 64 consecutive coordinates = one sign word: lane l < 32 hashes the word of
-    // register l, register a reads it back as a lane mask
-    const uint64_t mine = hash_word(key, ((uint64_t)tile << (kLo14Bits - 6)) + 8u * (lane & 31u) + wv);
 #pragma unroll
-    for (int a = 0; a < 32; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;   // + 0: no negative zeros
-    lo14_forward32(u, lds);
-    store_runs<kLo14Bits, BLOCKED>(u, lds + wv * kXbWave, Tc, tile, 64u * wv);
-    const double block_total = block_sum<512>(n2, red);
+    for (int a = 0; a < 16; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;   // + 0: no negative zeros
+    lo_forward16<P>(u, lds);
+    // whole lines: lane l holds coordinates 4 (64 j + l) .. + 3 of the wave's 1024.  BLOCKED: the 128-byte segments of kBlockRows
+    // consecutive rows are interleaved (see blocked_offset).  (Write-back stores: with the streaming hint this pass ran 13% slower; the pass
+    // that reads the tiles back does better with the hint on its loads.)
+    float4 x[4];
+    wave_quads(u, lds + wv * (Lo16<P>::LDS_FLOATS / WAVES), x);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t at = 1024u * wv + 256u * (uint32_t)j + 4u * lane;
+        *reinterpret_cast<float4 *>(Tc + (BLOCKED ? blocked_offset<P>(tile, at >> 5) + (at & 31u) : ((size_t)tile << P) + at)) = x[j];
+    }
+    const double block_total = block_sum<(int)THREADS>(n2, red);
     if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
-    enc_first_side<512>(tail, c, B.b_q8[c]);
+    enc_first_side<(int)THREADS>(tail, c, B.b_q8[c]);
 }
 
 // Decode, last pass: index bits 0..13 of H for every sender, that sender's sign diagonal (R^-1 = s o D^-1/2 H,
@@ -528,19 +494,20 @@ __global__ __launch_bounds__(256) void k_dec_lo14_combine(float *acc, uint64_t d
         if (i + e < d) acc[i + e] = s[e] / div;
 }
 
-uint32_t launch_enc_lo14_first(const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int blocked, int log2D, uint64_t seed, float *T,
-                               double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st) {
+uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int blocked, int log2D, uint64_t seed, float *T,
+                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st) {
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
-    uint32_t tiles = (uint32_t)((d + (1u << kLo14Bits) - 1) >> kLo14Bits);
+    uint32_t tiles = (uint32_t)((d + (1u << P) - 1) >> P);
     // blocked layout: whole blocks of rows are written (a tile beyond d reads zeros and stores zeros), so that the strided
     // pass finds no unwritten row inside a block
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
-#define EDEN_ENC_LO14(PRE, BLK) \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo14_first<PRE, BLK>), grid, dim3(512), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
-    if (pre) { if (blocked) EDEN_ENC_LO14(true, true); else EDEN_ENC_LO14(true, false); }
-    else { if (blocked) EDEN_ENC_LO14(false, true); else EDEN_ENC_LO14(false, false); }
-#undef EDEN_ENC_LO14
+#define EDEN_ENC_LO(P, PRE, BLK) \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, PRE, BLK>), grid, dim3(Lo16<P>::T), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
+    if (P == 12) { if (pre) EDEN_ENC_LO(12, true, false); else EDEN_ENC_LO(12, false, false); }
+    else if (pre) { if (blocked) EDEN_ENC_LO(14, true, true); else EDEN_ENC_LO(14, true, false); }
+    else { if (blocked) EDEN_ENC_LO(14, false, true); else EDEN_ENC_LO(14, false, false); }
+#undef EDEN_ENC_LO
     return grid.x;
 }
 void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,

@@ -21,8 +21,9 @@ struct Lo16 {
     static_assert(B == 12 || B == 14, "tiles that exist");
     static constexpr int T = 1 << (B - 4);                       // threads
     // floats between the LDS rows of two values of a.  B = 14: a row becomes one wave's 16 rows of 64 + 4 in exchange 2.  B = 12: four rows
-    // become its 4 x 16 rows of 16 + 4, and 336 = 16 (mod 64) keeps the four apart in the banks.
-    static constexpr int ROW = B == 14 ? 16 * 68 : 336;
+    // become its 4 x 16 rows of 16 (quads swizzled by the row instead of padding, so that eight workgroups fit a CU), and 272 = 16
+    // (mod 64) keeps the four apart in the banks.
+    static constexpr int ROW = B == 14 ? 16 * 68 : 272;
     static constexpr int LDS_FLOATS = 16 * ROW;
 };
 
@@ -69,11 +70,11 @@ __device__ inline void lo_forward16(float (&v)[16], float *lds) {
         fwht_regs<16>(v);
         wave_lds_sync();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[a2 * L::ROW + 20 * r + low] = v[r];
+        for (int r = 0; r < 16; ++r) mine[a2 * L::ROW + 16 * r + (low ^ (uint32_t)(4 * (r >> 2)))] = v[r];
         wave_lds_sync();
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const float4 x = *reinterpret_cast<const float4 *>(&mine[a2 * L::ROW + low * 20u + 4 * q]);
+            const float4 x = *reinterpret_cast<const float4 *>(&mine[a2 * L::ROW + 16u * low + 4u * ((uint32_t)q ^ (low >> 2))]);
             v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
         }
         fwht_regs<16>(v);
