@@ -575,7 +575,12 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             // Strided pass first (every sender on its own), contiguous pass last (sums the senders in registers
             // and touches acc once).  The workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).
             // (at D <= 2^18 the last pass works in place, one sender at a time: the same integers as fp32)
-            const int narrow = (pre == 2 || pl.wide) ? 0 : pl.lo_bits == 12 ? 2 : 1;
+            // m-of-64 senders (pre == 2) end up in fp32 slots from the start of the workspace; where it has room for their fp16 slots
+            // behind those, they too go through the matrix cores (whole decode, 16 senders of 11,173,962, m = 6 151 -> 143 us; 8 of
+            // them, m = 32 174 -> 137)
+            const bool behind = pre == 2 && pl.lo_bits == 14 && ((uint64_t)2 * nb << log2D) <= (uint64_t)ctx->slots * ctx->slot_floats;
+            float *const work = behind ? ctx->T + ((size_t)nb << log2D) : ctx->T;
+            const int narrow = ((pre == 2 && !behind) || pl.wide) ? 0 : pl.lo_bits == 12 ? 2 : 1;
             bool coins = false;                                  // the receiver draws and counts the same coins
             for (uint32_t i = 0; i < nb; ++i) coins = coins || coin_q8(B.b_q8[i]);
             if (coins) launch_coin_tables(B.client, B.b_q8, nullptr, nb, seed, log2D, ctx->coin, st);
@@ -590,10 +595,10 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             {
                 Timed t(ctx, EDEN_K_DEC_FIRST, nb, st);
                 if (pl.wide) launch_dec_wide_first(B, nb, round_up(d, 14 + pl.M), log2D, ctx->dec_scratch, ctx->T, st);
-                else if (pl.wg) launch_dec_hix_first(pl.M, pl.lo_bits, B, nb, d, log2D, seed, ctx->dec_scratch, narrow, ctx->T, ctx->coin,
+                else if (pl.wg) launch_dec_hix_first(pl.M, pl.lo_bits, B, nb, d, log2D, seed, ctx->dec_scratch, narrow, work, ctx->coin,
                                                 first_prepares ? &prep : nullptr, ctx->compute_units, st);
                 // what the last pass reads: whole tiles of it that hold part of the first d coordinates
-                else launch_dec_hi_first(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, prep, narrow, ctx->T,
+                else launch_dec_hi_first(pl.M, B, nb, round_up(d, pl.lo_bits), log2D, pl.lo_bits, seed, prep, narrow, work,
                                          ctx->coin, st);
             }
             if (pl.wide) {
@@ -604,7 +609,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             if (pl.lo_bits >= 15)
                 launch_dec_lo15_last(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, acc_dev, mean_n, st);
             else if (pl.lo_bits == 14)
-                launch_dec_lo14_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, narrow, acc_dev, 2 * ctx->compute_units,
+                launch_dec_lo14_last(B, nb, d_src, pre, log2D, seed, work, ctx->dec_scratch, narrow, acc_dev, ctx->T, 2 * ctx->compute_units,
                                      ctx->dec_partial, ctx->dec_partial_tiles, mean_n, st);
             else launch_dec_lo_last(B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, acc_dev, mean_n, st);
         }

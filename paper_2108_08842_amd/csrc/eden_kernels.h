@@ -95,8 +95,9 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d, i
 // `resident`: workgroups of the kernel the device holds at once (2 per CU); `partial`: room for `partial_tiles`
 // tiles of 2^14 floats, used when tiles are split over several workgroups by sender.
 // `mean_n` > 0 (pre == 0 only): acc is not read; acc[i] = (0 + the sum over the senders) / mean_n
-void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
-                          const DecScratch *scratch, int narrow, float *acc, uint32_t resident, float *partial,
+// pre == 2: sender c's decoded vector goes to out + (c << log2D); that may be T itself unless `narrow` (fp16 slots)
+void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, const float *T,
+                          const DecScratch *scratch, int narrow, float *acc, float *out, uint32_t resident, float *partial,
                           uint32_t partial_tiles, float mean_n, hipStream_t st);
 
 // 15- and 16-bit contiguous passes for D = 2^25 .. 2^27 (eden_kernels_lo15.hip): the encoder's always writes the blocked layout,

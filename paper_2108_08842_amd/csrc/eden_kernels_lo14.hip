@@ -83,9 +83,9 @@ __global__ __launch_bounds__(Lo16<P>::T, 8) void k_enc_lo_first(EncBatch B, uint
 // group k > 0 stores its sum in partial[k-1][tile - full_tiles][2^14]; k_dec_lo14_combine then adds those to
 // acc in the order k = 1, 2, ... (fixed, so the result does not depend on scheduling).
 //
-// `separate`: K = n, one sender per workgroup, nothing is summed: every sender's decoded tile is written back into its own
-// workspace slot (`partial` is then the workspace; fp32, in place: the workgroup has read the tile before it writes
-// it), for a caller that puts the values elsewhere afterwards.
+// `separate`: K = n, one sender per workgroup, nothing is summed: every sender's decoded tile goes to its slot of `partial`, for a
+// caller that puts the values elsewhere afterwards (fp32 slots: possibly the workspace itself, in place; the workgroup has
+// read the tile before it writes it).
 // WIDE_ONLY: no sender of the launch has an fp16 slot (every b > 1): the instance without that branch in the sender loop.
 // AHEAD: the values of sender c + 1 are on their way while those of sender c are transformed, for the launches that do not split
 // tiles (whole decode at b = 4, us, with / without: 4 senders of 11,173,962 92 / 95, 16 298 / 305; with split tiles the other workgroup
@@ -213,7 +213,7 @@ __device__ inline float minus_half(float x, uint32_t packed) {
 __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint32_t n, uint64_t d, int log2D, uint64_t seed,
                                                                const float *T, const DecScratch *scratch, float *acc,
                                                                uint32_t full_tiles, uint32_t K, uint32_t split_tiles,
-                                                               float *partial, float mean_n) {
+                                                               float *partial, int separate, float mean_n) {
     __shared__ __attribute__((aligned(16))) float lds[1 << kLo14Bits];
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block(), h = lane >> 5, m = lane & 31u;
     uint32_t tile = blockIdx.x, c_begin = 0, c_end = n;
@@ -223,7 +223,8 @@ __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint3
         tile = full_tiles + idx / K;
         c_begin = (uint32_t)(((uint64_t)n * k) / K);
         c_end = (uint32_t)(((uint64_t)n * (k + 1)) / K);
-        if (k > 0) part = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits);
+        if (separate) part = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits);
+        else if (k > 0) part = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits);
     }
     const uint64_t tile_base = (uint64_t)tile << kLo14Bits;
 
@@ -482,16 +483,33 @@ __global__ __launch_bounds__(256) void k_dec_lo14_combine(float *acc, uint64_t d
     const uint64_t i = ((uint64_t)full_tiles << kLo14Bits) + local;
     if (local >= ((uint64_t)split_tiles << kLo14Bits) || i >= d) return;
     float s[4];
+    const bool whole = i + 4 <= d;                               // (acc is 16-byte aligned)
+    if (whole) {
+        const float4 a = *reinterpret_cast<const float4 *>(acc + i);
+        s[0] = a.x; s[1] = a.y; s[2] = a.z; s[3] = a.w;
+    } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] = (i + e < d) ? acc[i + e] : 0.0f;
-    for (uint32_t k = 1; k < K; ++k) {
-        const float4 p = *reinterpret_cast<const float4 *>(partial + (((size_t)(k - 1) * split_tiles) << kLo14Bits) + local);
-        s[0] += p.x; s[1] += p.y; s[2] += p.z; s[3] += p.w;
+        for (int e = 0; e < 4; ++e) s[e] = (i + e < d) ? acc[i + e] : 0.0f;
+    }
+    // eight groups' loads on their way at a time: one after the other they took most of the kernel (whole decode, 8 senders of 300,007,
+    // b = 2, 23.7 -> 22.9 us; of 4,000,037 at 2.7 bits 120.6 -> 118.3)
+    for (uint32_t k0 = 1; k0 < K; k0 += 8) {
+        float4 p[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j)
+            if (k0 + j < K) p[j] = *reinterpret_cast<const float4 *>(partial + (((size_t)(k0 + j - 1) * split_tiles) << kLo14Bits) + local);
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j)
+            if (k0 + j < K) { s[0] += p[j].x; s[1] += p[j].y; s[2] += p[j].z; s[3] += p[j].w; }
     }
     const float div = mean_n > 0.0f ? mean_n : 1.0f;
+    if (whole) {
+        *reinterpret_cast<float4 *>(acc + i) = make_float4(s[0] / div, s[1] / div, s[2] / div, s[3] / div);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (i + e < d) acc[i + e] = s[e] / div;
+        for (int e = 0; e < 4; ++e)
+            if (i + e < d) acc[i + e] = s[e] / div;
+    }
 }
 
 uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int blocked, int log2D, uint64_t seed, float *T,
@@ -510,8 +528,8 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
 #undef EDEN_ENC_LO
     return grid.x;
 }
-void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
-                          const DecScratch *scratch, int narrow, float *acc, uint32_t resident, float *partial,
+void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, const float *T,
+                          const DecScratch *scratch, int narrow, float *acc, float *out, uint32_t resident, float *partial,
                           uint32_t partial_tiles, float mean_n, hipStream_t st) {
     const uint64_t d = pre == 1 ? (d_src + 1) / 2 : d_src;       // dimension of the decoded vectors
     const uint32_t tiles = (uint32_t)((d + (1u << kLo14Bits) - 1) >> kLo14Bits);     // tiles that reach below d
@@ -519,9 +537,13 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
         hipLaunchKernelGGL(k_dec_lo14_last_pairs, dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
         return;
     }
-    if (pre == 2) {                                              // every sender on its own, back into its workspace slot
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<true, false>), dim3(tiles * n), dim3(1024), 0, st, B, n, d_src, log2D, seed,
-                           T, scratch, 0, acc, 0u, n, tiles, T, 1, 0.0f);
+    if (pre == 2) {                                              // every sender on its own, into its slot of `out`
+        if (narrow)
+            hipLaunchKernelGGL(k_dec_lo14_last_mfma, dim3(tiles * n), dim3(512), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, 0u, n, tiles,
+                               out, 1, 0.0f);
+        else
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo14_last<true, false>), dim3(tiles * n), dim3(1024), 0, st, B, n, d_src, log2D, seed,
+                               T, scratch, 0, acc, 0u, n, tiles, out, 1, 0.0f);
         return;
     }
     bool all16 = narrow != 0;                                    // every sender's workspace slot holds fp16
@@ -546,7 +568,7 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
     dim3 grid(full + rest * K);
     if (all16)                                                   // |values| <= 2^10: ten of the bits on the matrix cores
         hipLaunchKernelGGL(k_dec_lo14_last_mfma, grid, dim3(512), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, full, K, rest,
-                           partial, mean_n);
+                           partial, 0, mean_n);
     else {
         bool none16 = true;                                      // no sender with an fp16 slot
         for (uint32_t c = 0; c < n; ++c) none16 = none16 && !(narrow && B.b_q8[c] <= 256u);
