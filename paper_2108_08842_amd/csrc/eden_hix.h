@@ -36,8 +36,7 @@ struct HiX {
 // neighbouring 64..128-byte pieces of the same rows (and, in decode, the same 64-byte sectors of the payload),
 // so runs of 16 consecutive tiles are kept on one XCD.
 template <int RUN = 16>
-__device__ inline uint32_t xcd_local_tile() {
-    uint32_t tile = blockIdx.x;
+__device__ inline uint32_t xcd_local_tile(uint32_t tile = blockIdx.x) {
     if (gridDim.x % (8u * RUN) == 0) {
         const uint32_t xcd = tile & 7u, q = tile >> 3;
         tile = ((q / RUN) * 8u + xcd) * RUN + (q % RUN);
@@ -54,6 +53,33 @@ __device__ inline uint32_t align_runs_to_lines(uint32_t tile, uint32_t cb_bits, 
     const uint32_t shift = (uint32_t)(reinterpret_cast<uintptr_t>(payload) / row_bytes) & (per_line - 1u);
     const uint32_t mask = (1u << cb_bits) - 1u;
     return (tile & ~mask) | ((tile - shift) & mask);
+}
+
+// Decode: the payload of a workgroup that starts later on this XCD, brought into its L2 while this one computes.  Every workgroup of a
+// first decode pass begins with a read of 2^M short pieces of the payload and can do nothing else until they are there; messages
+// that have just arrived lie in memory, and a run of 16 tiles (which share the lines) waited for them together.  The 16
+// workgroups of a run each read a word of 1/16 of the lines of the run 2^18 threads further on, about as many as the chip holds at a time.
+// The word is not used; the caller keeps it in a register until its own stores are out, so that nothing waits for it.
+// Mean of 16 senders of 11,173,962 on changing messages: b = 1 184.0 -> 170.0 us (the pass 93 -> 77), b = 4 400 -> 333, b = 2 307 -> 302;
+// of 8 of 2^25, b = 4 586 -> 541, b = 1 363 -> 316; of 8 of 2^27, b = 4 the pass 1354 -> 1225; where an encode has just left the messages in the memory-side cache
+// nothing is gained or lost (a round of 16 of 11,173,962, b = 4 755 -> 755).  Behind the first butterflies, where more registers are in
+// use, the read cost spills (b = 4 346).
+// (Every read is inside that sender's payload: rows below 2^M, tiles below TILES.)
+// THREADS: of a workgroup; TILES: per sender, a multiple of 128; `row_bytes`: payload bytes of one tile row.
+template <uint32_t THREADS, int M, uint32_t TILES>
+__device__ inline uint32_t touch_payload_ahead(const DecBatch &B, uint32_t row_bytes) {
+    constexpr uint32_t kAhead = (1u << 18) / THREADS, kRows = (1u << M) / 16u;
+    static_assert(TILES % 128u == 0, "runs of 16 tiles on each of 8 XCDs, see xcd_local_tile");
+    const uint32_t x = blockIdx.x + kAhead, c = blockIdx.y + x / TILES;
+    const uint32_t per_row = row_bytes > 8u ? 2u : 1u;           // lines of a payload row that a run of 16 tiles shares
+    if (c >= gridDim.y || wave_in_block() * 64u >= kRows * per_row || threadIdx.x >= kRows * per_row) return 0u;
+    if (B.b_q8[c] != B.b_q8[blockIdx.y]) return 0u;              // `row_bytes` would not be that sender's
+    const char *payload = static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES;
+    const uint32_t q = (x % TILES) >> 3, run = (q / 16u) * 8u + (x & 7u);
+    const uint32_t row = (q % 16u) * kRows + threadIdx.x / per_row;
+    uint32_t tile = run * 16u + threadIdx.x % per_row * 8u;
+    if ((row_bytes & (row_bytes - 1u)) == 0u) tile = align_runs_to_lines(tile, (uint32_t)__builtin_ctz(TILES), payload, row_bytes);
+    return *reinterpret_cast<const volatile uint32_t *>(payload + ((size_t)row * TILES + tile) * row_bytes);
 }
 
 template <int M>
