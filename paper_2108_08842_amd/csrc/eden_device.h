@@ -397,6 +397,21 @@ __device__ inline uint32_t quantize_one(float u, const Thresholds &th, const flo
     return neg ? (uint32_t)(H - 1) - mag : (uint32_t)H + mag;
 }
 
+// b = 2: the indices of 16 values side by side in one word, value i in bits 2 i, 2 i + 1.  Index = (2 | magnitude) with both bits turned
+// over where the value is negative: 7 instructions a value, no read of the table; sums in the order of quantize_one.
+__device__ inline uint32_t quantize_two_bits(const float *u, float thr1, float q0, float q1, float &ip) {
+    uint32_t mags = 0xAAAAAAAAu, signs = 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const bool outer = fabsf(u[i]) > thr1;
+        ip = fmaf(fabsf(u[i]), outer ? q1 : q0, ip);
+        mags |= outer ? 1u << (2 * i) : 0u;
+        const uint32_t mask = 3u << (2 * i);
+        signs = (signs & ~mask) | ((uint32_t)(__float_as_int(u[i]) >> 31) & mask);
+    }
+    return mags ^ signs;
+}
+
 // The same search in one guess and one compare, for kernels that spend their time on it (16 levels: fourteen instructions above).
 // The number of a Lloyd-Max threshold is nearly a quadratic function of its value: with r(t) = t (1 + c3 |t|), t = u c1, through
 // thresholds H / 2 and H - 1, r differs from the number of every other threshold of I_4 by less than 0.07.  The threshold with the

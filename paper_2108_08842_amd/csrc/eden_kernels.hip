@@ -65,6 +65,36 @@ __device__ inline void store_row_planes(const uint32_t (&plane)[4][2], uint32_t 
     }
 }
 
+// b = 2 and 4 (R >= 32 / K rows): instead of the ballots a lane collects the indices of 32 / K rows of its column in a word, and the
+// lanes of as many neighbouring columns transpose their words: each then holds one payload word of one row.  `base`: first
+// coordinate of the tile.  With the ballots (four v_writelane and two compares a value at b = 2, eight and four at b = 4) the pass was half
+// packing: encode of 10 senders of 2^20, b = 2 33.0 -> 31.4 us, b = 4 40.5 -> 34.7 (with the search by a guess; 38.4 without), one of them
+// 19.3 -> 17.0, 32 with 1/2, 1, 2 and 4 bits 82.3 -> 77.6.  From 32 rows on: below, the launch is too short for it to show (16 of 30,000,
+// b = 4 14.6 us, with the guess, which takes a barrier more, 15.5).
+template <int R, int K>
+__device__ inline void hi_quantize_transpose(const float (&v)[R], const EncScratch &es, const RankGuess<8> &guess, uint64_t base, int p,
+                                             uint32_t *payload, float &ip) {
+    constexpr int PER = 32 / K;
+    static_assert((K == 2 || K == 4) && R >= PER, "whole words");
+    const uint32_t lane = lane_id(), j = lane & (uint32_t)(PER - 1), q = lane / (uint32_t)PER;
+    const float thr1 = uniform(es.thr[1]), q0 = uniform(es.qpos[0]), q1 = uniform(es.qpos[1]);
+    static_for<R / PER>([&](auto B) {
+        constexpr int first = decltype(B)::value * PER;
+        uint32_t items;
+        if constexpr (K == 2) {
+            items = quantize_two_bits(&v[first], thr1, q0, q1, ip);
+        } else {
+            uint32_t at[PER];
+            items = 0u - 0x11111111u;                            // index + 1 in every place; a sum, so that 16 may carry in between
+            quantize_guess<8>(&v[first], guess, &es, at, ip);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) items += at[i] << (K * i);
+        }
+        items = transpose_items<K>(items, lane);
+        payload[((base + ((uint64_t)(first + j) << p)) >> (K == 2 ? 4 : 3)) + q] = items;
+    });
+}
+
 // Quantizes the R rows of a wave tile (register r = row r, one column per lane) and packs them.  K: bits of every
 // index in the first part of the payload.  MIX = 1 (b = K + 1/2, Sec. 4.1): the coordinate of every pair that the MIX
 // stream selects is quantized with I_{K+1}; the top bit of its index goes to the second part, one bit per pair.
@@ -133,6 +163,8 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
     __shared__ double red[4];
     __shared__ uint32_t last_flag;
     __shared__ EncScratch es;
+    constexpr bool GUESS = M >= 5 && (ONLY == 0u || ONLY == 1024u);
+    __shared__ RankGuess<8> guess;                               // b = 4: the interval search by a guess and one compare
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id();
     const uint32_t tile = blockIdx.x * 4u + wave_in_block();     // (2^(p-6) tiles: a multiple of 4)
@@ -152,6 +184,16 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
         // (the butterflies stand behind the norm's branch: in front of it the compiler moves half of them into it, and holds 138 registers)
         const bool valid = enc_valid_norm(es.n2);
         if (valid) fwht_regs<R>(v);
+        if constexpr (GUESS) {
+            if (b_q8 == 1024u) {
+                fill_rank_guess<8>(guess, &es, threadIdx.x);
+                if (es.guess_up != 1.0f) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) v[r] *= es.guess_up;
+                }
+                __syncthreads();
+            }
+        }
         uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
         const uint64_t my_row = base + ((uint64_t)(lane & (R - 1)) << p);       // lane r < R finishes row r
         if (!valid) {
@@ -217,15 +259,23 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
             } else
             switch (b_q8) {
                 case 384u: hi_quantize_pack<R, 1, 1>(v, sc, qtab, mixkey, my_row, payload, part_b, ip); break;
-                case 512u: hi_quantize_pack<R, 2, 0>(v, sc, qtab, mixkey, my_row, payload, part_b, ip); break;
+                case 512u:
+                    if constexpr (M >= 5) hi_quantize_transpose<R, 2>(v, es, guess, base, p, payload, ip);
+                    else hi_quantize_pack<R, 2, 0>(v, sc, qtab, mixkey, my_row, payload, part_b, ip);
+                    break;
                 case 640u: hi_quantize_pack<R, 2, 1>(v, sc, qtab, mixkey, my_row, payload, part_b, ip); break;
                 case 768u: hi_quantize_pack<R, 3, 0>(v, sc, qtab, mixkey, my_row, payload, part_b, ip); break;
                 case 896u: hi_quantize_pack<R, 3, 1>(v, sc, qtab, mixkey, my_row, payload, part_b, ip); break;
-                default: hi_quantize_pack<R, 4, 0>(v, sc, qtab, mixkey, my_row, payload, part_b, ip); break;
+                default:
+                    if constexpr (GUESS) hi_quantize_transpose<R, 4>(v, es, guess, base, p, payload, ip);
+                    else hi_quantize_pack<R, 4, 0>(v, sc, qtab, mixkey, my_row, payload, part_b, ip);
+                    break;
             }
         }
     }
-    const double block_total = block_sum<256>((double)ip, red);
+    double ip_sum = (double)ip;
+    if (GUESS && b_q8 == 1024u) ip_sum /= (double)es.guess_up;
+    const double block_total = block_sum<256>(ip_sum, red);
     enc_last_tail<256>(tail, B, c, log2D, seed, es.n2, block_total, partials + (size_t)c * partial_stride, &last_flag);
 }
 

@@ -25,10 +25,12 @@ __device__ inline uint32_t hix_word_row(int ph, int w) {
 // second part of the payload, one bit per pair = 16 bits per row segment of a tile.  MIX = 2 (coin budgets, Sec. 4.1):
 // the coordinates with a coin use I_{BITS+1}; their top bits go to the second part (`part_c`) in coordinate order, at the
 // place the prefix sums over the coins give the row segment.
-// TRANSPOSE (BITS = 4, MIX = 0): instead of the ballots, a lane collects the indices of eight registers (rows) of its
-// column in one word, and the lanes of eight neighbouring columns transpose their words: each then holds one payload word of
-// one row.  2 instructions per register instead of 12, but more code: only the kernel instance whose senders all have b = 4
-// uses it (in the instance shared by all budgets it raised the register spills and cost b = 2 a quarter of its speed).
+// TRANSPOSE (BITS = 2 or 4, MIX = 0): instead of the ballots, a lane collects the indices of 16 or eight registers (rows) of its
+// column in one word, and the lanes of as many neighbouring columns transpose their words: each then holds one payload word of
+// one row.  2 instructions per register instead of 12 (b = 4), but more code: only the kernel instances whose senders all have that
+// budget use it (in the instance shared by all budgets it raised the register spills and cost b = 2 a quarter of its speed).  Encode
+// at b = 2 with the instance of its own: 8 senders of 10^8 2960 -> 2399 us, 16 of 11,173,962 424 -> 408, 8 of 4,000,037 78.1 -> 74.4, one of
+// 1,500,000 20.9 -> 18.8.
 template <int M, int P, int BITS, int MIX, bool TRANSPOSE = false>
 __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph, const EncScratch *sc, const float *qtab,
                                          uint32_t *payload, uint16_t *part_b, uint64_t mixkey, uint64_t base, float &ip,
@@ -41,15 +43,22 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
     const uint32_t lane = lane_id(), col = lane & 31u;
     const uint32_t word0 = (uint32_t)(base >> 5);
     if constexpr (TRANSPOSE) {
-        static_assert(MIX == 0 && BITS == 4, "one nibble per coordinate");
+        static_assert(MIX == 0 && (BITS == 2 || BITS == 4), "words of whole indices");
         constexpr int PER = 32 / BITS;
         const uint32_t g = threadIdx.x >> 5, j = col & (uint32_t)(PER - 1), q = col / (uint32_t)PER;
+        const float thr1 = sc->thr[1], q0 = sc->qpos[0], q1 = sc->qpos[1];
         static_for<X::RP / PER>([&](auto K) {
             constexpr int k = decltype(K)::value;
-            uint32_t at[PER], items = 0u - 0x11111111u;          // index + 1 in every place; a sum, so that 16 may carry in between
-            quantize_guess<H>(&out[PER * k], *guess, sc, at, ip);
+            uint32_t items;
+            if constexpr (BITS == 2) {
+                items = quantize_two_bits(&out[PER * k], thr1, q0, q1, ip);
+            } else {
+                uint32_t at[PER];
+                items = 0u - 0x11111111u;                        // index + 1 in every place; a sum, so that 16 may carry in between
+                quantize_guess<H>(&out[PER * k], *guess, sc, at, ip);
 #pragma unroll
-            for (int i = 0; i < PER; ++i) items += at[i] << (BITS * i);
+                for (int i = 0; i < PER; ++i) items += at[i] << (BITS * i);
+            }
             items = transpose_items<BITS>(items, lane);
             const uint32_t row = hix_row2<M>(g, ph, (int)(PER * k + j));
             payload[(uint32_t)BITS * (word0 + (row << (p - 5))) + q] = items;
@@ -329,6 +338,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
                 else if (MODE == 2 && b_q8 == 384u) EDEN_HIX_PACK(1, 1);
                 else if (MODE == 2 && b_q8 == 640u) EDEN_HIX_PACK(2, 1);
                 else if (MODE == 2 && b_q8 == 896u) EDEN_HIX_PACK(3, 1);
+                else if (ONLY == 512u) hix_quantize_pack<M, P, 2, 0, true>(out, ph, sc, qtab, payload, part_b, mixkey, base, ip, ct, c, log2D, part_c);
                 else if (b_q8 == 512u) EDEN_HIX_PACK(2, 0);
                 else if (b_q8 == 768u) EDEN_HIX_PACK(3, 0);
                 else EDEN_HIX_PACK(4, 0);
@@ -450,9 +460,8 @@ uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint3
     // every other launch: one tile per workgroup (with the blocked workspace two tiles per workgroup are slower at every size:
     // 16 senders at D = 2^23, 0.151 -> 0.142 ms at b = 2, 0.34 -> 0.18 ms at b = 1.5, 0.255 -> 0.144 ms for the b = 4 instance)
     dim3 grid(tiles, n);
-    // One budget for all senders: b = 3 and the budgets k + 1/2 have instances that hold only their branch (16 senders at D = 2^24,
-    // against shared instances that still spilled: 0.40 -> 0.24 ms at b = 1.5, 0.277 -> 0.253 ms at b = 3; at b = 2 such an instance
-    // gained nothing).
+    // One budget for all senders: b = 2, 3 and the budgets k + 1/2 have instances that hold only their branch (16 senders at D = 2^24,
+    // against shared instances that still spilled: 0.40 -> 0.24 ms at b = 1.5, 0.277 -> 0.253 ms at b = 3; b = 2: see hix_quantize_pack).
     uint32_t same = B.b_q8[0];
     for (uint32_t c = 1; c < n; ++c) if (B.b_q8[c] != same) same = 0;
 #define EDEN_ENC_HIX_ONLY(MODE, ONLY)                                                                                         \
@@ -464,6 +473,7 @@ uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint3
                                               0, st, B, d, log2D, seed, T, partials, partial_stride, scratch, ct))            \
     }
     if (four) { EDEN_ENC_HIX_LAST(1, 3); }
+    else if (same == 512u) { EDEN_ENC_HIX_ONLY(1, 512u); }
     else if (same == 768u) { EDEN_ENC_HIX_ONLY(1, 768u); }
     else if (same == 384u) { EDEN_ENC_HIX_ONLY(2, 384u); }
     else if (same == 640u) { EDEN_ENC_HIX_ONLY(2, 640u); }

@@ -930,3 +930,34 @@ def test_m_of_64_decode_with_and_without_room_for_fp16_slots(m, d, n):
     roomy.close()
     if tight:
         tight.close()
+
+
+@pytest.mark.parametrize("d", [(1 << 17) - 5, 1 << 18, 300_001, 1 << 20])
+@pytest.mark.parametrize("b_q8", [512, 1024])
+def test_indices_of_wave_tiles_do_not_depend_on_the_scale(ctx, d, b_q8):
+    # three spikes whose sums are exact: every value, threshold and sum scales with a power of two, down to where the interval search of
+    # four bits has to multiply its values first; the same payload, <R(x),Q> scaled
+    x = torch.zeros(d, device="cuda")
+    x[0], x[d // 2], x[d - 1] = 1.0, -0.75, 0.5
+    want = ctx.encode([x], [5], [b_q8], 99)[0]
+    for k in (-125, -60, 60):
+        got = ctx.encode([x * 2.0 ** k], [5], [b_q8], 99)[0]
+        assert torch.equal(got[64:], want[64:]), k
+        ip = [float(m[48:56].cpu().numpy().view(np.float64)[0]) for m in (got, want)]
+        assert ip[0] == ip[1] * 2.0 ** k, k
+    assert ctx.last_device_status() == 0
+
+
+@pytest.mark.parametrize("d", [1_100_000, (1 << 22) - 3, 5_000_001, (1 << 24) - 1, (1 << 24) + 1, (1 << 25) + 1])
+def test_two_bit_launches_write_what_the_shared_kernel_writes(d):
+    # 7 to 11 strided bits: a launch of b = 2 alone packs through lane transposes, one with another budget beside it through ballots
+    from paper_2108_08842_amd import eden
+    c = eden.Context(d_max=d, n_max=2, device=0)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    xs = [torch.randn(d, generator=gen, device="cuda") for _ in range(2)]
+    alone = c.encode(xs, [1, 2], [512, 512], 7)
+    for other in (256, 768):
+        beside = c.encode(xs, [1, 2], [512, other], 7)
+        assert torch.equal(alone[0], beside[0]), other
+    assert c.last_device_status() == 0
+    c.close()
