@@ -140,6 +140,15 @@ __device__ inline void hix_exchange(const float (&v)[64], float *lds, float (&ou
     hix_exchange_read<M>(lds, out);
 }
 
+// ONLY of the kernels next to the payload, beside a budget: every sender of the launch has a coin budget k + f with this k
+constexpr uint32_t kCoinOnly = 0xC000u;          // + k
+static inline uint32_t coin_floor_of_all(const uint32_t *b_q8, uint32_t n) {     // 0: they differ, or some budget is of another kind
+    const uint32_t k = coin_q8(b_q8[0]) >> 8;
+    for (uint32_t c = 1; c < n; ++c)
+        if (coin_q8(b_q8[c]) >> 8 != k) return 0u;
+    return k;
+}
+
 static inline uint32_t hix_tiles(int M, int log2D) { return 1u << (log2D - M - 5); }
 
 // the plans that exist: M bits on top of a contiguous pass over P bits (D = 2^(P+M))

@@ -42,8 +42,8 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
     constexpr int NW = X::RP / 32;                               // registers come in blocks of 32 = one word lane each
     const uint32_t lane = lane_id(), col = lane & 31u;
     const uint32_t word0 = (uint32_t)(base >> 5);
-    if constexpr (TRANSPOSE) {
-        static_assert(MIX == 0 && (BITS == 2 || BITS == 4), "words of whole indices");
+    if constexpr (TRANSPOSE && MIX == 0) {
+        static_assert(BITS == 2 || BITS == 4, "words of whole indices");
         constexpr int PER = 32 / BITS;
         const uint32_t g = threadIdx.x >> 5, j = col & (uint32_t)(PER - 1), q = col / (uint32_t)PER;
         const float thr1 = sc->thr[1], q0 = sc->qpos[0], q1 = sc->qpos[1];
@@ -83,6 +83,7 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
             coin_off[w] = coins_before(ct, c, log2D, blk) + (upper ? (uint32_t)__popc(lo32(m64)) : 0u);
         }
     }
+    uint32_t items = 0;                                          // TRANSPOSE: the low bits of 16 registers
     static_for<X::RP>([&](auto S) {
         constexpr int s = decltype(S)::value;
         uint32_t code;
@@ -98,17 +99,27 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
         } else {
             code = quantize_one<H>(out[s], th, qtab, ip);
         }
+        if constexpr (TRANSPOSE && MIX == 2) {
+            items |= (code & 3u) << (2 * (s % 16));
+            if constexpr (s % 16 == 15) {
+                items = transpose_items<2>(items, lane);
+                payload[2u * (word0 + (hix_row2<M>(threadIdx.x >> 5, ph, s - 15 + (int)(col & 15u)) << (p - 5))) + (col >> 4)] = items;
+                items = 0;
+            }
+        } else {
 #pragma unroll
-        for (int b = 0; b < BITS; ++b) {
-            const uint64_t m = __ballot((code >> b) & 1u);
-            plane[b][s / 32] = put_lane<s % 32>(lo32(m), plane[b][s / 32]);
-            plane[b][s / 32] = put_lane<32 + s % 32>(hi32(m), plane[b][s / 32]);
+            for (int b = 0; b < BITS; ++b) {
+                const uint64_t m = __ballot((code >> b) & 1u);
+                plane[b][s / 32] = put_lane<s % 32>(lo32(m), plane[b][s / 32]);
+                plane[b][s / 32] = put_lane<32 + s % 32>(hi32(m), plane[b][s / 32]);
+            }
         }
     });
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const uint32_t word = word0 + (hix_word_row<M>(ph, w) << (p - 5));
-        if constexpr (BITS == 1) {
+        if constexpr (TRANSPOSE) {                               // (stored already)
+        } else if constexpr (BITS == 1) {
             payload[word] = plane[0][w];
         } else if constexpr (BITS == 2) {
             const uint32_t a = plane[0][w], b = plane[1][w];
@@ -211,7 +222,8 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
     constexpr int p = P;
     constexpr int NW = X::RP / 32;
     constexpr bool UNIT = MODE == 0;
-    constexpr bool SHARED = ONLY == 0u && (MODE == 1 || MODE == 2);
+    constexpr uint32_t COIN = ONLY > kCoinOnly && ONLY <= kCoinOnly + 3u ? ONLY - kCoinOnly : 0u;        // its k
+    constexpr bool SHARED = (ONLY == 0u || COIN) && (MODE == 1 || MODE == 2);
     const uint32_t c = blockIdx.y;
     const uint32_t tile0 = xcd_local_tile<16 / TPW>() * TPW;
     const uint32_t col = threadIdx.x & 31u, g = threadIdx.x >> 5;
@@ -219,7 +231,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
     if (BLK) rows_written = (rows_written + kBlockRows - 1u) / kBlockRows * kBlockRows;      // whole blocks of rows are written
     const rsrc_t rt = make_rsrc(T + ((size_t)c << log2D), rows_written << (p + 2));
     uint32_t *payload = reinterpret_cast<uint32_t *>(static_cast<char *>(B.msg[c]) + EDEN_HEADER_BYTES);
-    const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
+    const uint32_t b_q8 = ONLY && !COIN ? ONLY : B.b_q8[c];
     const EncScratch *sc = &scratch[c];
     // stage-1 rows: g + RL r.  Byte offset of (row, column) inside the slot = a per-thread part + a part that is the same for
     // the whole workgroup (row_off(r)) + the tile's column block
@@ -240,7 +252,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
     if constexpr (MODE == 3) fill_rank_guess<8>(guess, sc, threadIdx.x);     // published, like qtab, by the first barrier of the exchange
     if (!UNIT) {
         if (threadIdx.x < 16u) qtab[threadIdx.x] = sc->qpos[threadIdx.x];       // qpos and qpos2 are one run
-        if (byte_budget(b_q8)) {                                 // centroids, then thresholds: one run of 256 floats
+        if (!COIN && byte_budget(b_q8)) {                        // centroids, then thresholds: one run of 256 floats
             const float *byte_tab = sc->grid_c;
             for (uint32_t i = threadIdx.x; i < 256u; i += X::THREADS) gtab[i] = byte_tab[i];
         }
@@ -296,7 +308,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
                 }
                 hix_quantize_pack<M, P, 4, 0, true>(out, ph, sc, qtab, payload, reinterpret_cast<uint16_t *>(payload), mixkey, base, ip, ct,
                                                  c, log2D, payload, &guess);
-            } else if (SHARED && b_q8 <= 256u) {
+            } else if (SHARED && !COIN && b_q8 <= 256u) {
                 uint32_t words[NW];
                 hix_sign_words<M>(out, ip, words);
 #pragma unroll
@@ -305,7 +317,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
                     held[k][X::PH - 1][w] = words[w];
                 }
             }
-            else if (byte_budget(b_q8)) {
+            else if (!COIN && byte_budget(b_q8)) {
                 // uniform grid (Sec. 4.3) or b = 5..8: one byte per coordinate; a row segment of the tile is 32 bytes
                 uint8_t *bytes = (B.codes[c] ? B.codes[c] : reinterpret_cast<uint8_t *>(payload)) + base + col;
                 const float inv = sc->grid_inv;
@@ -332,7 +344,9 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
                 uint32_t *pieces = cq ? reinterpret_cast<uint32_t *>(B.codes[c]) : nullptr;
 #define EDEN_HIX_PACK(BITS, MIX) \
     hix_quantize_pack<M, P, BITS, MIX>(out, ph, sc, qtab, payload, part_b, mixkey, base, ip, ct, c, log2D, part_c, nullptr, pieces)
-                if (cq && ibits == 1) EDEN_HIX_PACK(1, 2);
+                if constexpr (COIN != 0u)
+                    hix_quantize_pack<M, P, (int)COIN, 2, COIN == 2u>(out, ph, sc, qtab, payload, part_b, mixkey, base, ip, ct, c, log2D, part_c, nullptr, pieces);
+                else if (cq && ibits == 1) EDEN_HIX_PACK(1, 2);
                 else if (cq && ibits == 2) EDEN_HIX_PACK(2, 2);
                 else if (cq) EDEN_HIX_PACK(3, 2);
                 else if (MODE == 2 && b_q8 == 384u) EDEN_HIX_PACK(1, 1);
@@ -346,7 +360,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
             }
         }
     }
-    if (UNIT || (MODE != 3 && b_q8 <= 256u)) {
+    if (UNIT || (MODE != 3 && !COIN && b_q8 <= 256u)) {
         // tile0 is a multiple of TPW: the TPW words of a row are neighbours, aligned to their common size
         const uint64_t base0 = hix_base<M>(tile0, p);
         const uint32_t word0 = (uint32_t)(base0 >> 5);
@@ -464,6 +478,9 @@ uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint3
     // against shared instances that still spilled: 0.40 -> 0.24 ms at b = 1.5, 0.277 -> 0.253 ms at b = 3; b = 2: see hix_quantize_pack).
     uint32_t same = B.b_q8[0];
     for (uint32_t c = 1; c < n; ++c) if (B.b_q8[c] != same) same = 0;
+    // Coin budgets of one floor: the halves share their code as in the shared instance (two copies spilled 42 registers, 150 us); the two
+    // bits of a floor of 2 go through lane transposes, the bit of a coin through ballots.  Encode, shared instance -> this: 8 senders of
+    // 4,000,037 at 2.7 bits 129 -> 125 us, of 2,000,000 at 3.3 83.4 -> 81.0; 16 of 11,173,962 at 2.7 771 -> 759.
 #define EDEN_ENC_HIX_ONLY(MODE, ONLY)                                                                                         \
     if (blocked) {                                                                                                            \
         EDEN_HIX_SWITCH(M, P, hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_hix_last<MM, PP, 1, MODE, true, ONLY>), grid, dim3(HiX<MM>::THREADS), \
@@ -478,6 +495,9 @@ uint32_t launch_enc_hix_last(int M, int P, int blocked, const EncBatch &B, uint3
     else if (same == 384u) { EDEN_ENC_HIX_ONLY(2, 384u); }
     else if (same == 640u) { EDEN_ENC_HIX_ONLY(2, 640u); }
     else if (same == 896u) { EDEN_ENC_HIX_ONLY(2, 896u); }
+    else if (const uint32_t cb = coin_floor_of_all(B.b_q8, n)) {
+        if (cb == 1u) { EDEN_ENC_HIX_ONLY(2, kCoinOnly + 1u); } else if (cb == 2u) { EDEN_ENC_HIX_ONLY(2, kCoinOnly + 2u); } else { EDEN_ENC_HIX_ONLY(2, kCoinOnly + 3u); }
+    }
     else if (mixed) { EDEN_ENC_HIX_LAST(1, 2); } else { EDEN_ENC_HIX_LAST(1, 1); }
 #undef EDEN_ENC_HIX_ONLY
 #undef EDEN_ENC_HIX_LAST

@@ -14,37 +14,41 @@ namespace eden {
 // P .. P+M-1 of H.
 // ONLY != 0: every sender of the launch has this budget (2, 3 or 4 bits, or k + 1/2; indices in the payload): the instance then
 // holds that one branch, which takes it from 128 registers and spills to 97 (16 senders at D = 2^24: 0.180 -> 0.160 ms).
+// kCoinOnly + k: coin budgets of this floor (one load per value for k < 3, no spills; 8 senders of 4,000,037 at 2.7 bits 67 -> 57 us).
 template <int M, int P, uint32_t ONLY = 0>
 __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B, uint64_t d, int log2D, uint64_t seed,
                                                                     const DecScratch *scratch, int narrow, float *T,
                                                                     CoinTables ct) {
     using X = HiX<M>;
     constexpr int p = P;
+    constexpr bool COIN = ONLY == kCoinOnly + 1u || ONLY == kCoinOnly + 2u || ONLY == kCoinOnly + 3u;
     __shared__ float lds[X::LDS_FLOATS];
     __shared__ float table[32];
     __shared__ float gtab[kGridMax + 1];                         // uniform grid: dequantized centres of mass
     const uint32_t c = blockIdx.y;
-    const uint32_t b_q8 = ONLY ? ONLY : B.b_q8[c];
+    const uint32_t b_q8 = ONLY && !COIN ? ONLY : B.b_q8[c];
     uint32_t tile = xcd_local_tile();
     {   // payload bytes of one tile row: 4 per index bit; the budgets with a power of two (2, 4, 8 bits) get aligned runs
         int tb, tk;
         budget_of(b_q8, tb, tk);
+        if (COIN) tb = (int)(ONLY - kCoinOnly);
         if (tk == 1 && (tb == 2 || tb == 4 || tb == 8) && !B.codes[c])
             tile = align_runs_to_lines(tile, p - 5, static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES, 4u * (uint32_t)tb);
     }
     const uint64_t base = hix_base<M>(tile, p);
     const uint32_t col = threadIdx.x & 31u, g = threadIdx.x >> 5, lane = lane_id();
     const uint32_t g0 = 2u * wave_in_block();
-    const bool i16 = narrow && b_q8 <= 256u;
+    const bool i16 = !COIN && narrow && b_q8 <= 256u;
     const DecScratch *sc = &scratch[c];
     if (threadIdx.x < 16) table[threadIdx.x] = (i16 && threadIdx.x == 1) ? 1.0f : sc->deq[threadIdx.x];
     else if (threadIdx.x < 32) table[threadIdx.x] = sc->deq2[threadIdx.x - 16];
-    if (byte_budget(b_q8))
+    if (!COIN && byte_budget(b_q8))
         for (uint32_t i = threadIdx.x; i <= (uint32_t)kGridMax; i += X::THREADS) gtab[i] = sc->grid_deq[i];
     __syncthreads();
     const uint32_t *payload = reinterpret_cast<const uint32_t *>(static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES);
     int bits, k;
     budget_of(b_q8, bits, k);
+    if (COIN) { bits = (int)(ONLY - kCoinOnly); k = 1; }
     const uint32_t payload_bytes = (uint32_t)(((((1ull << log2D) >> (k == 2)) * (uint32_t)bits + 63) >> 6) << 3);
 
     // rows of this wave whose packet arrived, as lane masks over the register index (bit r <-> register r)
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         recv_b = __ballot((bm[pb >> 5] >> (pb & 31u)) & 1u);
     }
     float v[64];
-    if (b_q8 == 128) {
+    if (!COIN && b_q8 == 128) {
         // b = 1/2: pair j = i >> 1 carries one bit; coordinate i was sent iff (i & 1) equals the pair's offset bit
         const uint64_t key = stream_key(seed, kStreamSubsample, B.client[c]);
         const uint32_t sh = 16u * (uint32_t)((base >> 5) & 3u);                  // this tile's 16 pairs inside a hash word
@@ -76,7 +80,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
             const uint32_t neg = (~(w >> bitpos) & 1u) << 31;                    // index 0 = negative
             v[r] = kept ? __uint_as_float(mag | neg) : 0.0f;
         }
-    } else if (byte_budget(b_q8)) {
+    } else if (!COIN && byte_budget(b_q8)) {
         // one byte per coordinate: the index on the uniform grid (Sec. 4.3) or of a 32..256-level quantizer
         const uint8_t *bytes = B.codes[c] ? B.codes[c] : reinterpret_cast<const uint8_t *>(payload);
         const rsrc_t rp = make_rsrc(bytes + base, (1u << log2D) - (uint32_t)base);
@@ -91,7 +95,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
 #pragma unroll
             for (int r = 0; r < 64; ++r) v[r] = dequantize_byte<false>(__float_as_uint(v[r]), H, gtab);
         }
-    } else if (coin_q8(b_q8)) {
+    } else if (COIN || coin_q8(b_q8)) {
         // coin budgets (Sec. 4.1): every coordinate has `bits` bits in the first part; a coordinate with a coin was
         // quantized with the finer table and has its top bit in the second part, at the position of its rank among the
         // coins.  Lane l fetches the coins of the two row segments the wave reads into register l.
@@ -119,7 +123,8 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         for (int r = 0; r < 64; ++r) {
             const int soff = (int)((((uint32_t)X::RL * r * (uint32_t)bits) << (p - 5)) * 4u);
             const uint32_t w0 = __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff, soff, 0);
-            const uint32_t w1 = __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff + 4, soff, 0);    // always: no branch per value
+            // (one and two bits never straddle two words; otherwise always: no branch per value)
+            const uint32_t w1 = COIN && ONLY < kCoinOnly + 3u ? 0u : __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff + 4, soff, 0);
             const uint32_t low = code_at(w0, w1, shift, bits);
             const uint32_t m = (lane < 32u) ? __builtin_amdgcn_readlane(ma, r) : __builtin_amdgcn_readlane(mb, r);
             const uint32_t wnd = (lane < 32u) ? __builtin_amdgcn_readlane(wa, r) : __builtin_amdgcn_readlane(wb, r);
@@ -196,7 +201,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
             v[r] = keep_where(v[r], m);
         }
     }
-    const uint32_t touched = ONLY != 0u ? touch_payload_ahead<X::THREADS, M, 1u << (P - 5)>(B, 4u * (ONLY >> 8)) : 0u;
+    const uint32_t touched = ONLY != 0u ? touch_payload_ahead<X::THREADS, M, 1u << (P - 5)>(B, 4u * (COIN ? ONLY - kCoinOnly : ONLY >> 8)) : 0u;
     fwht_regs<64>(v);
     const uint32_t base_off = (uint32_t)base * 4u;
     const uint32_t off2 = (((g * X::RHL * X::RL) << p) + col) * 4u;
@@ -685,7 +690,9 @@ bool launch_dec_hix_first(int M, int P, const DecBatch &B, uint32_t n, uint64_t 
     if (all2) { EDEN_DEC_HIX_FIRST(512u); } else if (all4) { EDEN_DEC_HIX_FIRST(1024u); }
     else if (same == 768u) { EDEN_DEC_HIX_FIRST(768u); } else if (same == 384u) { EDEN_DEC_HIX_FIRST(384u); }
     else if (same == 640u) { EDEN_DEC_HIX_FIRST(640u); } else if (same == 896u) { EDEN_DEC_HIX_FIRST(896u); }
-    else { EDEN_DEC_HIX_FIRST(0u); }
+    else if (const uint32_t cb = coin_floor_of_all(B.b_q8, n)) {
+        if (cb == 1u) { EDEN_DEC_HIX_FIRST(kCoinOnly + 1u); } else if (cb == 2u) { EDEN_DEC_HIX_FIRST(kCoinOnly + 2u); } else { EDEN_DEC_HIX_FIRST(kCoinOnly + 3u); }
+    } else { EDEN_DEC_HIX_FIRST(0u); }
 #undef EDEN_DEC_HIX_FIRST
     return false;
 }

@@ -961,3 +961,27 @@ def test_two_bit_launches_write_what_the_shared_kernel_writes(d):
         assert torch.equal(alone[0], beside[0]), other
     assert c.last_device_status() == 0
     c.close()
+
+
+@pytest.mark.parametrize("d", [1_100_000, (1 << 22) - 3, 5_000_001, (1 << 24) + 1, (1 << 25) + 1])
+@pytest.mark.parametrize("bits", [1.3, 2.7, 3.5])
+def test_coin_launches_against_the_shared_kernels(d, bits):
+    # launches whose senders all have coin budgets of one floor run in instances of their own, in both directions: the same messages as
+    # beside another budget, and the same sum as beside a message that adds nothing; with and without lost packets
+    from paper_2108_08842_amd import eden
+    c = eden.Context(d_max=d, n_max=2, device=0)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn(d, generator=gen, device="cuda")
+    budgets = [eden.B_COIN(bits), eden.B_COIN(bits + 0.1)]
+    alone = c.encode([x, -x], [1, 2], budgets, 7)
+    length = [eden.message_length(m[:64].cpu().numpy().tobytes()) for m in alone]
+    for k in (0, 1):
+        beside = c.encode([x if k == 0 else -x, torch.zeros_like(x)], [k + 1, 9], [budgets[k], 512], 7)
+        assert torch.equal(alone[k][:length[k]], beside[0][:length[k]]), k
+        for maps in (None, [c.make_loss_bitmap(7, k + 1, 1 << (d - 1).bit_length(), 1 << 30), None]):
+            acc = [torch.zeros(d, device="cuda") for _ in range(2)]
+            c.decode_accumulate(beside[:1], [k + 1], budgets[k:k + 1], d, 7, acc[0], None if maps is None else maps[:1])
+            c.decode_accumulate(beside, [k + 1, 9], [budgets[k], 512], d, 7, acc[1], maps)
+            assert acc[0].any().item()
+            assert (acc[0] - acc[1]).norm() <= 1e-6 * acc[0].norm()      # (sums of sender groups in another order)
+    c.close()
