@@ -304,6 +304,8 @@ __global__ __launch_bounds__(256) void k_enc_norm(EncBatch B, const double *part
 // last pass gained nothing from such an instance).
 constexpr uint32_t kSimple = 1u;
 __host__ __device__ inline bool simple_budget(uint32_t b_q8) { return b_q8 == 128u || b_q8 == 256u || b_q8 == 512u || b_q8 == 1024u; }
+// With either, one form of load serves all rows and budgets: the words are on their way while the header is checked and the table made
+// (mean of 32 senders of 2^20, those budgets mixed, 75.6 -> 63.9 us; of 10 with b = 1 29.8 -> 29.1, with b = 2 the same).
 template <int M, uint32_t ONLY = 0>
 __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(DecBatch B, uint64_t keep_elems, int log2D, int p, uint64_t seed,
                                                       DecPrepareArgs prep, int narrow, float *T, CoinTables ct) {
@@ -314,9 +316,25 @@ __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(D
     const uint32_t c = blockIdx.y;
     const uint32_t lane = lane_id(), wv = wave_in_block();
     const uint32_t tile = blockIdx.x * 4u + wv;
-    const uint32_t ntiles = 1u << (log2D - 6 - M);               // a multiple of 4
-    constexpr bool SIMPLE = ONLY == kSimple;
+    constexpr bool SIMPLE = ONLY == kSimple, EARLY = ONLY != 0u;
     const uint32_t b_q8 = ONLY > kSimple ? ONLY : B.b_q8[c];
+    uint64_t base;
+    hi_tile_origin<M>(tile, p, base);                            // (the grid has exactly as many waves as there are tiles)
+    const uint32_t *payload = reinterpret_cast<const uint32_t *>(static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES);
+    int bits, k;
+    budget_of(b_q8, bits, k);
+    const uint32_t payload_bytes = (uint32_t)(((((1ull << log2D) >> (k == 2)) * (uint32_t)bits + 63) >> 6) << 3);
+    const uint32_t shift = SIMPLE && k == 2 ? lane >> 1 : (lane * (uint32_t)bits) & 31u;         // EARLY: where a lane's index sits in its word
+    float v[R];
+    if constexpr (EARLY) {                                       // the words of all rows, on their way while the table is made
+        const uint32_t first = SIMPLE && k == 2 ? (uint32_t)(base >> 6) : (uint32_t)((base * (uint32_t)bits) >> 5);
+        const uint32_t row = SIMPLE && k == 2 ? 1u << (p - 4) : (uint32_t)bits << (p - 3);       // bytes of payload per row of the strided index
+        const uint32_t voff = SIMPLE && k == 2 ? 0u : ((lane * (uint32_t)bits) >> 5) * 4u;
+        const rsrc_t rp = make_rsrc(payload + first, payload_bytes - first * 4u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff, (int)((uint32_t)r * row), 0));
+        __builtin_amdgcn_sched_barrier(0);
+    }
     // Header checks, arrival counts and the dequantization table: every workgroup of a sender does them for itself (a launch of
     // its own took 4 us in front of passes of 5 to 15), the first one for the later passes and the status words too.  The unit
     // pattern of a b <= 1 sender needs none of it here.
@@ -329,27 +347,38 @@ __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(D
     if (first_wg)
         for (uint32_t i = threadIdx.x; i < sizeof(DecScratch) / 4; i += 256u)
             reinterpret_cast<uint32_t *>(&prep.scratch[c])[i] = reinterpret_cast<const uint32_t *>(&ds)[i];
-    if (tile >= ntiles) return;
-    uint64_t base;
-    hi_tile_origin<M>(tile, p, base);
     const bool unit = narrow != 0 && b_q8 <= 256u, i16 = narrow == 1 && b_q8 <= 256u;      // narrow == 2: the integers as fp32
     if (lane < 16) table[wv][lane] = (unit && lane == 1) ? 1.0f : ds.deq[lane];
     else if (lane < 32) table[wv][lane] = ds.deq2[lane - 16];
-    if (!SIMPLE && byte_budget(b_q8)) { gtabs[wv][lane] = ds.grid_deq[lane]; gtabs[wv][64 + lane] = ds.grid_deq[64 + lane]; }
+    if (!EARLY && byte_budget(b_q8)) { gtabs[wv][lane] = ds.grid_deq[lane]; gtabs[wv][64 + lane] = ds.grid_deq[64 + lane]; }
     wave_lds_sync();
     const float *tb = table[wv], *tb2 = table[wv] + 16;
-    const uint32_t *payload = reinterpret_cast<const uint32_t *>(static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES);
-    int bits, k;
-    budget_of(b_q8, bits, k);
-    const uint32_t payload_bytes = (uint32_t)(((((1ull << log2D) >> (k == 2)) * (uint32_t)bits + 63) >> 6) << 3);
     const uint64_t my_row = base + ((uint64_t)(lane & (R - 1)) << p);       // lane r looks after row r
     uint64_t recv = ~0ull;                                       // bit r: the packet of row r arrived
     if (const uint32_t *bm = B.bitmap[c]) {
         const uint32_t pk = (uint32_t)(my_row >> 10);
         recv = __ballot((bm[pk >> 5] >> (pk & 31u)) & 1u);
     }
-    float v[R];
-    if (b_q8 == 128) {
+    if constexpr (EARLY) {
+        const float mag = tb[1];
+        if (SIMPLE && k == 2) {
+            const uint64_t key = stream_key(seed, kStreamSubsample, B.client[c]);
+            const uint32_t offs_mine = (uint32_t)(hash_word(key, my_row >> 7) >> (32u * (uint32_t)((base >> 6) & 1u)));
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint32_t offs = __builtin_amdgcn_readlane(offs_mine, r);
+                const bool kept = ((offs >> (lane >> 1)) & 1u) == (lane & 1u);
+                const uint32_t neg = (~(__float_as_uint(v[r]) >> shift) & 1u) << 31;         // index 0 = negative
+                v[r] = kept ? __uint_as_float(__float_as_uint(mag) | neg) : 0.0f;
+            }
+        } else if (bits == 1) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = __uint_as_float(__float_as_uint(mag) | ((~(__float_as_uint(v[r]) >> shift) & 1u) << 31));
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = tb[(__float_as_uint(v[r]) >> shift) & ((1u << bits) - 1u)];
+        }
+    } else if (b_q8 == 128) {
         // b = 1/2: pair j = i >> 1 carries one bit; coordinate i was sent iff (i & 1) equals the pair's offset bit
         const uint64_t key = stream_key(seed, kStreamSubsample, B.client[c]);
         const uint32_t offs_mine = (uint32_t)(hash_word(key, my_row >> 7) >> (32u * (uint32_t)((base >> 6) & 1u)));
@@ -363,7 +392,7 @@ __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(D
             const uint32_t neg = (~(w >> (lane >> 1)) & 1u) << 31;          // index 0 = negative
             v[r] = kept ? __uint_as_float(mag | neg) : 0.0f;
         }
-    } else if (!SIMPLE && byte_budget(b_q8)) {
+    } else if (byte_budget(b_q8)) {
         // one byte per coordinate: the index on the uniform grid (Sec. 4.3) or of a 32..256-level quantizer
         const uint8_t *bytes = B.codes[c] ? B.codes[c] : reinterpret_cast<const uint8_t *>(payload);
         const rsrc_t rp = make_rsrc(bytes + base, (1u << log2D) - (uint32_t)base);
@@ -377,7 +406,7 @@ __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(D
 #pragma unroll
             for (int r = 0; r < R; ++r) v[r] = dequantize_byte<false>(__float_as_uint(v[r]), H, gtabs[wv]);
         }
-    } else if (!SIMPLE && budget_mixed(b_q8)) {
+    } else if (budget_mixed(b_q8)) {
         // b = bits + 1/2 (Sec. 4.1): every coordinate has `bits` bits in the first part; the coordinate of each pair
         // that the MIX stream selects was quantized with the finer table and has its top bit in the second part
         const uint64_t key = stream_key(seed, kStreamMix, B.client[c]);
@@ -399,7 +428,7 @@ __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(D
             const uint32_t top = (wb >> (lane >> 1)) & 1u;
             v[r] = up ? tb2[(top << bits) | low] : tb[low];
         }
-    } else if (!SIMPLE && coin_q8(b_q8)) {
+    } else if (coin_q8(b_q8)) {
         // coin budgets (Sec. 4.1): every coordinate has `bits` bits in the first part; a coordinate with a coin was
         // quantized with the finer table and has its top bit in the second part, at the position of its rank among the coins
         const uint32_t w = (uint32_t)(my_row >> 6);
@@ -428,7 +457,7 @@ __global__ __launch_bounds__(256, ONLY == kSimple ? 4 : 5) void k_dec_hi_first(D
             const uint32_t top = (uint32_t)(wave_read64(window_mine, r) >> lanes_below(m)) & 1u;
             v[r] = __builtin_amdgcn_inverse_ballot_w64(m) ? tb2[(top << bits) | low] : tb[low];
         }
-    } else if (!SIMPLE && bits == 3) {
+    } else if (bits == 3) {
         // 64 columns x 3 bits = 6 words per row; an index may straddle two words
         const uint32_t lbits = lane * 3u;
         const rsrc_t rp = make_rsrc(payload + (base >> 6) * 6u, payload_bytes - (uint32_t)(base >> 6) * 24u);
