@@ -275,7 +275,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                 coins = true;
                 part_b[i] = static_cast<char *>(B.msg[i]) + EDEN_HEADER_BYTES + payload_a_bytes(1ull << log2D, (int)(coin_q8(B.b_q8[i]) >> 8), 1);
             }
-            if (coins) launch_coin_tables(B.client, B.b_q8, part_b, nb, seed, log2D, ctx->coin, st);
+            if (coins) launch_coin_tables(B.client, B.b_q8, part_b, nb, seed, log2D, ctx->coin, !pl.wg, st);     // (workgroup tiles: the norm's launch scans)
             // Coin senders whose last pass runs in workgroup tiles leave the pieces of the second part in the byte-index buffer
             // (a word per 32 coordinates) and a small kernel strings them together: no atomics in the last pass.
             const uint32_t *pieces[kMaxBatch] = {};
@@ -306,7 +306,7 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             tail.n2_count = nparts_n2;
             if (need_thresholds && !two_launches) {
                 Timed t(ctx, EDEN_K_ENC_NORM, nb, st);
-                launch_enc_norm(B, nb, part_n2, ctx->partial_stride, nparts_n2, ctx->enc_scratch, ctx->tables, st);
+                launch_enc_norm(B, nb, part_n2, ctx->partial_stride, nparts_n2, ctx->enc_scratch, ctx->tables, log2D, coins ? &ctx->coin : nullptr, st);
             }
             if (pl.wide) {
                 Timed t(ctx, EDEN_K_MID, nb, st);
@@ -583,13 +583,13 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             const int narrow = ((pre == 2 && !behind) || pl.wide) ? 0 : pl.lo_bits == 12 ? 2 : 1;
             bool coins = false;                                  // the receiver draws and counts the same coins
             for (uint32_t i = 0; i < nb; ++i) coins = coins || coin_q8(B.b_q8[i]);
-            if (coins) launch_coin_tables(B.client, B.b_q8, nullptr, nb, seed, log2D, ctx->coin, st);
             // header checks, arrival counts and dequantization tables: a launch of its own, unless the first pass does them
             const DecPrepareArgs prep{hdr_d, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, flags_out + first};
             const bool first_prepares = pl.wg ? !coins && dec_hix_first_prepares(pl.M, pl.lo_bits, B, nb, narrow) : !pl.wide;
+            if (coins) launch_coin_tables(B.client, B.b_q8, nullptr, nb, seed, log2D, ctx->coin, first_prepares, st);
             if (!first_prepares) {
                 Timed t(ctx, EDEN_K_DEC_PREPARE, nb, st);
-                launch_dec_prepare(B, nb, hdr_d, log2D, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, ctx->coin.total,
+                launch_dec_prepare(B, nb, hdr_d, log2D, seed, ctx->tables, ctx->dec_scratch, ctx->dev_status, ctx->coin, coins,
                                    flags_out + first, st);
             }
             {

@@ -23,20 +23,21 @@ uint32_t launch_enc_hi_last(int M, const EncBatch &B, uint32_t n, uint64_t valid
 // (encode) points at the second part of every such sender's payload, which is cleared; null on the receiver's side
 void launch_coin_pack(const uint32_t *b_q8, const uint32_t *const *pieces, void *const *part_b, uint32_t n, int log2D,
                       const CoinTables &ct, hipStream_t st);
+// `scan` = false: the caller's launch_enc_norm or launch_dec_prepare adds the groups' totals up
 void launch_coin_tables(const uint32_t *clients, const uint32_t *b_q8, void *const *part_b, uint32_t n, uint64_t seed, int log2D,
-                        const CoinTables &ct, hipStream_t st);
+                        const CoinTables &ct, bool scan, hipStream_t st);
 // wide strided tiles (8 rows x 512 columns per wave) for the top three index bits of D >= 2^25, one-byte budgets only
 uint32_t launch_enc_wide_last(const EncBatch &B, uint32_t n, uint64_t valid_elems, int log2D, const float *T, double *partials,
                               uint32_t partial_stride, const EncScratch *scratch, hipStream_t st);
 void launch_dec_wide_first(const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, const DecScratch *scratch, float *T,
                            hipStream_t st);
 void launch_enc_norm(const EncBatch &B, uint32_t n, const double *partials, uint32_t partial_stride, uint32_t nparts,
-                     EncScratch *scratch, const DevTables *tab, hipStream_t st);
+                     EncScratch *scratch, const DevTables *tab, int log2D, const CoinTables *coins /* not null: their scan too */, hipStream_t st);
 void launch_enc_finish(const EncBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed,
                        const double *partials_n2, uint32_t nparts_n2, const double *partials_ip, uint32_t nparts_ip,
                        uint32_t partial_stride, uint32_t *dev_status, const uint32_t *coin_total, hipStream_t st);
 void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed, const DevTables *tab,
-                        DecScratch *scratch, uint32_t *dev_status, const uint32_t *coin_total, uint32_t *msg_flags,
+                        DecScratch *scratch, uint32_t *dev_status, const CoinTables &ct, bool scan, uint32_t *msg_flags,
                         hipStream_t st);
 // Does the work of launch_dec_prepare itself.  `narrow`: the slots of b <= 1 senders hold 0 = values, 1 = the integers before the scale as fp16, 2 = as fp32
 void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, int p, uint64_t seed,

@@ -15,7 +15,7 @@
 // XCD (workgroups i and i + 8), so the second read of a line is meant to find it in that XCD's L2.
 // (measured: the encoder's pass fetches every line from memory once).
 // It replaces a 14-bit contiguous pass and a second strided pass (one more trip through memory per direction).  8 senders of 2^27,
-// b = 4: this pass 1.96 ms (encode) and 1.10 ms (decode), the strided ones 1.37 and 1.39 ms; a round 8.03 -> 5.85 ms; at 2^25
+// b = 4: this pass 1.96 ms (encode) and 1.10 ms (decode), the strided ones 1.37 and 1.39 ms (1.22 with touch_payload_ahead); a round 8.03 -> 5.85 ms; at 2^25
 // 1.94 -> 1.16 ms, with b = 1 1.91 -> 0.91 ms.  With one workgroup per CU what is left is the time in which its waves all wait
 // for memory or all compute (vector instructions 48%, 31% of the time).
 #include "eden_device.h"
@@ -62,7 +62,7 @@ __device__ inline void lo15_tile(uint32_t &tile, uint32_t &half) {
     half = HALVES ? (blockIdx.x >> 3) & 1u : 0u;
 }
 
-// Encode, first pass: x -> T (see k_enc_lo14_first), always in the blocked layout.
+// Encode, first pass: x -> T (see k_enc_lo_first), always in the blocked layout.
 template <bool PRE, bool HALVES>
 __global__ __launch_bounds__(1024) void k_enc_lo15_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
                                                          double *partials, uint32_t partial_stride) {
