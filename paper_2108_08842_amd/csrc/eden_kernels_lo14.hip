@@ -1,9 +1,10 @@
 // The contiguous passes for D <= 2^24 (gfx950): the encoder's over 12 or 14 bits, the decoder's over 14.
 //
-// A workgroup owns 2^12 or 2^14 consecutive coordinates, 16 values per thread (eden_lo.h); where all values of a decode launch are small
-// integers, ten of the 14 bits run on the matrix cores.  The encode pass is bound by memory where a launch fills the chip (16 senders of
-// 11,173,962: 1.43 GB at 6.1 TB/s, 32 values per thread the same) and by the length of a wave's chain where it does not: encode of one
-// sender of 20,000, b = 2 12.9 -> 10.5 us, 8 of 131,072 15.2 -> 13.0 with four waves per 4096 coordinates instead of one.
+// A workgroup owns 2^12 or 2^14 consecutive coordinates, 16 values per thread (EncLo here, lo_forward16 of eden_lo.h in the decoder); where
+// all values of a decode launch are small integers, ten of the 14 bits run on the matrix cores.  The encode pass is bound by memory where a
+// launch fills the chip (16 senders of 11,173,962: 1.43 GB at 6.1 TB/s, 32 values per thread the same) and by the length of a wave's
+// chain where it does not: encode of one sender of 20,000, b = 2 12.9 -> 10.5 us, 8 of 131,072 15.2 -> 13.0 with four waves per 4096
+// coordinates instead of one.
 #include "eden_device.h"
 #include "eden_kernels.h"
 #include "eden_lo.h"
@@ -11,6 +12,96 @@
 namespace eden {
 
 constexpr int kLo14Bits = 14;
+
+// The encoder's transform of a tile of 2^P coordinates by 2^P / 16 threads with 16 values each: three groups of stages in registers,
+// exchanges through LDS between them, the first between all waves, the others inside a wave, in the place this wave alone has just read.
+// The order of the stages is part of the results: sums round differently in another one, and an index next to a threshold moves
+// (8e-6 of the bytes at b = 8).  It is 6 .. 11, 0 .. 5 for P = 12 and 9 .. 13, 4 .. 8, 0 .. 3 for P = 14, and the groups are cut so
+// that the bits a group needs are the ones the exchange before it can bring into registers.  Against groups from the top bit down, with
+// one exchange more for P = 14 (encode, us): one sender of 20,000, b = 2 9.9 and 9.8; 32 of 250,000, b = 1 23.4 and 23.3; 10 of 2^20, b = 2
+// 31.2 -> 29.5; 8 of 4,000,037, b = 8 109.4 -> 106.9; 16 of 11,173,962, b = 1 374 and 375, one of them 36.1 -> 34.2, 16 with pairs before
+// the rotation 233 -> 239 (a wave's neighbours read the other half of the tile).
+//   at(t):        coordinate in the tile of v[0] on entry; v[a] is STEP a further on.  A register of a wave is 64 consecutive coordinates
+//   quad(t, j):   first coordinate of x[j] on return
+template <int P> struct EncLo;
+
+//   P = 12  registers 6..9 | 10, 11, 0, 1 | 2..5; the waves are bits 10 and 11 before and bits 8 and 9 after the first exchange.
+//   A row of 64 coordinates keeps its place in LDS; its 16 quads are swizzled by bits 6, 7, 10, 11, so that both directions of the other
+//   exchanges, quads of bits 0 and 1 on one side and registers of bits 2..5 on the other, are free of bank conflicts.
+template <> struct EncLo<12> {
+    static constexpr uint32_t THREADS = 256, STEP = 64;
+    static __device__ inline uint32_t wave_at(uint32_t wv) { return 1024u * wv; }
+    static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) { return 1024u * j + 256u * wv + 4u * lane; }
+    static __device__ inline void forward(float (&v)[16], float *lds, float4 (&x)[4]) {
+        const uint32_t lane = lane_id(), wv = wave_in_block();
+        fwht_regs<16>(v);                                        // bits 6..9
+#pragma unroll
+        for (uint32_t a = 0; a < 16; ++a) lds[wave_at(wv) + STEP * a + lane] = v[a];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {                       // j: bits 10, 11
+            const float4 y = *reinterpret_cast<const float4 *>(&lds[quad(wv, lane, j)]);
+            v[j] = y.x; v[j + 4] = y.y; v[j + 8] = y.z; v[j + 12] = y.w;
+        }
+        fwht_regs<16>(v);                                        // bits 10, 11, 0, 1
+        // quad lane & 15 of row 16 j + 4 wv + (lane >> 4), swizzled by bits 6, 7 (lane >> 4) and 10, 11 (j)
+        const uint32_t mine = 256u * wv + 64u * (lane >> 4) + 4u * ((lane & 15u) ^ (lane >> 4));
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            *reinterpret_cast<float4 *>(&lds[1024u * j + (mine ^ (16u * j))]) = make_float4(v[j], v[j + 4], v[j + 8], v[j + 12]);
+        wave_lds_sync();
+        // lane: bits 0, 1, 6, 7, 10, 11; register r: bits 2..5
+        const uint32_t one = 1024u * (lane >> 4) + 256u * wv + 64u * ((lane >> 2) & 3u) + (lane & 3u) + 4u * (lane >> 2);
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) v[r] = lds[one ^ (4u * r)];
+        fwht_regs<16>(v);                                        // bits 2..5
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) lds[one ^ (4u * r)] = v[r];
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const float4 *>(&lds[1024u * j + (mine ^ (16u * j))]);
+    }
+};
+
+//   P = 14  registers 9..12 | 13, 4, 5, 6 | 7, 8, 0, 1, then 2 and 3 between the lanes of a quad; the waves are bits 6, 7, 8, 13 before and
+//   9..12 after the first exchange.  Bits 4 and 5 of the place in LDS are swizzled by bits 7 and 8 (no bank conflicts in any direction).
+//   The values leave as quads of bits 0 and 1 without a further exchange.
+template <> struct EncLo<14> {
+    static constexpr uint32_t THREADS = 1024, STEP = 512;
+    static __device__ inline uint32_t wave_at(uint32_t wv) { return 8192u * (wv >> 3) + 64u * (wv & 7u); }
+    static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) {
+        return 8192u * (lane >> 5) + 512u * wv + 128u * j + 4u * (lane & 31u);
+    }
+    static __device__ inline void forward(float (&v)[16], float *lds, float4 (&x)[4]) {
+        const uint32_t lane = lane_id(), wv = wave_in_block();
+        fwht_regs<16>(v);                                        // bits 9..12
+        const uint32_t from = wave_at(wv) + (lane ^ (16u * ((wv >> 1) & 3u)));
+#pragma unroll
+        for (uint32_t a = 0; a < 16; ++a) lds[from + STEP * a] = v[a];
+        __syncthreads();
+        // lane: bits 0..3, 7, 8; register r: bits 13, 4, 5, 6
+        const uint32_t one = 512u * wv + 128u * (lane >> 4) + (lane & 15u) + 16u * (lane >> 4);
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) v[r] = lds[(one ^ (16u * ((r >> 1) & 3u))) + 8192u * (r & 1u) + 64u * (r >> 3)];
+        fwht_regs<16>(v);                                        // bits 13, 4, 5, 6
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) lds[(one ^ (16u * ((r >> 1) & 3u))) + 8192u * (r & 1u) + 64u * (r >> 3)] = v[r];
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {                       // j: bits 7, 8; lane: bits 2..6, 13
+            const float4 y = *reinterpret_cast<const float4 *>(&lds[quad(wv, lane, j) ^ (16u * j)]);
+            v[j] = y.x; v[j + 4] = y.y; v[j + 8] = y.z; v[j + 12] = y.w;
+        }
+        fwht_regs<16>(v);                                        // bits 7, 8, 0, 1
+        quad_stage<1>(v);                                        // bit 2
+        quad_stage<2>(v);                                        // bit 3
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) x[j] = make_float4(v[j], v[j + 4], v[j + 8], v[j + 12]);
+    }
+};
 
 // Encode, first pass: x -> T.  Zero padding (Sec. 5: the transform needs a power of two), the sign diagonal of
 // the rotation from the shared seed (Sec. 2.1), |x|^2 for eta and S (Sec. 2.2.1, 2.3), index bits 0 .. P-1 of H, P = 12 or 14.
@@ -20,32 +111,34 @@ constexpr int kLo14Bits = 14;
 // PRE (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is x'[g] = 2 x[2g + o_g],
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
 template <int P, bool PRE, bool BLOCKED>
-__global__ __launch_bounds__(Lo16<P>::T, 8) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
-                                                             double *partials, uint32_t partial_stride, EncTail tail) {
-    constexpr uint32_t THREADS = Lo16<P>::T, WAVES = THREADS / 64;
-    __shared__ __attribute__((aligned(16))) float lds[Lo16<P>::LDS_FLOATS];
-    __shared__ double red[WAVES];
-    const uint32_t c = blockIdx.y, t = threadIdx.x, lane = t & 63u;
+__global__ __launch_bounds__(EncLo<P>::THREADS, 8) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
+                                                            double *partials, uint32_t partial_stride, EncTail tail) {
+    using L = EncLo<P>;
+    constexpr uint32_t THREADS = L::THREADS;
+    __shared__ __attribute__((aligned(16))) float lds[1 << P];
+    __shared__ double red[THREADS / 64];
+    const uint32_t c = blockIdx.y, lane = lane_id();
     const uint32_t wv = wave_in_block();
     const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));           // reads past d_src give the zero padding
     float *Tc = T + ((size_t)c << log2D);
     const uint32_t tile = blockIdx.x;                            // one tile per workgroup: the phases of two workgroups on a CU
                                                                  // interleave better than two tiles in one workgroup with the
                                                                  // second one's loads issued early
-    // element THREADS a + t of the tile: register a of this wave is 64 consecutive coordinates = one sign word; lane l hashes
-    // the word of register l % 16.  With PRE it comes from x[2 i + o_i], and the register is 64 pairs = one word of offsets
-    const uint64_t word = ((uint64_t)tile << (P - 6)) + WAVES * (lane & 15u) + wv;
+    // register a of this wave is 64 consecutive coordinates = one sign word; lane l hashes the word of register l % 16.  With PRE an
+    // element comes from x[2 i + o_i], and the register is 64 pairs = one word of offsets
+    const uint32_t first = (tile << P) + L::wave_at(wv);
+    const uint64_t word = (first >> 6) + (L::STEP / 64u) * (lane & 15u);
     float u[16];
     if constexpr (PRE) {
         const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), word);
 #pragma unroll
         for (int a = 0; a < 16; ++a) {
             const uint32_t odd = __builtin_amdgcn_inverse_ballot_w64(wave_read64(offs, a)) ? 4u : 0u;
-            u[a] = 2.0f * buf_load(rx, 8u * t + odd, (tile << (P + 3)) + 8u * THREADS * a);
+            u[a] = 2.0f * buf_load(rx, 8u * lane + odd, 8u * (first + L::STEP * a));
         }
     } else {
 #pragma unroll
-        for (int a = 0; a < 16; ++a) u[a] = buf_load(rx, 4u * t, (tile << (P + 2)) + 4u * THREADS * a);
+        for (int a = 0; a < 16; ++a) u[a] = buf_load(rx, 4u * lane, 4u * (first + L::STEP * a));
     }
     const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), word);
     double n2 = 0.0;
@@ -56,19 +149,18 @@ __global__ __launch_bounds__(Lo16<P>::T, 8) void k_enc_lo_first(EncBatch B, uint
     }
 #pragma unroll
     for (int a = 0; a < 16; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;   // + 0: no negative zeros
-    lo_forward16<P>(u, lds);
-    // whole lines: lane l holds coordinates 4 (64 j + l) .. + 3 of the wave's 1024.  BLOCKED: the 128-byte segments of kBlockRows
+    // whole lines leave: 64 lanes (P = 14: 32) hold as many consecutive quads.  BLOCKED: the 128-byte segments of kBlockRows
     // consecutive rows are interleaved (see blocked_offset).  (Write-back stores: with the streaming hint this pass ran 13% slower; the pass
     // that reads the tiles back does better with the hint on its loads.)
     float4 x[4];
-    wave_quads(u, lds + wv * (Lo16<P>::LDS_FLOATS / WAVES), x);
+    L::forward(u, lds, x);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t at = 1024u * wv + 256u * (uint32_t)j + 4u * lane;
+    for (uint32_t j = 0; j < 4; ++j) {
+        const uint32_t at = L::quad(wv, lane, j);
         *reinterpret_cast<float4 *>(Tc + (BLOCKED ? blocked_offset<P>(tile, at >> 5) + (at & 31u) : ((size_t)tile << P) + at)) = x[j];
     }
     const double block_total = block_sum<(int)THREADS>(n2, red);
-    if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+    if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
     enc_first_side<(int)THREADS>(tail, c, B.b_q8[c]);
 }
 
@@ -521,7 +613,7 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
 #define EDEN_ENC_LO(P, PRE, BLK) \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, PRE, BLK>), grid, dim3(Lo16<P>::T), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, PRE, BLK>), grid, dim3(EncLo<P>::THREADS), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
     if (P == 12) { if (pre) EDEN_ENC_LO(12, true, false); else EDEN_ENC_LO(12, false, false); }
     else if (pre) { if (blocked) EDEN_ENC_LO(14, true, true); else EDEN_ENC_LO(14, true, false); }
     else { if (blocked) EDEN_ENC_LO(14, false, true); else EDEN_ENC_LO(14, false, false); }

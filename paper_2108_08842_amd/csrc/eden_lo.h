@@ -1,4 +1,5 @@
-// The contiguous transform with 16 values per thread (gfx950): 2^B consecutive coordinates by 2^B / 16 threads, B = 12 or 14.
+// The decoder's contiguous transform with 16 values per thread (gfx950): 2^B consecutive coordinates by 2^B / 16 threads, B = 12 or 14.
+// (The encoder's, whose order of the stages is part of a message, is EncLo in eden_kernels_lo14.hip.)
 //
 //   group 1    bits B-4 .. B-1   v[a] = coordinate a T + t, T = 2^(B-4) threads (coalesced loads)
 //   exchange 1 through LDS between the waves: registers <-> bits B-8 .. B-5

@@ -1,0 +1,56 @@
+"""The order of the butterfly stages is part of a message: fp32 sums round differently in another order, and an index next to a threshold
+moves.  The encoder's transforms against plain fp32 butterflies in that order, byte for byte."""
+import numpy as np
+import pytest
+
+from oracle import eden_oracle as o
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _stages(log2D):
+    """Index bits in the order the encoder's passes take them."""
+    if log2D <= 18:                                              # contiguous pass over 12 bits, then the strided one
+        return [*range(6, 12), *range(0, 6), *range(12, log2D)]
+    low = [*range(9, 14), *range(4, 9), *range(0, 4)]
+    if log2D <= 20:
+        return low + [*range(14, log2D)]
+    return low + [*range(log2D - 6, log2D), *range(14, log2D - 6)]
+
+
+def _transformed(x, seed, client, log2D):
+    """H (s o pad(x)) in fp32."""
+    D = 1 << log2D
+    u = torch.zeros(D, device="cuda")
+    u[:x.numel()] = x
+    u = u * torch.from_numpy(o.rademacher(seed, client, D).astype(np.float32)).cuda() + 0.0
+    for bit in _stages(log2D):
+        pairs = u.view(-1, 2, 1 << bit)
+        u = torch.stack([pairs[:, 0] + pairs[:, 1], pairs[:, 0] - pairs[:, 1]], 1).view(-1)
+    return u
+
+
+# sizes: the smallest multi-pass dimension, both contiguous tiles with ragged ends, every kind of strided pass up to the last plan of two
+# launches' worth of bits (2^24).  No byte may differ: additions, thresholds and compares are the same operations.  (Another order
+# differed in 6e-6 to 8e-6 of the bytes: one or more from 2^18 on.)
+@pytest.mark.parametrize("d", [4097, 40_003, 250_000, 300_007, 1 << 20, 1_500_000, 4_000_037, (1 << 23) - 1, 11_173_962, 1 << 24])
+def test_bytes_are_those_of_plain_butterflies_in_the_same_order(d):
+    from paper_2108_08842_amd import eden
+    log2D = (d - 1).bit_length()
+    ctx = eden.Context(d_max=d, n_max=2, device=0)
+    edges = torch.tensor(eden.get_tables(8)[0], dtype=torch.float64, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    for seed in range(1 if d > 1 << 22 else 8):
+        xs = [torch.randn(d, generator=gen, device="cuda"), torch.randn(d, generator=gen, device="cuda").exp_()]
+        msgs = ctx.encode(xs, [3, 4], [2048, 2048], seed)
+        for x, client, msg in zip(xs, [3, 4], msgs):
+            thr = (edges[128:] * torch.sqrt((x.double() ** 2).sum())).float()
+            u = _transformed(x, seed, client, log2D)
+            mag = torch.searchsorted(thr, u.abs())               # thresholds below |u|
+            want = torch.where(torch.signbit(u), 127 - mag, 128 + mag).to(torch.uint8)
+            moved = int((msg[64:64 + want.numel()] != want).sum())
+            assert moved == 0, (seed, client, moved)
+    assert ctx.last_device_status() == 0
+    ctx.close()
