@@ -59,27 +59,30 @@ __device__ inline uint32_t align_runs_to_lines(uint32_t tile, uint32_t cb_bits, 
 // first decode pass begins with a read of 2^M short pieces of the payload and can do nothing else until they are there; messages
 // that have just arrived lie in memory, and a run of 16 tiles (which share the lines) waited for them together.  The 16
 // workgroups of a run each read a word of 1/16 of the lines of the run 2^18 threads further on, about as many as the chip holds at a time.
-// The word is not used; the caller keeps it in a register until its own stores are out, so that nothing waits for it.
-// Mean of 16 senders of 11,173,962 on changing messages: b = 1 184.0 -> 170.0 us (the pass 93 -> 77), b = 4 400 -> 333, b = 2 307 -> 302;
-// of 8 of 2^25, b = 4 586 -> 541, b = 1 363 -> 316; of 8 of 2^27, b = 4 the pass 1354 -> 1225; where an encode has just left the messages in the memory-side cache
-// nothing is gained or lost (a round of 16 of 11,173,962, b = 4 755 -> 755).  Behind the first butterflies, where more registers are in
-// use, the read cost spills (b = 4 346).
+// The word is not used.  The read is a volatile one behind a branch, so that its few waves wait for it before they go on; that is the better
+// way where values are looked up (hot messages, us, this / a buffer load that nothing waits for: mean of 16 senders of 11,173,962, b = 2
+// 307 / 313, b = 4 341 / 348, of 8 of 2^25, b = 4 538 / 546; b = 1, on the matrix cores, 169.3 / 168.3 and 312 / 311).
+// Against passes without it, the same two sets of messages in turn / single passes on messages that lie in no cache, us: mean of 16 senders of
+// 11,173,962, b = 1 184 -> 169 / 228 -> 218, b = 2 305 -> 299 / 442 -> 342, b = 4 418 -> 331 / 445 -> 341; of 8 of 2^25, b = 1
+// 364 -> 310 / 369 -> 319, b = 4 583 -> 539 / 607 -> 572; of 4 of 2^27, b = 4 1373 -> 1281 / 1399 -> 1303 (with what else changed between
+// the two builds: the sums of the last pass at b = 2 and 4).  Where an encode has just left the messages in the memory-side cache
+// nothing is gained or lost (a round of 16 of 11,173,962, b = 4 755 -> 755).
 // (Every read is inside that sender's payload: rows below 2^M, tiles below TILES.)
 // THREADS: of a workgroup; TILES: per sender, a multiple of 128; `row_bytes`: payload bytes of one tile row.
 template <uint32_t THREADS, int M, uint32_t TILES>
-__device__ inline uint32_t touch_payload_ahead(const DecBatch &B, uint32_t row_bytes) {
+__device__ inline void touch_payload_ahead(const DecBatch &B, uint32_t row_bytes) {
     constexpr uint32_t kAhead = (1u << 18) / THREADS, kRows = (1u << M) / 16u;
     static_assert(TILES % 128u == 0, "runs of 16 tiles on each of 8 XCDs, see xcd_local_tile");
     const uint32_t x = blockIdx.x + kAhead, c = blockIdx.y + x / TILES;
     const uint32_t per_row = row_bytes > 8u ? 2u : 1u;           // lines of a payload row that a run of 16 tiles shares
-    if (c >= gridDim.y || wave_in_block() * 64u >= kRows * per_row || threadIdx.x >= kRows * per_row) return 0u;
-    if (B.b_q8[c] != B.b_q8[blockIdx.y]) return 0u;              // `row_bytes` would not be that sender's
+    if (c >= gridDim.y || wave_in_block() * 64u >= kRows * per_row || threadIdx.x >= kRows * per_row) return;
+    if (B.b_q8[c] != B.b_q8[blockIdx.y]) return;                 // `row_bytes` would not be that sender's
     const char *payload = static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES;
     const uint32_t q = (x % TILES) >> 3, run = (q / 16u) * 8u + (x & 7u);
     const uint32_t row = (q % 16u) * kRows + threadIdx.x / per_row;
     uint32_t tile = run * 16u + threadIdx.x % per_row * 8u;
     if ((row_bytes & (row_bytes - 1u)) == 0u) tile = align_runs_to_lines(tile, (uint32_t)__builtin_ctz(TILES), payload, row_bytes);
-    return *reinterpret_cast<const volatile uint32_t *>(payload + ((size_t)row * TILES + tile) * row_bytes);
+    (void)*reinterpret_cast<const volatile uint32_t *>(payload + ((size_t)row * TILES + tile) * row_bytes);
 }
 
 template <int M>

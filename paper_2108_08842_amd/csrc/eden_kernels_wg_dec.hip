@@ -201,7 +201,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
             v[r] = keep_where(v[r], m);
         }
     }
-    const uint32_t touched = ONLY != 0u ? touch_payload_ahead<X::THREADS, M, 1u << (P - 5)>(B, 4u * (COIN ? ONLY - kCoinOnly : ONLY >> 8)) : 0u;
+    if constexpr (ONLY != 0u) touch_payload_ahead<X::THREADS, M, 1u << (P - 5)>(B, 4u * (COIN ? ONLY - kCoinOnly : ONLY >> 8));
     fwht_regs<64>(v);
     const uint32_t base_off = (uint32_t)base * 4u;
     const uint32_t off2 = (((g * X::RHL * X::RL) << p) + col) * 4u;
@@ -229,7 +229,6 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
 #pragma unroll
         for (int s = 0; s < X::RP; ++s) buf_store(rt, off2, hix_row2<M>(0, 1, s) << (p + 2), out[s]);
     }
-    asm volatile("" ::"v"(touched));
 }
 
 // First decode pass for senders with b <= 1, two columns per thread.  The unit pattern is +-1 or 0 and M <= 11
@@ -315,7 +314,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, PIECES == 2 ? 4 : M == 9 ? 2 : 3) 
             v32[r] = __float_as_uint(keep_where(__uint_as_float(v32[r]), m));
         }
     }
-    const uint32_t touched = touch_payload_ahead<X::THREADS, M, 1u << (P - 6)>(B, b_q8 == 256u ? 8u : 4u);
+    touch_payload_ahead<X::THREADS, M, 1u << (P - 6)>(B, b_q8 == 256u ? 8u : 4u);
     s16x2 v[64];
 #pragma unroll
     for (int r = 0; r < 64; ++r) v[r] = __builtin_bit_cast(s16x2, v32[r]);
@@ -345,7 +344,6 @@ __global__ __launch_bounds__(HiX<M>::THREADS, PIECES == 2 ? 4 : M == 9 ? 2 : 3) 
             __builtin_amdgcn_raw_buffer_store_b32(narrow_pair_from_int16(__builtin_bit_cast(uint32_t, out[s2])), rt, (int)off2,
                                                   (int)((hix_row2<M, PIECES>(0, ph, s2) << p) * 2u), kStream);
     }
-    asm volatile("" ::"v"(touched));
 }
 
 // First decode pass of a b = 1 round at D = 2^24 (ten strided bits) on the matrix cores: index bits 14..23 of the H in
@@ -468,7 +466,7 @@ __global__ __launch_bounds__(512, 4) void k_dec_hix_first_mfma(DecBatch B, uint6
     const uint32_t sign_mask = row_exists ? kFp8Sign : 0u, two_mask = row_exists ? 0x40404040u : 0u;
     const uint32_t dc = wv >> 2, cbyte = wv & 3u;                // this wave's eight columns: byte cbyte of payload word dc
 
-    uint32_t next_w[2][2], next_arrived[2], touched = 0;
+    uint32_t next_w[2][2], next_arrived[2];
     fetch(column_block(0), next_w, next_arrived);
 #pragma unroll 1
     for (uint32_t k = 0; k < (uint32_t)TPW; ++k) {
@@ -485,7 +483,7 @@ __global__ __launch_bounds__(512, 4) void k_dec_hix_first_mfma(DecBatch B, uint6
         }
         __syncthreads();                                         // also: every wave has read the previous tile's second half
         if (k + 1 < (uint32_t)TPW) fetch(column_block(k + 1), next_w, next_arrived);
-        if constexpr (TPW == 1) touched = touch_payload_ahead<512, M, 1u << (p - 6)>(B, HALF ? 4u : 8u);
+        if constexpr (TPW == 1) touch_payload_ahead<512, M, 1u << (p - 6)>(B, HALF ? 4u : 8u);
 
         // ---- this wave's byte of this lane's 16 rows, four rows per register
         uint32_t Gn[2][2], Z[2][2];                              // [instruction q][rows 4 eps .. 4 eps + 3 of its eight]
@@ -628,7 +626,6 @@ __global__ __launch_bounds__(512, 4) void k_dec_hix_first_mfma(DecBatch B, uint6
             }
         }
     }
-    asm volatile("" ::"v"(touched));
 }
 
 bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int narrow) {        // all b = 1 or all b = 1/2 at D = 2^22 .. 2^24
