@@ -48,12 +48,15 @@ __device__ inline uint32_t xcd_local_tile(uint32_t tile = blockIdx.x) {
 // tiles start: every line would be shared by two runs (two XCDs) and fetched twice (measured: 64 MiB for a 32 MiB payload).
 // Rotates the column-block index of a tile so that the runs start on line boundaries.  `row_bytes`: payload bytes of one
 // tile row, a power of two below 128; `cb_bits`: log2 of the column blocks per row.
-__device__ inline uint32_t align_runs_to_lines(uint32_t tile, uint32_t cb_bits, const void *payload, uint32_t row_bytes) {
+__host__ __device__ inline uint32_t align_runs_to_lines(uint32_t tile, uint32_t cb_bits, const void *payload, uint32_t row_bytes) {
     const uint32_t per_line = 128u / row_bytes;
     const uint32_t shift = (uint32_t)(reinterpret_cast<uintptr_t>(payload) / row_bytes) & (per_line - 1u);
     const uint32_t mask = (1u << cb_bits) - 1u;
     return (tile & ~mask) | ((tile - shift) & mask);
 }
+
+// whether the first decode pass in 32-column tiles does so: at one bit a run is half a line wherever the payload starts on a multiple of 64
+__host__ __device__ constexpr bool rotates_tiles(uint32_t bits) { return bits == 2u || bits == 4u || bits == 8u; }
 
 // Decode: the payload of a workgroup that starts later on this XCD, brought into its L2 while this one computes.  Every workgroup of a
 // first decode pass begins with a read of 2^M short pieces of the payload and can do nothing else until they are there; messages
@@ -67,22 +70,33 @@ __device__ inline uint32_t align_runs_to_lines(uint32_t tile, uint32_t cb_bits, 
 // 364 -> 310 / 369 -> 319, b = 4 583 -> 539 / 607 -> 572; of 4 of 2^27, b = 4 1373 -> 1281 / 1399 -> 1303 (with what else changed between
 // the two builds: the sums of the last pass at b = 2 and 4).  Where an encode has just left the messages in the memory-side cache
 // nothing is gained or lost (a round of 16 of 11,173,962, b = 4 755 -> 755).
-// (Every read is inside that sender's payload: rows below 2^M, tiles below TILES.)
-// THREADS: of a workgroup; TILES: per sender, a multiple of 128; `row_bytes`: payload bytes of one tile row.
-template <uint32_t THREADS, int M, uint32_t TILES>
-__device__ inline void touch_payload_ahead(const DecBatch &B, uint32_t row_bytes) {
-    constexpr uint32_t kAhead = (1u << 18) / THREADS, kRows = (1u << M) / 16u;
+// THREADS: of a workgroup; TILES: per sender, a multiple of 128; `row_bytes`: payload bytes of one tile row; `rotated`: the pass rotates
+// its tiles by align_runs_to_lines.
+//
+// lines of a payload row that a run of 16 tiles shares
+__host__ __device__ constexpr uint32_t touch_lines_per_row(uint32_t row_bytes) { return row_bytes > 8u ? 2u : 1u; }
+// Where the thread's word lies in the payload of the sender of workgroup x (counted on over the senders); ~0: it has none.  (Inside the
+// payload: rows below 2^M, tiles below TILES.)
+template <int M, uint32_t TILES>
+__host__ __device__ inline uint32_t touch_place(uint32_t x, uint32_t thread, const void *payload, uint32_t row_bytes, bool rotated) {
+    constexpr uint32_t kRows = (1u << M) / 16u;
     static_assert(TILES % 128u == 0, "runs of 16 tiles on each of 8 XCDs, see xcd_local_tile");
-    const uint32_t x = blockIdx.x + kAhead, c = blockIdx.y + x / TILES;
-    const uint32_t per_row = row_bytes > 8u ? 2u : 1u;           // lines of a payload row that a run of 16 tiles shares
-    if (c >= gridDim.y || wave_in_block() * 64u >= kRows * per_row || threadIdx.x >= kRows * per_row) return;
+    const uint32_t per_row = touch_lines_per_row(row_bytes);
+    if (thread >= kRows * per_row) return ~0u;
+    const uint32_t q = (x % TILES) >> 3, run = (q / 16u) * 8u + (x & 7u);
+    const uint32_t row = (q % 16u) * kRows + thread / per_row;
+    uint32_t tile = run * 16u + thread % per_row * 8u;
+    if (rotated) tile = align_runs_to_lines(tile, (uint32_t)__builtin_ctz(TILES), payload, row_bytes);
+    return (row * TILES + tile) * row_bytes;
+}
+template <uint32_t THREADS, int M, uint32_t TILES>
+__device__ inline void touch_payload_ahead(const DecBatch &B, uint32_t row_bytes, bool rotated) {
+    const uint32_t x = blockIdx.x + (1u << 18) / THREADS, c = blockIdx.y + x / TILES;
+    if (c >= gridDim.y || wave_in_block() * 64u >= (1u << M) / 16u * touch_lines_per_row(row_bytes)) return;
     if (B.b_q8[c] != B.b_q8[blockIdx.y]) return;                 // `row_bytes` would not be that sender's
     const char *payload = static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES;
-    const uint32_t q = (x % TILES) >> 3, run = (q / 16u) * 8u + (x & 7u);
-    const uint32_t row = (q % 16u) * kRows + threadIdx.x / per_row;
-    uint32_t tile = run * 16u + threadIdx.x % per_row * 8u;
-    if ((row_bytes & (row_bytes - 1u)) == 0u) tile = align_runs_to_lines(tile, (uint32_t)__builtin_ctz(TILES), payload, row_bytes);
-    (void)*reinterpret_cast<const volatile uint32_t *>(payload + ((size_t)row * TILES + tile) * row_bytes);
+    const uint32_t at = touch_place<M, TILES>(x, threadIdx.x, payload, row_bytes, rotated);
+    if (at != ~0u) (void)*reinterpret_cast<const volatile uint32_t *>(payload + at);
 }
 
 template <int M>

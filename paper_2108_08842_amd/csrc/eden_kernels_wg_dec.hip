@@ -32,7 +32,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         int tb, tk;
         budget_of(b_q8, tb, tk);
         if (COIN) tb = (int)(ONLY - kCoinOnly);
-        if (tk == 1 && (tb == 2 || tb == 4 || tb == 8) && !B.codes[c])
+        if (tk == 1 && rotates_tiles((uint32_t)tb) && !B.codes[c])
             tile = align_runs_to_lines(tile, p - 5, static_cast<const char *>(B.msg[c]) + EDEN_HEADER_BYTES, 4u * (uint32_t)tb);
     }
     const uint64_t base = hix_base<M>(tile, p);
@@ -201,7 +201,10 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
             v[r] = keep_where(v[r], m);
         }
     }
-    if constexpr (ONLY != 0u) touch_payload_ahead<X::THREADS, M, 1u << (P - 5)>(B, 4u * (COIN ? ONLY - kCoinOnly : ONLY >> 8));
+    if constexpr (ONLY != 0u) {
+        constexpr uint32_t row_bytes = 4u * (COIN ? ONLY - kCoinOnly : ONLY >> 8);
+        touch_payload_ahead<X::THREADS, M, 1u << (P - 5)>(B, row_bytes, rotates_tiles(row_bytes / 4u));
+    }
     fwht_regs<64>(v);
     const uint32_t base_off = (uint32_t)base * 4u;
     const uint32_t off2 = (((g * X::RHL * X::RL) << p) + col) * 4u;
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, PIECES == 2 ? 4 : M == 9 ? 2 : 3) 
             v32[r] = __float_as_uint(keep_where(__uint_as_float(v32[r]), m));
         }
     }
-    touch_payload_ahead<X::THREADS, M, 1u << (P - 6)>(B, b_q8 == 256u ? 8u : 4u);
+    touch_payload_ahead<X::THREADS, M, 1u << (P - 6)>(B, b_q8 == 256u ? 8u : 4u, true);
     s16x2 v[64];
 #pragma unroll
     for (int r = 0; r < 64; ++r) v[r] = __builtin_bit_cast(s16x2, v32[r]);
@@ -483,7 +486,7 @@ __global__ __launch_bounds__(512, 4) void k_dec_hix_first_mfma(DecBatch B, uint6
         }
         __syncthreads();                                         // also: every wave has read the previous tile's second half
         if (k + 1 < (uint32_t)TPW) fetch(column_block(k + 1), next_w, next_arrived);
-        if constexpr (TPW == 1) touch_payload_ahead<512, M, 1u << (p - 6)>(B, HALF ? 4u : 8u);
+        if constexpr (TPW == 1) touch_payload_ahead<512, M, 1u << (p - 6)>(B, HALF ? 4u : 8u, true);
 
         // ---- this wave's byte of this lane's 16 rows, four rows per register
         uint32_t Gn[2][2], Z[2][2];                              // [instruction q][rows 4 eps .. 4 eps + 3 of its eight]

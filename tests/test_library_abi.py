@@ -107,6 +107,21 @@ def test_header_is_plain_c_and_library_links_from_c(eden, tmp_path):
     assert "abi ok" in out.stdout
 
 
+def test_lines_read_ahead_are_those_the_later_workgroups_read(tmp_path):
+    """Host code of the kernels' index arithmetic: which payload words a workgroup of a first decode pass reads ahead."""
+    import shutil
+    import subprocess
+    from paper_2108_08842_amd import build
+    if shutil.which(build.hipcc_path()) is None:
+        pytest.skip("no hipcc")
+    exe = tmp_path / "touch_check"
+    subprocess.run([build.hipcc_path(), "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2108_08842_amd", "csrc"), os.path.join(ROOT, "tests", "c", "touch_check.hip"),
+                    "-o", str(exe)], check=True, capture_output=True, text=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0 and "touch ok" in out.stdout, out.stdout
+
+
 def test_arrays_of_a_batch_hold_the_elements_of_any_sequence(eden):
     # ids, budgets, sizes and pointers as the C side reads them, from lists, tuples, ranges, numpy arrays and bytes (whose elements
     # count, not their memory); negative and oversized integers wrap; what has no length or is no integer is refused
