@@ -575,10 +575,12 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             // Strided pass first (every sender on its own), contiguous pass last (sums the senders in registers
             // and touches acc once).  The workspace of a b <= 1 sender holds fp16 (narrow_bits in eden_device.h).
             // (at D <= 2^18 the last pass works in place, one sender at a time: the same integers as fp32)
-            // m-of-64 senders (pre == 2) end up in fp32 slots from the start of the workspace; where it has room for their fp16 slots
-            // behind those, they too go through the matrix cores (whole decode, 16 senders of 11,173,962, m = 6 151 -> 143 us; 8 of
-            // them, m = 32 174 -> 137)
-            const bool behind = pre == 2 && pl.lo_bits == 14 && ((uint64_t)2 * nb << log2D) <= (uint64_t)ctx->slots * ctx->slot_floats;
+            // m-of-64 senders (pre == 2) end up in fp32 slots from the start of the workspace; where the kept vectors are padded to half the
+            // vector's own power of two or less, there is room for their fp16 slots behind those (nb slots of 2^log2D floats, twice), and they
+            // too go through the matrix cores (whole decode, 16 senders of 11,173,962, m = 6 151 -> 143 us; 8 of them, m = 32 174 -> 137).
+            // The rule asks for no more room than a context of any size has: sums of integers round differently from sums of values,
+            // and a mean is not to depend on d_max, n_max or the number of messages in the call.
+            const bool behind = pre == 2 && pl.lo_bits == 14 && log2D < ceil_log2(hdr_d);
             float *const work = behind ? ctx->T + ((size_t)nb << log2D) : ctx->T;
             const int narrow = ((pre == 2 && !behind) || pl.wide) ? 0 : pl.lo_bits == 12 ? 2 : 1;
             bool coins = false;                                  // the receiver draws and counts the same coins
