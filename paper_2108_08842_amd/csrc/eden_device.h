@@ -755,7 +755,7 @@ __device__ inline void write_enc_header(const EncBatch &B, uint32_t c, uint64_t 
 //   line per sender 10).
 // Encode, us, launches of their own -> this: 10 senders of 2^20, b = 2 38.9 -> 34.3; 32 of 2^17, b = 2 25.2 -> 20.9; 24 of 300,007, b = 2
 // 35.4 -> 30.8; 32 of 250,000, b = 1 23.8 -> 22.5; one of 20,000, b = 2 (where the workgroup that arrived last filled the thresholds,
-// too) 14.1 -> 13.4.  The workgroup-tile passes (D >= 2^21) keep the separate launches: with 512 workgroups per sender the arrivals
+// too) 14.1 -> 12.9.  The workgroup-tile passes (D >= 2^21) keep the separate launches: with 512 workgroups per sender the arrivals
 // alone take longer, and adding up 684 partial sums per workgroup costs 16 senders of 2^24 at b = 4 9 us.
 struct EncTail {
     uint32_t *arrived;      // kEncCounterStride words apart, a counter per sender, 0 between calls; null: launches of their own

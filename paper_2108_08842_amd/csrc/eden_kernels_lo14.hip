@@ -650,9 +650,11 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d_src, int pre
         while (K > 1 && (uint64_t)(K - 1) * rest > partial_tiles) --K;    // what the partial buffer holds
         // No more groups than it takes for the longest one, where that spares a third of them or where the workgroups would take up
         // nearly every slot of the chip (a CU with one workgroup runs it faster).  Whole decode, us, all groups / fewer: 10 senders of
-        // 2^20, b = 2 (512 -> 320 workgroups) 42.2 / 38.4; 20 of 2^20 (512 -> 448) 58.1 / 54.2; 9 of 2,000,000 (492 -> 369) 60.5 / 58.1; 14 of
-        // 600,000 (481 -> 259) 40.0 / 36.1; but 12 of 1,500,000 (460 -> 368) 54.6 / 58.5, 8 of 1,500,000 at b = 1 34.6 / 35.9 and 31 of
-        // 600,000 (481 -> 407) 51.2 / 53.5, which keep them all.
+        // 2^20, b = 2 (512 -> 320 workgroups) 40.3 / 32.4; 20 of 2^20 (512 -> 448) 56.4 / 51.2, b = 1 40.4 / 37.0; 9 of 2,000,000 (492 -> 369)
+        // 57.5 / 49.3, b = 1 41.3 / 37.8; 14 of 600,000 (481 -> 259) 37.7 / 30.4, b = 1 30.8 / 28.5; 12 of 800,000, b = 3 44.2 / 36.6.  At b = 1
+        // the others do better with all of them or the same: 8 of 1,500,000 33.0 / 34.1, 31 of 600,000 (481 -> 407) 41.6 / 41.7.  The kernel for
+        // values would do better with fewer there too (b = 2: 12 of 1,500,000, 460 -> 368, 55.0 / 49.6; 31 of 600,000 51.5 / 47.0); the rule
+        // keeps them all at every budget.
         const uint32_t most = (n + K - 1) / K, fewer = (n + most - 1) / most;
         if (3 * fewer <= 2 * K || 20 * K * tiles >= 19 * resident) K = fewer;
     }

@@ -311,9 +311,9 @@ def test_zero_and_nonfinite_vectors_of_every_budget_in_two_launches(ctx, d, n):
 
 
 @pytest.mark.parametrize("d,n", [(65_536, 16), (131_072, 16), (250_000, 16), (1_000_000, 4)])
-def test_messages_do_not_depend_on_the_number_of_launches(ctx, d, n):
-    # an encode call is two, three or four launches by the coordinates of all its senders and by whether one of them needs thresholds:
-    # a sender alone, among others and among others that all have b <= 1 writes the same message, bit for bit
+def test_messages_do_not_depend_on_the_other_senders(ctx, d, n):
+    # the kernels' instances are chosen by the budgets of all senders of a call: a sender alone, among others and among others that all
+    # have b <= 1 writes the same message, bit for bit
     from paper_2108_08842_amd import eden
     kinds = [256, 512, 1536, 128, 1024, eden.B_COIN(1.6), 384, eden.B_GRID(0.5224), 2048, 768]
     gen = torch.Generator(device="cuda").manual_seed(d)
