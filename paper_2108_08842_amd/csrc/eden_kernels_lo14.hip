@@ -1,10 +1,12 @@
 // The contiguous passes for D <= 2^24 (gfx950): the encoder's over 12 or 14 bits, the decoder's over 14.
 //
-// A workgroup owns 2^12 or 2^14 consecutive coordinates, 16 values per thread (EncLo here, lo_forward16 of eden_lo.h in the decoder); where
-// all values of a decode launch are small integers, ten of the 14 bits run on the matrix cores.  The encode pass is bound by memory where a
-// launch fills the chip (16 senders of 11,173,962: 1.43 GB at 6.1 TB/s, 32 values per thread the same) and by the length of a wave's
-// chain where it does not: encode of one sender of 20,000, b = 2 12.9 -> 10.5 us, 8 of 131,072 15.2 -> 13.0 with four waves per 4096
-// coordinates instead of one.
+// A workgroup owns 2^12 or 2^14 consecutive coordinates.  The encoder's transform is EncLo here, the decoder's lo_forward16 of eden_lo.h;
+// where all values of a decode launch are small integers, ten of the 14 bits run on the matrix cores.  The encode pass is bound by memory
+// where a launch fills the chip (16 senders of 11,173,962: 1.43 GB at 6.2 TB/s) and by the length of a wave's chain and the waves to be
+// started where it does not: encode of one sender of 20,000, b = 2 12.9 -> 10.5 us, 8 of 131,072 15.2 -> 13.0 with four waves of 16 values
+// per lane for 4096 coordinates instead of one of 64.  For 2^14 coordinates eight waves of 32 values do better than sixteen of 16 (us):
+// one of 8,000,000, b = 1 25.9 against 30.9, 4 of 11,173,962, b = 4 117.9 and 123.8, 10 of 2^20, b = 2 31.1 and 34.8, 16 of 2^20, b = 8 70.4 and
+// 74.9; only one of 300,007 takes 12.9 against 12.1.
 #include "eden_device.h"
 #include "eden_kernels.h"
 #include "eden_lo.h"
@@ -13,23 +15,23 @@ namespace eden {
 
 constexpr int kLo14Bits = 14;
 
-// The encoder's transform of a tile of 2^P coordinates by 2^P / 16 threads with 16 values each: three groups of stages in registers,
+// The encoder's transform of a tile of 2^P coordinates, VALUES of them per thread: three groups of stages in registers,
 // exchanges through LDS between them, the first between all waves, the others inside a wave, in the place this wave alone has just read.
 // The order of the stages is part of the results: sums round differently in another one, and an index next to a threshold moves
 // (8e-6 of the bytes at b = 8).  It is 6 .. 11, 0 .. 5 for P = 12 and 9 .. 13, 4 .. 8, 0 .. 3 for P = 14, and the groups are cut so
-// that the bits a group needs are the ones the exchange before it can bring into registers.  Against groups from the top bit down, with
-// one exchange more for P = 14 (encode, us): one sender of 20,000, b = 2 9.9 and 9.8; 32 of 250,000, b = 1 23.4 and 23.3; 10 of 2^20, b = 2
-// 31.2 -> 29.5; 8 of 4,000,037, b = 8 109.4 -> 106.9; 16 of 11,173,962, b = 1 374 and 375, one of them 36.1 -> 34.2, 16 with pairs before
-// the rotation 233 -> 239 (a wave's neighbours read the other half of the tile).
-//   at(t):        coordinate in the tile of v[0] on entry; v[a] is STEP a further on.  A register of a wave is 64 consecutive coordinates
-//   quad(t, j):   first coordinate of x[j] on return
+// that the bits a group needs are the ones the exchange before it can bring into registers.  Against passes that went from the top
+// bit down (encode, us): one sender of 20,000, b = 2 9.9 and 9.8; 32 of 250,000, b = 1 23.4 and 23.3; one of 300,007, b = 1 12.3 -> 12.9; 10 of
+// 2^20, b = 2 32.6 -> 31.1; 2 of 4,000,037, b = 2 31.9 -> 28.7; 8 of them, b = 8 114.5 -> 110.3; one of 8,000,000, b = 1 29.3 -> 25.9; 16 of
+// 11,173,962, b = 1 373 and 372, one of them 37.2 -> 35.9, 16 with pairs before the rotation 234 -> 240.
+//   wave_at(wv) + lane + STEP a   coordinate in the tile of v[a] on entry: a register of a wave is 64 consecutive coordinates
+//   quad(wv, lane, j)             first coordinate of x[j] on return
 template <int P> struct EncLo;
 
-//   P = 12  registers 6..9 | 10, 11, 0, 1 | 2..5; the waves are bits 10 and 11 before and bits 8 and 9 after the first exchange.
+//   P = 12  16 values: registers 6..9 | 10, 11, 0, 1 | 2..5; the waves are bits 10 and 11 before and bits 8 and 9 after the first exchange.
 //   A row of 64 coordinates keeps its place in LDS; its 16 quads are swizzled by bits 6, 7, 10, 11, so that both directions of the other
 //   exchanges, quads of bits 0 and 1 on one side and registers of bits 2..5 on the other, are free of bank conflicts.
 template <> struct EncLo<12> {
-    static constexpr uint32_t THREADS = 256, STEP = 64;
+    static constexpr uint32_t THREADS = 256, VALUES = 16, STEP = 64;
     static __device__ inline uint32_t wave_at(uint32_t wv) { return 1024u * wv; }
     static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) { return 1024u * j + 256u * wv + 4u * lane; }
     static __device__ inline void forward(float (&v)[16], float *lds, float4 (&x)[4]) {
@@ -65,41 +67,36 @@ template <> struct EncLo<12> {
     }
 };
 
-//   P = 14  registers 9..12 | 13, 4, 5, 6 | 7, 8, 0, 1, then 2 and 3 between the lanes of a quad; the waves are bits 6, 7, 8, 13 before and
-//   9..12 after the first exchange.  Bits 4 and 5 of the place in LDS are swizzled by bits 7 and 8 (no bank conflicts in any direction).
+//   P = 14  32 values: registers 9..13 | 4..8 | 0 and 1, then 2 and 3 between the lanes of a quad; the waves are bits 6..8 before and
+//   11..13 after the first exchange.  Bits 4 and 5 of the place in LDS are swizzled by bits 9 and 10 (no bank conflicts in any direction).
 //   The values leave as quads of bits 0 and 1 without a further exchange.
 template <> struct EncLo<14> {
-    static constexpr uint32_t THREADS = 1024, STEP = 512;
-    static __device__ inline uint32_t wave_at(uint32_t wv) { return 8192u * (wv >> 3) + 64u * (wv & 7u); }
-    static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) {
-        return 8192u * (lane >> 5) + 512u * wv + 128u * j + 4u * (lane & 31u);
-    }
-    static __device__ inline void forward(float (&v)[16], float *lds, float4 (&x)[4]) {
+    static constexpr uint32_t THREADS = 512, VALUES = 32, STEP = 512;
+    static __device__ inline uint32_t wave_at(uint32_t wv) { return 64u * wv; }
+    static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) { return 2048u * wv + 256u * j + 4u * lane; }
+    static __device__ inline void forward(float (&v)[32], float *lds, float4 (&x)[8]) {
         const uint32_t lane = lane_id(), wv = wave_in_block();
-        fwht_regs<16>(v);                                        // bits 9..12
-        const uint32_t from = wave_at(wv) + (lane ^ (16u * ((wv >> 1) & 3u)));
+        fwht_regs<32>(v);                                        // bits 9..13
 #pragma unroll
-        for (uint32_t a = 0; a < 16; ++a) lds[from + STEP * a] = v[a];
+        for (uint32_t a = 0; a < 32; ++a) lds[wave_at(wv) + STEP * a + (lane ^ (16u * (a & 3u)))] = v[a];
         __syncthreads();
-        // lane: bits 0..3, 7, 8; register r: bits 13, 4, 5, 6
-        const uint32_t one = 512u * wv + 128u * (lane >> 4) + (lane & 15u) + 16u * (lane >> 4);
+        // lane: bits 0..3, 9, 10; register r: bits 4..8
+        const uint32_t one = 2048u * wv + 512u * (lane >> 4) + (lane & 15u) + 16u * (lane >> 4);
 #pragma unroll
-        for (uint32_t r = 0; r < 16; ++r) v[r] = lds[(one ^ (16u * ((r >> 1) & 3u))) + 8192u * (r & 1u) + 64u * (r >> 3)];
-        fwht_regs<16>(v);                                        // bits 13, 4, 5, 6
+        for (uint32_t r = 0; r < 32; ++r) v[r] = lds[(one ^ (16u * (r & 3u))) + 64u * (r >> 2)];
+        fwht_regs<32>(v);                                        // bits 4..8
         wave_lds_sync();
 #pragma unroll
-        for (uint32_t r = 0; r < 16; ++r) lds[(one ^ (16u * ((r >> 1) & 3u))) + 8192u * (r & 1u) + 64u * (r >> 3)] = v[r];
+        for (uint32_t r = 0; r < 32; ++r) lds[(one ^ (16u * (r & 3u))) + 64u * (r >> 2)] = v[r];
         wave_lds_sync();
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {                       // j: bits 7, 8; lane: bits 2..6, 13
-            const float4 y = *reinterpret_cast<const float4 *>(&lds[quad(wv, lane, j) ^ (16u * j)]);
-            v[j] = y.x; v[j + 4] = y.y; v[j + 8] = y.z; v[j + 12] = y.w;
+        for (uint32_t j = 0; j < 8; ++j) {                       // j: bits 8..10; lane: bits 2..7
+            const float4 y = *reinterpret_cast<const float4 *>(&lds[quad(wv, lane, j) ^ (16u * (j >> 1))]);
+            const float p = y.x + y.y, q = y.x - y.y, r = y.z + y.w, s = y.z - y.w;              // bit 0
+            x[j] = make_float4(p + r, q + s, p - r, q - s);                                      // bit 1
         }
-        fwht_regs<16>(v);                                        // bits 7, 8, 0, 1
-        quad_stage<1>(v);                                        // bit 2
-        quad_stage<2>(v);                                        // bit 3
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) x[j] = make_float4(v[j], v[j + 4], v[j + 8], v[j + 12]);
+        for (uint32_t j = 0; j < 8; ++j) { quad_stage<1>(x[j]); quad_stage<2>(x[j]); }           // bits 2, 3
     }
 };
 
@@ -111,10 +108,11 @@ template <> struct EncLo<14> {
 // PRE (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is x'[g] = 2 x[2g + o_g],
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
 template <int P, bool PRE, bool BLOCKED>
-__global__ __launch_bounds__(EncLo<P>::THREADS, 8) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
+__global__ __launch_bounds__(EncLo<P>::THREADS, P == 12 ? 8 : 4) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
                                                             double *partials, uint32_t partial_stride, EncTail tail) {
     using L = EncLo<P>;
     constexpr uint32_t THREADS = L::THREADS;
+    constexpr int N = (int)L::VALUES;
     __shared__ __attribute__((aligned(16))) float lds[1 << P];
     __shared__ double red[THREADS / 64];
     const uint32_t c = blockIdx.y, lane = lane_id();
@@ -124,38 +122,38 @@ __global__ __launch_bounds__(EncLo<P>::THREADS, 8) void k_enc_lo_first(EncBatch 
     const uint32_t tile = blockIdx.x;                            // one tile per workgroup: the phases of two workgroups on a CU
                                                                  // interleave better than two tiles in one workgroup with the
                                                                  // second one's loads issued early
-    // register a of this wave is 64 consecutive coordinates = one sign word; lane l hashes the word of register l % 16.  With PRE an
+    // register a of this wave is 64 consecutive coordinates = one sign word; lane l hashes the word of register l % N.  With PRE an
     // element comes from x[2 i + o_i], and the register is 64 pairs = one word of offsets
     const uint32_t first = (tile << P) + L::wave_at(wv);
-    const uint64_t word = (first >> 6) + (L::STEP / 64u) * (lane & 15u);
-    float u[16];
+    const uint64_t word = (first >> 6) + (L::STEP / 64u) * (lane & (uint32_t)(N - 1));
+    float u[N];
     if constexpr (PRE) {
         const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), word);
 #pragma unroll
-        for (int a = 0; a < 16; ++a) {
+        for (int a = 0; a < N; ++a) {
             const uint32_t odd = __builtin_amdgcn_inverse_ballot_w64(wave_read64(offs, a)) ? 4u : 0u;
             u[a] = 2.0f * buf_load(rx, 8u * lane + odd, 8u * (first + L::STEP * a));
         }
     } else {
 #pragma unroll
-        for (int a = 0; a < 16; ++a) u[a] = buf_load(rx, 4u * lane, 4u * (first + L::STEP * a));
+        for (int a = 0; a < N; ++a) u[a] = buf_load(rx, 4u * lane, 4u * (first + L::STEP * a));
     }
     const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), word);
     double n2 = 0.0;
 #pragma unroll
-    for (int a = 0; a < 16; ++a) {
+    for (int a = 0; a < N; ++a) {
         n2 += (double)u[a] * (double)u[a];
         if ((a & 7) == 7) __builtin_amdgcn_sched_barrier(0);     // keeps the widened values of one group live at a time
     }
 #pragma unroll
-    for (int a = 0; a < 16; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;   // + 0: no negative zeros
-    // whole lines leave: 64 lanes (P = 14: 32) hold as many consecutive quads.  BLOCKED: the 128-byte segments of kBlockRows
+    for (int a = 0; a < N; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;   // + 0: no negative zeros
+    // whole lines leave: the lanes of a wave hold consecutive quads.  BLOCKED: the 128-byte segments of kBlockRows
     // consecutive rows are interleaved (see blocked_offset).  (Write-back stores: with the streaming hint this pass ran 13% slower; the pass
     // that reads the tiles back does better with the hint on its loads.)
-    float4 x[4];
+    float4 x[N / 4];
     L::forward(u, lds, x);
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) {
+    for (uint32_t j = 0; j < (uint32_t)N / 4u; ++j) {
         const uint32_t at = L::quad(wv, lane, j);
         *reinterpret_cast<float4 *>(Tc + (BLOCKED ? blocked_offset<P>(tile, at >> 5) + (at & 31u) : ((size_t)tile << P) + at)) = x[j];
     }

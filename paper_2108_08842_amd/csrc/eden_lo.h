@@ -30,11 +30,17 @@ struct Lo16 {
 
 // one butterfly stage between lanes that differ in lane bit X = 1 or 2
 template <int X>
-__device__ inline void quad_stage(float (&v)[16]) {
+__device__ inline void quad_stage(float &v) {
     const float sign = (threadIdx.x & (uint32_t)X) ? -1.0f : 1.0f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) v[e] = fmaf(v[e], sign, __uint_as_float(lane_xor_u32<X>(__float_as_uint(v[e]))));
+    v = fmaf(v, sign, __uint_as_float(lane_xor_u32<X>(__float_as_uint(v))));
 }
+template <int X>
+__device__ inline void quad_stage(float (&v)[16]) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) quad_stage<X>(v[e]);
+}
+template <int X>
+__device__ inline void quad_stage(float4 &v) { quad_stage<X>(v.x); quad_stage<X>(v.y); quad_stage<X>(v.z); quad_stage<X>(v.w); }
 
 // in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed.  The caller puts a barrier between a
 // use of `lds` and the next one.
