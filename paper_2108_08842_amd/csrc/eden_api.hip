@@ -301,7 +301,8 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
             {
                 Timed t(ctx, EDEN_K_ENC_FIRST, nb, st);
                 nparts_n2 = pl.lo_bits >= 15 ? launch_enc_lo15_first(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
-                                             : launch_enc_lo_first(pl.lo_bits, B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail, st);
+                                             : launch_enc_lo_first(pl.lo_bits, B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail,
+                                                                   ctx->compute_units, st);
             }
             tail.n2_count = nparts_n2;
             if (need_thresholds && !two_launches) {

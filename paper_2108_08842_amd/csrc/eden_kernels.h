@@ -92,7 +92,7 @@ bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int nar
 // `blocked` (P = 14): write the workspace in the blocked layout (eden_device.h: blocked_offset) that launch_enc_hix_last reads
 // when told so; not for a first pass that works in place on the workspace
 uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d, int pre, int blocked, int log2D, uint64_t seed, float *T,
-                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st);
+                             double *partials, uint32_t partial_stride, const EncTail &tail, uint32_t compute_units, hipStream_t st);
 // `resident`: workgroups of the kernel the device holds at once (2 per CU); `partial`: room for `partial_tiles`
 // tiles of 2^14 floats, used when tiles are split over several workgroups by sender.
 // `mean_n` > 0 (pre == 0 only): acc is not read; acc[i] = (0 + the sum over the senders) / mean_n

@@ -4,9 +4,7 @@
 // where all values of a decode launch are small integers, ten of the 14 bits run on the matrix cores.  The encode pass is bound by memory
 // where a launch fills the chip (16 senders of 11,173,962: 1.43 GB at 6.2 TB/s) and by the length of a wave's chain and the waves to be
 // started where it does not: encode of one sender of 20,000, b = 2 12.9 -> 10.5 us, 8 of 131,072 15.2 -> 13.0 with four waves of 16 values
-// per lane for 4096 coordinates instead of one of 64.  For 2^14 coordinates eight waves of 32 values do better than sixteen of 16 (us):
-// one of 8,000,000, b = 1 25.9 against 30.9, 4 of 11,173,962, b = 4 117.9 and 123.8, 10 of 2^20, b = 2 31.1 and 34.8, 16 of 2^20, b = 8 70.4 and
-// 74.9; only one of 300,007 takes 12.9 against 12.1.
+// per lane for 4096 coordinates instead of one of 64.
 #include "eden_device.h"
 #include "eden_kernels.h"
 #include "eden_lo.h"
@@ -20,18 +18,18 @@ constexpr int kLo14Bits = 14;
 // The order of the stages is part of the results: sums round differently in another one, and an index next to a threshold moves
 // (8e-6 of the bytes at b = 8).  It is 6 .. 11, 0 .. 5 for P = 12 and 9 .. 13, 4 .. 8, 0 .. 3 for P = 14, and the groups are cut so
 // that the bits a group needs are the ones the exchange before it can bring into registers.  Against passes that went from the top
-// bit down (encode, us): one sender of 20,000, b = 2 9.9 and 9.8; 32 of 250,000, b = 1 23.4 and 23.3; one of 300,007, b = 1 12.3 -> 12.9; 10 of
+// bit down (encode, us): one sender of 20,000, b = 2 9.9 and 9.8; 32 of 250,000, b = 1 23.4 and 23.3; one of 300,007, b = 1 12.4 and 12.2; 10 of
 // 2^20, b = 2 32.6 -> 31.1; 2 of 4,000,037, b = 2 31.9 -> 28.7; 8 of them, b = 8 114.5 -> 110.3; one of 8,000,000, b = 1 29.3 -> 25.9; 16 of
 // 11,173,962, b = 1 373 and 372, one of them 37.2 -> 35.9, 16 with pairs before the rotation 234 -> 240.
 //   wave_at(wv) + lane + STEP a   coordinate in the tile of v[a] on entry: a register of a wave is 64 consecutive coordinates
 //   quad(wv, lane, j)             first coordinate of x[j] on return
-template <int P> struct EncLo;
+template <int P, int WAVES> struct EncLo;
 
-//   P = 12  16 values: registers 6..9 | 10, 11, 0, 1 | 2..5; the waves are bits 10 and 11 before and bits 8 and 9 after the first exchange.
+//   P = 12  4 waves, 16 values: registers 6..9 | 10, 11, 0, 1 | 2..5; the waves are bits 10 and 11 before and bits 8 and 9 after the first exchange.
 //   A row of 64 coordinates keeps its place in LDS; its 16 quads are swizzled by bits 6, 7, 10, 11, so that both directions of the other
 //   exchanges, quads of bits 0 and 1 on one side and registers of bits 2..5 on the other, are free of bank conflicts.
-template <> struct EncLo<12> {
-    static constexpr uint32_t THREADS = 256, VALUES = 16, STEP = 64;
+template <> struct EncLo<12, 4> {
+    static constexpr uint32_t VALUES = 16, STEP = 64;
     static __device__ inline uint32_t wave_at(uint32_t wv) { return 1024u * wv; }
     static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) { return 1024u * j + 256u * wv + 4u * lane; }
     static __device__ inline void forward(float (&v)[16], float *lds, float4 (&x)[4]) {
@@ -67,11 +65,11 @@ template <> struct EncLo<12> {
     }
 };
 
-//   P = 14  32 values: registers 9..13 | 4..8 | 0 and 1, then 2 and 3 between the lanes of a quad; the waves are bits 6..8 before and
+//   P = 14  8 waves, 32 values: registers 9..13 | 4..8 | 0 and 1, then 2 and 3 between the lanes of a quad; the waves are bits 6..8 before and
 //   11..13 after the first exchange.  Bits 4 and 5 of the place in LDS are swizzled by bits 9 and 10 (no bank conflicts in any direction).
 //   The values leave as quads of bits 0 and 1 without a further exchange.
-template <> struct EncLo<14> {
-    static constexpr uint32_t THREADS = 512, VALUES = 32, STEP = 512;
+template <> struct EncLo<14, 8> {
+    static constexpr uint32_t VALUES = 32, STEP = 512;
     static __device__ inline uint32_t wave_at(uint32_t wv) { return 64u * wv; }
     static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) { return 2048u * wv + 256u * j + 4u * lane; }
     static __device__ inline void forward(float (&v)[32], float *lds, float4 (&x)[8]) {
@@ -100,6 +98,43 @@ template <> struct EncLo<14> {
     }
 };
 
+//   P = 14  16 waves, 16 values: registers 9..12 | 13, 4, 5, 6 | 7, 8, 0, 1, then 2 and 3 between the lanes of a quad; the waves are bits
+//   6, 7, 8, 13 before and 9..12 after the first exchange.  Bits 4 and 5 of the place in LDS are swizzled by bits 7 and 8.
+template <> struct EncLo<14, 16> {
+    static constexpr uint32_t VALUES = 16, STEP = 512;
+    static __device__ inline uint32_t wave_at(uint32_t wv) { return 8192u * (wv >> 3) + 64u * (wv & 7u); }
+    static __device__ inline uint32_t quad(uint32_t wv, uint32_t lane, uint32_t j) {
+        return 8192u * (lane >> 5) + 512u * wv + 128u * j + 4u * (lane & 31u);
+    }
+    static __device__ inline void forward(float (&v)[16], float *lds, float4 (&x)[4]) {
+        const uint32_t lane = lane_id(), wv = wave_in_block();
+        fwht_regs<16>(v);                                        // bits 9..12
+        const uint32_t from = wave_at(wv) + (lane ^ (16u * ((wv >> 1) & 3u)));
+#pragma unroll
+        for (uint32_t a = 0; a < 16; ++a) lds[from + STEP * a] = v[a];
+        __syncthreads();
+        // lane: bits 0..3, 7, 8; register r: bits 13, 4, 5, 6
+        const uint32_t one = 512u * wv + 128u * (lane >> 4) + (lane & 15u) + 16u * (lane >> 4);
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) v[r] = lds[(one ^ (16u * ((r >> 1) & 3u))) + 8192u * (r & 1u) + 64u * (r >> 3)];
+        fwht_regs<16>(v);                                        // bits 13, 4, 5, 6
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t r = 0; r < 16; ++r) lds[(one ^ (16u * ((r >> 1) & 3u))) + 8192u * (r & 1u) + 64u * (r >> 3)] = v[r];
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {                       // j: bits 7, 8; lane: bits 2..6, 13
+            const float4 y = *reinterpret_cast<const float4 *>(&lds[quad(wv, lane, j) ^ (16u * j)]);
+            v[j] = y.x; v[j + 4] = y.y; v[j + 8] = y.z; v[j + 12] = y.w;
+        }
+        fwht_regs<16>(v);                                        // bits 7, 8, 0, 1
+        quad_stage<1>(v);                                        // bit 2
+        quad_stage<2>(v);                                        // bit 3
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) x[j] = make_float4(v[j], v[j + 4], v[j + 8], v[j + 12]);
+    }
+};
+
 // Encode, first pass: x -> T.  Zero padding (Sec. 5: the transform needs a power of two), the sign diagonal of
 // the rotation from the shared seed (Sec. 2.1), |x|^2 for eta and S (Sec. 2.2.1, 2.3), index bits 0 .. P-1 of H, P = 12 or 14.
 // Only the ceil(d / 2^P) tiles that hold part of x (rounded up to whole blocks of rows in the blocked layout) are
@@ -107,14 +142,15 @@ template <> struct EncLo<14> {
 // as zero through its buffer bounds.
 // PRE (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is x'[g] = 2 x[2g + o_g],
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
-template <int P, bool PRE, bool BLOCKED>
-__global__ __launch_bounds__(EncLo<P>::THREADS, P == 12 ? 8 : 4) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
+// WAVES: of a workgroup.  |x|^2 is the same to the last bit for both numbers at P = 14: eight waves keep the sums of the two values of
+// bit 13, which tell sixteen waves apart, to themselves.
+template <int P, int WAVES, bool PRE, bool BLOCKED>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 8) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
                                                             double *partials, uint32_t partial_stride, EncTail tail) {
-    using L = EncLo<P>;
-    constexpr uint32_t THREADS = L::THREADS;
+    using L = EncLo<P, WAVES>;
     constexpr int N = (int)L::VALUES;
     __shared__ __attribute__((aligned(16))) float lds[1 << P];
-    __shared__ double red[THREADS / 64];
+    __shared__ double red[WAVES * N / 16];
     const uint32_t c = blockIdx.y, lane = lane_id();
     const uint32_t wv = wave_in_block();
     const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));           // reads past d_src give the zero padding
@@ -139,10 +175,10 @@ __global__ __launch_bounds__(EncLo<P>::THREADS, P == 12 ? 8 : 4) void k_enc_lo_f
         for (int a = 0; a < N; ++a) u[a] = buf_load(rx, 4u * lane, 4u * (first + L::STEP * a));
     }
     const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), word);
-    double n2 = 0.0;
+    double n2[N / 16] = {};
 #pragma unroll
     for (int a = 0; a < N; ++a) {
-        n2 += (double)u[a] * (double)u[a];
+        n2[a / 16] += (double)u[a] * (double)u[a];
         if ((a & 7) == 7) __builtin_amdgcn_sched_barrier(0);     // keeps the widened values of one group live at a time
     }
 #pragma unroll
@@ -157,9 +193,19 @@ __global__ __launch_bounds__(EncLo<P>::THREADS, P == 12 ? 8 : 4) void k_enc_lo_f
         const uint32_t at = L::quad(wv, lane, j);
         *reinterpret_cast<float4 *>(Tc + (BLOCKED ? blocked_offset<P>(tile, at >> 5) + (at & 31u) : ((size_t)tile << P) + at)) = x[j];
     }
-    const double block_total = block_sum<(int)THREADS>(n2, red);
-    if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
-    enc_first_side<(int)THREADS>(tail, c, B.b_q8[c]);
+#pragma unroll
+    for (int i = 0; i < N / 16; ++i) {
+        const double sum = wave_sum(n2[i]);
+        if (lane == 0) red[i * WAVES + wv] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double total = 0.0;
+#pragma unroll
+        for (int i = 0; i < WAVES * N / 16; ++i) total += red[i];
+        partials[(size_t)c * partial_stride + blockIdx.x] = total;
+    }
+    enc_first_side<64 * WAVES>(tail, c, B.b_q8[c]);
 }
 
 // Decode, last pass: index bits 0..13 of H for every sender, that sender's sign diagonal (R^-1 = s o D^-1/2 H,
@@ -603,18 +649,28 @@ __global__ __launch_bounds__(256) void k_dec_lo14_combine(float *acc, uint64_t d
 }
 
 uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int blocked, int log2D, uint64_t seed, float *T,
-                             double *partials, uint32_t partial_stride, const EncTail &tail, hipStream_t st) {
+                             double *partials, uint32_t partial_stride, const EncTail &tail, uint32_t compute_units, hipStream_t st) {
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
     uint32_t tiles = (uint32_t)((d + (1u << P) - 1) >> P);
     // blocked layout: whole blocks of rows are written (a tile beyond d reads zeros and stores zeros), so that the strided
     // pass finds no unwritten row inside a block
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
-#define EDEN_ENC_LO(P, PRE, BLK) \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, PRE, BLK>), grid, dim3(EncLo<P>::THREADS), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
-    if (P == 12) { if (pre) EDEN_ENC_LO(12, true, false); else EDEN_ENC_LO(12, false, false); }
-    else if (pre) { if (blocked) EDEN_ENC_LO(14, true, true); else EDEN_ENC_LO(14, true, false); }
-    else { if (blocked) EDEN_ENC_LO(14, false, true); else EDEN_ENC_LO(14, false, false); }
+#define EDEN_ENC_LO(P, WAVES, PRE, BLK) \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, WAVES, PRE, BLK>), grid, dim3(64 * WAVES), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
+#define EDEN_ENC_LO14(WAVES) \
+    do { \
+        if (pre) { if (blocked) EDEN_ENC_LO(14, WAVES, true, true); else EDEN_ENC_LO(14, WAVES, true, false); } \
+        else { if (blocked) EDEN_ENC_LO(14, WAVES, false, true); else EDEN_ENC_LO(14, WAVES, false, false); } \
+    } while (0)
+    // Sixteen waves while every workgroup has a CU to itself, eight beyond.  Encode, us, sixteen / eight: one sender of 300,007, b = 1 (19
+    // workgroups) 12.2 / 12.8, of 2^20, b = 2 (64) 14.8 / 15.3, of 1,500,000, b = 1 (92) 15.9 / 16.3, 4 of 2^20, b = 2 (256) 17.8 / 18.5.  Beyond, cards
+    // of one kind differ: 10 of 2^20, b = 2 (640) 29.6 / 30.6 and one of 7,500,000, b = 1 (460) 23.9 / 24.9 on one, 34.8 / 31.1 and, of 8,000,000
+    // (492), 30.9 / 25.9 on another, where a launch of 16 waves a workgroup takes 17 or 23 us from one call to the next.
+    if (P == 12) { if (pre) EDEN_ENC_LO(12, 4, true, false); else EDEN_ENC_LO(12, 4, false, false); }
+    else if (tiles * n <= compute_units) EDEN_ENC_LO14(16);
+    else EDEN_ENC_LO14(8);
+#undef EDEN_ENC_LO14
 #undef EDEN_ENC_LO
     return grid.x;
 }

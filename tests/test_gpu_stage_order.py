@@ -54,3 +54,22 @@ def test_bytes_are_those_of_plain_butterflies_in_the_same_order(d):
             assert moved == 0, (seed, client, moved)
     assert ctx.last_device_status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("d,n", [(300_007, 16), (1 << 20, 5), (1_500_000, 3), (4_000_037, 2)])
+@pytest.mark.parametrize("b_q8", [512, 2048, "pre"])
+def test_messages_do_not_depend_on_the_waves_of_a_workgroup(d, n, b_q8):
+    # one sender's tiles have a CU each and sixteen waves, those of n senders more than 256 workgroups and eight waves: the same message,
+    # header and all (pairs before the rotation: half the tiles, so twice the senders)
+    from paper_2108_08842_amd import eden
+    if b_q8 == "pre":
+        b_q8, n = eden.B_HALF_PRE, 2 * n + 1
+    ctx = eden.Context(d_max=d, n_max=n, device=0)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    xs = [torch.randn(d, generator=gen, device="cuda") for _ in range(n)]
+    among = ctx.encode(xs, list(range(n)), [b_q8] * n, 11)
+    for c in (0, n - 1):
+        alone = ctx.encode([xs[c]], [c], [b_q8], 11)[0]
+        assert torch.equal(alone, among[c]), c
+    assert ctx.last_device_status() == 0
+    ctx.close()
