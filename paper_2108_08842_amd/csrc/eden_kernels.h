@@ -91,6 +91,7 @@ bool dec_hix_first_prepares(int M, int P, const DecBatch &B, uint32_t n, int nar
 // 12- and 14-bit contiguous passes for D <= 2^24 (eden_kernels_lo14.hip)
 // `blocked` (P = 14): write the workspace in the blocked layout (eden_device.h: blocked_offset) that launch_enc_hix_last reads
 // when told so; not for a first pass that works in place on the workspace
+// `compute_units`: of the device; a launch that gives every workgroup one of its own takes more waves per workgroup
 uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d, int pre, int blocked, int log2D, uint64_t seed, float *T,
                              double *partials, uint32_t partial_stride, const EncTail &tail, uint32_t compute_units, hipStream_t st);
 // `resident`: workgroups of the kernel the device holds at once (2 per CU); `partial`: room for `partial_tiles`
