@@ -32,9 +32,9 @@ def _transformed(x, seed, client, log2D):
     return u
 
 
-# sizes: the smallest multi-pass dimension, both contiguous tiles with ragged ends, every kind of strided pass up to the last plan of two
-# launches' worth of bits (2^24).  No byte may differ: additions, thresholds and compares are the same operations.  (Another order
-# differed in 6e-6 to 8e-6 of the bytes: one or more from 2^18 on.)
+# sizes: the smallest multi-pass dimension, both contiguous tiles with ragged ends and every kind of strided pass, up to the largest
+# dimension of a 14-bit contiguous pass.  No byte may differ: additions, thresholds and compares are the same operations.  (Another order
+# differed in 6e-6 to 8e-6 of the bytes: some at every size from 2^16 on.)
 @pytest.mark.parametrize("d", [4097, 40_003, 250_000, 300_007, 1 << 20, 1_500_000, 4_000_037, (1 << 23) - 1, 11_173_962, 1 << 24])
 def test_bytes_are_those_of_plain_butterflies_in_the_same_order(d):
     from paper_2108_08842_amd import eden
