@@ -300,7 +300,8 @@ static int encode_range(eden_ctx *ctx, const float *const *x_dev, const uint32_t
                 blocked = blocked && !(B.x[i] >= ctx->T && B.x[i] < ctx->T + (size_t)ctx->slots * ctx->slot_floats);
             {
                 Timed t(ctx, EDEN_K_ENC_FIRST, nb, st);
-                nparts_n2 = pl.lo_bits >= 15 ? launch_enc_lo15_first(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride, st)
+                nparts_n2 = pl.lo_bits >= 15 ? launch_enc_lo15_first(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, part_n2, ctx->partial_stride,
+                                                                     ctx->compute_units, st)
                                              : launch_enc_lo_first(pl.lo_bits, B, nb, d_src, pre, blocked, log2D, seed, ctx->T, part_n2, ctx->partial_stride, tail,
                                                                    ctx->compute_units, st);
             }

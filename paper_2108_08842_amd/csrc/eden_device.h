@@ -293,6 +293,18 @@ __device__ inline void lane_pair(uint32_t v, uint32_t &lower, uint32_t &upper) {
     const auto r = X == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
     lower = r[0]; upper = r[1];
 }
+// One butterfly stage between the halves of a wave: register pairs 2 i, 2 i + 1 swap, so that afterwards bit 0 of the register index
+// stands for what lane bit 5 stood for, and lane bit 5 for what bit 0 of the register index did.
+template <int N>
+__device__ inline void swap_stage32(float (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i += 2) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 1]), false, false);
+        const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
+        v[i] = a + b;
+        v[i + 1] = a - b;
+    }
+}
 template <int X>
 __device__ inline double pair_sum(double v) {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
@@ -898,38 +910,6 @@ template <int P>
 __host__ __device__ inline size_t blocked_offset(uint32_t row, uint32_t cb) {
     return ((size_t)(row >> kBlockRowBits) << (P + kBlockRowBits)) + ((size_t)cb << (5 + kBlockRowBits)) +
            ((size_t)(row & (kBlockRows - 1u)) << 5);
-}
-
-// Stores the 32 consecutive values every thread holds after the last stage of a contiguous pass over P bits as whole 128-byte lines: thread t's
-// run starts at coordinate 32 t of the (half) tile, so a wave owns 2048 consecutive coordinates; a wave-private
-// transpose through LDS (quads swizzled by the low three bits of the row: eight neighbouring lanes then hit 32
-// different banks in both directions; measured with SQ_LDS_BANK_CONFLICT) lets 8 neighbouring lanes store one line.
-// `L`: this wave's 2048 floats of LDS; `Tc`: the sender's workspace slot; `tile`: the tile = row of the strided
-// pass; `segment`: the wave's first run of 32 coordinates inside the row.
-// BLOCKED: the 128-byte segments of kBlockRows consecutive rows are interleaved (see blocked_offset): the strided pass
-// then finds kBlockRows of its 128-byte pieces next to each other.  Stores cost the same either way (6.9 TB/s in a pure
-// store loop); a pure read of the strided pattern went from 4.8 to 5.9 TB/s.
-template <int P, bool BLOCKED>
-__device__ inline void store_runs(const float (&v)[32], float *L, float *Tc, uint32_t tile, uint32_t segment) {
-    const uint32_t lane = threadIdx.x & 63u;
-    wave_lds_sync();
-    const uint32_t swz = lane & 7u;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        *reinterpret_cast<float4 *>(&L[lane * 32u + 4u * ((uint32_t)q ^ swz)]) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    wave_lds_sync();
-    const uint32_t pos = lane & 7u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint32_t row = 8u * (uint32_t)j + (lane >> 3);     // segment of 32 coordinates inside the wave's 2048
-        const float4 x = *reinterpret_cast<const float4 *>(&L[row * 32u + 4u * pos]);
-        const uint32_t quad = pos ^ (row & 7u);
-        // (write-back stores: with the streaming hint this pass ran 13% slower; the pass that reads the tiles back does
-        // better with the hint on its loads)
-        const size_t at = BLOCKED ? blocked_offset<P>(tile, segment + row) + 4u * quad
-                                  : ((size_t)tile << P) + 32u * (segment + row) + 4u * quad;
-        *reinterpret_cast<float4 *>(Tc + at) = x;
-    }
 }
 
 // ---- coin budgets: positions in the second part of the payload

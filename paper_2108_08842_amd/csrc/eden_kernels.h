@@ -105,7 +105,7 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, in
 // 15- and 16-bit contiguous passes for D = 2^25 .. 2^27 (eden_kernels_lo15.hip): the encoder's always writes the blocked layout,
 // the decoder's takes every b <= 1 sender's slot as fp16; pre == 2 (one output per sender) does not exist here
 uint32_t launch_enc_lo15_first(int P, const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
-                               double *partials, uint32_t partial_stride, hipStream_t st);
+                               double *partials, uint32_t partial_stride, uint32_t compute_units, hipStream_t st);
 void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, const float *T,
                           const DecScratch *scratch, float *acc, float mean_n, hipStream_t st);
 

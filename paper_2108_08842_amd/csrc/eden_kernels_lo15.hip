@@ -1,7 +1,7 @@
 // The contiguous passes of D = 2^25 .. 2^27 (gfx950): 15 or 16 index bits, so that two passes through memory do (the strided pass
 // takes the 10 or 11 bits above, eden_hix.h).
 //
-// A workgroup of 16 waves transforms 2^15 coordinates, 32 per thread, in three groups of five butterfly stages:
+// The decoder: a workgroup of 16 waves transforms 2^15 coordinates, 32 per thread, in three groups of five butterfly stages:
 //
 //   group 1   bits 10..14  v[a] = coordinate 1024 a + t (coalesced loads)
 //   exchange  through LDS between all waves (registers <-> bits 5..9), 128 KiB
@@ -13,13 +13,15 @@
 // 2^16; both read all of it, one transforms the sums of its halves, the other the differences (the stage over bit 15).  2^16
 // values and as many sums over the senders would be the whole register file of a CU.  The pair runs at the same time on the same
 // XCD (workgroups i and i + 8), so the second read of a line is meant to find it in that XCD's L2.
-// (measured: the encoder's pass fetches every line from memory once).
-// It replaces a 14-bit contiguous pass and a second strided pass (one more trip through memory per direction).  8 senders of 2^27,
-// b = 4: this pass 1.96 ms (encode) and 1.10 ms (decode), the strided ones 1.37 and 1.39 ms (1.22 with touch_payload_ahead); a round 8.03 -> 5.85 ms; at 2^25
-// 1.94 -> 1.16 ms, with b = 1 1.91 -> 0.91 ms.  With one workgroup per CU what is left is the time in which its waves all wait
-// for memory or all compute (vector instructions 48%, 31% of the time).
+// With one workgroup per CU what is left is the time in which its waves all wait for memory or all compute.
+//
+// The encoder has no sums to keep: see k_enc_lo15_first, k_enc_lo16_first.
+//
+// The two replace a 14-bit contiguous pass and a second strided pass (one more trip through memory per direction): a round of 8 senders of 2^27,
+// b = 4 8.03 -> 5.85 ms; at 2^25 1.94 -> 1.16 ms, with b = 1 1.91 -> 0.91 ms.
 #include "eden_device.h"
 #include "eden_kernels.h"
+#include "eden_lo.h"
 
 namespace eden {
 
@@ -63,20 +65,71 @@ __device__ inline void lo15_tile(uint32_t &tile, uint32_t &half) {
 }
 
 // Encode, first pass: x -> T (see k_enc_lo_first), always in the blocked layout.
-template <bool PRE, bool HALVES>
-__global__ __launch_bounds__(1024) void k_enc_lo15_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
-                                                         double *partials, uint32_t partial_stride) {
-    static_assert(!(PRE && HALVES), "a vector sparsified by pairs has at most 2^26 coordinates");
-    constexpr int P = HALVES ? 16 : 15;
-    __shared__ __attribute__((aligned(16))) float lds[kLo15LdsWords];
+//
+// The stages run over bits (15,) 10 .. 14, 5 .. 9, 0 .. 4 in this order (sums round differently in another one, and an index next to a
+// threshold moves).  Behind those over bits 10..14 the 1024 coordinates of a register are a transform of their own, so the tile goes through the
+// LDS in pieces of 16 registers, a wave taking one of them, 16 values per lane, through all ten stages left.  An exchange of the whole tile
+// took 144 KiB and one workgroup per CU; a piece takes 64 KiB, so that
+// - at P = 15 a second workgroup on the CU (64 registers) computes while the waves of the first wait for memory: encode of 4 senders of
+//   60,000,001 sparsified by pairs 363 -> 347 us, of 8 of 2^25, b = 1 617 -> 612 (this pass: 5.5 TB/s, a copy's rate);
+// - at P = 16 one workgroup holds the whole tile and loads the next one meanwhile, where two workgroups read it twice (k_enc_lo16_first).
+//   v[a] = coordinate 1024 a + t; piece q: a = 16 q + wave
+//   registers 5..8, lanes 0..4 and 9 | bit 9 against bit 5 between the halves of the wave | exchange inside the wave: quads of bits 0 and 1,
+//   then 2, 3, 4 between lanes 1, 2 and 8 apart
+// `mine`: the 1024 floats of LDS with this wave's coordinates; x[j] on return: the quad at lo15_quad(j), transformed
+__device__ inline uint32_t lo15_quad(uint32_t lane, uint32_t j) {
+    return 256u * j + 64u * (lane >> 4) + 32u * ((lane >> 2) & 1u) + 16u * ((lane >> 3) & 1u) + 4u * (lane & 3u);
+}
+__device__ inline void lo15_piece_forward(float *mine, uint32_t lane, float4 (&x)[4]) {
+    const float *from = mine + 512u * (lane >> 5) + (lane & 31u);
+    float y[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) y[r] = from[32 * r];
+    fwht_regs<16>(y);                                            // bits 5..8
+    swap_stage32(y);                                             // bit 9: register bit 0 now is bit 9, lane bit 5 is bit 5
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mine[512 * (r & 1) + 64 * (r >> 1) + lane] = y[r];
+    wave_lds_sync();
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+        const float4 z = *reinterpret_cast<const float4 *>(&mine[lo15_quad(lane, j)]);
+        const float p = z.x + z.y, q = z.x - z.y, r = z.z + z.w, s = z.z - z.w;                  // bit 0
+        x[j] = make_float4(p + r, q + s, p - r, q - s);                                          // bit 1
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { quad_stage<1>(x[j]); quad_stage<2>(x[j]); quad_stage<8>(x[j]); }       // bits 2, 3, 4
+}
+
+// stores them; `rt`: the sender's slot.  (Write-back stores: with the streaming hint the pass over 14 bits ran 13% slower.  Offsets in one vector
+// register: 64-bit addresses of all pieces were kept in registers, and spilled; none in a scalar one, see wide_stores_with_scalar_offset in
+// build.py.)
+template <int P>
+__device__ inline void lo15_store_piece(const float4 (&x)[4], rsrc_t rt, uint32_t tile, uint32_t block, uint32_t lane) {
+    static_assert(kBlockRows == 4, "rows of the blocked layout");
+    uint32_t at = ((tile >> kBlockRowBits) << (P + kBlockRowBits + 2)) + ((tile & (kBlockRows - 1u)) << 7) + (block << 14) +
+                  (lane >> 4 << 10) + (lane >> 2 & 1u) * 512u + (lane >> 3 & 1u) * 64u + 16u * (lane & 3u);
+    asm volatile("" : "+v"(at));
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+        const u32x4_t v = {__float_as_uint(x[j].x), __float_as_uint(x[j].y), __float_as_uint(x[j].z), __float_as_uint(x[j].w)};
+        __builtin_amdgcn_raw_buffer_store_b128(v, rt, (int)(at + 4096u * j), 0, 0);
+    }
+}
+
+template <bool PRE>
+__global__ __launch_bounds__(1024, 8) void k_enc_lo15_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
+                                                            double *partials, uint32_t partial_stride) {
+    constexpr int P = 15;
+    __shared__ __attribute__((aligned(16))) float lds[1 << 14];
     __shared__ double red[16];
-    const uint32_t c = blockIdx.y, t = threadIdx.x, lane = t & 63u, wv = wave_in_block();
-    uint32_t tile, half;
-    lo15_tile<HALVES>(tile, half);
+    const uint32_t c = blockIdx.y, t = threadIdx.x, lane = t & 63u, wv = wave_in_block(), tile = blockIdx.x;
     const rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));           // reads past d_src give the zero padding
-    float u[32], w[HALVES ? 32 : 1];
+    // register a of this wave = 64 consecutive coordinates = one sign word: lane a hashes the word of register a
+    const uint64_t word = ((uint64_t)tile << (P - 6)) + 16u * (lane & 31u) + wv;
+    float u[32];
     if constexpr (PRE) {
-        const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), ((uint64_t)tile << (P - 6)) + 16u * (lane & 31u) + wv);
+        const uint64_t offs = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), word);
 #pragma unroll
         for (int a = 0; a < 32; ++a) {
             const uint32_t odd = __builtin_amdgcn_inverse_ballot_w64(wave_read64(offs, a)) ? 4u : 0u;
@@ -85,35 +138,106 @@ __global__ __launch_bounds__(1024) void k_enc_lo15_first(EncBatch B, uint64_t d_
     } else {
 #pragma unroll
         for (int a = 0; a < 32; ++a) u[a] = buf_load(rx, 4u * t, (tile << (P + 2)) + 4096u * a);
-        if constexpr (HALVES) {
-#pragma unroll
-            for (int a = 0; a < 32; ++a) w[a] = buf_load(rx, 4u * t, (tile << (P + 2)) + (1u << 17) + 4096u * a);
-        }
     }
-    // register a of this wave = 64 consecutive coordinates = one sign word: lane a hashes the word of register a (lane 32 + a
-    // that of the same register of the upper half)
-    const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]),
-                                    ((uint64_t)tile << (P - 6)) + 16u * (lane & 31u) + wv + (HALVES ? 512u * (lane >> 5) : 0u));
-    const float side = half ? -1.0f : 1.0f;
+    const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), word);
     double n2 = 0.0;
 #pragma unroll
     for (int a = 0; a < 32; ++a) {
-        const float mine_only = HALVES && half ? w[HALVES ? a : 0] : u[a];       // each half of the tile is counted once
-        n2 += (double)mine_only * (double)mine_only;
-        if ((a & 7) == 7) __builtin_amdgcn_sched_barrier(0);     // keeps the widened values of one group live at a time
+        n2 += (double)u[a] * (double)u[a];
+        if ((a & 3) == 3) __builtin_amdgcn_sched_barrier(0);     // keeps the widened values of one group live at a time
     }
 #pragma unroll
-    for (int a = 0; a < 32; ++a) {
-        u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;  // + 0: no negative zeros
-        if constexpr (HALVES) {
-            const float upper = negate_where(w[a], wave_read64(mine, 32 + a)) + 0.0f;
-            u[a] = fmaf(upper, side, u[a]);                      // the stage over bit 15 (one rounding)
-        }
-    }
-    lo15_forward32(u, lds);
-    store_runs<P, true>(u, lds + wv * kLo15Wave, T + ((size_t)c << log2D), tile, 1024u * half + 64u * wv);
+    for (int a = 0; a < 32; ++a) u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;     // + 0: no negative zeros
+    fwht_regs<32>(u);                                            // bits 10..14
+    const rsrc_t rt = make_rsrc(T + ((size_t)c << log2D), 4u << log2D);
+    static_for<2>([&](auto H) {
+        constexpr int h = decltype(H)::value;
+        if (h) __syncthreads();                                  // the first half's regions have been read
+#pragma unroll
+        for (int i = 0; i < 16; ++i) lds[1024 * i + t] = u[16 * h + i];
+        __syncthreads();
+        float4 x[4];
+        lo15_piece_forward(lds + 1024u * wv, lane, x);
+        lo15_store_piece<P>(x, rt, tile, 16u * h + wv, lane);
+    });
     const double block_total = block_sum<1024>(n2, red);
     if (t == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
+}
+
+// The same at D = 2^27: 2^16 coordinates per tile, 64 per thread, in four pieces.  One workgroup per CU, which takes one tile after the
+// other: the registers of a piece are free once it lies in the LDS, and the loads of the next tile go out into them.  Bound by memory (the
+// copy of a vector of 4 GiB reaches 5.3 to 5.8 TB/s here).  Two workgroups per tile, one for the sums of its halves and one for the
+// differences, -> this, us: 8 senders of 2^27 1987 -> 1640 (4.3 -> 5.2 TB/s), of 80,000,001 1160 -> 992, one of 2^27 237 -> 190.  With a
+// workgroup per tile, or two or four of them per CU: 1630 .. 1650 and 202 .. 219.
+__global__ __launch_bounds__(1024) void k_enc_lo16_first(EncBatch B, uint32_t n, uint32_t tiles, uint64_t d_src, int log2D, uint64_t seed, float *T,
+                                                         double *partials, uint32_t partial_stride) {
+    constexpr int P = 16;
+    __shared__ __attribute__((aligned(16))) float lds[2][1 << 14];
+    __shared__ double red[2][16];
+    const uint32_t wv = wave_in_block(), total = n * tiles;
+    uint32_t t = threadIdx.x;
+    uint32_t c = blockIdx.x / tiles, tile = blockIdx.x % tiles;
+    rsrc_t rx = make_rsrc(B.x[c], (uint32_t)(d_src * 4));        // reads past d_src give the zero padding
+    float u[64];
+#pragma unroll
+    for (int a = 0; a < 64; ++a) u[a] = buf_load(rx, 4u * t, (tile << (P + 2)) + 4096u * a);
+#pragma unroll 1
+    for (uint32_t i = blockIdx.x; i < total; ) {
+        asm volatile("" : "+v"(t));                              // (what follows from it is not worth a register across the loop)
+        const uint32_t lane = t & 63u;
+        // register a of this wave = 64 consecutive coordinates = one sign word: lane a hashes the word of register a
+        const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), ((uint64_t)tile << (P - 6)) + 16u * lane + wv);
+        double n2[2] = {0.0, 0.0};
+#pragma unroll
+        for (int a = 0; a < 64; ++a) {
+            n2[a >> 5] += (double)u[a] * (double)u[a];
+            u[a] = negate_where(u[a], wave_read64(mine, a)) + 0.0f;      // + 0: no negative zeros
+            if ((a & 7) == 7) __builtin_amdgcn_sched_barrier(0); // keeps the widened values of one group live at a time
+        }
+        asm volatile("" : "+v"(n2[0]), "+v"(n2[1]));             // (left to itself the compiler adds one half up at the end and keeps its values)
+#pragma unroll
+        for (int a = 0; a < 32; ++a) {                           // bit 15
+            const float lo = u[a], hi = u[32 + a];
+            u[a] = lo + hi;
+            u[32 + a] = lo - hi;
+        }
+        fwht_regs_low<64, 5>(u);                                 // bits 10..14
+        // the next tile (none after the last one: bounds of 0, no traffic)
+        i += gridDim.x;
+        const bool more = i < total;
+        const uint32_t c_next = more ? i / tiles : 0u, tile_next = more ? i % tiles : 0u;
+        rx = make_rsrc(B.x[c_next], more ? (uint32_t)(d_src * 4) : 0u);
+        const rsrc_t rt = make_rsrc(T + ((size_t)c << log2D), 4u << log2D);
+        static_for<4>([&](auto Q) {
+            constexpr int q = decltype(Q)::value;
+            float *buf = lds[q & 1];                             // (two pieces later every wave has passed the barrier behind its reads)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) buf[1024 * r + t] = u[16 * q + r];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) u[16 * q + r] = buf_load(rx, 4u * t, (tile_next << (P + 2)) + 4096u * (16 * q + r));
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            float4 x[4];
+            lo15_piece_forward(buf + 1024u * wv, lane, x);
+            lo15_store_piece<P>(x, rt, tile, 16u * q + wv, lane);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const double sum = wave_sum(n2[h]);
+            if (lane == 0) red[h][wv] = sum;
+        }
+        __syncthreads();
+        if (t < 2u) {                                            // a partial sum per half of a tile
+            double sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) sum += red[t][w];
+            partials[(size_t)c * partial_stride + ((tile >> 3) << 4) + (t << 3) + (tile & 7u)] = sum;
+        }
+        c = c_next;
+        tile = tile_next;
+    }
 }
 
 // Decode, last pass (see k_dec_lo14_last): index bits 0..P-1 of H for every sender, its signs, the sum over the senders in
@@ -203,7 +327,7 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
         __syncthreads();                                         // LDS is reused by the next sender
     }
     // The wave's 64 runs of NS coordinates go out as whole 128-byte lines, eight lanes a line, through its region of the LDS (quads
-    // swizzled as in store_runs): with a run per lane every line was touched by eight instructions, and read from L2 as often
+    // swizzled by the low three bits of the run): with a run per lane every line was touched by eight instructions, and read from L2 as often
     // (whole decode: one sender of 5 * 10^7 sparsified by pairs, added to acc, 244 -> 98 us; of 10^8 466 -> 228; 4 senders of 2^27, b = 4,
     // 1483 -> 1384).
     const bool overwrite = mean_n > 0.0f;
@@ -255,15 +379,19 @@ static uint32_t lo15_tiles(uint64_t d, int P, uint32_t group) {
 }
 
 uint32_t launch_enc_lo15_first(int P, const EncBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, float *T,
-                               double *partials, uint32_t partial_stride, hipStream_t st) {
+                               double *partials, uint32_t partial_stride, uint32_t compute_units, hipStream_t st) {
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
-    const dim3 grid(P == 16 ? 2 * lo15_tiles(d, 16, 8) : lo15_tiles(d, 15, kBlockRows), n);
-    if (P == 16)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo15_first<false, true>), grid, dim3(1024), 0, st, B, d_src, log2D, seed, T, partials, partial_stride);
-    else if (pre)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo15_first<true, false>), grid, dim3(1024), 0, st, B, d_src, log2D, seed, T, partials, partial_stride);
+    if (P == 16) {
+        const uint32_t tiles = lo15_tiles(d, 16, 8), total = tiles * n;
+        hipLaunchKernelGGL(k_enc_lo16_first, dim3(total < compute_units ? total : compute_units), dim3(1024), 0, st, B, n, tiles, d_src, log2D, seed, T,
+                           partials, partial_stride);
+        return 2 * tiles;
+    }
+    const dim3 grid(lo15_tiles(d, 15, kBlockRows), n);
+    if (pre)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo15_first<true>), grid, dim3(1024), 0, st, B, d_src, log2D, seed, T, partials, partial_stride);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo15_first<false, false>), grid, dim3(1024), 0, st, B, d_src, log2D, seed, T, partials, partial_stride);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo15_first<false>), grid, dim3(1024), 0, st, B, d_src, log2D, seed, T, partials, partial_stride);
     return grid.x;
 }
 void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d_src, int pre, int log2D, uint64_t seed, const float *T,
