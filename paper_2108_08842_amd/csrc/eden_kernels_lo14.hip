@@ -142,9 +142,10 @@ template <> struct EncLo<14, 16> {
 // as zero through its buffer bounds.
 // PRE (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is x'[g] = 2 x[2g + o_g],
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
+// KEEP: x and the workspace of the launch fit the memory-side cache together: the loads of x then leave it there, see launch_enc_lo_first.
 // WAVES: of a workgroup.  |x|^2 is the same to the last bit for both numbers at P = 14: eight waves keep the sums of the two values of
 // bit 13, which tell sixteen waves apart, to themselves.
-template <int P, int WAVES, bool PRE, bool BLOCKED>
+template <int P, int WAVES, bool PRE, bool BLOCKED, bool KEEP>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 8) void k_enc_lo_first(EncBatch B, uint64_t d_src, int log2D, uint64_t seed, float *T,
                                                             double *partials, uint32_t partial_stride, EncTail tail) {
     using L = EncLo<P, WAVES>;
@@ -172,7 +173,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 8) void k_enc_lo_first
         }
     } else {
 #pragma unroll
-        for (int a = 0; a < N; ++a) u[a] = buf_load(rx, 4u * lane, 4u * (first + L::STEP * a));
+        for (int a = 0; a < N; ++a) {
+            const uint32_t at = 4u * (first + L::STEP * a);
+            u[a] = KEEP ? buf_load_keep(rx, 4u * lane, at) : buf_load(rx, 4u * lane, at);
+        }
     }
     const uint64_t mine = hash_word(stream_key(seed, kStreamSign, B.client[c]), word);
     double n2[N / 16] = {};
@@ -656,8 +660,15 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
     // pass finds no unwritten row inside a block
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
+    // Up to 128 MiB of x and workspace x is read with the default policy: it has often just been written, or is encoded again, and is then found in
+    // the memory-side cache; beyond, with the streaming one (a pure read 7.2 against 6.4 TB/s).  Encode, us, streaming / default: 24 senders
+    // of 300,007, b = 2 30.5 / 27.1; 10 of 2^20, b = 2 32.8 / 29.5; one of 11,173,962, b = 1 36.9 / 34.0, of 15,000,000 46.3 / 39.8; 32 of 2^20 (256 MiB),
+    // 1/2 to 4 bits, a round 147 / 150; 8 of 11,173,962, b = 1 178 / 192, 16 of them 373 / 399.  First passes on new inputs take the same.
+    const bool keep = !pre && (d_src + ((uint64_t)tiles << P)) * n * 4u <= (128u << 20);
+#define EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, KEEP) \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, WAVES, PRE, BLK, KEEP>), grid, dim3(64 * WAVES), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
 #define EDEN_ENC_LO(P, WAVES, PRE, BLK) \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, WAVES, PRE, BLK>), grid, dim3(64 * WAVES), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
+    do { if (keep) EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, !(PRE)); else EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, false); } while (0)
 #define EDEN_ENC_LO14(WAVES) \
     do { \
         if (pre) { if (blocked) EDEN_ENC_LO(14, WAVES, true, true); else EDEN_ENC_LO(14, WAVES, true, false); } \
@@ -671,6 +682,7 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
     else if (tiles * n <= compute_units) EDEN_ENC_LO14(16);
     else EDEN_ENC_LO14(8);
 #undef EDEN_ENC_LO14
+#undef EDEN_ENC_LO_LAUNCH
 #undef EDEN_ENC_LO
     return grid.x;
 }
