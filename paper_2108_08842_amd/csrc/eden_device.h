@@ -279,7 +279,7 @@ __device__ inline void fwht_regs(float (&v)[N]) {
 // that way): lane ^ 1, lane ^ 2 inside a quad; then, since every lane of a quad (8, 16 lanes) already holds the same sum, the mirrored
 // lane of 8 and of 16 stand for lane ^ 4 and lane ^ 8.
 template <int CTRL>
-__device__ inline uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false); }
+__device__ inline uint32_t dpp_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true); }
 template <int CTRL>
 __device__ inline double dpp_f64(double v) {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
@@ -498,9 +498,9 @@ __device__ inline void static_for(F &&f) {                       // f(integral_c
 template <int X>
 __device__ inline uint32_t lane_xor_u32(uint32_t v) {
     static_assert(X == 1 || X == 2 || X == 4 || X == 8, "one lane bit");
-    if constexpr (X == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);        // quad_perm [1,0,3,2]
-    else if constexpr (X == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
-    else if constexpr (X == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);  // row_ror:8
+    if constexpr (X == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);         // quad_perm [1,0,3,2]
+    else if constexpr (X == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
+    else if constexpr (X == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);   // row_ror:8
     else return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x001F | (4 << 10));
 }
 // A word holds N = 32 / BITS items of BITS bits; the N lanes that differ only in their low log2 N lane bits transpose

@@ -338,8 +338,11 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
 // Register (u, j) of thread (wave w, lane l = 32 h + m) then holds coordinate 1024 u + 32 n' + m of the tile with
 // n' = 8 (w / 2) + 4 h + 2 (w % 2) + j: 32 lanes cover one 128-byte line of acc, and the 32 sign bits of those lanes are one
 // half (j) of one 64-bit word of the sender's SIGN stream.
-// Per coordinate and sender this leaves about 9 vector instructions (split 2, butterflies 4, sign and accumulate 3)
-// where the all-vector version spends 19, and one exchange instead of two.
+// Per coordinate and sender this leaves about 11 vector instructions (split 2, butterflies 4, sign and accumulate 3)
+// where the all-vector version spends 19, and one exchange instead of two.  The loads of the next sender go out into the registers that the
+// products of step 1 have just read (issued in front of them they cost 32 moves), their descriptors come from scalar registers (out of vector
+// registers every load went through a loop), the sign words from the LDS: 16 senders of 11,173,962, us, 96.6 -> 86.3 (decode 169.6 -> 160.3), one of
+// them 19.3 -> 18.6, 20 of 600,000 23.3 -> 22.3.
 // x - (float)h for the fp16 in the low (HIGH = 0) or high half of `packed`: one mixed-precision fused multiply-add
 // (-1 * h + x, exact: h is x truncated to 11 bits)
 template <int HIGH>
@@ -355,14 +358,16 @@ __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint3
                                                                uint32_t full_tiles, uint32_t K, uint32_t split_tiles,
                                                                float *partial, int separate, float mean_n) {
     __shared__ __attribute__((aligned(16))) float lds[1 << kLo14Bits];
+    __shared__ uint64_t words[1 << (kLo14Bits - 6)];             // the tile's words of the sender's SIGN stream
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block(), h = lane >> 5, m = lane & 31u;
     uint32_t tile = blockIdx.x, c_begin = 0, c_end = n;
     float *part = nullptr;                                       // this tile in the partial buffer
     if (blockIdx.x >= full_tiles) {
         const uint32_t idx = blockIdx.x - full_tiles, k = idx % K;
         tile = full_tiles + idx / K;
-        c_begin = (uint32_t)(((uint64_t)n * k) / K);
-        c_end = (uint32_t)(((uint64_t)n * (k + 1)) / K);
+        // (in scalar registers, which the compiler does not see behind the divisions: a buffer descriptor made from them would go through a loop)
+        c_begin = __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)n * k) / K));
+        c_end = __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)n * (k + 1)) / K));
         if (separate) part = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits);
         else if (k > 0) part = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits);
     }
@@ -387,39 +392,34 @@ __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint3
 
     // raw[2 s + q]: fp16 k = 16 h + 8 q .. + 7 of row n = m of unit u = wv + 8 s
     const uint32_t lane_off = (m * 32u + 16u * h) * 2u;
-    auto load = [&](uint32_t c, uint32_t (&raw)[4][4]) {
-        const rsrc_t r16 = make_rsrc(T + ((size_t)c << log2D), 2u << log2D);       // the tile lies inside the slot
+    u32x4_t raw[4];
+    auto load = [&](uint32_t c, int s) {                         // (beyond the last sender: bounds of 0, no traffic)
+        const rsrc_t r16 = make_rsrc(T + ((size_t)(c < c_end ? c : c_begin) << log2D), c < c_end ? 2u << log2D : 0u);     // the tile lies inside the slot
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                // (default cache policy: the two instructions q take the two 16-byte halves of every 32 bytes, and with the
-                // streaming hint the second one fetched some lines again: 106 against 103 us)
-                const auto x = __builtin_amdgcn_raw_buffer_load_b128(
-                    r16, (int)lane_off, (int)(((uint32_t)tile_base + (wv + 8u * s) * 1024u + 8u * q) * 2u), 0);
-                raw[2 * s + q][0] = x[0]; raw[2 * s + q][1] = x[1]; raw[2 * s + q][2] = x[2]; raw[2 * s + q][3] = x[3];
-            }
-    };
-    // sign words of this wave's coordinates: word (u, hh) = 16 u + 4 (wv / 2) + (wv % 2) + 2 hh of the tile; lane 16 hh + u
-    // of either half of the wave hashes it
-    const uint32_t my_word = 16u * (lane & 15u) + 4u * (wv >> 1) + (wv & 1u) + 2u * ((lane >> 4) & 1u);
-
-    uint32_t raw[4][4];
-    if (c_begin < c_end) load(c_begin, raw);
-    for (uint32_t c = c_begin; c < c_end; ++c) {
-        half8_t x[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const u32x4_t v = {raw[i][0], raw[i][1], raw[i][2], raw[i][3]};
-            x[i] = __builtin_bit_cast(half8_t, v);
+        for (int q = 0; q < 2; ++q) {
+            // (default cache policy: the two instructions q take the two 16-byte halves of every 32 bytes, and with the
+            // streaming hint the second one fetched some lines again: 106 against 103 us)
+            const auto x = __builtin_amdgcn_raw_buffer_load_b128(
+                r16, (int)lane_off, (int)(((uint32_t)tile_base + (wv + 8u * s) * 1024u + 8u * q) * 2u), 0);
+            raw[2 * s + q] = u32x4_t{x[0], x[1], x[2], x[3]};
         }
-        if (c + 1 < c_end) load(c + 1, raw);
-        if (c > c_begin) __syncthreads();                        // every wave has read the previous sender's values
+    };
+    // sign bits of this thread's coordinates: bit m of the halves (j) of words 16 u + my_word of the tile
+    const uint32_t my_word = 4u * (wv >> 1) + (wv & 1u) + 2u * h;
+
+    load(c_begin, 0);
+    load(c_begin, 1);
+    for (uint32_t c = c_begin; c < c_end; ++c) {
+        if (c > c_begin) __syncthreads();                        // every wave has read the previous sender's values and words
+        // four waves in turn hash the tile's words for all of them (per lane and register pair, for itself, every wave hashed twice as many, and
+        // took two lane reads a value to bring the bits into scalar registers)
+        if ((wv >> 2) == (c & 1u)) words[t & 255u] = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t & 255u));
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             float16_t d1 = {0};
-            d1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[2 * s], Hk[0], d1, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[2 * s + 1], Hk[1], d1, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, raw[2 * s]), Hk[0], d1, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, raw[2 * s + 1]), Hk[1], d1, 0, 0, 0);
+            load(c + 1, s);                                      // into the registers the products have just read
             u32x4_t hi[2], lo[2];                                  // fp16 pairs: registers 2 i, 2 i + 1 of d1
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
@@ -445,21 +445,14 @@ __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint3
         fwht_regs<16>(v0);
         fwht_regs<16>(v1);
         const uint32_t scale = __float_as_uint(scratch[c].deq[1]) & 0x7FFFFFFFu;     // > 0
-        const uint64_t key = stream_key(seed, kStreamSign, B.client[c]);
-        const uint64_t mine = hash_word(key, (tile_base >> 6) + my_word);
-        const uint32_t mine_lo = (uint32_t)mine, mine_hi = (uint32_t)(mine >> 32);
-        const float pos = __uint_as_float(scale);
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
-            // hash bit 1 -> s_i = -1.  Lanes u and 16 + u hold the words of the two halves of the wave: their low (j = 0) or high
-            // (j = 1) halves, side by side in a scalar register pair, are the 64 sign bits of the wave's lanes, and a select
-            // driven by that pair needs no lane to fetch or shift anything
-            const uint64_t neg0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine_lo, 16 + u) << 32) |
-                                  (uint32_t)__builtin_amdgcn_readlane((int)mine_lo, u);
-            const uint64_t neg1 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine_hi, 16 + u) << 32) |
-                                  (uint32_t)__builtin_amdgcn_readlane((int)mine_hi, u);
-            sum[u] = fmaf(v0[u], __builtin_amdgcn_inverse_ballot_w64(neg0) ? -pos : pos, sum[u]);
-            sum[16 + u] = fmaf(v1[u], __builtin_amdgcn_inverse_ballot_w64(neg1) ? -pos : pos, sum[16 + u]);
+            // hash bit 1 -> s_i = -1: the factor is the scale with the bit moved to the sign position
+            const uint64_t w = words[my_word + 16u * (uint32_t)u];
+            const uint32_t f0 = (scale & 0x7FFFFFFFu) | ((lo32(w) << (31u - m)) & 0x80000000u);
+            const uint32_t f1 = (scale & 0x7FFFFFFFu) | ((hi32(w) << (31u - m)) & 0x80000000u);
+            sum[u] = fmaf(v0[u], __uint_as_float(f0), sum[u]);
+            sum[16 + u] = fmaf(v1[u], __uint_as_float(f1), sum[16 + u]);
         }
     }
     // register (u, j): coordinate 1024 u + 32 n' + m of the tile
