@@ -372,9 +372,8 @@ __device__ inline bool arrive_last(uint32_t *counter, uint32_t total, uint32_t *
 // (Sec. 2.2.1, Sec. 3), and its contribution |u| q to sum_i u_i Q_i (Sec. 2.3).  H = 2^(b-1) levels per sign.
 // A value exactly on a threshold stays in the interval closer to zero (strict compare); u = +0 is
 // non-negative.  thr[0] is unused (it is the threshold 0, decided by the sign).
-// The thresholds are wave-uniform scalars (Thresholds); the centroid is looked up in `qtab`, the workgroup's copy of qpos
-// (entries 0..7) and qpos2 (8..15) in LDS: counting the thresholds below |u| and one LDS read cost 2 H + 3
-// instructions where a select chain that carries the centroid along costs 3 H (measured 20% on a b = 4 pass).
+// The thresholds are wave-uniform (Thresholds); the centroid is looked up in `qtab`, the workgroup's copy of qpos
+// (entries 0..7) and qpos2 (8..15) in LDS.
 struct Thresholds {
     float thr[8], thr2[8];
 };
@@ -393,24 +392,8 @@ __device__ inline Thresholds uniform_thresholds(const EncScratch &s /* shared */
     }
     return t;
 }
-template <int H>
-__device__ inline uint32_t magnitude_rank(float a, const float (&thr)[8]) {
-    uint32_t mag = 0;
-#pragma unroll
-    for (int t = 1; t < H; ++t) mag += (a > thr[t]) ? 1u : 0u;
-    return mag;
-}
-template <int H>
-__device__ inline uint32_t quantize_one(float u, const Thresholds &th, const float *qtab, float &ip) {
-    const float a = fabsf(u);
-    const uint32_t mag = magnitude_rank<H>(a, th.thr);
-    ip = fmaf(a, qtab[mag], ip);
-    const uint32_t neg = __float_as_uint(u) >> 31;
-    return neg ? (uint32_t)(H - 1) - mag : (uint32_t)H + mag;
-}
-
 // b = 2: the indices of 16 values side by side in one word, value i in bits 2 i, 2 i + 1.  Index = (2 | magnitude) with both bits turned
-// over where the value is negative: 7 instructions a value, no read of the table; sums in the order of quantize_one.
+// over where the value is negative: 7 instructions a value, no read of the table.
 __device__ inline uint32_t quantize_two_bits(const float *u, float thr1, float q0, float q1, float &ip) {
     uint32_t mags = 0xAAAAAAAAu, signs = 0u;
 #pragma unroll
@@ -424,11 +407,12 @@ __device__ inline uint32_t quantize_two_bits(const float *u, float thr1, float q
     return mags ^ signs;
 }
 
-// The same search in one guess and one compare, for kernels that spend their time on it (16 levels: fourteen instructions above).
+// The search in one guess and one compare, for kernels that hold b = 4 alone (quantize_one_table, which leaves lane masks, takes 21 instructions with
+// the packing by ballots; this 14 with the packing by lane transposes).
 // The number of a Lloyd-Max threshold is nearly a quadratic function of its value: with r(t) = t (1 + c3 |t|), t = u c1, through
 // thresholds H / 2 and H - 1, r differs from the number of every other threshold of I_4 by less than 0.07.  The threshold with the
 // number nearest to r is therefore the one above or the one below u, and comparing u with it alone gives the index.  The
-// result is the one of quantize_one for every input: the margin (0.43 of a number) is far beyond the rounding of r, t is capped
+// result is the one of quantize_one_table for every input: the margin (0.43 of a number) is far beyond the rounding of r, t is capped
 // above the outermost threshold where r still rises, and the compare is exact: a value on a positive threshold stays below
 // it, one on a negative threshold (or on 0) stays above it, which "u > the float just below the threshold" says with
 // the same compare.  Where c1 would overflow (|x| below 2e-38) values and thresholds are multiplied by 2^60 first, exactly.  Where
@@ -633,18 +617,90 @@ __device__ inline float dequantize_byte(uint32_t byte, uint32_t H, const float *
 }
 __device__ inline uint32_t wide_half_levels(uint32_t b_q8) { return wide_bits(b_q8) ? 1u << (wide_bits(b_q8) - 1u) : 0u; }
 
-// b = K + 1/2 (Sec. 4.1): the index of one coordinate, K+1 bits wide where `up` (quantized with I_{K+1}), else K
-// bits (I_K), and its contribution |u| q to sum_i u_i Q_i.
+// b = K + 1/2 and the coin budgets (Sec. 4.1): one coordinate per lane, quantized with I_{K+1} in the lanes of `up` (the index has K+1 bits there), else with
+// I_K.  low[]: the low K bits of the index as lane masks, top: the bit above them (clear outside `up`).  Masks stand in scalar registers and are combined
+// there; a value costs a select and a compare per step of a search in which both quantizers share their steps, and the sums.  (Counting the thresholds of
+// both below |u| and putting both indices together took 36 vector instructions a value at K = 2, with the packing; this 17.)
+// Measured (strided encode pass): 16 x 11,173,962 at b = 2.7 460 -> 372 us, b = 2.5 343 -> 251, b = 1.5 241 -> 217; 8 x 4,000,037 at b = 2.7 60.9 -> 50.3.
+//   magnitude rank: in the lanes of `up` c0 c1 .. (K bits: 2^K - 1 thresholds), else c0 .. (K - 1 bits)
+//   index before the sign: up 1, rank; else 1, rank; the sign turns all of its bits over
+// Returns 4 times the entry of the centroid in a table that holds I_K's from entry 0 and I_{K+1}'s from entry 8 (qtab).
+__device__ inline float select_where(uint64_t mask, float x, float y) { return __builtin_amdgcn_inverse_ballot_w64(mask) ? x : y; }
 template <int K>
-__device__ inline uint32_t quantize_mixed(float u, bool up, const Thresholds &th, const float *qtab, float &ip) {
-    constexpr int HL = 1 << (K - 1), HH = 1 << K;
+__device__ inline uint32_t quantize_two_tables(float u, uint64_t up, const Thresholds &th, uint64_t (&low)[K], uint64_t &top) {
     const float a = fabsf(u);
-    const uint32_t mag_lo = magnitude_rank<HL>(a, th.thr), mag_hi = magnitude_rank<HH>(a, th.thr2);
-    ip = fmaf(a, qtab[up ? 8u + mag_hi : mag_lo], ip);
-    const bool neg = (__float_as_uint(u) >> 31) != 0u;
-    const uint32_t code_lo = neg ? (uint32_t)(HL - 1) - mag_lo : (uint32_t)HL + mag_lo;
-    const uint32_t code_hi = neg ? (uint32_t)(HH - 1) - mag_hi : (uint32_t)HH + mag_hi;
-    return up ? code_hi : code_lo;
+    uint64_t v[K];                                               // the low bits before the sign, v[0] the lowest
+    if constexpr (K == 1) {
+        v[0] = ~up | __ballot(a > th.thr2[1]);
+    } else if constexpr (K == 2) {
+        const uint64_t c0 = __ballot(a > select_where(up, th.thr2[2], th.thr[1]));
+        const uint64_t c1 = __ballot(a > select_where(c0, th.thr2[3], th.thr2[1]));
+        v[1] = ~up | c0;
+        v[0] = (up & c1) | (~up & c0);
+    } else {
+        static_assert(K == 3, "budgets that exist");
+        const uint64_t c0 = __ballot(a > select_where(up, th.thr2[4], th.thr[2]));
+        const float above = select_where(up, th.thr2[6], th.thr[3]), below = select_where(up, th.thr2[2], th.thr[1]);
+        const uint64_t c1 = __ballot(a > select_where(c0, above, below));
+        const float upper = select_where(c1, th.thr2[7], th.thr2[5]), lower = select_where(c1, th.thr2[3], th.thr2[1]);
+        const uint64_t c2 = __ballot(a > select_where(c0, upper, lower));
+        v[2] = ~up | c0;
+        v[1] = (up & c1) | (~up & c0);
+        v[0] = (up & c2) | (~up & c1);
+    }
+    // entry 8 + rank, or rank = v without its leading 1
+    uint32_t at = __builtin_amdgcn_inverse_ballot_w64(up) ? 32u : 0u - (4u << (K - 1));
+#pragma unroll
+    for (int b = 0; b < K; ++b) at += __builtin_amdgcn_inverse_ballot_w64(v[b]) ? 4u << b : 0u;
+    const uint64_t neg = __ballot(__float_as_int(u) < 0);
+#pragma unroll
+    for (int b = 0; b < K; ++b) low[b] = v[b] ^ neg;
+    top = up & ~neg;
+    return at;
+}
+// The same for b = 2, 3, 4 alone (low: the whole index; entries 0 .. of qtab).  K = 3: 14 vector instructions a value with the packing, 23 while the thresholds
+// below |u| were counted.  Encode of 4 x 100,000,001 at b = 3 1388 -> 1191 us, of 10 x 2^20 39.8 -> 35.6; of a launch of b = 1, 2, 3, 4 and 1.5 (16 x 11,173,962)
+// 496 -> 457.
+template <int K>
+__device__ inline uint32_t quantize_one_table(float u, const Thresholds &th, uint64_t (&low)[K]) {
+    static_assert(K >= 2 && K <= 4, "budgets that exist");
+    const float a = fabsf(u);
+    uint64_t v[K];
+    v[K - 1] = ~0ull;
+    if constexpr (K == 2) {
+        v[0] = __ballot(a > th.thr[1]);
+    } else if constexpr (K == 3) {
+        v[1] = __ballot(a > th.thr[2]);
+        v[0] = __ballot(a > select_where(v[1], th.thr[3], th.thr[1]));
+    } else {
+        v[2] = __ballot(a > th.thr[4]);
+        v[1] = __ballot(a > select_where(v[2], th.thr[6], th.thr[2]));
+        const float upper = select_where(v[1], th.thr[7], th.thr[5]), lower = select_where(v[1], th.thr[3], th.thr[1]);
+        v[0] = __ballot(a > select_where(v[2], upper, lower));
+    }
+    uint32_t at = 0;
+#pragma unroll
+    for (int b = 0; b + 1 < K; ++b) at += __builtin_amdgcn_inverse_ballot_w64(v[b]) ? 4u << b : 0u;
+    const uint64_t neg = __ballot(__float_as_int(u) < 0);
+#pragma unroll
+    for (int b = 0; b < K; ++b) low[b] = v[b] ^ neg;
+    return at;
+}
+// adds |u| times the centroids of N values to ip: their reads go out together, one after the other every value would wait for the LDS
+template <int N>
+__device__ inline void add_centroids(const float *u, const uint32_t (&at)[N], const float *qtab, float &ip) {
+    float q[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) q[i] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(qtab) + at[i]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) ip = fmaf(fabsf(u[i]), q[i], ip);
+    asm volatile("" : "+v"(ip));                                 // (left to itself the compiler adds up at the end and keeps the values)
+}
+// the 32 coordinates of 16 pairs whose offset bits are `offs`: a mask of the chosen ones
+__device__ inline uint32_t chosen_of_pairs(uint32_t offs) {
+    const uint32_t second = spread2(offs);
+    return (second << 1) | (second ^ 0x55555555u);
 }
 
 // ---- encode: what the quantizers derive from |x|^2

@@ -105,37 +105,35 @@ template <int R, int K, int MIX>
 __device__ inline void hi_quantize_pack(const float (&v)[R], const Thresholds &th, const float *qtab, uint64_t mixkey,
                                         uint64_t my_row, uint32_t *part_a, uint32_t *part_b, float &ip,
                                         uint64_t my_mask = 0, uint32_t my_off = 0) {
-    constexpr int H = 1 << (K - 1);
     const uint32_t lane = lane_id();
     uint32_t plane[4][2], top[2] = {0u, 0u};
 #pragma unroll
     for (int b = 0; b < 4; ++b) plane[b][0] = plane[b][1] = 0;
-    // 64 pairs per hash word = 128 coordinates; a row segment uses 32 of them
-    const uint32_t offs_mine = MIX == 1 ? (uint32_t)(hash_word(mixkey, my_row >> 7) >> (32u * (uint32_t)((my_row >> 6) & 1u))) : 0u;
+    // the coordinates of this lane's row with I_{K+1}; 64 pairs per hash word = 128 coordinates, 32 of them in a row segment
+    uint64_t chosen = my_mask;
+    if constexpr (MIX == 1) {
+        const uint32_t offs = (uint32_t)(hash_word(mixkey, my_row >> 7) >> (32u * (uint32_t)((my_row >> 6) & 1u)));
+        chosen = (uint64_t)chosen_of_pairs(offs >> 16) << 32 | chosen_of_pairs(offs);
+    }
+    constexpr int NA = R < 4 ? R : 4;
+    uint32_t at[NA];                                             // where the centroids of a few values lie in qtab
     static_for<R>([&](auto RR) {
         constexpr int r = decltype(RR)::value;
-        uint32_t code;
+        uint64_t bit[K];                                         // lane masks of the index's low bits
         if constexpr (MIX != 0) {
-            bool up;
-            if constexpr (MIX == 1) {
-                const uint32_t offs = __builtin_amdgcn_readlane(offs_mine, r);
-                up = ((offs >> (lane >> 1)) & 1u) == (lane & 1u);
-            } else {
-                up = __builtin_amdgcn_inverse_ballot_w64(wave_read64(my_mask, r));
-            }
-            code = quantize_mixed<K>(v[r], up, th, qtab, ip);
-            const uint64_t m = __ballot((code >> K) & 1u);
-            top[0] = put_lane<r>(lo32(m), top[0]);
-            top[1] = put_lane<r>(hi32(m), top[1]);
+            uint64_t high;
+            at[r % NA] = quantize_two_tables<K>(v[r], wave_read64(chosen, r), th, bit, high);
+            top[0] = put_lane<r>(lo32(high), top[0]);
+            top[1] = put_lane<r>(hi32(high), top[1]);
         } else {
-            code = quantize_one<H>(v[r], th, qtab, ip);
+            at[r % NA] = quantize_one_table<K>(v[r], th, bit);
         }
 #pragma unroll
         for (int b = 0; b < K; ++b) {
-            const uint64_t m = __ballot((code >> b) & 1u);
-            plane[b][0] = put_lane<r>(lo32(m), plane[b][0]);
-            plane[b][1] = put_lane<r>(hi32(m), plane[b][1]);
+            plane[b][0] = put_lane<r>(lo32(bit[b]), plane[b][0]);
+            plane[b][1] = put_lane<r>(hi32(bit[b]), plane[b][1]);
         }
+        if constexpr (r % NA == NA - 1) add_centroids<NA>(&v[r - (NA - 1)], at, qtab, ip);
     });
     if (lane < R) {
         store_row_planes<K>(plane, part_a, my_row);

@@ -66,42 +66,48 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
         return;
     }
     const Thresholds th = thresholds_of(sc);
-    uint32_t plane[BITS][NW], top[NW], offs16[NW], coin_off[NW];
+    uint32_t plane[BITS][NW], top[NW], chosen[NW], coin_off[NW];   // chosen: of this lane's row segments, the coordinates with I_{BITS+1}
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         top[w] = 0;
 #pragma unroll
         for (int b = 0; b < BITS; ++b) plane[b][w] = 0;
-        // this lane's row for register block w, and the 16 pair offsets of that row segment (64 pairs per hash word)
+        // this lane's row for register block w; 64 pairs per hash word of the MIX stream, 16 of them in that row segment
         const uint64_t first = base + ((uint64_t)hix_word_row<M>(ph, w) << p);
-        offs16[w] = MIX == 1 ? (uint32_t)(hash_word(mixkey, first >> 7) >> (16u * (uint32_t)((first >> 5) & 3u))) & 0xFFFFu : 0u;
+        chosen[w] = MIX == 1 ? chosen_of_pairs((uint32_t)(hash_word(mixkey, first >> 7) >> (16u * (uint32_t)((first >> 5) & 3u)))) : 0u;
         coin_off[w] = 0;
         if constexpr (MIX == 2) {                                // the 32 coins of that row segment: half of a block of 64
             const uint32_t blk = (uint32_t)(first >> 6), upper = (uint32_t)(first >> 5) & 1u;
             const uint64_t m64 = coin_mask_of(ct, c, log2D, blk);
-            offs16[w] = upper ? hi32(m64) : lo32(m64);
+            chosen[w] = upper ? hi32(m64) : lo32(m64);
             coin_off[w] = coins_before(ct, c, log2D, blk) + (upper ? (uint32_t)__popc(lo32(m64)) : 0u);
         }
     }
-    uint32_t items = 0;                                          // TRANSPOSE: the low bits of 16 registers
+    uint32_t items = 0, three = 0;                               // TRANSPOSE: the low bits of 16 and of three registers
+    uint32_t at[4];                                              // where the centroids of four values lie in qtab
     static_for<X::RP>([&](auto S) {
         constexpr int s = decltype(S)::value;
-        uint32_t code;
+        uint64_t bit[BITS];                                      // lane masks of the index's low bits
         if constexpr (MIX != 0) {
-            const uint32_t oa = __builtin_amdgcn_readlane(offs16[s / 32], s % 32);
-            const uint32_t ob = __builtin_amdgcn_readlane(offs16[s / 32], 32 + s % 32);
-            const uint32_t offs = (lane < 32u) ? oa : ob;
-            const bool up = MIX == 1 ? ((offs >> (col >> 1)) & 1u) == (col & 1u) : ((offs >> col) & 1u) != 0u;
-            code = quantize_mixed<BITS>(out[s], up, th, qtab, ip);
-            const uint64_t m = __ballot((code >> BITS) & 1u);
-            top[s / 32] = put_lane<s % 32>(lo32(m), top[s / 32]);
-            top[s / 32] = put_lane<32 + s % 32>(hi32(m), top[s / 32]);
+            const uint64_t up = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)chosen[s / 32], 32 + s % 32) << 32 |
+                                (uint32_t)__builtin_amdgcn_readlane((int)chosen[s / 32], s % 32);
+            uint64_t high;
+            at[s % 4] = quantize_two_tables<BITS>(out[s], up, th, bit, high);
+            top[s / 32] = put_lane<s % 32>(lo32(high), top[s / 32]);
+            top[s / 32] = put_lane<32 + s % 32>(hi32(high), top[s / 32]);
         } else {
-            code = quantize_one<H>(out[s], th, qtab, ip);
+            at[s % 4] = quantize_one_table<BITS>(out[s], th, bit);
         }
         if constexpr (TRANSPOSE && MIX == 2) {
-            items |= (code & 3u) << (2 * (s % 16));
-            if constexpr (s % 16 == 15) {
+            // (three values at a time, whose places fit an instruction's inline constants: with a place of its own every value took two registers)
+            constexpr int i = s % 16, place = 2 * (i % 3);
+            three |= (__builtin_amdgcn_inverse_ballot_w64(bit[0]) ? 1u << place : 0u) | (__builtin_amdgcn_inverse_ballot_w64(bit[1]) ? 2u << place : 0u);
+            asm volatile("" : "+v"(three));                      // (not the masks of all sixteen first)
+            if constexpr (i % 3 == 2 || i == 15) {
+                items |= three << (2 * (i - i % 3));
+                three = 0;
+            }
+            if constexpr (i == 15) {
                 items = transpose_items<2>(items, lane);
                 payload[2u * (word0 + (hix_row2<M>(threadIdx.x >> 5, ph, s - 15 + (int)(col & 15u)) << (p - 5))) + (col >> 4)] = items;
                 items = 0;
@@ -109,11 +115,11 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
         } else {
 #pragma unroll
             for (int b = 0; b < BITS; ++b) {
-                const uint64_t m = __ballot((code >> b) & 1u);
-                plane[b][s / 32] = put_lane<s % 32>(lo32(m), plane[b][s / 32]);
-                plane[b][s / 32] = put_lane<32 + s % 32>(hi32(m), plane[b][s / 32]);
+                plane[b][s / 32] = put_lane<s % 32>(lo32(bit[b]), plane[b][s / 32]);
+                plane[b][s / 32] = put_lane<32 + s % 32>(hi32(bit[b]), plane[b][s / 32]);
             }
         }
+        if constexpr (s % 4 == 3) add_centroids<4>(&out[s - 3], at, qtab, ip);
     });
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -141,11 +147,11 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
         }
         if constexpr (MIX == 1) part_b[word] = (uint16_t)even_bits(top[w] | (top[w] >> 1));    // only the chosen one can be set
         if constexpr (MIX == 2) {                                // only a coordinate with a coin can have the bit
-            const uint32_t piece = (uint32_t)compress_bits(top[w], offs16[w]);
+            const uint32_t piece = (uint32_t)compress_bits(top[w], chosen[w]);
             // either the piece goes to the staging array (word = number of the segment of 32 coordinates; k_coin_pack strings
             // the pieces together) or straight to its bits of the second part, which neighbouring tiles share: atomics
             if (pieces) pieces[word] = piece;
-            else or_bits(part_c, coin_off[w], piece, (uint32_t)__popc(offs16[w]));
+            else or_bits(part_c, coin_off[w], piece, (uint32_t)__popc(chosen[w]));
         }
     }
 }
