@@ -85,10 +85,8 @@ __device__ inline void hi_quantize_transpose(const float (&v)[R], const EncScrat
             items = quantize_two_bits(&v[first], thr1, q0, q1, ip);
         } else {
             uint32_t at[PER];
-            items = 0u - 0x11111111u;                            // index + 1 in every place; a sum, so that 16 may carry in between
             quantize_guess<8>(&v[first], guess, &es, at, ip);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) items += at[i] << (K * i);
+            items = pack_guesses(at);
         }
         items = transpose_items<K>(items, lane);
         payload[((base + ((uint64_t)(first + j) << p)) >> (K == 2 ? 4 : 3)) + q] = items;
@@ -187,7 +185,7 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
                 fill_rank_guess<8>(guess, &es, threadIdx.x);
                 if (es.guess_up != 1.0f) {
 #pragma unroll
-                    for (int r = 0; r < R; ++r) v[r] *= es.guess_up;
+                    for (int r = 0; r < R; ++r) v[r] = scale_for_guess(v[r], es.guess_up);
                 }
                 __syncthreads();
             }
@@ -271,8 +269,7 @@ __global__ __launch_bounds__(256) void k_enc_hi_last(EncBatch B, uint64_t valid_
             }
         }
     }
-    double ip_sum = (double)ip;
-    if (GUESS && b_q8 == 1024u) ip_sum /= (double)es.guess_up;
+    const double ip_sum = GUESS && b_q8 == 1024u ? unscale_sum(ip, es.guess_up) : (double)ip;
     const double block_total = block_sum<256>(ip_sum, red);
     enc_last_tail<256>(tail, B, c, log2D, seed, es.n2, block_total, partials + (size_t)c * partial_stride, &last_flag);
 }

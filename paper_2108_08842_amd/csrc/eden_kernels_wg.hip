@@ -54,10 +54,8 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
                 items = quantize_two_bits(&out[PER * k], thr1, q0, q1, ip);
             } else {
                 uint32_t at[PER];
-                items = 0u - 0x11111111u;                        // index + 1 in every place; a sum, so that 16 may carry in between
                 quantize_guess<H>(&out[PER * k], *guess, sc, at, ip);
-#pragma unroll
-                for (int i = 0; i < PER; ++i) items += at[i] << (BITS * i);
+                items = pack_guesses(at);
             }
             items = transpose_items<BITS>(items, lane);
             const uint32_t row = hix_row2<M>(g, ph, (int)(PER * k + j));
@@ -310,7 +308,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
             else if (MODE == 3) {
                 if (sc->guess_up != 1.0f) {
 #pragma unroll
-                    for (int s2 = 0; s2 < X::RP; ++s2) out[s2] *= sc->guess_up;
+                    for (int s2 = 0; s2 < X::RP; ++s2) out[s2] = scale_for_guess(out[s2], sc->guess_up);
                 }
                 hix_quantize_pack<M, P, 4, 0, true>(out, ph, sc, qtab, payload, reinterpret_cast<uint16_t *>(payload), mixkey, base, ip, ct,
                                                  c, log2D, payload, &guess);
@@ -403,8 +401,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, TPW == 1 ? 4 : 1) void k_enc_hix_l
             }
         }
     }
-    double ip_sum = (double)ip;
-    if (MODE == 3) ip_sum /= (double)sc->guess_up;
+    const double ip_sum = MODE == 3 ? unscale_sum(ip, sc->guess_up) : (double)ip;
     const double block_total = block_sum<X::THREADS>(ip_sum, red);
     if (threadIdx.x == 0) partials[(size_t)c * partial_stride + blockIdx.x] = block_total;
 }

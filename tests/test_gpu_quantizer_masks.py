@@ -53,3 +53,20 @@ def test_an_index_does_not_depend_on_the_budget_beside_it(d, spiked):
             assert np.array_equal(low, alone[256 * k][0][~up]), b
             assert np.array_equal(idx[up], alone[256 * (k + 1)][0][up]), b
     ctx.close()
+
+
+# the guess of b = 4 multiplies values and thresholds by a power of two where the outermost threshold is below 2^-60 or above 2^60: a vector times a power of
+# two has the same indices, and <R(x), Q> times that power, at both sides of both lines (the threshold is 2.4 |x|: here 2^11 to 2^13 times the factor)
+@pytest.mark.parametrize("d", [300_007, (1 << 21) - 3, (1 << 23) + 1])
+def test_four_bits_of_a_scaled_vector(d):
+    from paper_2108_08842_amd import eden
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn(d, generator=gen, device="cuda")
+    x = torch.where(x.abs() < 2.0 ** -20, x.sign() * 2.0 ** -20, x)    # (no factor makes a subnormal)
+    ctx = eden.Context(d_max=d, n_max=1, device=0)
+    want = parity.to_oracle_message(ctx.encode([x], [3], [1024], 5)[0])
+    for k in (-100, -74, -72, -71, 46, 47, 48, 50, 100):
+        got = parity.to_oracle_message(ctx.encode([x * 2.0 ** k], [3], [1024], 5)[0])
+        assert np.array_equal(got.payload, want.payload) and got.IP == want.IP * 2.0 ** k and got.N2 == want.N2 * 4.0 ** k, k
+    assert ctx.last_device_status() == 0
+    ctx.close()
