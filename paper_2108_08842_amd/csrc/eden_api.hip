@@ -611,7 +611,7 @@ static int decode_range(eden_ctx *ctx, const void *const *msgs_dev, const uint32
             }
             Timed t(ctx, EDEN_K_DEC_LAST, nb, st);
             if (pl.lo_bits >= 15)
-                launch_dec_lo15_last(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, acc_dev, mean_n, st);
+                launch_dec_lo15_last(pl.lo_bits, B, nb, d_src, pre, log2D, seed, ctx->T, ctx->dec_scratch, acc_dev, mean_n, ctx->compute_units, st);
             else if (pl.lo_bits == 14)
                 launch_dec_lo14_last(B, nb, d_src, pre, log2D, seed, work, ctx->dec_scratch, narrow, acc_dev, ctx->T, 2 * ctx->compute_units,
                                      ctx->dec_partial, ctx->dec_partial_tiles, mean_n, st);

@@ -107,7 +107,7 @@ void launch_dec_lo14_last(const DecBatch &B, uint32_t n, uint64_t d, int pre, in
 uint32_t launch_enc_lo15_first(int P, const EncBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, float *T,
                                double *partials, uint32_t partial_stride, uint32_t compute_units, hipStream_t st);
 void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d, int pre, int log2D, uint64_t seed, const float *T,
-                          const DecScratch *scratch, float *acc, float mean_n, hipStream_t st);
+                          const DecScratch *scratch, float *acc, float mean_n, uint32_t compute_units, hipStream_t st);
 
 }  // namespace eden
 #endif

@@ -42,6 +42,28 @@ __device__ inline void quad_stage(float (&v)[16]) {
 template <int X>
 __device__ inline void quad_stage(float4 &v) { quad_stage<X>(v.x); quad_stage<X>(v.y); quad_stage<X>(v.z); quad_stage<X>(v.w); }
 
+// The same in one instruction, where signs can be turned over before or after: v + (v of the other lane) or its negative.
+//   AFTER:  the lane with bit X gets (own) - (other), the stage's difference with its sign turned over
+//   BEFORE: that lane's input has its sign turned over; the results are the stage's
+// Signs that depend on the lane pass through the stages over other bits as they are, so that several such stages leave (expect) them turned
+// over where the coordinate has an odd number of ones in their bits: the caller turns them over with those of the rotation.
+// (Written out, four values at a time: the compiler leaves the exchange and the multiply-add two instructions.  A value written by the instruction before
+// may be read by another lane two wait states later, which the s_nop sees to; inside the block every instruction reads a value of its own.)
+template <int X, bool BEFORE>
+__device__ inline void flip_stage(float &a, float &b, float &c, float &d) {
+    static_assert(X == 1 || X == 2 || X == 8, "patterns that exist");
+    const float sign = ((threadIdx.x & (uint32_t)X) != 0u) == BEFORE ? 1.0f : -1.0f;
+#define EDEN_FLIP(PATTERN)                                                                                                                  \
+    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %0, %4 " PATTERN "\n\tv_fmac_f32_dpp %1, %1, %4 " PATTERN "\n\tv_fmac_f32_dpp %2, %2, %4 " PATTERN   \
+        "\n\tv_fmac_f32_dpp %3, %3, %4 " PATTERN : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "v"(sign))
+    if constexpr (X == 1) EDEN_FLIP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
+    else if constexpr (X == 2) EDEN_FLIP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
+    else EDEN_FLIP("row_ror:8 row_mask:0xf bank_mask:0xf");
+#undef EDEN_FLIP
+}
+template <int X, bool BEFORE>
+__device__ inline void flip_stage(float4 &v) { flip_stage<X, BEFORE>(v.x, v.y, v.z, v.w); }
+
 // in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed.  The caller puts a barrier between a
 // use of `lds` and the next one.
 template <int B>
