@@ -128,10 +128,12 @@ template <> struct EncLo<14, 16> {
             v[j] = y.x; v[j + 4] = y.y; v[j + 8] = y.z; v[j + 12] = y.w;
         }
         fwht_regs<16>(v);                                        // bits 7, 8, 0, 1
-        quad_stage<1>(v);                                        // bit 2
-        quad_stage<2>(v);                                        // bit 3
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) x[j] = make_float4(v[j], v[j + 4], v[j + 8], v[j + 12]);
+        for (uint32_t j = 0; j < 4; ++j) {
+            x[j] = make_float4(v[j], v[j + 4], v[j + 8], v[j + 12]);
+            quad_stage<1>(x[j]);                                 // bit 2
+            quad_stage<2>(x[j]);                                 // bit 3
+        }
     }
 };
 
@@ -240,6 +242,11 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
                                                        uint32_t full_tiles, uint32_t K, uint32_t split_tiles,
                                                        float *partial, int separate, float mean_n) {
     __shared__ __attribute__((aligned(16))) float lds[Lo16<14>::LDS_FLOATS];
+    // Four threads share a word of the SIGN stream.  Where four waves hash all of them by turns, for the others, the launches that do not split tiles
+    // are faster (16 of 11,173,962, b = 4 297 against 291 us, 32 of 2^20 with 1/2, 1, 2 and 4 bits 66.0 / 64.5), those that do slower (8 of 4,000,037,
+    // b = 3 74.9 / 76.5): there every thread hashes its own.
+    constexpr bool BY_TURNS = AHEAD || !WIDE_ONLY;
+    __shared__ uint64_t words[2][BY_TURNS ? 1 << (kLo14Bits - 6) : 1];
     const int narrow = WIDE_ONLY ? 0 : narrow_arg;
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block();
     uint32_t tile = blockIdx.x, c_begin = 0, c_end = n;
@@ -247,8 +254,8 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
     if (blockIdx.x >= full_tiles) {
         const uint32_t idx = blockIdx.x - full_tiles, k = idx % K;
         tile = full_tiles + idx / K;
-        c_begin = (uint32_t)(((uint64_t)n * k) / K);
-        c_end = (uint32_t)(((uint64_t)n * (k + 1)) / K);
+        c_begin = __builtin_amdgcn_readfirstlane(n * k / K);
+        c_end = __builtin_amdgcn_readfirstlane(n * (k + 1u) / K);
         if (separate) part_tile = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits);
         else if (k > 0) part_tile = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits);
     }
@@ -274,16 +281,20 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
     for (uint32_t c = c_begin; c < c_end; ++c) {
         const bool i16 = narrow && B.b_q8[c] <= 256u;
         if (!AHEAD) load(c, next);
+        if (BY_TURNS && (wv >> 2) == (c & 3u)) words[c & 1u][t & 255u] = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t & 255u));
+        __builtin_amdgcn_sched_barrier(0);                       // (while the values are on their way)
         float u[16];
 #pragma unroll
         for (int a = 0; a < 16; ++a) u[a] = i16 ? narrow_value((short)__float_as_int(next[a])) : next[a];
         __builtin_amdgcn_sched_barrier(0);                       // the conversions stay above the next sender's loads
         if (AHEAD && c + 1 < c_end) load(c + 1, next);
         if (c > c_begin) __syncthreads();                        // LDS is free again
-        lo_forward16<kLo14Bits>(u, lds);
+        lo_forward16<kLo14Bits>(u, lds);                         // (with a barrier)
         const uint32_t scale = __float_as_uint(i16 ? scratch[c].deq[1] : 1.0f) & 0x7FFFFFFFu;   // > 0; x*1+s is exact
-        const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t >> 2));
-        const uint32_t bits = (uint32_t)(word >> (16u * (t & 3u)));      // 16 sign bits of this thread's run
+        // 16 sign bits of this thread's run, turned over where the stages between lanes left the values so
+        uint32_t bits = 0u - ((t ^ t >> 1) & 1u);
+        if constexpr (BY_TURNS) bits ^= reinterpret_cast<const uint16_t *>(words[c & 1u])[t];
+        else bits ^= (uint32_t)(hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t >> 2)) >> (16u * (t & 3u)));
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             // hash bit 1 -> s_i = -1: the factor is the scale with bit e of the sign word moved to the sign position
@@ -366,8 +377,8 @@ __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint3
         const uint32_t idx = blockIdx.x - full_tiles, k = idx % K;
         tile = full_tiles + idx / K;
         // (in scalar registers, which the compiler does not see behind the divisions: a buffer descriptor made from them would go through a loop)
-        c_begin = __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)n * k) / K));
-        c_end = __builtin_amdgcn_readfirstlane((uint32_t)(((uint64_t)n * (k + 1)) / K));
+        c_begin = __builtin_amdgcn_readfirstlane(n * k / K);
+        c_end = __builtin_amdgcn_readfirstlane(n * (k + 1u) / K);
         if (separate) part = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits);
         else if (k > 0) part = partial + (((size_t)(k - 1) * split_tiles + (tile - full_tiles)) << kLo14Bits);
     }

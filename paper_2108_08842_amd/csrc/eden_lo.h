@@ -35,14 +35,9 @@ __device__ inline void quad_stage(float &v) {
     v = fmaf(v, sign, __uint_as_float(lane_xor_u32<X>(__float_as_uint(v))));
 }
 template <int X>
-__device__ inline void quad_stage(float (&v)[16]) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) quad_stage<X>(v[e]);
-}
-template <int X>
 __device__ inline void quad_stage(float4 &v) { quad_stage<X>(v.x); quad_stage<X>(v.y); quad_stage<X>(v.z); quad_stage<X>(v.w); }
-
-// The same in one instruction, where signs can be turned over before or after: v + (v of the other lane) or its negative.
+// The same in one instruction, where signs can be turned over before or after: the other lane's value times 1 or -1 is added.  (Nothing gained in the
+// encoder's pass over 14 bits, which waits for memory.)
 //   AFTER:  the lane with bit X gets (own) - (other), the stage's difference with its sign turned over
 //   BEFORE: that lane's input has its sign turned over; the results are the stage's
 // Signs that depend on the lane pass through the stages over other bits as they are, so that several such stages leave (expect) them turned
@@ -64,7 +59,8 @@ __device__ inline void flip_stage(float &a, float &b, float &c, float &d) {
 template <int X, bool BEFORE>
 __device__ inline void flip_stage(float4 &v) { flip_stage<X, BEFORE>(v.x, v.y, v.z, v.w); }
 
-// in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed.  The caller puts a barrier between a
+// in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed (B = 14: with the sign turned over where t has an odd
+// number of ones in bits 0 and 1, see flip_stage).  The caller puts a barrier between a
 // use of `lds` and the next one.
 template <int B>
 __device__ inline void lo_forward16(float (&v)[16], float *lds) {
@@ -89,8 +85,11 @@ __device__ inline void lo_forward16(float (&v)[16], float *lds) {
             v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
         }
         fwht_regs<16>(v);
-        quad_stage<1>(v);
-        quad_stage<2>(v);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            flip_stage<1, false>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+            flip_stage<2, false>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        }
     } else {
         const uint32_t a = t >> 4, low = t & 15u, a2 = a & 3u;
         float *mine = lds + (a >> 2) * (4 * L::ROW);             // the four rows of this wave
