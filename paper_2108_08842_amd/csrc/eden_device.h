@@ -1014,16 +1014,45 @@ __device__ inline uint64_t coin_mask_of(const CoinTables &ct, uint32_t c, int lo
 __device__ inline uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi(hi32(mask), __builtin_amdgcn_mbcnt_lo(lo32(mask), 0u));
 }
-// the bits of `value` at the set positions of `mask`, moved together towards bit 0 in the same order
-__device__ inline uint64_t compress_bits(uint64_t value, uint64_t mask) {
-    uint64_t out = 0, place = 1;
-    while (mask) {
-        const uint64_t lowest = mask & (0 - mask);
-        if (value & lowest) out |= place;
-        place <<= 1;
-        mask ^= lowest;
+// Bits of a word to and from the set positions of `mask`, in order, by moves of 1, 2, 4, 8 and 16 places (the parallel suffix method of Warren's Hacker's
+// Delight, chapter 7): step i moves what has an odd number of multiples of 2^i clear positions below it.  About 85 instructions whatever the mask; a loop over the set bits
+// took ten for each of the most that a lane of the wave had (strided encode pass of 8 senders of 4,000,037 at 2.7 bits 47.5 -> 41.5 us).
+struct BitMoves {
+    uint32_t step[5];                                            // in step i these move by 2^i
+    __device__ inline explicit BitMoves(uint32_t mask) {
+        uint32_t below = ~mask << 1;                             // clear positions below: those that still count
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            uint32_t odd = below;
+#pragma unroll
+            for (int s = 1; s < 32; s <<= 1) odd ^= odd << s;
+            step[i] = odd & mask;
+            mask = (mask ^ step[i]) | (step[i] >> (1 << i));
+            below &= ~odd;
+        }
     }
-    return out;
+};
+// the bits of `value` at the set positions of `mask`, moved together towards bit 0 in the same order
+__device__ inline uint32_t compress_bits(uint32_t value, uint32_t mask) {
+    const BitMoves moves(mask);
+    value &= mask;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const uint32_t moved = value & moves.step[i];
+        value = (value ^ moved) | (moved >> (1 << i));
+    }
+    return value;
+}
+__device__ inline uint64_t compress_bits(uint64_t value, uint64_t mask) {
+    return compress_bits(lo32(value), lo32(mask)) | (uint64_t)compress_bits(hi32(value), hi32(mask)) << __popc(lo32(mask));
+}
+// the other way round: bit k of `value` at the set position number k of `mask`
+__device__ inline uint32_t expand_bits(uint32_t value, uint32_t mask) {
+    const BitMoves moves(mask);
+#pragma unroll
+    for (int i = 4; i >= 0; --i)
+        value = (uint32_t)__builtin_amdgcn_bitop3_b32((int)moves.step[i], (int)(value << (1 << i)), (int)value, 0xCA);      // step ? moved : value
+    return value & mask;
 }
 // ORs the low `count` bits of `value` (the others are zero) into a zeroed little-endian bit string at bit `off`.  The string
 // starts on an 8-byte boundary (the second part of a payload does) and is a whole number of 8-byte words long: 64-bit atomics,

@@ -145,7 +145,7 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
         }
         if constexpr (MIX == 1) part_b[word] = (uint16_t)even_bits(top[w] | (top[w] >> 1));    // only the chosen one can be set
         if constexpr (MIX == 2) {                                // only a coordinate with a coin can have the bit
-            const uint32_t piece = (uint32_t)compress_bits(top[w], chosen[w]);
+            const uint32_t piece = compress_bits(top[w], chosen[w]);
             // either the piece goes to the staging array (word = number of the segment of 32 coordinates; k_coin_pack strings
             // the pieces together) or straight to its bits of the second part, which neighbouring tiles share: atomics
             if (pieces) pieces[word] = piece;

@@ -110,15 +110,16 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         const uint32_t voff = (((g * (uint32_t)bits) << (p - 5)) + (cbits >> 5)) * 4u;
         const uint32_t shift = cbits & 31u;
         const rsrc_t rb = make_rsrc(payload + payload_bytes / 4u, (uint32_t)coin_b_bytes(ct.total[c]));
-        const uint32_t below = (1u << col) - 1u;
         // the top bits of a row segment's coins are at most 32 consecutive bits of the second part, from bit oa (ob) on: this
-        // lane fetches them for "its" two rows once (beyond the part: 0), and every lane finds its bit in the window
+        // lane fetches them for "its" two rows once (beyond the part: 0) and puts them to the coordinates with a coin, so that both are lane masks:
+        // counting the coins below each coordinate took 16 instructions a value, this 9 (8 senders of 4,000,037 at 2.7 bits 54.8 -> 39.0 us,
+        // 16 of 11,173,962 at 1.3 401 -> 274)
         auto window = [&](uint32_t first_bit) {
             const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)((first_bit >> 5) * 4u), 0, 0);
             const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)((first_bit >> 5) * 4u + 4u), 0, 0);
             return __builtin_amdgcn_alignbit(hi, lo, first_bit & 31u);
         };
-        const uint32_t wa = window(oa), wb = window(ob);
+        const uint32_t ta = expand_bits(window(oa), ma), tb = expand_bits(window(ob), mb);
 #pragma unroll
         for (int r = 0; r < 64; ++r) {
             const int soff = (int)((((uint32_t)X::RL * r * (uint32_t)bits) << (p - 5)) * 4u);
@@ -126,10 +127,10 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
             // (one and two bits never straddle two words; otherwise always: no branch per value)
             const uint32_t w1 = COIN && ONLY < kCoinOnly + 3u ? 0u : __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff + 4, soff, 0);
             const uint32_t low = code_at(w0, w1, shift, bits);
-            const uint32_t m = (lane < 32u) ? __builtin_amdgcn_readlane(ma, r) : __builtin_amdgcn_readlane(mb, r);
-            const uint32_t wnd = (lane < 32u) ? __builtin_amdgcn_readlane(wa, r) : __builtin_amdgcn_readlane(wb, r);
-            const uint32_t top = (wnd >> (uint32_t)__popc(m & below)) & 1u;
-            v[r] = ((m >> col) & 1u) ? table[16u + ((top << bits) | low)] : table[low];
+            const uint64_t coin = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mb, r) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)ma, r);
+            const uint64_t top = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)tb, r) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)ta, r);
+            // entry `low`, or 16 + (top, low)
+            v[r] = table[low + (__builtin_amdgcn_inverse_ballot_w64(coin) ? 16u : 0u) + (__builtin_amdgcn_inverse_ballot_w64(top) ? 1u << bits : 0u)];
         }
     } else if (budget_mixed(b_q8)) {
         // b = bits + 1/2 (Sec. 4.1): every coordinate has `bits` bits in the first part; the coordinate of each pair
@@ -138,26 +139,27 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         const uint32_t sh = 16u * (uint32_t)((base >> 5) & 3u);                  // this tile's 16 pairs inside a hash word
         const uint32_t fa = (uint32_t)(hash_word(key, (base + row_a) >> 7) >> sh) & 0xFFFFu;
         const uint32_t fb = (uint32_t)(hash_word(key, (base + row_b) >> 7) >> sh) & 0xFFFFu;
-        const uint32_t both = fa | (fb << 16);
         const uint32_t cbits = col * (uint32_t)bits;
         const rsrc_t rp = make_rsrc(payload + ((base * (uint32_t)bits) >> 5), payload_bytes - (uint32_t)((base * (uint32_t)bits) >> 5) * 4u);
         const uint32_t voff = (((g * (uint32_t)bits) << (p - 5)) + (cbits >> 5)) * 4u;
         const uint32_t shift = cbits & 31u;
-        // second part: 16 bits per row segment; the descriptor starts at the part (8-byte aligned) so that the
-        // half-words can be fetched as whole dwords
+        // second part: 16 bits per row segment.  Lane l fetches those of the two row segments the wave reads into register l and puts them to the chosen
+        // coordinates, so that both are lane masks (with a load, a shift and a compare a value: 16 senders of 11,173,962 at 2.5 bits 261 -> 219 us,
+        // 8 of 4,000,037 at 1.5 40.7 -> 33.6)
         const rsrc_t rb = make_rsrc(payload + payload_bytes / 4u, (uint32_t)payload_b_bytes(1ull << log2D, b_q8));
-        const uint32_t voffb = ((uint32_t)(base >> 5) + (g << (p - 5))) * 2u;
+        const uint32_t ma = chosen_of_pairs(fa), mb = chosen_of_pairs(fb);
+        const uint32_t pa = spread2(buf_load_half(rb, (uint32_t)((base + row_a) >> 5) * 2u, 0u)), pb = spread2(buf_load_half(rb, (uint32_t)((base + row_b) >> 5) * 2u, 0u));
+        const uint32_t ta = (pa | (pa << 1)) & ma, tb = (pb | (pb << 1)) & mb;
 #pragma unroll
         for (int r = 0; r < 64; ++r) {
             const int soff = (int)((((uint32_t)X::RL * r * (uint32_t)bits) << (p - 5)) * 4u);
             const uint32_t w0 = __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff, soff, 0);
-            const uint32_t w1 = __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff + 4, soff, 0);    // always: no branch per value
+            // (one and two bits never straddle two words; otherwise always: no branch per value)
+            const uint32_t w1 = ONLY == 384u || ONLY == 640u ? 0u : __builtin_amdgcn_raw_buffer_load_b32(rp, (int)voff + 4, soff, 0);
             const uint32_t low = code_at(w0, w1, shift, bits);
-            const uint32_t hb = buf_load_half(rb, voffb, (((uint32_t)X::RL * r) << (p - 5)) * 2u);
-            const uint32_t offs = __builtin_amdgcn_readlane(both, r) >> (16u * (lane >> 5));
-            const bool up = ((offs >> (col >> 1)) & 1u) == (col & 1u);
-            const uint32_t top = (hb >> (col >> 1)) & 1u;
-            v[r] = up ? table[16u + ((top << bits) | low)] : table[low];
+            const uint64_t up = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mb, r) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)ma, r);
+            const uint64_t top = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)tb, r) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)ta, r);
+            v[r] = table[low + (__builtin_amdgcn_inverse_ballot_w64(up) ? 16u : 0u) + (__builtin_amdgcn_inverse_ballot_w64(top) ? 1u << bits : 0u)];
         }
     } else {
         const uint32_t cbits = col * (uint32_t)bits;
