@@ -706,6 +706,15 @@ __device__ inline uint32_t block_exclusive_scan_256(uint32_t mine, uint32_t *wav
     block_total = all;
     return before + incl - mine;
 }
+// bit j of byte b to bit b of byte j (Hacker's Delight, section 7-3)
+__device__ inline uint64_t transpose_8x8(uint64_t x) {
+    uint64_t t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
+    x = x ^ t ^ (t << 7);
+    t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
+    x = x ^ t ^ (t << 14);
+    t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
+    return x ^ t ^ (t << 28);
+}
 __global__ __launch_bounds__(256) void k_coin_masks(CoinBatch B, uint64_t seed, int log2D, CoinTables ct) {
     __shared__ uint32_t wave_totals[4];
     const uint32_t c = blockIdx.y;
@@ -716,13 +725,23 @@ __global__ __launch_bounds__(256) void k_coin_masks(CoinBatch B, uint64_t seed, 
     uint64_t m = 0;
     if (w < words) {
         const uint64_t key = stream_key(seed, kStreamMix, B.client[c]);
+        // Byte b of hash word j is below frac?  Four bytes at a time, the answers in their top bits: those of the low seven bits by a subtraction that cannot
+        // borrow.  The answers of word j end in bit j of every byte, 8 x 8 bits to be transposed.  (A compare, a select and an or per byte, with
+        // a wait for each compare's mask: encode of 8 senders of 4,000,037 at 2.7 bits 105.9 -> 103.7 us, decode 89.4 -> 87.4.)
+        const uint32_t f = frac * 0x01010101u, f7 = f & 0x7F7F7F7Fu;
+        uint32_t rows[2] = {0u, 0u};
 #pragma unroll
         for (uint32_t j = 0; j < 8; ++j) {
             const uint64_t h = hash_word(key, 8ull * w + j);
 #pragma unroll
-            for (uint32_t b = 0; b < 8; ++b)
-                if (((uint32_t)(h >> (8u * b)) & 0xFFu) < frac) m |= 1ull << (8u * j + b);
+            for (int half = 0; half < 2; ++half) {
+                const uint32_t x = half ? hi32(h) : lo32(h), not_below = (x | 0x80808080u) - f7;
+                // (~x & f) | (~(x ^ f) & ~not_below)
+                const uint32_t below = (uint32_t)__builtin_amdgcn_bitop3_b32((int)x, (int)f, (int)not_below, 0x4D);
+                rows[half] = (rows[half] >> 1) | (below & 0x80808080u);
+            }
         }
+        m = transpose_8x8((uint64_t)rows[1] << 32 | rows[0]);
     }
     uint32_t group_total;
     const uint32_t before = block_exclusive_scan_256((uint32_t)__popcll(m), wave_totals, group_total);
