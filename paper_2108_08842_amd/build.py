@@ -53,6 +53,46 @@ def wide_stores_with_scalar_offset(obj_dir: str = OBJ_DIR):
     return bad
 
 
+def lane_reads_without_waits(obj_dir: str = OBJ_DIR):
+    """Inline assembly of the last build that reads other lanes' registers (data-parallel primitives) too early.  A register that a vector
+    instruction has written may be read from another lane two wait states later.  The compiler sees to that between its own
+    instructions, but neither inside a block of inline assembly nor across its two ends, whatever stands there: a block that reads other
+    lanes' registers has to keep the distance to what comes before it, inside it, and to what comes behind it."""
+    bad = []
+    for path in sorted(glob.glob(os.path.join(obj_dir, "*-hip-amdgcn-amd-amdhsa-gfx950.s"))):
+        block = None
+        for n, line in enumerate(open(path), 1):
+            if "#ASMSTART" in line:
+                block = []
+            elif "#ASMEND" in line and block is not None:
+                if any("_dpp" in text for _, text in block):
+                    bad += [f"{os.path.basename(path)}:{at}: {text}" for at, text in _early_lane_reads(block)]
+                block = None
+            elif block is not None and line.strip():
+                block.append((n, line.strip()))
+    return bad
+
+
+def _early_lane_reads(block):
+    def registers(operand):
+        m = re.fullmatch(r"v(\d+)|v\[(\d+):(\d+)\]", operand)
+        return [] if not m else [int(m[1])] if m[1] else range(int(m[2]), int(m[3]) + 1)
+
+    now, written, early = 0, {}, []                              # wait states since the block's begin; register -> those when it was written
+    for at, text in block:
+        name, _, rest = text.partition(" ")
+        if name == "s_nop":
+            now += 1 + int(rest, 0)
+            continue
+        operands = [x.split()[0] for x in rest.split(",") if x.strip()]
+        if "_dpp" in name and any(now - written.get(r, 0) < 2 for r in registers(operands[1])):
+            early.append((at, text))
+        now += 1
+        if name.startswith("v_"):
+            written.update((r, now) for r in registers(operands[0]))
+    return early + [(block[-1][0], f"block ends with v{r} just written") for r, when in written.items() if now - when < 2]
+
+
 def build(verbose: bool = True, incremental: bool = False) -> str:
     """Compiles every source to an object file (in parallel, one hipcc each) and links the shared library.
     `incremental`: skip sources whose object file is newer than the source and every header."""
@@ -70,6 +110,9 @@ def build(verbose: bool = True, incremental: bool = False) -> str:
     bad = wide_stores_with_scalar_offset()
     if bad:
         raise RuntimeError("128-bit buffer stores with a scalar offset register (see wide_stores_with_scalar_offset):\n" + "\n".join(bad))
+    bad = lane_reads_without_waits()
+    if bad:
+        raise RuntimeError("inline assembly that reads other lanes' registers too early (see lane_reads_without_waits):\n" + "\n".join(bad))
     outs.append(_run([hipcc_path(), "--offload-arch=gfx950", "-fPIC", "-shared"] + objs + ["-o", LIB], verbose))
     if verbose:
         text = "\n".join(o for o in outs if o.strip())

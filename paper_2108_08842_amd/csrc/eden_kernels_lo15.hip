@@ -41,7 +41,7 @@ constexpr uint64_t kFlipped = 0xF00F0FF0F00F0FF0ull;             // of 64 consec
 __device__ inline uint32_t lo15_quad(uint32_t lane, uint32_t j) {
     return 256u * j + 64u * (lane >> 4) + 32u * ((lane >> 2) & 1u) + 16u * ((lane >> 3) & 1u) + 4u * (lane & 3u);
 }
-// The stages between lanes leave (BEFORE: expect) the values with the signs of kFlipped turned over: flip_stage.
+// The stages between lanes leave (BEFORE: expect) the values with the signs of kFlipped turned over: flip_stages.
 template <bool BEFORE>
 __device__ inline void lo15_piece_forward(float *mine, uint32_t lane, float4 (&x)[4]) {
     const float *from = mine + 512u * (lane >> 5) + (lane & 31u);
@@ -61,7 +61,7 @@ __device__ inline void lo15_piece_forward(float *mine, uint32_t lane, float4 (&x
         x[j] = make_float4(p + r, q + s, p - r, q - s);                                          // bit 1
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { flip_stage<1, BEFORE>(x[j]); flip_stage<2, BEFORE>(x[j]); flip_stage<8, BEFORE>(x[j]); }       // bits 2, 3, 4
+    for (int j = 0; j < 4; ++j) flip_stages<BEFORE, true>(x[j].x, x[j].y, x[j].z, x[j].w);       // bits 2, 3, 4
 }
 
 // stores them; `rt`: the sender's slot.  (Write-back stores: with the streaming hint the pass over 14 bits ran 13% slower.  Offsets in one vector

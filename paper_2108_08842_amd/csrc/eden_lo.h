@@ -36,31 +36,36 @@ __device__ inline void quad_stage(float &v) {
 }
 template <int X>
 __device__ inline void quad_stage(float4 &v) { quad_stage<X>(v.x); quad_stage<X>(v.y); quad_stage<X>(v.z); quad_stage<X>(v.w); }
-// The same in one instruction, where signs can be turned over before or after: the other lane's value times 1 or -1 is added.  (Nothing gained in the
-// encoder's pass over 14 bits, which waits for memory.)
-//   AFTER:  the lane with bit X gets (own) - (other), the stage's difference with its sign turned over
+// The stages over lane bits 1, 2 (and 8) of four values, one instruction a stage and value, where signs can be turned over before or after: the
+// other lane's value times 1 or -1 is added.  (Nothing gained in the encoder's pass over 14 bits, which waits for memory.)
+//   AFTER:  in every stage the lane with bit X gets (own) - (other), the stage's difference with its sign turned over
 //   BEFORE: that lane's input has its sign turned over; the results are the stage's
-// Signs that depend on the lane pass through the stages over other bits as they are, so that several such stages leave (expect) them turned
-// over where the coordinate has an odd number of ones in their bits: the caller turns them over with those of the rotation.
-// (Written out, four values at a time: the compiler leaves the exchange and the multiply-add two instructions.  A value written by the instruction before
-// may be read by another lane two wait states later, which the s_nop sees to; inside the block every instruction reads a value of its own.)
-template <int X, bool BEFORE>
-__device__ inline void flip_stage(float &a, float &b, float &c, float &d) {
-    static_assert(X == 1 || X == 2 || X == 8, "patterns that exist");
-    const float sign = ((threadIdx.x & (uint32_t)X) != 0u) == BEFORE ? 1.0f : -1.0f;
-#define EDEN_FLIP(PATTERN)                                                                                                                  \
-    asm("s_nop 1\n\tv_fmac_f32_dpp %0, %0, %4 " PATTERN "\n\tv_fmac_f32_dpp %1, %1, %4 " PATTERN "\n\tv_fmac_f32_dpp %2, %2, %4 " PATTERN   \
-        "\n\tv_fmac_f32_dpp %3, %3, %4 " PATTERN : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "v"(sign))
-    if constexpr (X == 1) EDEN_FLIP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
-    else if constexpr (X == 2) EDEN_FLIP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
-    else EDEN_FLIP("row_ror:8 row_mask:0xf bank_mask:0xf");
+// Signs that depend on the lane pass through the stages over other bits as they are, so that the stages leave (expect) them turned over where the
+// coordinate has an odd number of ones in their bits: the caller turns them over with those of the rotation.
+// Written out, because the compiler leaves the exchange and the multiply-add two instructions.  What an instruction has written may be read from another
+// lane two wait states later: the s_nop at the front keeps that distance to the instructions before the block, the one at the end to
+// those behind it (the compiler does not look inside), and the three other values stand between two stages of one.  build.py checks the built code.
+template <bool BEFORE, bool BIT8>
+__device__ inline void flip_stages(float &a, float &b, float &c, float &d) {
+    const float sign1 = ((threadIdx.x & 1u) != 0u) == BEFORE ? 1.0f : -1.0f;
+    const float sign2 = ((threadIdx.x & 2u) != 0u) == BEFORE ? 1.0f : -1.0f;
+#define EDEN_FLIP(SIGN, PATTERN)                                                                                            \
+    "v_fmac_f32_dpp %0, %0, " SIGN " " PATTERN " row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %1, %1, " SIGN " " PATTERN   \
+    " row_mask:0xf bank_mask:0xf\n\tv_fmac_f32_dpp %2, %2, " SIGN " " PATTERN " row_mask:0xf bank_mask:0xf\n\t"           \
+    "v_fmac_f32_dpp %3, %3, " SIGN " " PATTERN " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (BIT8) {
+        const float sign8 = ((threadIdx.x & 8u) != 0u) == BEFORE ? 1.0f : -1.0f;
+        asm("s_nop 1\n\t" EDEN_FLIP("%4", "quad_perm:[1,0,3,2]") EDEN_FLIP("%5", "quad_perm:[2,3,0,1]") EDEN_FLIP("%6", "row_ror:8") "s_nop 1"
+            : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "v"(sign1), "v"(sign2), "v"(sign8));
+    } else {
+        asm("s_nop 1\n\t" EDEN_FLIP("%4", "quad_perm:[1,0,3,2]") EDEN_FLIP("%5", "quad_perm:[2,3,0,1]") "s_nop 1"
+            : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "v"(sign1), "v"(sign2));
+    }
 #undef EDEN_FLIP
 }
-template <int X, bool BEFORE>
-__device__ inline void flip_stage(float4 &v) { flip_stage<X, BEFORE>(v.x, v.y, v.z, v.w); }
 
 // in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed (B = 14: with the sign turned over where t has an odd
-// number of ones in bits 0 and 1, see flip_stage).  The caller puts a barrier between a
+// number of ones in bits 0 and 1, see flip_stages).  The caller puts a barrier between a
 // use of `lds` and the next one.
 template <int B>
 __device__ inline void lo_forward16(float (&v)[16], float *lds) {
@@ -86,10 +91,7 @@ __device__ inline void lo_forward16(float (&v)[16], float *lds) {
         }
         fwht_regs<16>(v);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            flip_stage<1, false>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-            flip_stage<2, false>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-        }
+        for (int q = 0; q < 4; ++q) flip_stages<false, false>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     } else {
         const uint32_t a = t >> 4, low = t & 15u, a2 = a & 3u;
         float *mine = lds + (a >> 2) * (4 * L::ROW);             // the four rows of this wave

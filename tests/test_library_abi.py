@@ -85,6 +85,30 @@ def test_no_wide_buffer_store_keeps_its_offset_in_a_scalar_register(tmp_path):
     assert build.wide_stores_with_scalar_offset() == []
 
 
+def test_inline_assembly_keeps_its_distance_from_other_instructions(tmp_path):
+    # the build's own check of blocks that read other lanes' registers (two wait states behind the write, whoever wrote it): it finds a block that starts,
+    # goes on or ends too early, and the assembly the last build left has none
+    import glob
+    from paper_2108_08842_amd import build
+    stage = "\tv_fmac_f32_dpp {0}, {0}, v9 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n"
+    blocks = {"good": ["\ts_nop 1\n", *map(stage.format, ["v1", "v2", "v3", "v1", "v2", "v3"]), "\ts_nop 1\n"],
+              "front": [stage.format("v1"), "\ts_nop 1\n"],
+              "front, one state": ["\ts_nop 0\n", stage.format("v1"), "\ts_nop 1\n"],
+              "inside": ["\ts_nop 1\n", *map(stage.format, ["v1", "v2", "v1"]), "\ts_nop 1\n"],
+              "end": ["\ts_nop 1\n", *map(stage.format, ["v1", "v2", "v3"])],
+              "end, one state": ["\ts_nop 1\n", *map(stage.format, ["v1", "v2", "v3"]), "\ts_nop 0\n"],
+              "no lanes": ["\tv_fma_mix_f32 v0, v1, v2, v0 op_sel:[0,0,0] op_sel_hi:[1,0,0]\n"]}
+    found = {}
+    for name, lines in blocks.items():
+        sample = tmp_path / "k-hip-amdgcn-amd-amdhsa-gfx950.s"
+        sample.write_text("\t;;#ASMSTART\n" + "".join(lines) + "\t;;#ASMEND\n" + stage.format("v3"))
+        found[name] = len(build.lane_reads_without_waits(str(tmp_path)))
+    assert found == {"good": 0, "front": 1, "front, one state": 1, "inside": 1, "end": 2, "end, one state": 1, "no lanes": 0}
+    if not glob.glob(os.path.join(build.OBJ_DIR, "*-hip-amdgcn-amd-amdhsa-gfx950.s")):
+        pytest.skip("no device assembly from a build in this tree")
+    assert build.lane_reads_without_waits() == []
+
+
 def test_error_strings(eden):
     assert eden.strerror(0) == "ok"
     assert "argument" in eden.strerror(eden.ERR_INVALID_ARG)
