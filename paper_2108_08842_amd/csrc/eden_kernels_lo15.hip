@@ -219,7 +219,7 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
     constexpr int P = HALVES ? 16 : 15;
     constexpr bool UP_AHEAD = KIND != kMixed;                    // (both kinds of loads for 64 registers spilled: 692 us against 403, 4 senders of 10^8, b = 1 and 4)
     __shared__ __attribute__((aligned(16))) float lds[2][1 << 14];
-    __shared__ uint64_t words[16][32];                           // each wave's sign words
+    __shared__ uint32_t words[16][64];                           // halves of each wave's sign words
     uint32_t t = threadIdx.x;
     const uint32_t wv = wave_in_block();
     float sum[32];
@@ -265,7 +265,12 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
         // 32 sign words for the wave's 2048 coordinates: lane l < 32 hashes the word l & 15 of its block in piece l / 16
         const uint64_t row = ((uint64_t)tile << P) + ((uint64_t)half << 15);     // first coordinate
         const uint64_t word = (row >> 6) + ((lane & 16u) << 4) + 16u * wv + (lane & 15u);
-        if (lane < 32u) words[wv][lane] = hash_word(stream_key(seed, kStreamSign, B.client[c]), word) ^ kFlipped;
+        wave_lds_sync();                                         // the last sender's have been read
+        if (lane < 32u) {
+            const uint64_t signs = hash_word(stream_key(seed, kStreamSign, B.client[c]), word) ^ kFlipped;
+            words[wv][2u * lane] = lo32(signs);
+            words[wv][2u * lane + 1u] = hi32(signs);
+        }
         if constexpr (HALVES) {
             const float side = half ? -1.0f : 1.0f;
             if constexpr (!UP_AHEAD) load(slot(c, ((uint64_t)tile << P) < d_src), i16, (tile << P) + (1u << 15), up, integral_constant<int, 0>{}, integral_constant<int, 32>{});
@@ -296,7 +301,7 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
             float4 x[4];
             lo15_piece_forward<false>(buf + 1024u * wv, lane, x);
             // the quad's four bits lie in one half of a word
-            const uint32_t *my_words = reinterpret_cast<const uint32_t *>(words[wv]) + 2u * (lane >> 4) + ((lane >> 2) & 1u);
+            const uint32_t *my_words = words[wv] + 2u * (lane >> 4) + ((lane >> 2) & 1u);
             const uint32_t place = 16u * ((lane >> 3) & 1u) + 4u * (lane & 3u);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
