@@ -284,8 +284,10 @@ __global__ __launch_bounds__(512) void k_sparse_scatter_list(DecBatch B, uint32_
         for (uint32_t k = 0; k < 4u; ++k) {
             if (c0 + k >= n) break;
 #pragma unroll
-            for (uint32_t j = 0; j < (uint32_t)NI; ++j)
+            for (uint32_t j = 0; j < (uint32_t)NI; ++j) {
                 if (lane + 64u * j < mine) sums[at[k][j]] += value[k][j];
+                wave_lds_sync();                                 // the next sender's value for that sum may be another lane's
+            }
         }
     }
     __syncthreads();

@@ -74,3 +74,10 @@ def test_sign_words_of_the_next_sender_wait_for_the_last_reads():
     for name, lines in _kernels("eden_kernels_lo15.hip", "k_dec_lo15_last").items():
         assert any(re.search(r"= load (i32|i64|<\d+ x i32>), ptr addrspace\(3\)", line) for line in lines), name
         assert _unfenced(lines, r"= load (i32|i64|<\d+ x i32>), ptr addrspace\(3\)", r"store (i32|i64|<\d+ x i32>) .*, ptr addrspace\(3\)") == [], name
+
+
+def test_sums_of_the_kept_values_wait_for_the_sender_before():
+    # k_sparse_scatter_list: a sum that one lane has added to may be added to by another lane for the next sender
+    for name, lines in _kernels("eden_kernels_sparse.hip", "k_sparse_scatter_list").items():
+        assert any(re.search(r"store float .*, ptr addrspace\(3\)", line) for line in lines), name
+        assert _unfenced(lines, r"store float .*, ptr addrspace\(3\)", r"= load float, ptr addrspace\(3\)") == [], name
