@@ -246,7 +246,7 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
     // are faster (16 of 11,173,962, b = 4 297 against 291 us, 32 of 2^20 with 1/2, 1, 2 and 4 bits 66.0 / 64.5), those that do slower (8 of 4,000,037,
     // b = 3 74.9 / 76.5): there every thread hashes its own.
     constexpr bool BY_TURNS = AHEAD || !WIDE_ONLY;
-    __shared__ uint64_t words[2][BY_TURNS ? 1 << (kLo14Bits - 6) : 1];
+    __shared__ uint32_t words[2][BY_TURNS ? 1 << (kLo14Bits - 5) : 1];           // in halves
     const int narrow = WIDE_ONLY ? 0 : narrow_arg;
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block();
     uint32_t tile = blockIdx.x, c_begin = 0, c_end = n;
@@ -281,7 +281,11 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
     for (uint32_t c = c_begin; c < c_end; ++c) {
         const bool i16 = narrow && B.b_q8[c] <= 256u;
         if (!AHEAD) load(c, next);
-        if (BY_TURNS && (wv >> 2) == (c & 3u)) words[c & 1u][t & 255u] = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t & 255u));
+        if (BY_TURNS && (wv >> 2) == (c & 3u)) {
+            const uint64_t word = hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t & 255u));
+            words[c & 1u][2u * (t & 255u)] = lo32(word);
+            words[c & 1u][2u * (t & 255u) + 1u] = hi32(word);
+        }
         __builtin_amdgcn_sched_barrier(0);                       // (while the values are on their way)
         float u[16];
 #pragma unroll
@@ -293,7 +297,7 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
         const uint32_t scale = __float_as_uint(i16 ? scratch[c].deq[1] : 1.0f) & 0x7FFFFFFFu;   // > 0; x*1+s is exact
         // 16 sign bits of this thread's run, turned over where the stages between lanes left the values so
         uint32_t bits = 0u - ((t ^ t >> 1) & 1u);
-        if constexpr (BY_TURNS) bits ^= reinterpret_cast<const uint16_t *>(words[c & 1u])[t];
+        if constexpr (BY_TURNS) bits ^= words[c & 1u][t >> 1] >> (16u * (t & 1u));
         else bits ^= (uint32_t)(hash_word(stream_key(seed, kStreamSign, B.client[c]), (tile_base >> 6) + (t >> 2)) >> (16u * (t & 3u)));
 #pragma unroll
         for (int e = 0; e < 16; ++e) {

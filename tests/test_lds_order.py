@@ -81,3 +81,9 @@ def test_sums_of_the_kept_values_wait_for_the_sender_before():
     for name, lines in _kernels("eden_kernels_sparse.hip", "k_sparse_scatter_list").items():
         assert any(re.search(r"store float .*, ptr addrspace\(3\)", line) for line in lines), name
         assert _unfenced(lines, r"store float .*, ptr addrspace\(3\)", r"= load float, ptr addrspace\(3\)") == [], name
+
+
+def test_sign_words_are_read_in_the_type_they_are_written_in():
+    # k_dec_lo14_last and its matrix-core forms: of the LDS's whole numbers none is read as half of what was stored
+    for name, lines in _kernels("eden_kernels_lo14.hip", "k_dec_lo14_last").items():
+        assert not any(re.search(r"= load i16, ptr addrspace\(3\)", line) for line in lines), name
