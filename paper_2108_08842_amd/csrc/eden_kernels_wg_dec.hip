@@ -52,7 +52,7 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
     const uint32_t payload_bytes = (uint32_t)(((((1ull << log2D) >> (k == 2)) * (uint32_t)bits + 63) >> 6) << 3);
 
     // rows of this wave whose packet arrived, as lane masks over the register index (bit r <-> register r)
-    const uint64_t row_a = (uint64_t)hix_row1<M>(g0, lane) << p, row_b = (uint64_t)hix_row1<M>(g0 + 1, lane) << p;
+    const uint32_t row_a = hix_row1<M>(g0, lane) << p, row_b = hix_row1<M>(g0 + 1, lane) << p;
     uint64_t recv_a = ~0ull, recv_b = ~0ull;
     const uint32_t *bm = B.bitmap[c];
     if (bm) {
@@ -88,12 +88,20 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
 #pragma unroll
         for (int r = 0; r < 64; ++r) v[r] = __uint_as_float(buf_load_byte(rp, voff, ((uint32_t)X::RL * r) << p));
         const uint32_t H = wide_half_levels(b_q8);
-        if (grid_q15(b_q8)) {                                    // the values replace the bytes in their registers
+        // the values replace the bytes in their registers, eight at a time: what the compiler had in flight beyond that spilled, and every
+        // spilled byte was waited for on its own (8 senders of 11,173,962, b = 8, whole decode 213 -> 202 us, b = 6 238.5 -> 228; 32 of 2^23, b = 8 517 -> 490)
+        if (grid_q15(b_q8)) {
 #pragma unroll
-            for (int r = 0; r < 64; ++r) v[r] = dequantize_byte<true>(__float_as_uint(v[r]), H, gtab);
+            for (int r = 0; r < 64; ++r) {
+                v[r] = dequantize_byte<true>(__float_as_uint(v[r]), H, gtab);
+                if (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+            }
         } else {
 #pragma unroll
-            for (int r = 0; r < 64; ++r) v[r] = dequantize_byte<false>(__float_as_uint(v[r]), H, gtab);
+            for (int r = 0; r < 64; ++r) {
+                v[r] = dequantize_byte<false>(__float_as_uint(v[r]), H, gtab);
+                if (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+            }
         }
     } else if (COIN || coin_q8(b_q8)) {
         // coin budgets (Sec. 4.1): every coordinate has `bits` bits in the first part; a coordinate with a coin was
