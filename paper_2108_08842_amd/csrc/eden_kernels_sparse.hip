@@ -151,7 +151,7 @@ __device__ inline void load4_padded(const float *x, uint32_t i, uint32_t d, bool
 // A wave takes 64 blocks = 4096 coordinates of sender blockIdx.y.  x goes straight into the LDS, all of it on its way while the wave selects; the
 // kept coordinates are then picked from there by a list, and leave in one run.  (Loads behind the selection and a test of every coordinate
 // against the masks: encode, us, m = 6 188 -> 169, one sender 30.2 -> 27.3, 2 of 4,000,037 25.2 -> 22.2; m = 32, 8 senders of 11,173,962 206 -> 184;
-// m = 63 383 -> 325; half of each by the selection itself.)
+// half of each by the selection itself.)
 template <int POLICY>
 __global__ __launch_bounds__(64) void k_sparse_gather(EncBatch B, uint32_t d, uint32_t m, uint64_t seed, float *out, int log2_stride) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
@@ -310,10 +310,8 @@ __global__ __launch_bounds__(512) void k_sparse_scatter_list(DecBatch B, uint32_
     }
 }
 
-// The same by a workgroup of eight waves per 64 blocks, for launches that would leave most of the chip idle: one wave selects while the
-// others wait with their 512 coordinates in registers, then all of them compact and store.  (Up to 1024 groups of 64 blocks; whole
-// encode, against two waves on their own: one sender of 2^20, m = 32, 23.7 -> 21.1 us; 8 of 300,007 29.4 -> 27.2; one of 4,000,037
-// 32.1 -> 29.3; beyond, 2048 groups of 8 senders of 2^20 28.7 -> 30.4 and one sender of 7,000,001 34.3 -> 34.8.)
+// The same by a workgroup of eight waves per 64 blocks (see launch_sparse_gather): one wave selects while the others wait with their 512 coordinates in
+// registers, then all of them test theirs against the masks, compact and store.
 __global__ __launch_bounds__(512) void k_sparse_gather_team(EncBatch B, uint32_t d, uint32_t m, uint64_t seed, float *out, int log2_stride) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     const uint32_t lane = lane_id(), wv = wave_in_block(), c = blockIdx.y;
@@ -349,12 +347,18 @@ __global__ __launch_bounds__(512) void k_sparse_gather_team(EncBatch B, uint32_t
 void launch_sparse_gather(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, float *out, int log2_stride, hipStream_t st) {
     const uint32_t blocks = (uint32_t)((d + 63) / 64);
     const uint32_t groups = (blocks + kSparseWave - 1) / kSparseWave;
-    if ((uint64_t)groups * n <= 1024) {
+    // Launches that would leave most of the chip idle, and those that keep so many that the serial list of k_sparse_gather (a step for each of m) takes longer
+    // than the test of every coordinate: the team.  Whole encode, us, team / one wave: one sender of 2^21, m = 16 (512 groups) 16.6 / 17.9, m = 63 26.9 / 29.5;
+    // 8 of 500,001, m = 6 (984) 14.6 / 15.8; beyond 1024 groups 8 of 1,000,000, m = 6 19.4 / 18.2, m = 16 23.3 / 22.7; m = 24, 32 senders of 200,003 (1568)
+    // 25.3 / 27.2, 2 of 2^24 (8192) 65.9 / 66.8, 4 of 2^24 127.8 / 122.9; m = 32, the same 25.4 / 28.7, 74.1 / 77.5, 146.8 / 145.3; m = 48 29.4 / 33.7, 97.7 / 103.6,
+    // 16 of 11,173,962 491 / 516; m = 63 31.0 / 39.6, 119 / 130, 633 / 685.
+    const uint64_t waves = (uint64_t)groups * n;
+    if (waves <= 1024 || m >= 48u || (m >= 24u && waves <= 8192)) {
         hipLaunchKernelGGL(k_sparse_gather_team, dim3(groups, n), dim3(512), 2u * kSparseWave * (uint32_t)sizeof(KeptHalf) + kSparseWave * m * 4u, st,
                            B, (uint32_t)d, m, seed, out, log2_stride);
         return;
     }
-    const uint32_t bytes = 64u * kSparseWave * (uint32_t)sizeof(float) + kSparseWave * m * (uint32_t)sizeof(uint16_t);    // at most 24 KiB
+    const uint32_t bytes = 64u * kSparseWave * (uint32_t)sizeof(float) + kSparseWave * m * (uint32_t)sizeof(uint16_t);    // at most 22 KiB
     // x beyond the size of the memory-side cache is read with the streaming policy.  Whole encode, us, default / streaming: one sender of 50,000,001,
     // m = 6 60.1 / 61.6, 2 of 25,000,001, m = 16 75.4 / 80.0; one of 2^27, m = 6 145 / 133, 16 of 11,173,962 184 / 166.
     if ((uint64_t)n * d * 4u <= (256u << 20))
