@@ -377,8 +377,10 @@ void launch_sparse_scatter(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m
     const uint32_t waves = n < 8u && groups * 8u > 4096u ? 4u : 8u;
     // Up to 16 kept of 64, eight senders or two of large vectors: by lists.  Whole decode, us, by masks / by lists: m = 6, 16 senders of 11,173,962
     // 124.0 / 104.5, 4 48.1 / 43.2, 2 35.0 / 32.7 (with eight waves 37.0), one 28.5 / 28.8; 32 of 4,000,037 95.8 / 82.1; 16 of 300,007 21.9 / 20.7;
-    // 4 of 2^20 15.1 / 15.5; m = 16, 16 of 11,173,962 171.7 / 159.7, 32 of 4,000,037 128.0 / 119.2; m = 32, 8 of 4,000,037 57.1 / 59.2.
-    if (m <= 16u && (n >= 8u || (n >= 2u && groups > 512u))) {
+    // 4 of 2^20 15.1 / 15.5; m = 16, 16 of 11,173,962 171.7 / 159.7, 32 of 4,000,037 128.0 / 119.2; m = 32, 8 of 4,000,037 57.1 / 59.2.  Not for up to half
+    // of one group of blocks: the lists hold all 64 blocks' values, the masks are asked for real coordinates only (32 senders of 1000, m = 16
+    // 24.0 / 28.2, of 2000 26.9 / 28.8, of 3000 31.0 / 29.8).
+    if (m <= 16u && blocks > 32u && (n >= 8u || (n >= 2u && groups > 512u))) {
         const uint32_t list_waves = n >= 4u ? 8u : 4u, turns = (kSparseWave / list_waves * m + 63u) / 64u;       // at most 4
         const uint32_t bytes = 64u * kSparseWave * (uint32_t)sizeof(float) + n * kSparseWave * m * (uint32_t)sizeof(uint16_t);   // at most 80 KiB
 #define EDEN_SCATTER_LIST(NI) \

@@ -1,6 +1,7 @@
 """The m-of-64 budgets by lists of the kept coordinates (k_sparse_gather, k_sparse_scatter_list) against the kernels that test every coordinate against
 masks: a few groups of 64 blocks are gathered by a team of waves, one sender's values scattered by masks.  The same values in the same
-order of additions: equal to the last bit."""
+order of additions: equal to the last bit.  (A vector of up to half a group is scattered by masks whatever the number of senders; from 24 kept on, large
+launches alone gather by lists.)"""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -10,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 # whole groups of 4096 coordinates, one coordinate more and less, a ragged block; senders that do not fill the last turn of four; m at which a wave has one,
 # two and three or four values per lane, and the first m that takes masks again; vectors on every alignment of four bytes
-@pytest.mark.parametrize("d,n", [(300_007, 17), (73 * 4096, 15), (61 * 4096 + 1, 18), (511 * 4096 - 1, 3), (513 * 4096 + 65, 2), (520 * 4096 - 63, 5)])
+@pytest.mark.parametrize("d,n", [(2048, 8), (2049, 8), (300_007, 17), (73 * 4096, 15), (61 * 4096 + 1, 18), (511 * 4096 - 1, 3), (513 * 4096 + 65, 2), (520 * 4096 - 63, 5)])
 @pytest.mark.parametrize("m", [1, 6, 8, 9, 16, 17, 63])
 def test_lists_and_masks_agree(d, n, m):
     from paper_2108_08842_amd import eden
