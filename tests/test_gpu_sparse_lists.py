@@ -32,9 +32,27 @@ def test_lists_and_masks_agree(d, n, m):
         ctx.decode_accumulate([msgs[c]], [ids[c]], [b], d, 99, acc)
     ctx.finalize_mean(acc, n)
     assert torch.equal(mean, acc)
-    more = torch.full((d,), 0.5, device="cuda")
+    # added to what is there: the sum of all senders first, then that to the old value, one fp32 addition for each call
+    total = torch.zeros(d, device="cuda")
+    ctx.decode_accumulate(msgs, ids, [b] * n, d, 99, total)
+    ctx.finalize_mean(total.clone(), n, out=mean)
+    assert torch.equal(mean, acc)
+    one = torch.zeros(d, device="cuda")
+    ctx.decode_accumulate(msgs[:1], ids[:1], [b], d, 99, one)
+    more = torch.randn(d, generator=gen, device="cuda")
+    want = more + total
     ctx.decode_accumulate(msgs, ids, [b] * n, d, 99, more)
+    assert torch.equal(more, want)
     ctx.decode_accumulate(msgs[:1], ids[:1], [b], d, 99, more)
-    assert bool(torch.isfinite(more).all())
+    assert torch.equal(more, want + one)
+    ctx.decode_accumulate(msgs, ids, [b] * n, d, 99, more)
+    assert torch.equal(more, (want + one) + total)
     assert ctx.last_device_status() == 0
     ctx.close()
+
+
+# the two largest forms: more than 64 KiB of lists in the scatter (32 senders, 16 of 64 kept), and x beyond the size of the memory-side cache, which the gather
+# reads with another policy (ragged end, vectors on every alignment; 47 of 64: lists in the launch of seven, masks in that of one)
+@pytest.mark.parametrize("d,n,m", [(50_001, 32, 16), (10_000_001, 7, 6), (10_000_001, 7, 47)])
+def test_the_largest_lists(d, n, m):
+    test_lists_and_masks_agree(d, n, m)
