@@ -363,8 +363,11 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
     }
 }
 
-// The same for senders sparsified by pairs (b = 1, P = 15, one output coordinate of each pair): 64 sums a thread.  The tile goes through the LDS as a whole, 32
-// coordinates in a row per thread; with the pieces of k_dec_lo15_last, which ties the pair's choice to the quads, 4 senders of 60,000,001 took 149 us, this 137.
+// The same for launches of fp16 slots at P = 15, the tile through the LDS as a whole: a thread then has 32 coordinates in a row, after 628 vector
+// instructions a sender where the pieces take 676 and 17 waits.  A CU that goes through many senders is bound by those; with few of
+// them it is the loads ahead that count (see launch_dec_lo15_last).
+// PAIRS: senders sparsified by pairs (one output coordinate of each pair): 64 sums a thread.  With the pieces, which tie the pair's choice to the
+// quads, 4 senders of 60,000,001 took 149 us, this 137.
 constexpr int kLo15Row = 36;                     // 32 values + 4: rows of consecutive lanes start 4 banks apart
 constexpr int kLo15Wave = 64 * kLo15Row;         // one wave's region of the second exchange
 constexpr int kLo15LdsWords = 16 * kLo15Wave;    // 147456 bytes; the first exchange needs 2^15 words
@@ -397,25 +400,32 @@ __device__ __forceinline__ void lo15_forward32(float (&v)[32], float *lds) {
     fwht_regs<32>(v);                                            // bits 0..4
 }
 
-
-__global__ __launch_bounds__(1024) void k_dec_lo15_last_pairs(DecBatch B, uint32_t n, uint64_t d_src, int log2D, uint64_t seed, const float *T,
-                                                              const DecScratch *scratch, float *acc, float mean_n) {
-    constexpr int NS = 64;                                       // accumulator coordinates per thread
+template <bool PAIRS>
+__global__ __launch_bounds__(1024) void k_dec_lo15_last_rows(DecBatch B, uint32_t n, uint64_t d_src, int log2D, uint64_t seed, const float *T,
+                                                             const DecScratch *scratch, float *acc, float mean_n) {
+    constexpr int NS = PAIRS ? 64 : 32;                          // accumulator coordinates per thread
     __shared__ __attribute__((aligned(16))) float lds[kLo15LdsWords];
     const uint32_t t = threadIdx.x, lane = t & 63u, wv = wave_in_block();
     const uint64_t row = (uint64_t)blockIdx.x << 15;             // first coordinate of the tile in a slot
     float sum[NS];
 #pragma unroll
     for (int e = 0; e < NS; ++e) sum[e] = 0.0f;
-    for (uint32_t c = 0; c < n; ++c) {
-        // (through a buffer descriptor: one offset register for all loads; with flat addresses the kernel spilled 44 registers)
-        const rsrc_t r = make_rsrc(T + ((size_t)c << log2D), 4u << log2D);
-        float u[32];
+    // (through a buffer descriptor: one offset register for all loads; with flat addresses the kernel spilled 44 registers)
+    auto load = [&](uint32_t c, float (&v)[32]) {                // (beyond the last sender: bounds of 0, no traffic)
+        const rsrc_t r = make_rsrc(T + ((size_t)(c < n ? c : 0u) << log2D), c < n ? 4u << log2D : 0u);
 #pragma unroll
         for (int a = 0; a < 32; ++a)
-            u[a] = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b16(r, (int)(2u * t), (int)(2u * (uint32_t)row + 2048u * a), kStream));
+            v[a] = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b16(r, (int)(2u * t), (int)(2u * (uint32_t)row + 2048u * a), kStream));
+    };
+    float ahead[32];
+    if (!PAIRS) load(0, ahead);
+    for (uint32_t c = 0; c < n; ++c) {
+        if (PAIRS) load(c, ahead);
+        float u[32];
 #pragma unroll
-        for (int a = 0; a < 32; ++a) u[a] = narrow_value((short)__float_as_int(u[a]));
+        for (int a = 0; a < 32; ++a) u[a] = narrow_value((short)__float_as_int(ahead[a]));
+        __builtin_amdgcn_sched_barrier(0);                       // the conversions stay above the next sender's loads
+        if (!PAIRS) load(c + 1, ahead);
         lo15_forward32(u, lds);
         const uint32_t scale = __float_as_uint(scratch[c].deq[1]) & 0x7FFFFFFFu;         // > 0
         // the wave's 2048 coordinates use 32 sign words: lane l < 32 hashes word l, every thread fetches its own
@@ -424,16 +434,25 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last_pairs(DecBatch B, uint32
         const uint32_t wlo = (uint32_t)__shfl((int)(uint32_t)mine, (int)(lane >> 1), 64);
         const uint32_t whi = (uint32_t)__shfl((int)(uint32_t)(mine >> 32), (int)(lane >> 1), 64);
         const uint32_t bits = (t & 1u) ? whi : wlo;              // 32 sign bits of this thread's run
-        const uint64_t omine = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), word0 + (lane & 31u));
-        const uint32_t olo = (uint32_t)__shfl((int)(uint32_t)omine, (int)(lane >> 1), 64);
-        const uint32_t ohi = (uint32_t)__shfl((int)(uint32_t)(omine >> 32), (int)(lane >> 1), 64);
-        const uint32_t offs = (t & 1u) ? ohi : olo;          // which member of each of this thread's 32 pairs
+        if constexpr (PAIRS) {
+            const uint64_t omine = hash_word(stream_key(seed, kStreamSubsample, B.client[c]), word0 + (lane & 31u));
+            const uint32_t olo = (uint32_t)__shfl((int)(uint32_t)omine, (int)(lane >> 1), 64);
+            const uint32_t ohi = (uint32_t)__shfl((int)(uint32_t)(omine >> 32), (int)(lane >> 1), 64);
+            const uint32_t offs = (t & 1u) ? ohi : olo;          // which member of each of this thread's 32 pairs
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
-            const float val = u[e] * __uint_as_float(scale | ((bits << (31 - e)) & 0x80000000u));
-            const bool odd = (offs >> e) & 1u;
-            sum[2 * e] += odd ? 0.0f : val;
-            sum[2 * e + 1] += odd ? val : 0.0f;
+            for (int e = 0; e < 32; ++e) {
+                const float val = u[e] * __uint_as_float(scale | ((bits << (31 - e)) & 0x80000000u));
+                const bool odd = (offs >> e) & 1u;
+                sum[2 * e] += odd ? 0.0f : val;
+                sum[2 * e + 1] += odd ? val : 0.0f;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 32; ++e) {
+                // hash bit 1 -> s_i = -1: the factor is the scale with bit e of the sign word moved to the sign position
+                const uint32_t shifted = bits << (31 - e);
+                sum[e] = fmaf(u[e], __uint_as_float((scale & 0x7FFFFFFFu) | (shifted & 0x80000000u)), sum[e]);
+            }
         }
         __syncthreads();                                         // LDS is reused by the next sender
     }
@@ -442,7 +461,7 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last_pairs(DecBatch B, uint32
     // (whole decode: one sender of 5 * 10^7, added to acc, 244 -> 98 us; of 10^8 466 -> 228).
     const bool overwrite = mean_n > 0.0f;
     const float div = overwrite ? mean_n : 1.0f;
-    const uint64_t out0 = 2u * (row + 2048u * wv);        // the wave's first coordinate of acc
+    const uint64_t out0 = (PAIRS ? 2u : 1u) * (row + 2048u * wv);        // the wave's first coordinate of acc
     float *L = lds + wv * kLo15Wave;
     const uint32_t swz = lane & 7u;
 #pragma unroll
@@ -509,7 +528,7 @@ void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d_src, 
     const uint64_t d = pre ? (d_src + 1) / 2 : d_src;
     const uint32_t tiles = P == 16 ? 2 * lo15_tiles(d, 16, 8) : lo15_tiles(d, 15, 1);
     if (pre) {                                                   // (these senders have b = 1: fp16 slots)
-        hipLaunchKernelGGL(k_dec_lo15_last_pairs, dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo15_last_rows<true>), dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
         return;
     }
     // a workgroup per CU, which goes from tile to tile with the next one's loads on their way (whole groups of pairs)
@@ -517,6 +536,12 @@ void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d_src, 
     const dim3 grid(tiles < resident ? tiles : resident);
     bool wide = true, small = true;                              // no sender, every sender with an fp16 slot
     for (uint32_t c = 0; c < n; ++c) { wide = wide && B.b_q8[c] > 256u; small = small && B.b_q8[c] <= 256u; }
+    // Nine senders or more as a whole.  Whole decode at b = 1, us, in pieces / as a whole: one sender of 2^26 128 / 148, 4 355 / 372, 8 644 / 646,
+    // 12 937 / 923, 16 1227 / 1193, 32 2392 / 2293; 8 of 2^24 + 1 236 / 233, of 2^25 298 / 305, 16 571 / 547, 32 1080 / 1031.
+    if (small && P == 15 && n > 8u) {
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo15_last_rows<false>), dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
+        return;
+    }
 #define EDEN_DEC_LO15(HALVES, KIND) \
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo15_last<HALVES, KIND>), grid, dim3(1024), 0, st, B, n, tiles, d_src, log2D, seed, T, scratch, acc, mean_n)
     if (P == 16) { if (wide) EDEN_DEC_LO15(true, kWide); else if (small) EDEN_DEC_LO15(true, kNarrow); else EDEN_DEC_LO15(true, kMixed); }

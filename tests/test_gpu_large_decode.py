@@ -29,9 +29,9 @@ def _decoded(msg, d, seed, client, bits):
 
 
 # tiles of 2^15 and 2^16 (two workgroups each), fewer and more of them than compute units, ragged ends inside a quad and a tile; one sender, several, and
-# both kinds of workspace slots side by side
+# both kinds of workspace slots side by side; from nine senders of one bit on the tile goes through the LDS as a whole
 @pytest.mark.parametrize("d,budgets", [((1 << 24) + 1, [1024]), ((1 << 25) - 70_003, [256, 256]), ((1 << 26) - 1, [1024, 256, 1024]), ((1 << 26) + 65_538, [256]),
-                                       ((1 << 26) + 5, [256, 1024]), ((1 << 27) - 131_071, [1024])])
+                                       ((1 << 26) + 5, [256, 1024]), ((1 << 27) - 131_071, [1024]), ((1 << 24) + 1, [256] * 9), ((1 << 25) + 70_003, [256] * 10)])
 def test_means_of_large_vectors(d, budgets):
     from paper_2108_08842_amd import eden
     n, seed = len(budgets), 17
