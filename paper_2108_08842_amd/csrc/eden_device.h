@@ -51,8 +51,8 @@ __host__ __device__ inline uint32_t sparse_m(uint32_t b_q8) {
     return ((b_q8 & ~0xFFFFu) == kSparseFlag && m >= 1 && m <= 63) ? m : 0;
 }
 // Uniform-grid quantizer of Sec. 4.3: the intervals [Delta (n - 1/2), Delta (n + 1/2)], Delta = (b_q8 & 0xFFFF) / 32768;
-// the index n of the interval that holds z (endpoints: closer to zero), clipped to +-127, travels as one signed byte (what an entropy coder would shrink to
-// about H(Delta) bits); the value of an interval is its centre of mass under N(0,1).
+// the index n of the interval that holds z (endpoints: closer to zero), clipped to +-127, travels as one signed byte (what an entropy
+// coder would shrink to about H(Delta) bits); the value of an interval is its centre of mass under N(0,1).
 constexpr uint32_t kGridFlag = 0x30000u;
 constexpr int kGridMax = 127;
 __host__ __device__ inline uint32_t grid_q15(uint32_t b_q8) {
@@ -235,9 +235,6 @@ __device__ inline void buf_store(rsrc_t r, uint32_t lane_off, uint32_t wave_off,
 __device__ inline float buf_load_keep(rsrc_t r, uint32_t lane_off, uint32_t wave_off) {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)lane_off, (int)wave_off, 0));
 }
-__device__ inline void buf_store_keep(rsrc_t r, uint32_t lane_off, uint32_t wave_off, float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)lane_off, (int)wave_off, 0);
-}
 
 // Sub-word accesses of neighbouring lanes go through whole dwords (a byte or half-word load per lane is not merged
 // with its neighbours': measured 3x slower on the first decode pass of the one-byte budgets).
@@ -407,21 +404,22 @@ __device__ inline uint32_t quantize_two_bits(const float *u, float thr1, float q
     return mags ^ signs;
 }
 
-// The search in one guess and one compare, for kernels that hold b = 4 alone (quantize_one_table, which leaves lane masks, takes 21 instructions with
-// the packing by ballots; this 12 with the packing by lane transposes).
+// The search in one guess and one compare, for kernels that hold b = 4 alone (quantize_one_table, which leaves lane masks, takes 21
+// instructions with the packing by ballots; this 12 with the packing by lane transposes).
 // The number of a Lloyd-Max threshold is nearly a quadratic function of its value: with r(u) = u (c1 + c3 |u|) through
 // thresholds H / 2 and H - 1, r differs from the number of every other threshold of I_4 by less than 0.07.  The threshold with the
 // number nearest to r is therefore the one above or the one below u, and comparing u with it alone gives the index.  The
 // result is the one of quantize_one_table for every input: the margin (0.43 of a number) is far beyond the rounding of r, u is capped
 // above the outermost threshold where r still rises, and the compare is exact: a value on a positive threshold stays below
 // it, one on a negative threshold (or on 0) stays above it, which "u > the float just below the threshold" says with
-// the same compare.  c3 goes with 1 / |x|^2: where the outermost threshold is below 2^-60 or above 2^60, values and thresholds are multiplied by a power of
-// two first (guess_up, scale_for_guess).  Where |x| is so large that outer thresholds are +inf (beyond 1.4e38), no value exceeds one of those: the cap then
-// is the u at which r is 0.4 above the last finite threshold's number, so that this one decides about everything beyond.
+// the same compare.  c3 goes with 1 / |x|^2: where the outermost threshold is below 2^-60 or above 2^60, values and thresholds are
+// multiplied by a power of two first (guess_up, scale_for_guess).  Where |x| is so large that outer thresholds are +inf (beyond 1.4e38),
+// no value exceeds one of those: the cap then is the u at which r is 0.4 above the last finite threshold's number, so that this one
+// decides about everything beyond.
 // |x| = 0 or not finite, u = NaN: any index in range will do, the payload is cleared afterwards (the cap keeps it in range).
 // kGuessRound added to r + H leaves the nearest whole number in the low bits of the float.
-// Measured against a guess through u / |x|, a conversion and shifts of the indices (26 vector instructions a value with the butterflies, now 20): strided pass of
-// 16 x 11,173,962 222.6 -> 211.3 us, of 8 x 4,000,037 33.9 -> 32.5; encode of 16 x 250,000 23.6 -> 23.1.
+// Measured against a guess through u / |x|, a conversion and shifts of the indices (26 vector instructions a value with the butterflies,
+// now 20): strided pass of 16 x 11,173,962 222.6 -> 211.3 us, of 8 x 4,000,037 33.9 -> 32.5; encode of 16 x 250,000 23.6 -> 23.1.
 // Two four-byte reads of tables of 18 entries (lanes that hit one bank read one address: no conflicts); a table of 64 cells
 // with the threshold, both centroids and the count in 16 bytes cost three times their LDS time.
 template <int H>
@@ -456,7 +454,8 @@ constexpr uint32_t kGuessBits = 0x4B400000u;                     // its bit patt
 template <int H, int N>
 __device__ inline void quantize_guess(const float *u, const RankGuess<H> &g, const EncScratch *sc, uint32_t (&at)[N], float &ip) {
     const float c1 = sc->guess_c1, c3 = sc->guess_c3, cap = sc->guess_cap;
-    // an entry's address from the bits as they are and one scalar register (left to add up the constants by itself the compiler takes three instructions)
+    // an entry's address from the bits as they are and one scalar register (left to add up the constants by itself the compiler takes
+    // three instructions)
     uint32_t zero = lds_address(g.thr) - 4u * kGuessBits;
     asm("" : "+s"(zero));
     float t[N];
@@ -648,11 +647,13 @@ __device__ inline float dequantize_byte(uint32_t byte, uint32_t H, const float *
 }
 __device__ inline uint32_t wide_half_levels(uint32_t b_q8) { return wide_bits(b_q8) ? 1u << (wide_bits(b_q8) - 1u) : 0u; }
 
-// b = K + 1/2 and the coin budgets (Sec. 4.1): one coordinate per lane, quantized with I_{K+1} in the lanes of `up` (the index has K+1 bits there), else with
-// I_K.  low[]: the low K bits of the index as lane masks, top: the bit above them (clear outside `up`).  Masks stand in scalar registers and are combined
-// there; a value costs a select and a compare per step of a search in which both quantizers share their steps, and the sums.  (Counting the thresholds of
-// both below |u| and putting both indices together took 36 vector instructions a value at K = 2, with the packing; this 17.)
-// Measured (strided encode pass): 16 x 11,173,962 at b = 2.7 460 -> 372 us, b = 2.5 343 -> 251, b = 1.5 241 -> 217; 8 x 4,000,037 at b = 2.7 60.9 -> 50.3.
+// b = K + 1/2 and the coin budgets (Sec. 4.1): one coordinate per lane, quantized with I_{K+1} in the lanes of `up` (the index has K+1
+// bits there), else with I_K.  low[]: the low K bits of the index as lane masks, top: the bit above them (clear outside `up`).  Masks
+// stand in scalar registers and are combined there; a value costs a select and a compare per step of a search in which both quantizers
+// share their steps, and the sums.  (Counting the thresholds of both below |u| and putting both indices together took 36 vector
+// instructions a value at K = 2, with the packing; this 17.)
+// Measured (strided encode pass): 16 x 11,173,962 at b = 2.7 460 -> 372 us, b = 2.5 343 -> 251, b = 1.5 241 -> 217; 8 x 4,000,037 at b =
+// 2.7 60.9 -> 50.3.
 //   magnitude rank: in the lanes of `up` c0 c1 .. (K bits: 2^K - 1 thresholds), else c0 .. (K - 1 bits)
 //   index before the sign: up 1, rank; else 1, rank; the sign turns all of its bits over
 // Returns 4 times the entry of the centroid in a table that holds I_K's from entry 0 and I_{K+1}'s from entry 8 (qtab).
@@ -689,9 +690,9 @@ __device__ inline uint32_t quantize_two_tables(float u, uint64_t up, const Thres
     top = up & ~neg;
     return at;
 }
-// The same for b = 2, 3, 4 alone (low: the whole index; entries 0 .. of qtab).  K = 3: 14 vector instructions a value with the packing, 23 while the thresholds
-// below |u| were counted.  Encode of 4 x 100,000,001 at b = 3 1388 -> 1191 us, of 10 x 2^20 39.8 -> 35.6; of a launch of b = 1, 2, 3, 4 and 1.5 (16 x 11,173,962)
-// 496 -> 457.
+// The same for b = 2, 3, 4 alone (low: the whole index; entries 0 .. of qtab).  K = 3: 14 vector instructions a value with the packing,
+// 23 while the thresholds below |u| were counted.  Encode of 4 x 100,000,001 at b = 3 1388 -> 1191 us, of 10 x 2^20 39.8 -> 35.6; of a
+// launch of b = 1, 2, 3, 4 and 1.5 (16 x 11,173,962) 496 -> 457.
 template <int K>
 __device__ inline uint32_t quantize_one_table(float u, const Thresholds &th, uint64_t (&low)[K]) {
     static_assert(K >= 2 && K <= 4, "budgets that exist");
@@ -992,8 +993,9 @@ __device__ inline uint32_t narrow_pair_from_int16(uint32_t w) {
 // ---- blocked layout of the encoder's workspace between the contiguous pass over P bits and a workgroup-tile strided pass that
 // covers all the bits above it.  Element (row r, column block cb of 32 coordinates, column) of a sender's slot sits, in
 // floats, at ((r / R) * 512 + cb) * (R * 32) + (r % R) * 32 + column with R = kBlockRows: the 128-byte segments of R
-// consecutive rows are interleaved.  Row-major would be r * 2^14 + cb * 32 + column.  (P = 14; rows of 2^P coordinates have 2^(P-5) column blocks.)  (At 16 senders of 2^24: R = 4 took the
-// strided pass from 170 to 156 us and left the contiguous pass where it was; R = 8 slowed both passes by 10 us.)
+// consecutive rows are interleaved.  Row-major would be r * 2^14 + cb * 32 + column.  (P = 14; rows of 2^P coordinates have 2^(P-5)
+// column blocks.)  (At 16 senders of 2^24: R = 4 took the strided pass from 170 to 156 us and left the contiguous pass where it was; R =
+// 8 slowed both passes by 10 us.)
 constexpr uint32_t kBlockRows = 4;
 constexpr uint32_t kBlockRowBits = 2;
 template <int P>
@@ -1014,9 +1016,10 @@ __device__ inline uint64_t coin_mask_of(const CoinTables &ct, uint32_t c, int lo
 __device__ inline uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi(hi32(mask), __builtin_amdgcn_mbcnt_lo(lo32(mask), 0u));
 }
-// Bits of a word to and from the set positions of `mask`, in order, by moves of 1, 2, 4, 8 and 16 places (the parallel suffix method of Warren's Hacker's
-// Delight, chapter 7): step i moves what has an odd number of multiples of 2^i clear positions below it.  About 85 instructions whatever the mask; a loop over the set bits
-// took ten for each of the most that a lane of the wave had (strided encode pass of 8 senders of 4,000,037 at 2.7 bits 47.5 -> 41.5 us).
+// Bits of a word to and from the set positions of `mask`, in order, by moves of 1, 2, 4, 8 and 16 places (the parallel suffix method of
+// Warren's Hacker's Delight, chapter 7): step i moves what has an odd number of multiples of 2^i clear positions below it.  About 85
+// instructions whatever the mask; a loop over the set bits took ten for each of the most that a lane of the wave had (strided encode pass
+// of 8 senders of 4,000,037 at 2.7 bits 47.5 -> 41.5 us).
 struct BitMoves {
     uint32_t step[5];                                            // in step i these move by 2^i
     __device__ inline explicit BitMoves(uint32_t mask) {

@@ -39,7 +39,8 @@ void launch_enc_finish(const EncBatch &B, uint32_t n, uint64_t hdr_d, int log2D,
 void launch_dec_prepare(const DecBatch &B, uint32_t n, uint64_t hdr_d, int log2D, uint64_t seed, const DevTables *tab,
                         DecScratch *scratch, uint32_t *dev_status, const CoinTables &ct, bool scan, uint32_t *msg_flags,
                         hipStream_t st);
-// Does the work of launch_dec_prepare itself.  `narrow`: the slots of b <= 1 senders hold 0 = values, 1 = the integers before the scale as fp16, 2 = as fp32
+// Does the work of launch_dec_prepare itself.  `narrow`: the slots of b <= 1 senders hold 0 = values, 1 = the integers before the scale
+// as fp16, 2 = as fp32
 void launch_dec_hi_first(int M, const DecBatch &B, uint32_t n, uint64_t keep_elems, int log2D, int p, uint64_t seed,
                          const DecPrepareArgs &prep, int narrow, float *T, const CoinTables &ct, hipStream_t st);
 // pre: 0 = sum the senders into acc; 1 = the same with the pairs scatter of EDEN_B_HALF_PRE; 2 = no sum, every sender's

@@ -725,9 +725,10 @@ __global__ __launch_bounds__(256) void k_coin_masks(CoinBatch B, uint64_t seed, 
     uint64_t m = 0;
     if (w < words) {
         const uint64_t key = stream_key(seed, kStreamMix, B.client[c]);
-        // Byte b of hash word j is below frac?  Four bytes at a time, the answers in their top bits: those of the low seven bits by a subtraction that cannot
-        // borrow.  The answers of word j end in bit j of every byte, 8 x 8 bits to be transposed.  (A compare, a select and an or per byte, with
-        // a wait for each compare's mask: encode of 8 senders of 4,000,037 at 2.7 bits 105.9 -> 103.7 us, decode 89.4 -> 87.4.)
+        // Byte b of hash word j is below frac?  Four bytes at a time, the answers in their top bits: those of the low seven bits by a
+        // subtraction that cannot borrow.  The answers of word j end in bit j of every byte, 8 x 8 bits to be transposed.  (A compare, a
+        // select and an or per byte, with a wait for each compare's mask: encode of 8 senders of 4,000,037 at 2.7 bits 105.9 -> 103.7 us,
+        // decode 89.4 -> 87.4.)
         const uint32_t f = frac * 0x01010101u, f7 = f & 0x7F7F7F7Fu;
         uint32_t rows[2] = {0u, 0u};
 #pragma unroll
@@ -775,7 +776,8 @@ __global__ __launch_bounds__(256) void k_coin_scan(CoinBatch B, int log2D, CoinT
     if (coin_q8(B.b_q8[blockIdx.x])) coin_scan(blockIdx.x, log2D, ct);
 }
 // Where another launch of one workgroup per sender stands between the masks and the pass that reads the sums, it does the scan as well
-// (4.7 us a launch; round of 8 senders of 4,000,037 at 2.7 bits 245 -> 243 us, of 2,000,000 at 3.3 162 -> 159; encode of one of 1,500,000 at 1.3 33.9 -> 32.4).
+// (4.7 us a launch; round of 8 senders of 4,000,037 at 2.7 bits 245 -> 243 us, of 2,000,000 at 3.3 162 -> 159; encode of one of 1,500,000
+// at 1.3 33.9 -> 32.4).
 __global__ __launch_bounds__(256) void k_enc_norm_scan(EncBatch B, const double *partials, uint32_t partial_stride, uint32_t nparts,
                                                        EncScratch *scratch, const DevTables *tab, int log2D, CoinTables ct) {
     __shared__ double red[4];

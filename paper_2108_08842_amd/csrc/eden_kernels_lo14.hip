@@ -221,9 +221,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 4 : 8) void k_enc_lo_first
 //
 // Work split.  A workgroup's time is proportional to the senders it sums and the chip holds `2 x CUs` of these
 // workgroups at once, so a tile count far below that would leave most of the chip idle.  The first `full_tiles`
-// tiles get one workgroup each that sums all n senders into acc.  Each of the remaining tiles gets K workgroups: group 0 sums its share of the senders into acc,
-// group k > 0 stores its sum in partial[k-1][tile - full_tiles][2^14]; k_dec_lo14_combine then adds those to
-// acc in the order k = 1, 2, ... (fixed, so the result does not depend on scheduling).
+// tiles get one workgroup each that sums all n senders into acc.  Each of the remaining tiles gets K workgroups: group 0 sums its share
+// of the senders into acc, group k > 0 stores its sum in partial[k-1][tile - full_tiles][2^14]; k_dec_lo14_combine then adds those to acc
+// in the order k = 1, 2, ... (fixed, so the result does not depend on scheduling).
 //
 // `separate`: K = n, one sender per workgroup, nothing is summed: every sender's decoded tile goes to its slot of `partial`, for a
 // caller that puts the values elsewhere afterwards (fp32 slots: possibly the workspace itself, in place; the workgroup has
@@ -242,9 +242,9 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
                                                        uint32_t full_tiles, uint32_t K, uint32_t split_tiles,
                                                        float *partial, int separate, float mean_n) {
     __shared__ __attribute__((aligned(16))) float lds[Lo16<14>::LDS_FLOATS];
-    // Four threads share a word of the SIGN stream.  Where four waves hash all of them by turns, for the others, the launches that do not split tiles
-    // are faster (16 of 11,173,962, b = 4 297 against 291 us, 32 of 2^20 with 1/2, 1, 2 and 4 bits 66.0 / 64.5), those that do slower (8 of 4,000,037,
-    // b = 3 74.9 / 76.5): there every thread hashes its own.
+    // Four threads share a word of the SIGN stream.  Where four waves hash all of them by turns, for the others, the launches that do not
+    // split tiles are faster (16 of 11,173,962, b = 4 297 against 291 us, 32 of 2^20 with 1/2, 1, 2 and 4 bits 66.0 / 64.5), those that
+    // do slower (8 of 4,000,037, b = 3 74.9 / 76.5): there every thread hashes its own.
     constexpr bool BY_TURNS = AHEAD || !WIDE_ONLY;
     __shared__ uint32_t words[2][BY_TURNS ? 1 << (kLo14Bits - 5) : 1];           // in halves
     const int narrow = WIDE_ONLY ? 0 : narrow_arg;
@@ -353,11 +353,11 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
 // Register (u, j) of thread (wave w, lane l = 32 h + m) then holds coordinate 1024 u + 32 n' + m of the tile with
 // n' = 8 (w / 2) + 4 h + 2 (w % 2) + j: 32 lanes cover one 128-byte line of acc, and the 32 sign bits of those lanes are one
 // half (j) of one 64-bit word of the sender's SIGN stream.
-// Per coordinate and sender this leaves about 11 vector instructions (split 2, butterflies 4, sign and accumulate 3)
+// Per coordinate and sender this leaves 9 vector instructions (split 2, butterflies 4, sign and accumulate 3)
 // where the all-vector version spends 19, and one exchange instead of two.  The loads of the next sender go out into the registers that the
 // products of step 1 have just read (issued in front of them they cost 32 moves), their descriptors come from scalar registers (out of vector
-// registers every load went through a loop), the sign words from the LDS: 16 senders of 11,173,962, us, 96.6 -> 86.3 (decode 169.6 -> 160.3), one of
-// them 19.3 -> 18.6, 20 of 600,000 23.3 -> 22.3.
+// registers every load went through a loop), the sign words from the LDS: 16 senders of 11,173,962, us, 96.6 -> 86.3 (decode 169.6 ->
+// 160.3), one of them 19.3 -> 18.6, 20 of 600,000 23.3 -> 22.3.
 // x - (float)h for the fp16 in the low (HIGH = 0) or high half of `packed`: one mixed-precision fused multiply-add
 // (-1 * h + x, exact: h is x truncated to 11 bits)
 template <int HIGH>
@@ -380,7 +380,8 @@ __global__ __launch_bounds__(512, 4) void k_dec_lo14_last_mfma(DecBatch B, uint3
     if (blockIdx.x >= full_tiles) {
         const uint32_t idx = blockIdx.x - full_tiles, k = idx % K;
         tile = full_tiles + idx / K;
-        // (in scalar registers, which the compiler does not see behind the divisions: a buffer descriptor made from them would go through a loop)
+        // (in scalar registers, which the compiler does not see behind the divisions: a buffer descriptor made from them would go through
+        // a loop)
         c_begin = __builtin_amdgcn_readfirstlane(n * k / K);
         c_end = __builtin_amdgcn_readfirstlane(n * (k + 1u) / K);
         if (separate) part = partial + ((size_t)k << log2D) + ((size_t)tile << kLo14Bits);
@@ -668,13 +669,15 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
     // pass finds no unwritten row inside a block
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
-    // Up to 128 MiB of x and workspace x is read with the default policy: it has often just been written, or is encoded again, and is then found in
-    // the memory-side cache; beyond, with the streaming one (a pure read 7.2 against 6.4 TB/s).  Encode, us, streaming / default: 24 senders
-    // of 300,007, b = 2 30.5 / 27.1; 10 of 2^20, b = 2 32.8 / 29.5; one of 11,173,962, b = 1 36.9 / 34.0, of 15,000,000 46.3 / 39.8; 32 of 2^20 (256 MiB),
-    // 1/2 to 4 bits, a round 147 / 150; 8 of 11,173,962, b = 1 178 / 192, 16 of them 373 / 399.  First passes on new inputs take the same.
+    // Up to 128 MiB of x and workspace x is read with the default policy: it has often just been written, or is encoded again, and is
+    // then found in the memory-side cache; beyond, with the streaming one (a pure read 7.2 against 6.4 TB/s).  Encode of the same vectors
+    // over and over, us, streaming / default: 24 senders of 300,007, b = 2 30.5 / 27.1; 10 of 2^20, b = 2 32.8 / 29.5; one of 11,173,962, b = 1 36.9 / 34.0, of
+    // 15,000,000 46.3 / 39.8; 32 of 2^20 (256 MiB), 1/2 to 4 bits, a round 147 / 150; 8 of 11,173,962, b = 1 178 / 192, 16 of them 373 /
+    // 399.  Vectors that lie in no cache take the same either way.
     const bool keep = !pre && (d_src + ((uint64_t)tiles << P)) * n * 4u <= (128u << 20);
 #define EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, KEEP) \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, WAVES, PRE, BLK, KEEP>), grid, dim3(64 * WAVES), 0, st, B, d_src, log2D, seed, T, partials, partial_stride, tail)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, WAVES, PRE, BLK, KEEP>), grid, dim3(64 * WAVES), 0, st, B, d_src, log2D, seed, T, \
+                       partials, partial_stride, tail)
 #define EDEN_ENC_LO(P, WAVES, PRE, BLK) \
     do { if (keep) EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, !(PRE)); else EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, false); } while (0)
 #define EDEN_ENC_LO14(WAVES) \
@@ -683,9 +686,10 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
         else { if (blocked) EDEN_ENC_LO(14, WAVES, false, true); else EDEN_ENC_LO(14, WAVES, false, false); } \
     } while (0)
     // Sixteen waves while every workgroup has a CU to itself, eight beyond.  Encode, us, sixteen / eight: one sender of 300,007, b = 1 (19
-    // workgroups) 12.2 / 12.8, of 2^20, b = 2 (64) 14.8 / 15.3, of 1,500,000, b = 1 (92) 15.9 / 16.3, 4 of 2^20, b = 2 (256) 17.8 / 18.5.  Beyond, cards
-    // of one kind differ: 10 of 2^20, b = 2 (640) 29.6 / 30.6 and one of 7,500,000, b = 1 (460) 23.9 / 24.9 on one, 34.8 / 31.1 and, of 8,000,000
-    // (492), 30.9 / 25.9 on another, where a launch of 16 waves a workgroup takes 17 or 23 us from one call to the next.
+    // workgroups) 12.2 / 12.8, of 2^20, b = 2 (64) 14.8 / 15.3, of 1,500,000, b = 1 (92) 15.9 / 16.3, 4 of 2^20, b = 2 (256) 17.8 /
+    // 18.5.  Beyond, cards of one kind differ: 10 of 2^20, b = 2 (640) 29.6 / 30.6 and one of 7,500,000, b = 1 (460) 23.9 / 24.9 on one,
+    // 34.8 / 31.1 and, of 8,000,000 (492), 30.9 / 25.9 on another, where a launch of 16 waves a workgroup takes 17 or 23 us from one call
+    // to the next.
     if (P == 12) { if (pre) EDEN_ENC_LO(12, 4, true, false); else EDEN_ENC_LO(12, 4, false, false); }
     else if (tiles * n <= compute_units) EDEN_ENC_LO14(16);
     else EDEN_ENC_LO14(8);

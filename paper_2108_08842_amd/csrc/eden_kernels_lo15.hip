@@ -64,9 +64,9 @@ __device__ inline void lo15_piece_forward(float *mine, uint32_t lane, float4 (&x
     for (int j = 0; j < 4; ++j) flip_stages<BEFORE, true>(x[j].x, x[j].y, x[j].z, x[j].w);       // bits 2, 3, 4
 }
 
-// stores them; `rt`: the sender's slot.  (Write-back stores: with the streaming hint the pass over 14 bits ran 13% slower.  Offsets in one vector
-// register: 64-bit addresses of all pieces were kept in registers, and spilled; none in a scalar one, see wide_stores_with_scalar_offset in
-// build.py.)
+// stores them; `rt`: the sender's slot.  (Write-back stores: with the streaming hint the pass over 14 bits ran 13% slower.  Offsets in
+// one vector register: 64-bit addresses of all pieces were kept in registers, and spilled; none in a scalar one, see
+// wide_stores_with_scalar_offset in build.py.)
 template <int P>
 __device__ inline void lo15_store_piece(const float4 (&x)[4], rsrc_t rt, uint32_t tile, uint32_t block, uint32_t lane) {
     static_assert(kBlockRows == 4, "rows of the blocked layout");
@@ -131,7 +131,8 @@ __global__ __launch_bounds__(1024, 8) void k_enc_lo15_first(EncBatch B, uint64_t
 // other: the registers of a piece are free once it lies in the LDS, and the loads of the next tile go out into them.  Bound by memory (the
 // copy of a vector of 4 GiB reaches 5.3 to 5.8 TB/s here).  Two workgroups per tile, one for the sums of its halves and one for the
 // differences, -> this, us: 8 senders of 2^27 1987 -> 1640 (4.3 -> 5.2 TB/s), of 80,000,001 1160 -> 992, one of 2^27 237 -> 190.  With a
-// workgroup per tile, or two or four of them per CU: 1630 .. 1650 and 202 .. 219.
+// workgroup per tile, or two or four of them per CU: 1630 .. 1650 and 202 .. 219.  (83 scalar registers are spilled, to lanes of vector
+// registers; none to memory.)
 __global__ __launch_bounds__(1024) void k_enc_lo16_first(EncBatch B, uint32_t n, uint32_t tiles, uint64_t d_src, int log2D, uint64_t seed, float *T,
                                                          double *partials, uint32_t partial_stride) {
     constexpr int P = 16;
@@ -208,16 +209,17 @@ __global__ __launch_bounds__(1024) void k_enc_lo16_first(EncBatch B, uint32_t n,
 // have at least 512 (half) tiles: no split by sender.
 // Neither memory nor the vector units were busy half of the time while a workgroup, alone on its CU, waited for all of a sender's tile and then
 // computed.  So a workgroup goes through the senders of a tile and on to its next tile with the loads of what comes next on their way: the upper
-// half's registers are free after the stage over bit 15, those of a piece once it lies in the LDS.  Mean, last pass, us: 8 senders of 2^27, b = 4
-// 1110 -> 1000 (4.8 TB/s; with a workgroup per tile 1062), b = 1 949 -> 875, one of 2^27 285 -> 212, 8 of 2^25, b = 4 239 -> 211, 4 of 10^8, b = 1 and 4
-// 680 -> 400, b = 2 497 -> 417.
+// half's registers are free after the stage over bit 15, those of a piece once it lies in the LDS.  Mean, last pass, us: 8 senders of
+// 2^27, b = 4 1110 -> 1000 (4.8 TB/s; with a workgroup per tile 1062), b = 1 949 -> 875, one of 2^27 285 -> 212, 8 of 2^25, b = 4 239 ->
+// 211, 4 of 10^8, b = 1 and 4 680 -> 400, b = 2 497 -> 417.
 // KIND: kWide: no sender of the launch has an fp16 slot (every b > 1), kNarrow: every sender has one, kMixed.
 enum : int { kMixed = 0, kWide = 1, kNarrow = 2 };
 template <bool HALVES, int KIND>
 __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, uint32_t tiles, uint64_t d_src, int log2D, uint64_t seed, const float *T,
                                                         const DecScratch *scratch, float *acc, float mean_n) {
     constexpr int P = HALVES ? 16 : 15;
-    constexpr bool UP_AHEAD = KIND != kMixed;                    // (both kinds of loads for 64 registers spilled: 692 us against 403, 4 senders of 10^8, b = 1 and 4)
+    // (both kinds of loads for 64 registers spilled: 692 us against 403, 4 senders of 10^8, b = 1 and 4)
+    constexpr bool UP_AHEAD = KIND != kMixed;
     __shared__ __attribute__((aligned(16))) float lds[2][1 << 14];
     __shared__ uint32_t words[16][64];                           // halves of each wave's sign words
     uint32_t t = threadIdx.x;
@@ -226,8 +228,8 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
 #pragma unroll
     for (int e = 0; e < 32; ++e) sum[e] = 0.0f;
     auto is_narrow = [&](uint32_t c) { return KIND == kNarrow || (KIND == kMixed && B.b_q8[c] <= 256u); };
-    // (through a buffer descriptor: one offset register for all loads.  After the last sender of the last tile the bounds are 0: no branch around
-    // the loads, and no traffic)
+    // (through a buffer descriptor: one offset register for all loads.  After the last sender of the last tile the bounds are 0: no
+    // branch around the loads, and no traffic)
     auto load = [&](rsrc_t r, bool i16, uint32_t first, float (&v)[32], auto A0, auto COUNT) {
         constexpr int a0 = decltype(A0)::value, count = decltype(COUNT)::value;
         if (i16) {
@@ -273,7 +275,9 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
         }
         if constexpr (HALVES) {
             const float side = half ? -1.0f : 1.0f;
-            if constexpr (!UP_AHEAD) load(slot(c, ((uint64_t)tile << P) < d_src), i16, (tile << P) + (1u << 15), up, integral_constant<int, 0>{}, integral_constant<int, 32>{});
+            if constexpr (!UP_AHEAD)
+                load(slot(c, ((uint64_t)tile << P) < d_src), i16, (tile << P) + (1u << 15), up, integral_constant<int, 0>{},
+                     integral_constant<int, 32>{});
 #pragma unroll
             for (int a = 0; a < 32; ++a) {                       // the stage over bit 15 (one rounding)
                 u[a] = fmaf(value(up[a], i16), side, value(u[a], i16));
@@ -363,11 +367,11 @@ __global__ __launch_bounds__(1024) void k_dec_lo15_last(DecBatch B, uint32_t n, 
     }
 }
 
-// The same for launches of fp16 slots at P = 15, the tile through the LDS as a whole: a thread then has 32 coordinates in a row, after 628 vector
-// instructions a sender where the pieces take 676 and 17 waits.  A CU that goes through many senders is bound by those; with few of
-// them it is the loads ahead that count (see launch_dec_lo15_last).
-// PAIRS: senders sparsified by pairs (one output coordinate of each pair): 64 sums a thread.  With the pieces, which tie the pair's choice to the
-// quads, 4 senders of 60,000,001 took 149 us, this 137.
+// The same for launches of fp16 slots at P = 15, the tile through the LDS as a whole: a thread then has 32 coordinates in a row, after
+// 628 vector instructions a sender where the pieces take 676 and 17 waits.  A CU that goes through many senders is bound by those; with
+// few of them it is the loads ahead that count (see launch_dec_lo15_last).
+// PAIRS: senders sparsified by pairs (one output coordinate of each pair): 64 sums a thread.  With the pieces, which tie the pair's
+// choice to the quads, 4 senders of 60,000,001 took 149 us, this 137.
 constexpr int kLo15Row = 36;                     // 32 values + 4: rows of consecutive lanes start 4 banks apart
 constexpr int kLo15Wave = 64 * kLo15Row;         // one wave's region of the second exchange
 constexpr int kLo15LdsWords = 16 * kLo15Wave;    // 147456 bytes; the first exchange needs 2^15 words
@@ -536,8 +540,8 @@ void launch_dec_lo15_last(int P, const DecBatch &B, uint32_t n, uint64_t d_src, 
     const dim3 grid(tiles < resident ? tiles : resident);
     bool wide = true, small = true;                              // no sender, every sender with an fp16 slot
     for (uint32_t c = 0; c < n; ++c) { wide = wide && B.b_q8[c] > 256u; small = small && B.b_q8[c] <= 256u; }
-    // Nine senders or more as a whole.  Whole decode at b = 1, us, in pieces / as a whole: one sender of 2^26 128 / 148, 4 355 / 372, 8 644 / 646,
-    // 12 937 / 923, 16 1227 / 1193, 32 2392 / 2293; 8 of 2^24 + 1 236 / 233, of 2^25 298 / 305, 16 571 / 547, 32 1080 / 1031.
+    // Nine senders or more as a whole.  Whole decode at b = 1, us, in pieces / as a whole: one sender of 2^26 128 / 148, 4 355 / 372, 8
+    // 644 / 646, 12 937 / 923, 16 1227 / 1193, 32 2392 / 2293; 8 of 2^24 + 1 236 / 233, of 2^25 298 / 305, 16 571 / 547, 32 1080 / 1031.
     if (small && P == 15 && n > 8u) {
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_dec_lo15_last_rows<false>), dim3(tiles), dim3(1024), 0, st, B, n, d_src, log2D, seed, T, scratch, acc, mean_n);
         return;

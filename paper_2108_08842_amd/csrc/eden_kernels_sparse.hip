@@ -148,10 +148,10 @@ __device__ inline void load4_padded(const float *x, uint32_t i, uint32_t d, bool
 }
 
 // out[c][block m + slot] = x_c[i] for the kept coordinates (0 for a kept position beyond d), out[c] = out + (c << log2_stride).
-// A wave takes 64 blocks = 4096 coordinates of sender blockIdx.y.  x goes straight into the LDS, all of it on its way while the wave selects; the
-// kept coordinates are then picked from there by a list, and leave in one run.  (Loads behind the selection and a test of every coordinate
-// against the masks: encode, us, m = 6 188 -> 169, one sender 30.2 -> 27.3, 2 of 4,000,037 25.2 -> 22.2; m = 32, 8 senders of 11,173,962 206 -> 184;
-// half of each by the selection itself.)
+// A wave takes 64 blocks = 4096 coordinates of sender blockIdx.y.  x goes straight into the LDS, all of it on its way while the wave
+// selects; the kept coordinates are then picked from there by a list, and leave in one run.  (Loads behind the selection and a test of
+// every coordinate against the masks: encode, us, m = 6 188 -> 169, one sender 30.2 -> 27.3, 2 of 4,000,037 25.2 -> 22.2; m = 32, 8
+// senders of 11,173,962 206 -> 184; half of each by the selection itself.)
 template <int POLICY>
 __global__ __launch_bounds__(64) void k_sparse_gather(EncBatch B, uint32_t d, uint32_t m, uint64_t seed, float *out, int log2_stride) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
@@ -252,8 +252,9 @@ __global__ __launch_bounds__(512) void k_sparse_scatter(DecBatch B, uint32_t n, 
 }
 
 // The same for few kept coordinates (see launch_sparse_scatter): instead of asking for every coordinate and sender whether it was kept
-// (560 issue slots per 64 blocks and sender), a wave goes through the kept values of its blocks, sender by sender, and adds them to sums in the LDS.  (A sender has at most one value for a
-// coordinate, and one wave adds all of a coordinate's: the same sums in the same order.)
+// (560 issue slots per 64 blocks and sender), a wave goes through the kept values of its blocks, sender by sender, and adds them to sums
+// in the LDS.  (A sender has at most one value for a coordinate, and one wave adds all of a coordinate's: the same sums in the same
+// order.)
 template <int NI>
 __global__ __launch_bounds__(512) void k_sparse_scatter_list(DecBatch B, uint32_t n, uint32_t d, uint32_t m, uint64_t seed, const float *in,
                                                              int log2_stride, float *acc, float mean_n) {
@@ -310,8 +311,8 @@ __global__ __launch_bounds__(512) void k_sparse_scatter_list(DecBatch B, uint32_
     }
 }
 
-// The same by a workgroup of eight waves per 64 blocks (see launch_sparse_gather): one wave selects while the others wait with their 512 coordinates in
-// registers, then all of them test theirs against the masks, compact and store.
+// The same by a workgroup of eight waves per 64 blocks (see launch_sparse_gather): one wave selects while the others wait with their 512
+// coordinates in registers, then all of them test theirs against the masks, compact and store.
 __global__ __launch_bounds__(512) void k_sparse_gather_team(EncBatch B, uint32_t d, uint32_t m, uint64_t seed, float *out, int log2_stride) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     const uint32_t lane = lane_id(), wv = wave_in_block(), c = blockIdx.y;
@@ -347,11 +348,12 @@ __global__ __launch_bounds__(512) void k_sparse_gather_team(EncBatch B, uint32_t
 void launch_sparse_gather(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m, uint64_t seed, float *out, int log2_stride, hipStream_t st) {
     const uint32_t blocks = (uint32_t)((d + 63) / 64);
     const uint32_t groups = (blocks + kSparseWave - 1) / kSparseWave;
-    // Launches that would leave most of the chip idle, and those that keep so many that the serial list of k_sparse_gather (a step for each of m) takes longer
-    // than the test of every coordinate: the team.  Whole encode, us, team / one wave: one sender of 2^21, m = 16 (512 groups) 16.6 / 17.9, m = 63 26.9 / 29.5;
-    // 8 of 500,001, m = 6 (984) 14.6 / 15.8; beyond 1024 groups 8 of 1,000,000, m = 6 19.4 / 18.2, m = 16 23.3 / 22.7; m = 24, 32 senders of 200,003 (1568)
-    // 25.3 / 27.2, 2 of 2^24 (8192) 65.9 / 66.8, 4 of 2^24 127.8 / 122.9; m = 32, the same 25.4 / 28.7, 74.1 / 77.5, 146.8 / 145.3; m = 48 29.4 / 33.7, 97.7 / 103.6,
-    // 16 of 11,173,962 491 / 516; m = 63 31.0 / 39.6, 119 / 130, 633 / 685.
+    // Launches that would leave most of the chip idle, and those that keep so many that the serial list of k_sparse_gather (a step for
+    // each of m) takes longer than the test of every coordinate: the team.  Whole encode, us, team / one wave: one sender of 2^21, m =
+    // 16 (512 groups) 16.6 / 17.9, m = 63 26.9 / 29.5; 8 of 500,001, m = 6 (984) 14.6 / 15.8; beyond 1024 groups 8 of 1,000,000, m = 6
+    // 19.4 / 18.2, m = 16 23.3 / 22.7; m = 24, 32 senders of 200,003 (1568) 25.3 / 27.2, 2 of 2^24 (8192) 65.9 / 66.8, 4 of 2^24 127.8
+    // / 122.9; m = 32, the same 25.4 / 28.7, 74.1 / 77.5, 146.8 / 145.3; m = 48 29.4 / 33.7, 97.7 / 103.6, 16 of 11,173,962 491 / 516;
+    // m = 63 31.0 / 39.6, 119 / 130, 633 / 685.
     const uint64_t waves = (uint64_t)groups * n;
     if (waves <= 1024 || m >= 48u || (m >= 24u && waves <= 8192)) {
         hipLaunchKernelGGL(k_sparse_gather_team, dim3(groups, n), dim3(512), 2u * kSparseWave * (uint32_t)sizeof(KeptHalf) + kSparseWave * m * 4u, st,
@@ -359,8 +361,9 @@ void launch_sparse_gather(const EncBatch &B, uint32_t n, uint64_t d, uint32_t m,
         return;
     }
     const uint32_t bytes = 64u * kSparseWave * (uint32_t)sizeof(float) + kSparseWave * m * (uint32_t)sizeof(uint16_t);    // at most 22 KiB
-    // x beyond the size of the memory-side cache is read with the streaming policy.  Whole encode, us, default / streaming: one sender of 50,000,001,
-    // m = 6 60.1 / 61.6, 2 of 25,000,001, m = 16 75.4 / 80.0; one of 2^27, m = 6 145 / 133, 16 of 11,173,962 184 / 166.
+    // x beyond the size of the memory-side cache is read with the streaming policy (the line of launch_enc_lo_first lies lower because a
+    // workspace as large as x is written beside it; here it is m/64 of it).  Whole encode, us, default / streaming: one sender of
+    // 50,000,001, m = 6 60.1 / 61.6, 2 of 25,000,001, m = 16 75.4 / 80.0; one of 2^27, m = 6 145 / 133, 16 of 11,173,962 184 / 166.
     if ((uint64_t)n * d * 4u <= (256u << 20))
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_sparse_gather<0>), dim3(groups, n), dim3(64), bytes, st, B, (uint32_t)d, m, seed, out, log2_stride);
     else
@@ -375,11 +378,11 @@ void launch_sparse_scatter(const DecBatch &B, uint32_t n, uint64_t d, uint32_t m
     // NQ = 4 and with 8: one of 4,000,037 37.6, 35.4, 32.9, 36.6; of 11,173,962 58.7, 56.7, 57.4, 66.0; two of 11,173,962 84.2, 80.4,
     // 78.6, 88.1; four of 2^24, NQ = 1, 154.9 with four, 160.7 with eight; six 229 and 240.)
     const uint32_t waves = n < 8u && groups * 8u > 4096u ? 4u : 8u;
-    // Up to 16 kept of 64, eight senders or two of large vectors: by lists.  Whole decode, us, by masks / by lists: m = 6, 16 senders of 11,173,962
-    // 124.0 / 104.5, 4 48.1 / 43.2, 2 35.0 / 32.7 (with eight waves 37.0), one 28.5 / 28.8; 32 of 4,000,037 95.8 / 82.1; 16 of 300,007 21.9 / 20.7;
-    // 4 of 2^20 15.1 / 15.5; m = 16, 16 of 11,173,962 171.7 / 159.7, 32 of 4,000,037 128.0 / 119.2; m = 32, 8 of 4,000,037 57.1 / 59.2.  Not for up to half
-    // of one group of blocks: the lists hold all 64 blocks' values, the masks are asked for real coordinates only (32 senders of 1000, m = 16
-    // 24.0 / 28.2, of 2000 26.9 / 28.8, of 3000 31.0 / 29.8).
+    // Up to 16 kept of 64, eight senders or two of large vectors: by lists.  Whole decode, us, by masks / by lists: m = 6, 16 senders of
+    // 11,173,962 124.0 / 104.5, 4 48.1 / 43.2, 2 35.0 / 32.7 (with eight waves 37.0), one 28.5 / 28.8; 32 of 4,000,037 95.8 / 82.1; 16 of
+    // 300,007 21.9 / 20.7; 4 of 2^20 15.1 / 15.5; m = 16, 16 of 11,173,962 171.7 / 159.7, 32 of 4,000,037 128.0 / 119.2; m = 32, 8 of
+    // 4,000,037 57.1 / 59.2.  Not for up to half of one group of blocks: the lists hold all 64 blocks' values, the masks are asked for
+    // real coordinates only (32 senders of 1000, m = 16 24.0 / 28.2, of 2000 26.9 / 28.8, of 3000 31.0 / 29.8).
     if (m <= 16u && blocks > 32u && (n >= 8u || (n >= 2u && groups > 512u))) {
         const uint32_t list_waves = n >= 4u ? 8u : 4u, turns = (kSparseWave / list_waves * m + 63u) / 64u;       // at most 4
         const uint32_t bytes = 64u * kSparseWave * (uint32_t)sizeof(float) + n * kSparseWave * m * (uint32_t)sizeof(uint16_t);   // at most 80 KiB

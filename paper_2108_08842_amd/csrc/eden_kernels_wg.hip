@@ -97,7 +97,8 @@ __device__ inline void hix_quantize_pack(const float (&out)[HiX<M>::RP], int ph,
             at[s % 4] = quantize_one_table<BITS>(out[s], th, bit);
         }
         if constexpr (TRANSPOSE && MIX == 2) {
-            // (three values at a time, whose places fit an instruction's inline constants: with a place of its own every value took two registers)
+            // (three values at a time, whose places fit an instruction's inline constants: with a place of its own every value took two
+            // registers)
             constexpr int i = s % 16, place = 2 * (i % 3);
             three |= (__builtin_amdgcn_inverse_ballot_w64(bit[0]) ? 1u << place : 0u) | (__builtin_amdgcn_inverse_ballot_w64(bit[1]) ? 2u << place : 0u);
             asm volatile("" : "+v"(three));                      // (not the masks of all sixteen first)

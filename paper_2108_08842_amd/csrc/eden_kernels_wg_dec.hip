@@ -89,7 +89,8 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         for (int r = 0; r < 64; ++r) v[r] = __uint_as_float(buf_load_byte(rp, voff, ((uint32_t)X::RL * r) << p));
         const uint32_t H = wide_half_levels(b_q8);
         // the values replace the bytes in their registers, eight at a time: what the compiler had in flight beyond that spilled, and every
-        // spilled byte was waited for on its own (8 senders of 11,173,962, b = 8, whole decode 213 -> 202 us, b = 6 238.5 -> 228; 32 of 2^23, b = 8 517 -> 490)
+        // spilled byte was waited for on its own (8 senders of 11,173,962, b = 8, whole decode 213 -> 202 us, b = 6 238.5 -> 228; 32 of
+        // 2^23, b = 8 517 -> 490)
         if (grid_q15(b_q8)) {
 #pragma unroll
             for (int r = 0; r < 64; ++r) {
@@ -119,8 +120,8 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         const uint32_t shift = cbits & 31u;
         const rsrc_t rb = make_rsrc(payload + payload_bytes / 4u, (uint32_t)coin_b_bytes(ct.total[c]));
         // the top bits of a row segment's coins are at most 32 consecutive bits of the second part, from bit oa (ob) on: this
-        // lane fetches them for "its" two rows once (beyond the part: 0) and puts them to the coordinates with a coin, so that both are lane masks:
-        // counting the coins below each coordinate took 16 instructions a value, this 9 (8 senders of 4,000,037 at 2.7 bits 54.8 -> 39.0 us,
+        // lane fetches them for "its" two rows once (beyond the part: 0) and puts them to the coordinates with a coin, so that both are
+        // lane masks: counting the coins below each coordinate took 16 instructions a value, this 9 (8 senders of 4,000,037 at 2.7 bits 54.8 -> 39.0 us,
         // 16 of 11,173,962 at 1.3 401 -> 274)
         auto window = [&](uint32_t first_bit) {
             const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b32(rb, (int)((first_bit >> 5) * 4u), 0, 0);
@@ -151,12 +152,13 @@ __global__ __launch_bounds__(HiX<M>::THREADS, 4) void k_dec_hix_first(DecBatch B
         const rsrc_t rp = make_rsrc(payload + ((base * (uint32_t)bits) >> 5), payload_bytes - (uint32_t)((base * (uint32_t)bits) >> 5) * 4u);
         const uint32_t voff = (((g * (uint32_t)bits) << (p - 5)) + (cbits >> 5)) * 4u;
         const uint32_t shift = cbits & 31u;
-        // second part: 16 bits per row segment.  Lane l fetches those of the two row segments the wave reads into register l and puts them to the chosen
-        // coordinates, so that both are lane masks (with a load, a shift and a compare a value: 16 senders of 11,173,962 at 2.5 bits 261 -> 219 us,
-        // 8 of 4,000,037 at 1.5 40.7 -> 33.6)
+        // second part: 16 bits per row segment.  Lane l fetches those of the two row segments the wave reads into register l and puts
+        // them to the chosen coordinates, so that both are lane masks (with a load, a shift and a compare a value: 16 senders of
+        // 11,173,962 at 2.5 bits 261 -> 219 us, 8 of 4,000,037 at 1.5 40.7 -> 33.6)
         const rsrc_t rb = make_rsrc(payload + payload_bytes / 4u, (uint32_t)payload_b_bytes(1ull << log2D, b_q8));
         const uint32_t ma = chosen_of_pairs(fa), mb = chosen_of_pairs(fb);
-        const uint32_t pa = spread2(buf_load_half(rb, (uint32_t)((base + row_a) >> 5) * 2u, 0u)), pb = spread2(buf_load_half(rb, (uint32_t)((base + row_b) >> 5) * 2u, 0u));
+        const uint32_t pa = spread2(buf_load_half(rb, (uint32_t)((base + row_a) >> 5) * 2u, 0u));
+        const uint32_t pb = spread2(buf_load_half(rb, (uint32_t)((base + row_b) >> 5) * 2u, 0u));
         const uint32_t ta = (pa | (pa << 1)) & ma, tb = (pb | (pb << 1)) & mb;
 #pragma unroll
         for (int r = 0; r < 64; ++r) {

@@ -40,11 +40,12 @@ __device__ inline void quad_stage(float4 &v) { quad_stage<X>(v.x); quad_stage<X>
 // other lane's value times 1 or -1 is added.  (Nothing gained in the encoder's pass over 14 bits, which waits for memory.)
 //   AFTER:  in every stage the lane with bit X gets (own) - (other), the stage's difference with its sign turned over
 //   BEFORE: that lane's input has its sign turned over; the results are the stage's
-// Signs that depend on the lane pass through the stages over other bits as they are, so that the stages leave (expect) them turned over where the
-// coordinate has an odd number of ones in their bits: the caller turns them over with those of the rotation.
-// Written out, because the compiler leaves the exchange and the multiply-add two instructions.  What an instruction has written may be read from another
-// lane two wait states later: the s_nop at the front keeps that distance to the instructions before the block, the one at the end to
-// those behind it (the compiler does not look inside), and the three other values stand between two stages of one.  build.py checks the built code.
+// Signs that depend on the lane pass through the stages over other bits as they are, so that the stages leave (expect) them turned over
+// where the coordinate has an odd number of ones in their bits: the caller turns them over with those of the rotation.
+// Written out, because the compiler leaves the exchange and the multiply-add two instructions.  What an instruction has written may be
+// read from another lane two wait states later: the s_nop at the front keeps that distance to the instructions before the block, the one
+// at the end to those behind it (the compiler does not look inside), and the three other values stand between two stages of one.
+// build.py checks the built code.
 template <bool BEFORE, bool BIT8>
 __device__ inline void flip_stages(float &a, float &b, float &c, float &d) {
     const float sign1 = ((threadIdx.x & 1u) != 0u) == BEFORE ? 1.0f : -1.0f;
@@ -64,9 +65,8 @@ __device__ inline void flip_stages(float &a, float &b, float &c, float &d) {
 #undef EDEN_FLIP
 }
 
-// in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed (B = 14: with the sign turned over where t has an odd
-// number of ones in bits 0 and 1, see flip_stages).  The caller puts a barrier between a
-// use of `lds` and the next one.
+// in: v[a] = coordinate a T + t of the tile; out: v[e] = coordinate 16 t + e, fully transformed (B = 14: with the sign turned over where
+// t has an odd number of ones in bits 0 and 1, see flip_stages).  The caller puts a barrier between a use of `lds` and the next one.
 template <int B>
 __device__ inline void lo_forward16(float (&v)[16], float *lds) {
     using L = Lo16<B>;
