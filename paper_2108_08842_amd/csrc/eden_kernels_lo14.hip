@@ -144,7 +144,7 @@ template <> struct EncLo<14, 16> {
 // as zero through its buffer bounds.
 // PRE (b = 1/2 with the sparsification first, Sec. 4.1): the vector that is transformed is x'[g] = 2 x[2g + o_g],
 // g < ceil(d_src/2), o_g from the SUB-SAMPLING stream; x is read as 0 beyond d_src.
-// KEEP: x and the workspace of the launch fit the memory-side cache together: the loads of x then leave it there, see launch_enc_lo_first.
+// KEEP: x and the workspace of the launch fit the memory-side cache together: the loads of x leave it there, see launch_enc_lo_first.
 // WAVES: of a workgroup.  |x|^2 is the same to the last bit for both numbers at P = 14: eight waves keep the sums of the two values of
 // bit 13, which tell sixteen waves apart, to themselves.
 template <int P, int WAVES, bool PRE, bool BLOCKED, bool KEEP>
@@ -669,11 +669,12 @@ uint32_t launch_enc_lo_first(int P, const EncBatch &B, uint32_t n, uint64_t d_sr
     // pass finds no unwritten row inside a block
     if (blocked) tiles = (tiles + kBlockRows - 1) / kBlockRows * kBlockRows;
     dim3 grid(tiles, n);
-    // Up to 128 MiB of x and workspace x is read with the default policy: it has often just been written, or is encoded again, and is
-    // then found in the memory-side cache; beyond, with the streaming one (a pure read 7.2 against 6.4 TB/s).  Encode of the same vectors
-    // over and over, us, streaming / default: 24 senders of 300,007, b = 2 30.5 / 27.1; 10 of 2^20, b = 2 32.8 / 29.5; one of 11,173,962, b = 1 36.9 / 34.0, of
-    // 15,000,000 46.3 / 39.8; 32 of 2^20 (256 MiB), 1/2 to 4 bits, a round 147 / 150; 8 of 11,173,962, b = 1 178 / 192, 16 of them 373 /
-    // 399.  Vectors that lie in no cache take the same either way.
+    // Up to 128 MiB of x and workspace x is read with the default policy, so that vectors that are encoded again are found in the
+    // memory-side cache; beyond, with the streaming one (a pure read 7.2 against 6.4 TB/s). Encode, us, streaming / default, of the
+    // same vectors over and over: one sender of 11,173,962, b = 1 36.9 / 35.1, of 15,000,000 45.5 / 40.4; 10 of 2^20, b = 2 33.0 /
+    // 31.0; 24 of 300,007 30.9 / 26.2; of vectors that another kernel has just written: 36.8 / 36.9, 41.7 / 42.1, 40.2 / 39.6, 40.6 /
+    // 40.5; of vectors that lie in no cache, whose lines then take the workspace's place: 36.6 / 37.8, 45.2 / 45.5, 32.5 / 33.4, 31.0
+    // / 26.5. 32 of 2^20 (256 MiB), 1/2 to 4 bits, a round 147 / 150; 8 of 11,173,962, b = 1 178 / 192, 16 of them 373 / 399.
     const bool keep = !pre && (d_src + ((uint64_t)tiles << P)) * n * 4u <= (128u << 20);
 #define EDEN_ENC_LO_LAUNCH(P, WAVES, PRE, BLK, KEEP) \
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_enc_lo_first<P, WAVES, PRE, BLK, KEEP>), grid, dim3(64 * WAVES), 0, st, B, d_src, log2D, seed, T, \

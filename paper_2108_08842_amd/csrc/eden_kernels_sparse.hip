@@ -9,8 +9,8 @@
 // they are all kept and the search goes on among the others.  About 750 issue slots per wave of 64 blocks, 320 of them the hash
 // (1000 and 110 registers while the compiler chose the forms of the masks and multiplied the counter anew for every word; now 46
 // registers); a bitonic sort of the keys across lanes took 3000.
-// 16 senders of 11,173,962, m = 6, us: gather 283 with the sort, 151 with masks and one load form, 122 now (782 MB: 6.4 TB/s); scatter 218, 130
-// (95% of the issue slots), 67 now.
+// 16 senders of 11,173,962, m = 6, us (averages of kernel traces): gather 283 with the sort, 147 with masks and one load form, 126 now
+// (782 MB: 6.2 TB/s); scatter 218, 109 (95% of the issue slots), 72 now (84% with two sets of vectors in turn, 84 us).
 #include "eden_device.h"
 #include "eden_kernels.h"
 
