@@ -356,8 +356,8 @@ __global__ __launch_bounds__(1024, 8) void k_dec_lo14_last(DecBatch B, uint32_t 
 // Per coordinate and sender this leaves 9 vector instructions (split 2, butterflies 4, sign and accumulate 3)
 // where the all-vector version spends 19, and one exchange instead of two.  The loads of the next sender go out into the registers that the
 // products of step 1 have just read (issued in front of them they cost 32 moves), their descriptors come from scalar registers (out of vector
-// registers every load went through a loop), the sign words from the LDS: 16 senders of 11,173,962, us, 96.6 -> 86.3 (decode 169.6 ->
-// 160.3), one of them 19.3 -> 18.6, 20 of 600,000 23.3 -> 22.3.
+// registers every load went through a loop), the sign words from the LDS: 16 senders of 11,173,962, us, 103.8 -> 91.3 (averages of a kernel
+// trace; decode 169.6 -> 160.3), one of them 19.3 -> 18.6, 20 of 600,000 23.3 -> 22.3.
 // x - (float)h for the fp16 in the low (HIGH = 0) or high half of `packed`: one mixed-precision fused multiply-add
 // (-1 * h + x, exact: h is x truncated to 11 bits)
 template <int HIGH>
